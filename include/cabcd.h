@@ -156,8 +156,11 @@ typedef struct cabcd_opts {
                                 /* step's companion update)                       */
 #define CABCD_PHASE_REDUCE 2    /* sum of the Gram partials, scale and overlap     */
 #define CABCD_PHASE_SOLVE 3     /* s block solves + recurrence + x[idx] += d;      */
-                                /* also the launches that invert the diagonal     */
-                                /* blocks of Grams computed ahead                 */
+                                /* also the launches that invert the block        */
+                                /* triangles (or diagonal blocks) of Grams        */
+                                /* computed ahead; a dense step of such a Gram    */
+                                /* (b <= 16) is one launch, counted here, with    */
+                                /* its companion update and the next step's Y u   */
 #define CABCD_PHASE_UPDATE 4    /* companion update with Y^T delta (counted only   */
                                 /* when launched: not when it is left to the next */
                                 /* step's Gram or made moot by the exact          */
@@ -166,7 +169,8 @@ typedef struct cabcd_opts {
 #define CABCD_PHASE_MONITOR 6   /* objective evaluation                            */
 #define CABCD_PHASE_CHECK 7     /* full residual of the stopping test              */
 #define CABCD_PHASE_YU 8        /* Y u as its own gathered-row pass (steps whose
-                                   Gram was computed ahead)                        */
+                                   Gram was computed ahead; dense ones with b <= 16
+                                   only where no step before them formed it)       */
 #define CABCD_NPHASES 9
 
 /* Fill *o with defaults: h0 0, no flags, no recompute, no monitor, sampler on,

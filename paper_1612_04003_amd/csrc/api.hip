@@ -41,6 +41,11 @@ constexpr int kDenseAhead = 32;             // dense: the same, when one Gram is
 constexpr int kDenseFill = 512;             // workgroups that fill the GPU (two per CU)
 constexpr int64_t kAheadRowBytes = 8 << 20; // dense: gathered rows small enough to read twice
 constexpr int64_t kAheadDoubles = (int64_t)8 << 20;   // their buffers (64 MiB at most)
+constexpr int kHalfGpu = 128;               // workgroups of a 256-row Gram launch ahead
+constexpr int kFirstBatch = 6;              // steps of a chain's first batch (at least)
+constexpr int kChainAhead = 32;             // dense steps of a chain: Grams per launch (max)
+constexpr int kChainFewRows = 32;           // steps of so few rows are a chain up to
+constexpr int64_t kChainRowBytes = 40 << 20;   // so many gathered bytes
 constexpr int kSplitMinRows = 256;          // CSR: the split Gram from this many rows a step
 constexpr int kSplitMaxRows = 512;
 constexpr int kSplitAhead = 16;             // steps per split Gram launch (at most)
@@ -222,7 +227,8 @@ size_t max_partials(const Mat& M, int sb_max) {
 // out = [beta base | out] + gamma * sum_p A[row(p)]^T v[p]
 hipError_t mat_scatter(const Mat& M, const int32_t* idx, int64_t m, const double* v,
                        double gamma, const double* base, double beta, bool accumulate,
-                       double* out, double* scratch, hipStream_t st) {
+                       double* out, double* scratch, hipStream_t st,
+                       const XScatter& xs = XScatter{}) {
   if (M.lowp())
     return launch_gemv_t_lp(M.dtype, M.Q, M.ld, M.cols, M.rs, idx, m, v, gamma, base, beta,
                             accumulate, out, st);
@@ -233,7 +239,7 @@ hipError_t mat_scatter(const Mat& M, const int32_t* idx, int64_t m, const double
     hipError_t e = launch_fill(out, M.cols, base, beta, st);
     if (e != hipSuccess) return e;
   }
-  return launch_csr_scatter(M.C, idx, m, v, gamma, out, st);
+  return launch_csr_scatter(M.C, idx, m, v, gamma, out, xs, st);
 }
 
 // out[p] = A[p] . v + beta base[p]
@@ -484,41 +490,102 @@ hipError_t mat_gram(const Mat& M, const int32_t* idx, int m, const double* u, do
   return timer ? timer->run(CABCD_PHASE_REDUCE, r) : r();
 }
 
-// Gram slots of the step buffers: the Grams of several future outer steps are
-// computed in one launch (they depend on the sampled indices only) when one
-// step's Gram cannot fill the GPU: always for CSR (a latency-bound walk per
-// row), and for dense rows too short to give the split-K Gram enough slabs.
-// Y u then takes a second pass over the gathered rows, so dense look-ahead is
-// kept to gathered rows of a few MiB.
-int gram_slots(const Mat& M, int64_t sb) {
-  if (M.csr)
-    return (int)std::max<int64_t>(1, std::min<int64_t>(kCsrAhead, kAheadDoubles / (sb * sb)));
+// How the outer steps of a call are computed.  The Grams of several future
+// outer steps come from one launch (they depend on the sampled indices only)
+// when one step's Gram cannot fill the GPU: always for CSR (a latency-bound
+// walk per row), and for dense rows too short to give the split-K Gram enough
+// slabs.  Y u then takes a second pass over the gathered rows, so dense
+// look-ahead is kept to gathered rows of a few MiB.  With b <= 16 such steps
+// are a chain (chain.hip): their Grams' block triangles are inverted ahead too,
+// and a dense step is one launch.  That saves the reduction, the solve and the
+// launches of a step, about 16 us, against the second pass, so steps of at most
+// kChainFewRows rows (whose Gram is no more work than that pass) are a chain
+// up to kChainRowBytes.
+struct Ahead {
+  int slots = 1;          // Grams per launch
+  ChainPlan chain{};      // chain.ok: the steps are a chain
+  GramPlan plan{};        // dense: the plan of one Gram
+  int first = 1;          // Grams of a call's first launch
+};
+
+// The column slabs of FP64 Grams computed ahead for a chain: launches of
+// several steps fill the GPU with longer slabs than one Gram alone needs, which
+// saves partial sums: at most 256 KiB of rows a slab, as the first launch of a
+// call waits for whole slabs, and eight slabs of a short step.
+GramPlan plan_ahead_f64(int m, int64_t cols) {
+  GramPlan p = plan_gram_f64(m, cols);
+  const int64_t row = 16 * p.nb * 8;   // bytes a column
+  int64_t chunk = std::min<int64_t>(256 << 10, std::max<int64_t>(32 << 10, cols * row / 8)) / row;
+  chunk = std::max<int64_t>(p.kt, chunk / p.kt * p.kt);
+  p.chunk = chunk;
+  p.nsplit = (int)((cols + chunk - 1) / chunk);
+  return p;
+}
+
+Ahead plan_ahead(const Mat& M, int b, int64_t sb, bool chain = true) {
+  Ahead a;
+  if (chain) a.chain = chain_plan((int)sb, b);
+  if (!M.csr) {   // whole 16-byte chunks, on their boundaries for codes
+    const int es = M.dtype == CABCD_F64 ? 8 : (M.dtype == CABCD_BF16 ? 2 : 1);
+    a.chain.ok = a.chain.ok && M.cols * es >= 16 &&
+                 (!M.lowp() || ((reinterpret_cast<uintptr_t>(M.Q) & 15) == 0 &&
+                                (M.ld * es & 15) == 0));
+  }
+  if (M.csr) {
+    a.slots = (int)std::max<int64_t>(1, std::min<int64_t>(kCsrAhead, kAheadDoubles / (sb * sb)));
+    if (a.slots == 1) a.chain.ok = false;
+    a.first = std::min(a.slots, sb >= kSplitMinRows ? 8 : sb >= 64 ? 12 : a.slots);
+    return a;
+  }
+  a.plan = plan_for(M, (int)sb);
   const int64_t elem = M.dtype == CABCD_F64 ? 8 : (M.dtype == CABCD_BF16 ? 2 : 1);
-  if (sb > kGramRows || sb * M.cols * elem > kAheadRowBytes) return 1;
-  const GramPlan p = plan_for(M, (int)sb);
-  if (p.nsplit >= kDenseFill) return 1;
-  const int64_t per = (int64_t)gram_partial_doubles(p) + sb * sb;   // partials and G
-  int64_t k = (kDenseFill + p.nsplit - 1) / p.nsplit;
+  const int64_t bytes = sb * M.cols * elem;
+  const bool few = a.chain.ok && sb <= kChainFewRows && bytes <= kChainRowBytes;
+  if (sb > kGramRows || (!few && (bytes > kAheadRowBytes || a.plan.nsplit >= kDenseFill))) {
+    a.chain.ok = false;
+    return a;
+  }
+  if (a.chain.ok && !M.lowp()) a.plan = plan_ahead_f64((int)sb, M.cols);
+  const int64_t per = (int64_t)gram_partial_doubles(a.plan) + sb * sb;   // partials and G
+  int64_t k = a.chain.ok ? kChainAhead : (kDenseFill + a.plan.nsplit - 1) / a.plan.nsplit;
   k = std::min<int64_t>(k, kDenseAhead);
-  k = std::min<int64_t>(k, kAheadDoubles / per);
-  return (int)std::max<int64_t>(k, 1);
+  k = std::min<int64_t>(k, (a.chain.ok ? 2 : 1) * kAheadDoubles / per);
+  a.slots = (int)std::max<int64_t>(k, 1);
+  if (a.slots == 1) {   // one Gram per step, by the plan of one Gram
+    a.chain.ok = false;
+    a.plan = plan_for(M, (int)sb);
+  }
+  a.first = a.chain.ok
+                ? std::min(a.slots, std::max(kFirstBatch, kHalfGpu / a.plan.nsplit))
+                : a.slots;
+  return a;
 }
 
 // The Grams of nsteps full outer steps (indices idx + k m for step k) into G +
 // k m^2, without Y u.
-hipError_t mat_gram_steps(const Mat& M, const int32_t* idx, int m, int nsteps, double scale,
-                          double shift, double* G, double* partials, hipStream_t st,
-                          PhaseTimer* timer) {
+hipError_t mat_gram_steps(const Mat& M, const GramPlan& plan, const int32_t* idx, int m,
+                          int nsteps, double scale, double shift, double* G, double* partials,
+                          hipStream_t st, PhaseTimer* timer) {
   if (M.csr)
     return timer->run_on(st, CABCD_PHASE_GRAM, [&] {
       return launch_csr_gram_steps(M.C, idx, m, nsteps, scale, shift, true, G, st);
     });
-  const GramPlan plan = plan_for(M, m);
-  hipError_t e = timer->run_on(st, CABCD_PHASE_GRAM, [&] {
-    return M.lowp() ? launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, idx, m, nullptr, partials,
-                                     st, nsteps)
-                    : launch_gram_f64(plan, M.X, M.ld, M.cols, idx, m, nullptr, partials, st,
-                                      nsteps);
+  // The 256-row kernels take a whole CU per workgroup: a launch that fills the
+  // GPU would keep the running steps' workgroups waiting for its own (52 us
+  // instead of 16 for a dense dual step), so they go out half a GPU at a time.
+  const int per = plan.nb == 16 ? std::max(1, kHalfGpu / plan.nsplit) : nsteps;
+  const size_t set = gram_partial_doubles(plan);
+  hipError_t e = timer->run_on(st, CABCD_PHASE_GRAM, [&]() -> hipError_t {
+    for (int k = 0; k < nsteps; k += per) {
+      const int ns = std::min(per, nsteps - k);
+      const hipError_t he =
+          M.lowp() ? launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, idx + (int64_t)k * m, m,
+                                    nullptr, partials + k * set, st, ns)
+                   : launch_gram_f64(plan, M.X, M.ld, M.cols, idx + (int64_t)k * m, m, nullptr,
+                                     partials + k * set, st, ns);
+      if (he != hipSuccess) return he;
+    }
+    return hipSuccess;
   });
   if (e != hipSuccess) return e;
   return timer->run_on(st, CABCD_PHASE_REDUCE, [&] {
@@ -529,50 +596,63 @@ hipError_t mat_gram_steps(const Mat& M, const int32_t* idx, int m, int nsteps, d
 
 // CSR steps of kSplitMinRows..kSplitMaxRows rows whose Grams are computed
 // ahead take the split Gram (heavy columns dense, light ones by column lists).
-bool use_split(const Mat& M, int64_t sb) {
+bool use_split(const Mat& M, int64_t sb, const Ahead& ah) {
   return M.csr && sb >= kSplitMinRows && sb <= kSplitMaxRows && M.cols <= kSplitMaxCols &&
-         gram_slots(M, sb) > 1;
+         ah.slots > 1;
 }
 
 struct StepBuffers {
   int* split_prep;   // the split Gram's per-matrix numbering of heavy columns
   int* status;
   int32_t* idx;      // kIdxChunkSteps * s * b
-  double* G;         // gram_slots x sb x sb (twice when computed ahead)
-  double* G2;        // the second buffer of Grams computed ahead (or G)
+  double* G[2];      // slots x sb x sb (the second buffer: Grams computed ahead)
   double* Yu;        // sb
   double* delta;     // sb
-  double* partials;  // dense Gram partials
-  double* partials2; // the second buffer of the ahead path's partials (or partials)
+  double* partials[2];   // dense Gram partials (the second: Grams computed ahead)
   double* scratch;   // gemv row-group partials
   double* obj;       // objective scratch
   double* rtmp;      // residual temporary (monitoring)
   double* rho;       // full residual of the stopping test (rows)
   double* rnorm;     // its norm
+  // the chain of steps whose Grams are computed ahead
+  double* tri[2];    // slots inverses of the Grams' block triangles
+  double* dinv;      // scratch of one launch
+  int* link[2];      // slots x sb links of repeated indices
+  double* P[2];      // dense: partial Y u of a step and of the next one
+  double* xg[2];     // dense: x (and y, row scales) at their indices
 };
 
 // Layout of the step workspace.
-size_t layout(Carve& c, StepBuffers& B, const Mat& M, int b, int s, int64_t rtmp_len,
-              bool checks) {
+size_t layout(Carve& c, StepBuffers& B, const Mat& M, const Ahead& ah, int b, int s,
+              int64_t rtmp_len, bool checks) {
   const int sb = s * b;
-  B.split_prep = c.take<int>(use_split(M, sb) ? csr_split_prepare_ints(M.C) : 1);
+  B.split_prep = c.take<int>(use_split(M, sb, ah) ? csr_split_prepare_ints(M.C) : 1);
   B.status = c.take<int>(1);
   B.idx = c.take<int32_t>((size_t)kIdxChunkSteps * sb);
-  const int slots = gram_slots(M, sb);
+  const size_t slots = ah.slots;
   const int nbuf = slots > 1 ? 2 : 1;   // Grams computed ahead: the next batch's buffer too
-  B.G = c.take<double>((size_t)nbuf * slots * sb * sb);
-  B.G2 = B.G + (size_t)(nbuf - 1) * slots * sb * sb;
+  B.G[0] = c.take<double>(nbuf * slots * sb * sb);
+  B.G[1] = B.G[0] + (nbuf - 1) * slots * sb * sb;
   B.Yu = c.take<double>(sb);
   B.delta = c.take<double>(sb);
-  const size_t ahead_p =
-      M.csr || slots == 1 ? (size_t)0 : (size_t)slots * gram_partial_doubles(plan_for(M, sb));
-  B.partials = c.take<double>(std::max(max_partials(M, sb), nbuf * ahead_p));
-  B.partials2 = B.partials + (nbuf - 1) * ahead_p;
+  const size_t ahead_p = M.csr || slots == 1 ? (size_t)0 : slots * gram_partial_doubles(ah.plan);
+  B.partials[0] = c.take<double>(std::max(max_partials(M, sb), nbuf * ahead_p));
+  B.partials[1] = B.partials[0] + (nbuf - 1) * ahead_p;
   B.scratch = c.take<double>(mat_scratch_doubles(M, sb));
   B.obj = c.take<double>(objective_scratch_doubles(0, 0));
   B.rtmp = c.take<double>(std::max<int64_t>(rtmp_len, 1));
   B.rho = c.take<double>(checks ? M.rows : 1);
   B.rnorm = c.take<double>(1);
+  if (ah.chain.ok) {
+    B.dinv = c.take<double>(slots * ah.chain.dinv);
+    const size_t pd = M.csr ? 1 : chain_slabs(M.dtype, sb, M.cols).partial;
+    for (int q = 0; q < 2; ++q) {
+      B.tri[q] = c.take<double>(slots * ah.chain.tri);
+      B.link[q] = c.take<int>(slots * sb);
+      B.P[q] = c.take<double>(pd);
+      B.xg[q] = c.take<double>(M.csr ? 1 : 2 * sb);
+    }
+  }
   return c.off + 256;
 }
 
@@ -675,14 +755,22 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   // monitoring needs the residual X^T w - y of length n (primal: cols, dual: rows)
   const int64_t rtmp_len = o.monitor_every > 0 ? (dual ? rows : cols) : 1;
   StepBuffers B{};
-  Carve probe{nullptr};
   const bool checks = o.check_every > 0;
-  const size_t need = layout(probe, B, M, b, s, rtmp_len, checks);
+  Ahead ah = plan_ahead(M, b, (int64_t)s * b);
+  Carve probe{nullptr};
+  size_t need = layout(probe, B, M, ah, b, s, rtmp_len, checks);
+  if (ah.chain.ok && o.workspace != nullptr && o.workspace_bytes < need) {
+    // a caller workspace without room for the chain's buffers: the solves stay
+    // with their steps
+    ah = plan_ahead(M, b, (int64_t)s * b, false);
+    Carve again{nullptr};
+    need = layout(again, B, M, ah, b, s, rtmp_len, checks);
+  }
   void* ws = nullptr;
   cabcd_status e = get_workspace(&o, need, &ws);
   if (e != CABCD_OK) return e;
   Carve carve{static_cast<char*>(ws)};
-  layout(carve, B, M, b, s, rtmp_len, checks);
+  layout(carve, B, M, ah, b, s, rtmp_len, checks);
   if (o.iters_done != nullptr) *o.iters_done = 0;
   if (o.resid_norm != nullptr) *o.resid_norm = std::nan("");
   e = check_csr_device(M, B.status, st);
@@ -693,7 +781,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   // that has room for it beyond `need`; otherwise the Grams stay on the
   // row-pair kernel).
   const int64_t sb_full = (int64_t)s * b;
-  bool split = use_split(M, sb_full);
+  bool split = use_split(M, sb_full, ah);
   CsrSplitInfo sinfo{};
   int ksplit = 0;
   double* split_d[2] = {nullptr, nullptr};   // the scratch of two launches (see the loop)
@@ -703,7 +791,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   }
   if (split && sinfo.maxrow >= kSplitMaxRowLen) split = false;   // entry keys need < 2^22
   if (split) {
-    ksplit = std::min(gram_slots(M, sb_full), kSplitAhead);
+    ksplit = std::min(ah.slots, kSplitAhead);
     // a launch takes 1..ksplit steps; its doubles, then its ints, must fit
     size_t dmax = 0, imax = 0;
     auto bytes_of = [&](int k) {
@@ -776,15 +864,17 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   if (!(o.flags & CABCD_FLAG_STATE_VALID))
     HIP_TRY(timer.run(CABCD_PHASE_RECOMPUTE, exact_companion));
 
-  const int K = gram_slots(M, (int64_t)s * b);   // Grams per launch (computed ahead)
-  // Grams computed ahead get their diagonal blocks inverted in one launch, and
-  // the one-barrier solves (b <= 16, s BP <= 512 lanes) skip their own
+  const int K = ah.slots;   // Grams per launch (computed ahead)
+  const bool chain = ah.chain.ok;
+  // Grams computed ahead outside a chain (short workspaces, codes on odd
+  // boundaries) get their diagonal blocks inverted in one launch, and the
+  // one-barrier solves (b <= 16, s BP <= 512 lanes) skip their own
   // inversion: sparse dual solve at b = 16, s = 1 / 8 / 32: 11.9 -> 8.9 /
   // 15.9 -> 12.3 / 43 -> 34 us (the 512-thread solve without the inversion
   // code also stops spilling registers).
   int bp = 1;
   while (bp < b) bp *= 2;
-  const bool pre_inv = K > 1 && bp <= 16 && (int64_t)s * bp <= 512;
+  const bool pre_inv = K > 1 && !chain && bp <= 16 && (int64_t)s * bp <= 512;
   // CABCD_FLAG_FOLD_UPDATE: the dense 256-row Gram applies the previous
   // step's companion update on its way (one pass over both steps' rows, the
   // update's traffic beside the matrix cores' work instead of a pass of its
@@ -801,6 +891,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   const int32_t* pend_idx = nullptr;
   int ahead = 0, gslot = 0;                       // precomputed Grams left, next slot
   int split_nst = 0;                              // steps of the current batch
+  int grow = chain ? ah.first : K;                // steps the next batch may take
   int64_t h = 0, k = 0, slot = 0;
   int64_t chunk_begin = -1, chunk_end = -1;
   const int64_t chunk_iters = kIdxChunkSteps * (int64_t)s;
@@ -809,8 +900,8 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   // While the steps of one batch run on the call's stream, the next batch's
   // Grams (whose indices are at hand) are computed on a second stream into
   // the other of two buffers; the first step of that batch waits for them.
-  double* const Gbuf[2] = {B.G, B.G2};
-  double* const Pbuf[2] = {B.partials, B.partials2};
+  // The first batch of a chain is short where its Grams fill the GPU, so that the
+  // steps start early; the batches double from there.
   int cur = 0;                                    // buffer of the current batch
   bool pf_ready = false;                          // next batch launched on the side stream
   int64_t pf_h = -1;
@@ -828,28 +919,64 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   auto batch_steps = [&](int64_t hb) -> int {
     int64_t avail = (H - hb) / s;
     if (o.explicit_idx == nullptr) avail = std::min(avail, (chunk_end - hb) / s);
-    return (int)std::min<int64_t>(split ? ksplit : K, std::max<int64_t>(avail, 0));
+    avail = std::min<int64_t>(avail, split ? std::min(grow, ksplit) : grow);
+    return (int)std::max<int64_t>(avail, 0);
   };
   auto launch_batch = [&](int64_t hb, int nst, int buf, hipStream_t bs) -> hipError_t {
     const int32_t* ib = o.explicit_idx != nullptr ? o.explicit_idx + hb * b
                                                   : B.idx + (hb - chunk_begin) * b;
     const int mb = s * b;
+    grow = std::min(2 * grow, K);
     hipError_t he;
     if (split)
       he = timer.run_on(bs, CABCD_PHASE_GRAM, [&] {
-        return launch_csr_gram_split(M.C, sinfo, ib, mb, nst, scale, shift, true, Gbuf[buf],
+        return launch_csr_gram_split(M.C, sinfo, ib, mb, nst, scale, shift, true, B.G[buf],
                                      split_d[buf], split_i[buf], bs);
       });
     else
-      he = mat_gram_steps(M, ib, mb, nst, scale, shift, Gbuf[buf], Pbuf[buf], bs, &timer);
+      he = mat_gram_steps(M, ah.plan, ib, mb, nst, scale, shift, B.G[buf], B.partials[buf], bs,
+                          &timer);
     if (he != hipSuccess) return he;
     // their diagonal blocks inverted together, off the solves' chains
     if (pre_inv)
       he = timer.run_on(bs, CABCD_PHASE_SOLVE, [&] {
-        return launch_invert_diag(Gbuf[buf], nst, mb, b, B.status, bs);
+        return launch_invert_diag(B.G[buf], nst, mb, b, B.status, bs);
+      });
+    if (chain)
+      he = timer.run_on(bs, CABCD_PHASE_SOLVE, [&] {
+        return launch_chain_prepare(ah.chain, B.G[buf], nst, mb, b, ib, B.tri[buf], B.dinv,
+                                    B.link[buf], B.status, bs);
       });
     return he;
   };
+  // Dense chains: P[par] and xg[par] hold the partial Y u of the coming step and
+  // x at its indices while have_dots.
+  const ChainSlabs slabs = chain && !M.csr ? chain_slabs(M.dtype, s * b, cols) : ChainSlabs{};
+  int par = 0;
+  bool have_dots = false;
+  ChainStep cs{};
+  if (chain && !M.csr) {
+    cs.A = static_cast<const uint8_t*>(M.lowp() ? M.Q : static_cast<const void*>(M.X));
+    cs.ld = M.ld;
+    cs.cols = cols;
+    cs.rs = M.rs;
+    cs.m = s * b;
+    cs.b = b;
+    cs.gb = ah.chain.gb;
+    cs.nsb = ah.chain.nsb;
+    cs.lc = slabs.lc;
+    cs.ps = slabs.ps;
+    cs.nslab = slabs.nslab;
+    cs.tail = slabs.tail;
+    cs.u = comp;
+    cs.x = coord;
+    cs.y = y;
+    cs.mode = dual ? 1 : 0;
+    cs.lambda = lambda;
+    cs.n = n;
+    cs.gamma = gamma;
+    cs.status = B.status;
+  }
   while (h < H) {
     const int sk = (int)std::min<int64_t>(s, H - h);
     const int m = sk * b;
@@ -867,7 +994,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
       }
       idx = B.idx + (h - chunk_begin) * b;
     }
-    const double* Gk = B.G;
+    const double* Gk = B.G[0];
     const bool from_ahead = K > 1 && sk == s;
     if (from_ahead) {
       if (ahead == 0) {
@@ -896,70 +1023,114 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
           pf_nst = n2;
         }
       }
-      Gk = Gbuf[cur] + (size_t)gslot * m * m;
+      Gk = B.G[cur] + (size_t)gslot * m * m;
       ++gslot;
       --ahead;
-      HIP_TRY(timer.run(CABCD_PHASE_YU, [&] {
-        return mat_rows_dot(M, idx, m, comp, B.Yu, B.scratch, st);
-      }));
+      if (!chain || M.csr)
+        HIP_TRY(timer.run(CABCD_PHASE_YU, [&] {
+          return mat_rows_dot(M, idx, m, comp, B.Yu, B.scratch, st);
+        }));
     } else if (pending) {
       HIP_TRY(timer.run(CABCD_PHASE_GRAM, [&] {
-        return launch_gram_f64_upd(fplan, M.X, M.ld, M.cols, idx, m, B.partials,
+        return launch_gram_f64_upd(fplan, M.X, M.ld, M.cols, idx, m, B.partials[0],
                                    D16Upd{pend_idx, B.delta, gamma, comp}, st);
       }));
       HIP_TRY(timer.run(CABCD_PHASE_REDUCE, [&] {
-        return launch_gram_reduce(fplan, B.partials, idx, m, scale, shift, true, B.G, B.Yu, st,
-                                  partial_layout(M, fplan), nullptr);
+        return launch_gram_reduce(fplan, B.partials[0], idx, m, scale, shift, true, B.G[0], B.Yu,
+                                  st, partial_layout(M, fplan), nullptr);
       }));
       pending = false;
     } else {
       HIP_TRY(
-          mat_gram(M, idx, m, comp, scale, shift, true, B.G, B.Yu, B.partials, st, &timer));
+          mat_gram(M, idx, m, comp, scale, shift, true, B.G[0], B.Yu, B.partials[0], st, &timer));
     }
-    SolveArgs sa{};
-    sa.G = Gk;
-    sa.Yu = B.Yu;
-    sa.idx = idx;
-    sa.y = y;
-    sa.x = coord;
-    sa.delta = B.delta;
-    sa.status = B.status;
-    sa.m = m;
-    sa.b = b;
-    sa.s = sk;
-    sa.mode = dual ? 1 : 0;
-    sa.lambda = lambda;
-    sa.n = n;
-    sa.pre_inverted = from_ahead && pre_inv ? 1 : 0;
-    HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] { return launch_solve(sa, st); }));
-    HIP_TRY(timer.run(CABCD_PHASE_UPDATE, [&] {
-      // an exact recomputation right after this step rebuilds the companion
-      // from the coordinates alone, so the update would be overwritten
-      if (o.resid_every > 0 && (k + 1) % o.resid_every == 0) {
-        timer.drop();
-        return hipSuccess;
+    const bool fresh_next = o.resid_every > 0 && (k + 1) % o.resid_every == 0;
+    const double* tri =
+        from_ahead && chain ? B.tri[cur] + (size_t)(gslot - 1) * ah.chain.tri : nullptr;
+    const int* link = from_ahead && chain ? B.link[cur] + (size_t)(gslot - 1) * m : nullptr;
+    if (from_ahead && chain && !M.csr) {
+      cs.ix = idx;
+      cs.idx = idx;
+      cs.tri = tri;
+      cs.link = link;
+      cs.P = B.P[par];
+      cs.xg = B.xg[par];
+      if (!have_dots) {   // (what P and xg hold is not used)
+        cs.step = 0;
+        cs.idx1 = idx;
+        cs.P1 = B.P[par];
+        cs.xg1 = B.xg[par];
+        HIP_TRY(timer.run(CABCD_PHASE_YU, [&] { return launch_chain_step(M.dtype, cs, st); }));
       }
-      // steps whose Gram came from a split launch: the deterministic update
-      // from its panel and sorted lists
-      if (from_ahead && split)
-        return launch_csr_update_split(M.C, sinfo, idx, m, split_nst, gslot - 1, B.delta, gamma,
-                                       comp, split_d[cur], split_i[cur], st);
-      if (fuse_kind && m == kGramRows) {
-        const int64_t h1 = h + sk, k1 = k + 1;
-        const bool reads_comp =
-            (o.resid_every > 0 && k1 % o.resid_every == 0) ||
-            (o.monitor_every > 0 && k1 % o.monitor_every == 0 && slot < o.trace_len) ||
-            (checks && k1 % o.check_every == 0);
-        if (H - h1 >= s && !reads_comp && (o.explicit_idx != nullptr || h1 < chunk_end)) {
-          pending = true;
-          pend_idx = idx;
+      cs.step = 1;
+      cs.upd = fresh_next ? 0 : 1;   // an exact recomputation would overwrite the update
+      // the next step's products, when it is a full step whose indices are at
+      // hand and nothing rewrites the companion before it
+      const int64_t h1 = h + sk;
+      have_dots = !fresh_next && H - h1 >= s && (o.explicit_idx != nullptr || h1 < chunk_end);
+      cs.idx1 = have_dots ? idx + m : nullptr;
+      par ^= 1;
+      cs.P1 = B.P[par];
+      cs.xg1 = B.xg[par];
+      // (the next launch's inverse: from 64 KiB on, its superblocks wait for the
+      // memory-side cache otherwise; one step of 256 rows 14.8 -> 13.3 us)
+      cs.tri1 = have_dots && ahead > 0 && ah.chain.tri >= 8192 ? tri + ah.chain.tri : nullptr;
+      HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] { return launch_chain_step(M.dtype, cs, st); }));
+    } else {
+      SolveArgs sa{};
+      sa.G = Gk;
+      sa.Yu = B.Yu;
+      sa.idx = idx;
+      sa.y = y;
+      sa.x = coord;
+      sa.delta = B.delta;
+      sa.status = B.status;
+      sa.m = m;
+      sa.b = b;
+      sa.s = sk;
+      sa.mode = dual ? 1 : 0;
+      sa.lambda = lambda;
+      sa.n = n;
+      sa.pre_inverted = from_ahead && pre_inv ? 1 : 0;
+      XScatter xs{};
+      if (from_ahead && chain) {
+        xs = XScatter{idx, link, B.delta, m, coord};
+        HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] {
+          return launch_chain_delta(ah.chain, tri, B.Yu, idx, coord, y, m, b, sa.mode, lambda, n,
+                                    B.delta, B.status, st);
+        }));
+      } else {
+        HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] { return launch_solve(sa, st); }));
+      }
+      HIP_TRY(timer.run(CABCD_PHASE_UPDATE, [&] {
+        // an exact recomputation right after this step rebuilds the companion
+        // from the coordinates alone, so the update would be overwritten
+        if (fresh_next && xs.x == nullptr) {
           timer.drop();
           return hipSuccess;
         }
-        return launch_update_f64(fplan, M.X, M.ld, M.cols, D16Upd{idx, B.delta, gamma, comp}, st);
-      }
-      return mat_scatter(M, idx, m, B.delta, gamma, nullptr, 0.0, true, comp, B.scratch, st);
-    }));
+        // steps whose Gram came from a split launch: the deterministic update
+        // from its panel and sorted lists
+        if (from_ahead && split)
+          return launch_csr_update_split(M.C, sinfo, idx, m, split_nst, gslot - 1, B.delta, gamma,
+                                         comp, split_d[cur], split_i[cur], xs, st);
+        if (fuse_kind && m == kGramRows) {
+          const int64_t h1 = h + sk, k1 = k + 1;
+          const bool reads_comp =
+              (o.resid_every > 0 && k1 % o.resid_every == 0) ||
+              (o.monitor_every > 0 && k1 % o.monitor_every == 0 && slot < o.trace_len) ||
+              (checks && k1 % o.check_every == 0);
+          if (H - h1 >= s && !reads_comp && (o.explicit_idx != nullptr || h1 < chunk_end)) {
+            pending = true;
+            pend_idx = idx;
+            timer.drop();
+            return hipSuccess;
+          }
+          return launch_update_f64(fplan, M.X, M.ld, M.cols, D16Upd{idx, B.delta, gamma, comp}, st);
+        }
+        return mat_scatter(M, idx, m, B.delta, gamma, nullptr, 0.0, true, comp, B.scratch, st, xs);
+      }));
+    }
     h += sk;
     ++k;
     const bool fresh = o.resid_every > 0 && k % o.resid_every == 0;
@@ -1277,7 +1448,8 @@ size_t cabcd_workspace_bytes(const cabcd_matrix* A, int32_t b, int32_t s) {
   if (b < 1 || s < 1 || (int64_t)s * b > max_rows_per_gram(M)) return 0;
   StepBuffers B{};
   Carve probe{nullptr};
-  return layout(probe, B, M, b, s, std::max(A->rows, A->cols), true);
+  return layout(probe, B, M, plan_ahead(M, b, (int64_t)s * b), b, s, std::max(A->rows, A->cols),
+                true);
 }
 
 }  // extern "C"

@@ -1,0 +1,816 @@
+// The dependent chain of outer steps whose Grams are computed ahead.
+//
+// The s inner solves of an outer step are one block forward substitution with
+// the lower block triangle T of the overlap-augmented Gram (solve_dev.h).  T
+// depends on the sampled indices only, so for Grams computed ahead its inverse
+// is formed ahead too, off the chain, and the solves of a step become one
+// product delta = T^-1 c with no dependent inner steps.  (As one workgroup's
+// forward substitution they took 15.5 us of a 38 us dense dual step at b = 8,
+// s = 32 and 42 us of an 81 us sparse one at b = 16, s = 32.)
+//
+// T^-1 is formed in superblocks of gb = b floor(16 / b) <= 16 rows, padded to
+// 16 with the identity:
+//   * chain_diag_kernel: the superblocks on the diagonal (block lower triangular
+//     inside) by Gauss-Jordan elimination, one row per lane; their pivots are
+//     those of the b x b blocks Gamma_j, so a pivot <= 0 is reported as before;
+//   * chain_panel_kernel: one workgroup per superblock column J runs the forward
+//     substitution Z_IJ = -D_I^-1 sum_{J<=t<I} G_It Z_tJ on the FP64 matrix
+//     cores.  An FP64 MFMA result holds item i at row 4 i + lane / 16, which is
+//     the operand layout of k-slice i, so Z feeds the next product from the
+//     registers it was written from (kept in LDS).
+// T^-1 is stored as its lower 16 x 16 superblocks in that result layout, items
+// 2 i and 2 i + 1 of a lane side by side (256 doubles each, row-major over the
+// block triangle), which the product reads with two 16-byte loads a lane.
+//
+// Dense steps then take one launch each (chain_step_kernel): the companion u is
+// cut into column slabs, one workgroup per slab.  Every workgroup adds the
+// slabs' partial Y u of the step (written by the launch before), forms c and
+// delta = T^-1 c for itself (T^-1 comes from L2), updates its slab of u with
+// the step's rows, and forms its slab's partial products of the next step's
+// rows with the updated slab, which it still holds.  One more workgroup
+// updates x and gathers x at the next step's indices.  What bounds a launch is
+// latency: the partial sums come from other XCDs' workgroups, and delta needs
+// all of them; the rows are prefetched into registers before that wait.  Sparse
+// steps keep their row products and updates and take chain_delta_kernel between
+// them.
+//
+// Measured per outer step in a long run, before -> now (us): dense primal d =
+// 64, n = 1024, b = 4, s = 8: 14 -> 8.5 (the launch 7.9); d = 2048, n = 2^18, b =
+// 8, s = 1: 28 -> 15.8 (12.0: 33.5 MB of rows at 2.8 TB/s); dense dual d = 2048, b
+// = 8, s = 32: 38.6 in four launches -> 17.2 (13.2, of which T^-1 c takes 3.9: 278
+// KB of T^-1 into each of 64 CUs); sparse dual b = 16, s = 8: 25 -> 16.5; s = 32: 81
+// -> 46, now the Gram's pace.
+#include "chain_dev.h"
+#include "gram_dev.h"
+#include "lowp_dev.h"
+#include "solve_dev.h"
+
+#include <algorithm>
+#include <type_traits>
+
+namespace cabcd {
+namespace {
+
+using cdev::kLinkFirst;
+using gdev::d16_row_sum;
+using gdev::d4;
+
+__host__ __device__ constexpr int tri_block(int i, int j) { return i * (i + 1) / 2 + j; }
+
+// Place of item i of a lane in a stored superblock.
+__host__ __device__ constexpr int tri_at(int i, int lane) {
+  return (i >> 1) * 128 + 2 * lane + (i & 1);
+}
+
+// v / b for v < 16, 1 <= b <= 16, as a product with bm = block_mul(b).
+__host__ __device__ constexpr int block_mul(int b) { return (255 + b) / b; }
+__device__ __forceinline__ int block_of(int v, int bm) { return (v * bm) >> 8; }
+
+// ------------------------------------------------------------------ T^-1
+
+// Superblock I of step blockIdx.y: four per wave, one row per lane.
+__global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict__ G, int m, int b,
+                                                        int gb, int nsb, double* __restrict__ tri,
+                                                        double* __restrict__ dinv, int* status) {
+  G += (int64_t)blockIdx.y * m * m;
+  tri += (int64_t)blockIdx.y * tri_block(nsb, 0) * 256;
+  dinv += (int64_t)blockIdx.y * nsb * 256;
+  const int I = blockIdx.x * 4 + (threadIdx.x >> 4);
+  const int u = threadIdx.x & 15;
+  const int r0 = I * gb;
+  const bool live = I < nsb && u < gb && r0 + u < m;
+  // unconditional loads at clamped places, so that they go out together
+  double e[16];
+#pragma unroll
+  for (int v = 0; v < 16; ++v) e[v] = G[(int64_t)min(r0 + v, m - 1) * m + min(r0 + u, m - 1)];
+  const int bm = block_mul(b), bu = block_of(u, bm);
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    e[v] = live && block_of(v, bm) <= bu && v < gb && r0 + v < m ? e[v] : (u == v ? 1.0 : 0.0);
+  bool bad = false;
+  sdev::gj_rows16<0>(e, u, bad);   // every lane takes part in the row broadcasts
+  if (bad) raise_status(status, DEV_NOTSPD);
+  if (I >= nsb) return;
+  double* t = tri + (int64_t)tri_block(I, I) * 256;
+  double* d = dinv + (int64_t)I * 256 + u;   // the matrix-core operand order: k-slice, lane
+#pragma unroll
+  for (int v = 0; v < 16; ++v) {
+    t[tri_at(u >> 2, (u & 3) * 16 + v)] = e[v];
+    d[(v >> 2) * 64 + (v & 3) * 16] = e[v];
+  }
+}
+
+// Workgroup x < gridDim.x - 1: superblock column J = x of step blockIdx.y by
+// four waves; the last workgroup builds the step's links.  FULL: gb = 16 and m a
+// multiple of 16.
+//
+// A column is a chain over its rows: row R (superblock J + R) needs Z of every
+// row before it.  Wave w holds the rows r = w mod 4 and adds their products to
+// its part of row R; the parts meet in LDS and wave R mod 4, the only one that
+// reads Z_R afterwards, finishes the row.  So the other waves run ahead into
+// the next row meanwhile (the parts are double-buffered), and one barrier a row
+// is enough.  PF operand blocks a wave are in flight; Z goes to memory at the
+// end (stores in the loop made the loads after them wait: 50 us for 13 steps of
+// 256 rows with one wave a column and stores in the loop, 190 us for 16 of 512).
+constexpr int kPanelWaves = 4;
+template <bool FULL>
+__global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
+    const double* __restrict__ G, int m, int gb, int nsb, double* __restrict__ tri,
+    const double* __restrict__ dinv, const int32_t* __restrict__ idx, int* __restrict__ link) {
+  extern __shared__ __attribute__((aligned(16))) double zs[];
+  const int64_t step = blockIdx.y;
+  if (blockIdx.x == gridDim.x - 1) {
+    int* ix = reinterpret_cast<int*>(zs);
+    idx += step * m;
+    link += step * m;
+    for (int p = threadIdx.x; p < m; p += blockDim.x) ix[p] = idx[p];
+    __syncthreads();
+    for (int p = threadIdx.x; p < m; p += blockDim.x) {
+      const int i = ix[p];
+      bool first = true;
+      for (int q = 0; q < p; ++q) first &= ix[q] != i;
+      int next = 0;
+      for (int q = m - 1; q > p; --q) next = ix[q] == i ? q + 1 : next;
+      link[p] = (first ? kLinkFirst : 0) | next;
+    }
+    return;
+  }
+  constexpr int PF = 4;
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l15 = lane & 15, l16 = lane >> 4;
+  const int J = blockIdx.x, nr = nsb - J;
+  const gptr<const double> Gs = glb(G) + step * m * m;
+  const gptr<double> T = glb(tri) + step * tri_block(nsb, 0) * 256;
+  const gptr<const double> D = glb(dinv) + (step * nsb + J) * 256 + lane;
+  double* part = zs + lane;                           // two sets of four parts
+  double* Z = zs + 2 * kPanelWaves * 256 + lane;      // Z of row r at r * 256
+
+  // operand block (R, r): rows of superblock J + R against columns of J + r,
+  // read as its transpose (G is symmetric): 16 consecutive doubles a row
+  auto load = [&](int R, int r, double(&a)[4]) {
+    const int col = (J + R) * gb + l15;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kk = 4 * s + l16, row = (J + r) * gb + kk;
+      if constexpr (FULL) {
+        a[s] = Gs[(int64_t)row * m + col];
+      } else {
+        const bool ok = kk < gb && l15 < gb && row < m && col < m;
+        const double v = Gs[ok ? (int64_t)row * m + col : 0];
+        a[s] = ok ? v : 0.0;
+      }
+    }
+  };
+  double ring[PF][4], da[4];
+  int Rn = w + 1, rn = w;   // the next block to load (clamped past the last)
+  auto next_load = [&](double(&a)[4]) {
+    load(min(Rn, nr - 1), min(rn, nr - 1), a);
+    rn += kPanelWaves;
+    const bool end = rn >= Rn;
+    Rn += end ? 1 : 0;
+    rn = end ? w : rn;
+  };
+  int Rd = w == 0 ? kPanelWaves : w;   // the next row this wave finishes
+  auto load_d = [&] {
+#pragma unroll
+    for (int s = 0; s < 4; ++s) da[s] = D[(int64_t)min(Rd, nr - 1) * 256 + 64 * s];
+  };
+#pragma unroll
+  for (int q = 0; q < PF; ++q) next_load(ring[q]);
+  load_d();
+  if (w == 0) {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) Z[64 * i] = T[(int64_t)tri_block(J, J) * 256 + tri_at(i, lane)];
+  }
+  int R = 1, r = w;
+  d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+  auto end_row = [&] {
+    double* set = part + (R & 1) * kPanelWaves * 256;
+    const d4 sum = acc[0] + acc[1];
+    acc[0] = acc[1] = d4{0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+    for (int s = 0; s < 4; ++s) set[w * 256 + 64 * s] = sum[s];
+    lds_barrier();
+    if (w == (R & (kPanelWaves - 1))) {
+      double v[4];
+#pragma unroll
+      for (int s = 0; s < 4; ++s)
+        v[s] = (set[64 * s] + set[256 + 64 * s]) + (set[512 + 64 * s] + set[768 + 64 * s]);
+      d4 z0 = {0.0, 0.0, 0.0, 0.0}, z1 = {0.0, 0.0, 0.0, 0.0};
+      z0 = gdev::mfma(da[0], -v[0], z0);
+      z1 = gdev::mfma(da[1], -v[1], z1);
+      z0 = gdev::mfma(da[2], -v[2], z0);
+      z1 = gdev::mfma(da[3], -v[3], z1);
+      z0 += z1;
+#pragma unroll
+      for (int s = 0; s < 4; ++s) Z[R * 256 + 64 * s] = z0[s];
+      Rd += kPanelWaves;
+      load_d();
+    }
+    ++R;
+    r = w;
+  };
+  while (R < nr) {
+#pragma unroll
+    for (int q = 0; q < PF; ++q) {
+      while (R < nr && r >= R) end_row();   // uniform
+      if (R < nr) {
+        const double* z = Z + r * 256;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[s & 1] = gdev::mfma(ring[q][s], z[64 * s], acc[s & 1]);
+        next_load(ring[q]);
+        r += kPanelWaves;
+      }
+    }
+  }
+  // wave w wrote the rows R = w mod 4
+  for (int R1 = Rd - kPanelWaves; R1 > 0; R1 -= kPanelWaves) {
+    const gptr<double> to = T + (int64_t)tri_block(J + R1, J) * 256;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) to[tri_at(s, lane)] = Z[R1 * 256 + 64 * s];
+  }
+}
+
+// ------------------------------------------------------------------ delta = T^-1 c
+
+// c_p of the step's right-hand side (solve_dev.h) from Y u and x at its index.
+__device__ __forceinline__ double rhs_of(int mode, double lambda, double n, double yu, double xi,
+                                         double yi) {
+  return mode == 0 ? (-lambda * xi - yu / n) : ((yu - xi - yi) / n);
+}
+
+// This lane's items of the stored superblock at t.
+__device__ __forceinline__ void tri_load(gptr<const double> t, int lane, double (&v)[4]) {
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  const dv2 x = *(gptr<const dv2>)(t + 2 * lane), y = *(gptr<const dv2>)(t + 128 + 2 * lane);
+  v[0] = x.x;
+  v[1] = x.y;
+  v[2] = y.x;
+  v[3] = y.y;
+}
+
+// Bit i: item i of this lane in a diagonal superblock is in the lower block
+// triangle.
+__device__ __forceinline__ int diag_mask(int bm, int lane) {
+  int mask = 0;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+    if (block_of(lane & 15, bm) <= block_of(4 * i + (lane >> 4), bm)) mask |= 1 << i;
+  return mask;
+}
+
+// Adds a superblock's products to the four row sums of this lane (cj: the
+// right-hand side at this lane's column).  Entries above the block diagonal are
+// skipped (mask), not multiplied by zero, so a non-finite entry of c reaches
+// its own block and the later ones only.
+__device__ __forceinline__ void tri_fma(const double (&v)[4], double cj, bool diag, int mask,
+                                        double (&acc)[4]) {
+  if (diag) {   // uniform
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+      const double t = fma(v[i], cj, acc[i]);
+      acc[i] = (mask >> i) & 1 ? t : acc[i];
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < 4; ++i) acc[i] = fma(v[i], cj, acc[i]);
+  }
+}
+
+constexpr int kStepThreads = 512;
+constexpr int kMaxSuper = 32;   // superblocks of a chain step
+constexpr int kMaxRows = 512;
+
+// Sparse steps: Y u comes from the row products, x is updated by the companion
+// update's launch.  Workgroup i takes superblock rows i and nsb - 1 - i, four
+// waves each (wave w the columns J = w mod 4).
+__global__ __launch_bounds__(kStepThreads) void chain_delta_kernel(
+    const double* __restrict__ tri, const double* __restrict__ Yu, const int32_t* __restrict__ idx,
+    const double* __restrict__ x, const double* __restrict__ y, int m, int b, int gb, int nsb,
+    int mode, double lambda, double n, double* __restrict__ delta, int* status) {
+  __shared__ double c[kMaxSuper * 16];
+  __shared__ double red[2][4][16];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int I = wave < 4 ? (int)blockIdx.x : nsb - 1 - (int)blockIdx.x;
+  const int w = wave & 3;
+  const gptr<const double> T = glb(tri) + (int64_t)tri_block(I, 0) * 256;
+  const int diag = diag_mask(block_mul(b), lane);
+  constexpr int U = 8;   // columns in flight (at most 8 per wave: J < 32)
+  double v[U][4];
+#pragma unroll
+  for (int q = 0; q < U; ++q) tri_load(T + (int64_t)min(w + 4 * q, I) * 256, lane, v[q]);
+  c[tid] = 0.0;
+  lds_barrier();
+  if (tid < m) {
+    const int i = idx[tid];
+    c[tid / gb * 16 + tid % gb] =
+        rhs_of(mode, lambda, n, Yu[tid], x[i], mode == 0 ? 0.0 : y[i]);
+  }
+  lds_barrier();
+  double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+  for (int q = 0; q < U; ++q) {
+    const int J = w + 4 * q;
+    if (J <= I) tri_fma(v[q], c[J * 16 + (lane & 15)], J == I, diag, acc);
+  }
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const double s = d16_row_sum(acc[i]);
+    if ((lane & 15) == 0) red[wave >> 2][w][4 * i + (lane >> 4)] = s;
+  }
+  lds_barrier();
+  if (tid < 32) {
+    const int h = tid >> 4, r = tid & 15;
+    const int Ir = h == 0 ? (int)blockIdx.x : nsb - 1 - (int)blockIdx.x;
+    const int p = Ir * gb + r;
+    if (r < gb && p < m && (h == 0 || Ir != (int)blockIdx.x)) {
+      const double d = (red[h][0][r] + red[h][1][r]) + (red[h][2][r] + red[h][3][r]);
+      delta[p] = d;
+      if (!isfinite(d)) raise_status(status, DEV_NONFINITE);
+    }
+  }
+}
+
+// ------------------------------------------------------------------ dense steps
+
+template <int FMT>
+struct Chunk {
+  static constexpr int ES = FMT == CABCD_F64 ? 8 : (FMT == CABCD_BF16 ? 2 : 1);
+  static constexpr int EPC = 16 / ES;
+  // 16 bytes of a row.  FP64 rows may start on any 8-byte boundary: the load
+  // needs dword alignment only (codes: 16-byte boundaries).
+  static __device__ __forceinline__ uint4 load(gptr<const uint8_t> p) {
+    typedef unsigned int uv4 __attribute__((ext_vector_type(4)));
+    typedef unsigned int uv4_8 __attribute__((ext_vector_type(4), aligned(8)));
+    if constexpr (FMT == CABCD_F64) {
+      const uv4_8 t = *(gptr<const uv4_8>)p;
+      return make_uint4(t.x, t.y, t.z, t.w);
+    } else {
+      const uv4 t = *(gptr<const uv4>)p;
+      return make_uint4(t.x, t.y, t.z, t.w);
+    }
+  }
+  static __device__ __forceinline__ void decode(const uint4& x, double (&e)[EPC]) {
+    if constexpr (FMT == CABCD_F64)
+      __builtin_memcpy(e, &x, 16);
+    else
+      ldev::lp_decode_all<FMT>(x, e);
+  }
+  // element e of a row
+  static __device__ __forceinline__ double one(gptr<const uint8_t> row, int64_t e) {
+    if constexpr (FMT == CABCD_F64)
+      return *(gptr<const double>)(row + 8 * e);
+    else if constexpr (FMT == CABCD_BF16)
+      return decode_bf16(*(gptr<const uint16_t>)(row + 2 * e));
+    else
+      return (double)__builtin_amdgcn_cvt_pk_f32_fp8((int)row[e], false)[0];
+  }
+};
+
+__device__ __forceinline__ double wave_total(double v) {
+  v = d16_row_sum(v);
+  return (gdev::d16_read_lane(v, 0) + gdev::d16_read_lane(v, 16)) +
+         (gdev::d16_read_lane(v, 32) + gdev::d16_read_lane(v, 48));
+}
+
+// LDS of a step launch (doubles): the row sums of Y u, c, delta, then the slab
+// of u, then the region where row groups and waves meet.
+__host__ __device__ constexpr int64_t step_lds(int epc, int lc, int m) {
+  const int slab = lc * epc;
+  const int groups = lc >= 64 ? kStepThreads : 8 * lc;   // (row group, chunk) pairs that meet
+  const int part = lc > 64 ? lc / 64 * m : 0;
+  return 2 * kStepThreads + kMaxSuper * 16 + kMaxRows + slab +
+         (groups * epc > part ? groups * epc : part);
+}
+
+// One launch of the chain of dense steps (see the file header).  Workgroups
+// x < slabs take LC = 2^lc whole 16-byte chunks of the columns each: thread t
+// owns chunk t % LC for the rows t / LC + RG q (RG = 512 / LC row groups; LC is
+// 16 or at least 64, so a chunk's lanes meet inside rows of sixteen or whole
+// waves).  With `tail` one more takes the columns past the last whole chunk,
+// thread p row p.  The last one updates x.
+//
+// Everything a workgroup reads from memory is asked for up front, with no
+// branch between the loads (clamped places instead), because the launch is a
+// chain of latencies: row indices, rows, partial sums and T^-1 in one go, then
+// LDS-only barriers, which leave the loads in flight.  Sums over slabs, row
+// groups and lanes run in fixed orders, and the products with the next step's
+// rows are the same code with and without the step before them, so a run gives
+// the same bits however it is split into calls.
+//
+// TALL: more than kFewRows rows a step (few slabs, deep prefetch, one workgroup
+// a CU); else two workgroups fit a CU, so that 256 wide slabs and the
+// workgroup that updates x run at once.
+constexpr int kFewRows = 32;
+constexpr int kPrefetchWgs = 8;
+template <int FMT, bool TALL>
+__global__ __launch_bounds__(kStepThreads, TALL ? 2 : 4) void chain_step_kernel(ChainStep a) {
+  using C = Chunk<FMT>;
+  constexpr int ES = C::ES, EPC = C::EPC;
+  // rows in flight per thread and pass
+  constexpr int U = FMT == CABCD_F64 ? 8 : TALL || FMT == CABCD_BF16 ? 4 : 2;
+  constexpr int PT = TALL ? 6 : 2;                 // superblocks of T^-1 in flight per wave
+  constexpr int UP = TALL ? 12 : 2;                // partial sums in flight per thread
+  extern __shared__ __attribute__((aligned(16))) double sm[];
+  const int m = a.m, LC = 1 << a.lc, RG = kStepThreads >> a.lc;
+  double* red = sm;
+  double* c = red + 2 * kStepThreads;
+  double* dl = c + kMaxSuper * 16;
+  double* us = dl + kMaxRows;
+  double* meet = us + (int64_t)LC * EPC;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  // workgroups past the one that updates x bring the next step's T^-1 into the
+  // L2 caches (workgroups go to the eight XCDs in turn)
+  const int nwork = (int)gridDim.x - (a.tri1 != nullptr ? kPrefetchWgs : 0);
+  if ((int)blockIdx.x >= nwork) {
+    const gptr<const uint4> t1 = (gptr<const uint4>)glb(a.tri1);
+    const int n = tri_block(a.nsb, 0) * 128;   // 16-byte pieces
+    for (int q = threadIdx.x; q < n; q += 4 * kStepThreads) {
+      typedef unsigned int uv4 __attribute__((ext_vector_type(4)));
+      uv4 v[4];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) v[i] = *(gptr<const uv4>)(t1 + min(q + i * kStepThreads, n - 1));
+#pragma unroll
+      for (int i = 0; i < 4; ++i) asm volatile("" ::"v"(v[i]));
+    }
+    return;
+  }
+  const bool xwg = (int)blockIdx.x == nwork - 1;            // updates x
+  const bool twg = a.tail && (int)blockIdx.x == a.nslab - 1;   // the ragged columns
+  const int cp = tid & (LC - 1), rg = tid >> a.lc;
+  const int64_t nchunk = a.cols / EPC;
+  const int64_t chunk = (int64_t)blockIdx.x * LC + cp;
+  const bool live = chunk < nchunk;
+  const bool upd = a.step && a.upd;
+  const bool dots = a.idx1 != nullptr;
+  const int64_t kb = (live ? chunk : 0) * 16;               // byte offset in a row
+  const gptr<const uint8_t> A = glb(a.A) + kb;
+  const int32_t* ixa = upd ? a.idx : a.ix;                  // a.ix: any step's indices
+  const int32_t* ixb = dots ? a.idx1 : a.ix;
+
+  // ---- the loads
+  int i0[U], i1[U];
+  auto load_index = [&](const int32_t* ix, int p0, int(&i)[U]) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) i[q] = ix[min(p0 + q * RG, m - 1)];
+  };
+  load_index(ixa, rg, i0);
+  load_index(ixb, rg, i1);
+  // partial Y u: a thread adds two neighbouring rows of the slabs gp + NG t
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  const int PS = 1 << a.ps, PH = PS >> 1, gp = tid >> (a.ps - 1), NG = kStepThreads >> (a.ps - 1);
+  const int pt = min(tid, m - 1);
+  const double xi = a.xg[pt];
+  const double sc = FMT != CABCD_F64 ? a.xg[m + pt] : 1.0;
+  dv2 pv[UP];
+  const gptr<const double> P = glb(a.P) + 2 * (tid & (PH - 1));
+  const int np = (a.nslab + NG - 1) / NG;   // partial sums a thread adds
+  auto pload = [&](int t0) {
+#pragma unroll
+    for (int t = 0; t < UP; ++t)
+      pv[t] = *(gptr<const dv2>)(P + (int64_t)min(gp + (t0 + t) * NG, a.nslab - 1) * PS);
+  };
+  pload(0);
+  // this wave's superblocks: the rows w, 15 - w, 16 + w and 31 - w below nsb
+  double ring[PT][4];
+  int In = wave, Jn = 0;   // the next superblock to load
+  int I = wave, J = 0;     // the next superblock to use
+  const gptr<const double> T = glb(a.tri);
+  auto tload = [&](double(&v)[4]) {
+    const int blk = In < a.nsb ? tri_block(In, Jn) : 0;
+    tri_load(T + (int64_t)blk * 256, lane, v);
+    const bool end = Jn == In;
+    Jn = end ? 0 : Jn + 1;
+    In += !end ? 0 : (In & 8) ? 2 * wave + 1 : 15 - 2 * wave;
+  };
+#pragma unroll
+  for (int t = 0; t < PT; ++t) tload(ring[t]);
+  uint4 c0[U], c1[U];
+  auto load_rows = [&](const int(&ix)[U], uint4(&v)[U]) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) v[q] = C::load(A + (int64_t)ix[q] * a.ld * ES);
+  };
+  load_rows(i0, c0);
+  load_rows(i1, c1);
+  double uo[EPC];   // (the owners of u are the threads below LC)
+  {
+    const gptr<const double> ug = glb(a.u) + (live ? chunk : 0) * EPC;
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) uo[e] = ug[e];
+  }
+
+  // ---- c and delta = T^-1 c
+  if (a.step) {
+    double y0 = 0.0, y1 = 0.0;
+    for (int t0 = 0;;) {
+#pragma unroll
+      for (int t = 0; t < UP; ++t) {
+        const bool in = gp + (t0 + t) * NG < a.nslab;
+        y0 += in ? pv[t].x : 0.0;
+        y1 += in ? pv[t].y : 0.0;
+      }
+      t0 += UP;
+      if (t0 >= np) break;
+      pload(t0);
+    }
+    for (int off = PH; off < 64; off <<= 1) {
+      y0 += __shfl_xor(y0, off, 64);
+      y1 += __shfl_xor(y1, off, 64);
+    }
+    const int groups = PH < 64 ? 8 : NG;
+    if (PH >= 64 || lane < PH)
+      *reinterpret_cast<dv2*>(red + (PH >= 64 ? gp : wave) * PS + 2 * (tid & (PH - 1))) =
+          dv2{y0, y1};
+    c[tid] = 0.0;
+    lds_barrier();
+    if (tid < m) {
+      double v[8], s = 0.0;
+#pragma unroll
+      for (int g = 0; g < 8; ++g) v[g] = red[min(g, groups - 1) * PS + tid];
+#pragma unroll
+      for (int g = 0; g < 8; ++g) s += g < groups ? v[g] : 0.0;
+      const int sb = (tid * a.gbm) >> 16;   // tid / gb
+      c[16 * sb + tid - sb * a.gb] = rhs_of(a.mode, a.lambda, a.n, sc * s, xi, 0.0);
+    }
+    lds_barrier();
+    const int diag = diag_mask(a.bm, lane);
+    double acc[4] = {0.0, 0.0, 0.0, 0.0};
+    while (I < a.nsb) {
+#pragma unroll
+      for (int t = 0; t < PT; ++t) {
+        if (I < a.nsb) {   // uniform
+          tri_fma(ring[t], c[J * 16 + (lane & 15)], J == I, diag, acc);
+          tload(ring[t]);
+          if (J++ == I) {
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+              const double s = d16_row_sum(acc[i]);
+              acc[i] = 0.0;
+              const int row = 4 * i + (lane >> 4);
+              if ((lane & 15) == 0 && row < a.gb && I * a.gb + row < m) dl[I * a.gb + row] = s;
+            }
+            J = 0;
+            I += (I & 8) ? 2 * wave + 1 : 15 - 2 * wave;
+          }
+        }
+      }
+    }
+    lds_barrier();
+  }
+
+  // ---- x[idx] += delta, and x at the next step's indices
+  if (xwg) {
+    if (a.step) {
+      if (tid < m && !isfinite(dl[tid])) raise_status(a.status, DEV_NONFINITE);
+      cdev::scatter_delta<kStepThreads>(a.idx, a.link, dl, m, a.x);
+      __syncthreads();
+    }
+    if (dots && tid < m) {   // (the dual's right-hand side takes x + y)
+      const int i = a.idx1[tid];
+      a.xg1[tid] = a.mode != 0 ? a.x[i] + a.y[i] : a.x[i];
+      if (FMT != CABCD_F64) a.xg1[m + tid] = a.rs != nullptr ? (double)a.rs[i] : 1.0;
+    }
+    return;
+  }
+  if (FMT != CABCD_F64 && upd && a.rs != nullptr) {
+    if (tid < m) dl[tid] *= sc;
+    lds_barrier();
+  }
+
+  // ---- the ragged columns: thread p holds row p's elements
+  if (twg) {
+    const int rem = (int)(a.cols - nchunk * EPC);
+    const gptr<const uint8_t> At = glb(a.A);
+    const gptr<const uint8_t> row0 = At + (int64_t)ixa[pt] * a.ld * ES;
+    const gptr<const uint8_t> row1 = At + (int64_t)ixb[pt] * a.ld * ES;
+    double t1 = 0.0;
+    for (int e = 0; e < rem; ++e) {
+      const int64_t k = nchunk * EPC + e;
+      double un = glb(a.u)[k];
+      if (upd) {
+        const double d = tid < m ? dl[tid] : 0.0;
+        const double x = tid < m ? C::one(row0, k) : 0.0;
+        const double w = wave_total(x * d);
+        if (lane == 0) red[wave] = w;
+        lds_barrier();
+        double s = 0.0;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) s += red[g];
+        lds_barrier();
+        un += a.gamma * s;
+        if (tid == 0) glb(a.u)[k] = un;
+      }
+      if (dots && tid < m) t1 = fma(C::one(row1, k), un, t1);
+    }
+    if (dots && tid < m) a.P1[(int64_t)blockIdx.x * PS + tid] = t1;
+    return;
+  }
+
+  // ---- the slab of u
+  if (upd) {
+    double acc[EPC];
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
+    for (int p0 = rg;;) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) {
+        const int p = p0 + q * RG;
+        double x[EPC];
+        C::decode(c0[q], x);
+        const double d = dl[min(p, m - 1)];
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[e] = p < m ? fma(x[e], d, acc[e]) : acc[e];
+      }
+      p0 += U * RG;
+      if (p0 - rg >= m) break;   // uniform
+      load_index(ixa, p0, i0);
+      load_rows(i0, c0);
+    }
+    // the row groups of a chunk: inside a wave, then through LDS
+    if (LC == 16) {
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], 16, 64);
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] += __shfl_xor(acc[e], 32, 64);
+    }
+    const int groups = LC == 16 ? 8 : RG;
+    if (groups > 1) {
+      if (LC >= 64 || lane < 16) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e)
+          meet[((LC == 16 ? wave : rg) * EPC + e) * LC + cp] = acc[e];
+      }
+      lds_barrier();
+      if (tid < LC) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) {
+          double s = 0.0, v[8];
+#pragma unroll
+          for (int g = 0; g < 8; ++g) v[g] = meet[(min(g, groups - 1) * EPC + e) * LC + tid];
+#pragma unroll
+          for (int g = 0; g < 8; ++g) s += g < groups ? v[g] : 0.0;
+          acc[e] = s;
+        }
+      }
+    }
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) uo[e] += a.gamma * acc[e];
+    if (tid < LC && live) {
+      const gptr<double> ug = glb(a.u) + chunk * EPC;
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) ug[e] = uo[e];
+    }
+  }
+  if (!dots) return;
+
+  // ---- the slab's products with the next step's rows
+  if (tid < LC) {
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) us[e * LC + tid] = uo[e];
+  }
+  lds_barrier();
+  double ul[EPC];
+#pragma unroll
+  for (int e = 0; e < EPC; ++e) ul[e] = us[e * LC + cp];
+  const gptr<double> P1 = glb(a.P1) + (int64_t)blockIdx.x * PS;
+  for (int p0 = rg;;) {
+    double t[U];
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      double x[EPC];
+      C::decode(c1[q], x);
+      t[q] = 0.0;
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) t[q] = fma(x[e], ul[e], t[q]);
+      t[q] = live ? t[q] : 0.0;
+    }
+    if (LC == 16) {
+#pragma unroll
+      for (int q = 0; q < U; ++q) t[q] = d16_row_sum(t[q]);
+      if (cp == 0) {
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+          if (p0 + q * RG < m) P1[p0 + q * RG] = t[q];
+      }
+    } else {
+#pragma unroll
+      for (int q = 0; q < U; ++q) t[q] = wave_total(t[q]);
+      if (lane == 0) {
+#pragma unroll
+        for (int q = 0; q < U; ++q)
+          if (p0 + q * RG < m) {
+            if (LC == 64)
+              P1[p0 + q * RG] = t[q];
+            else
+              meet[(wave & (LC / 64 - 1)) * m + p0 + q * RG] = t[q];
+          }
+      }
+    }
+    p0 += U * RG;
+    if (p0 - rg >= m) break;   // uniform
+    load_index(ixb, p0, i1);
+    load_rows(i1, c1);
+  }
+  if (LC > 64) {
+    lds_barrier();
+    if (tid < m) {
+      double s = 0.0;
+      for (int w = 0; w < LC / 64; ++w) s += meet[w * m + tid];
+      P1[tid] = s;
+    }
+  }
+}
+
+}  // namespace
+
+ChainPlan chain_plan(int m, int b) {
+  ChainPlan p{};
+  if (b < 1 || b > 16 || m < 1 || m > kMaxRows || m % b != 0) return p;
+  p.gb = 16 / b * b;
+  p.nsb = (m + p.gb - 1) / p.gb;
+  p.ok = p.nsb <= kMaxSuper;
+  p.tri = (size_t)tri_block(p.nsb, 0) * 256;
+  p.dinv = (size_t)p.nsb * 256;
+  return p;
+}
+
+hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
+                                const int32_t* idx, double* tri, double* dinv, int* link,
+                                int* status, hipStream_t st) {
+  if (!p.ok || nsteps < 1 || nsteps > 65535) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(chain_diag_kernel, dim3((unsigned)((p.nsb + 3) / 4), (unsigned)nsteps),
+                     dim3(64), 0, st, G, m, b, p.gb, p.nsb, tri, dinv, status);
+  hipError_t e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  const size_t lds = std::max((size_t)(2 * kPanelWaves + p.nsb) * 256 * sizeof(double),
+                              (size_t)m * sizeof(int));
+  const bool full = p.gb == 16 && m % 16 == 0;
+  auto kern = full ? chain_panel_kernel<true> : chain_panel_kernel<false>;
+  if (lds > 64 * 1024) {
+    e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                            hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb, (unsigned)nsteps), dim3(64 * kPanelWaves), lds,
+                     st, G, m, p.gb, p.nsb, tri, dinv, idx, link);
+  return hipGetLastError();
+}
+
+hipError_t launch_chain_delta(const ChainPlan& p, const double* tri, const double* Yu,
+                              const int32_t* idx, const double* x, const double* y, int m, int b,
+                              int mode, double lambda, double n, double* delta, int* status,
+                              hipStream_t st) {
+  if (!p.ok) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(chain_delta_kernel, dim3((unsigned)((p.nsb + 1) / 2)), dim3(kStepThreads), 0,
+                     st, tri, Yu, idx, x, y, m, b, p.gb, p.nsb, mode, lambda, n, delta, status);
+  return hipGetLastError();
+}
+
+// The slabs of u: 16 or 64 to 512 chunks a workgroup, so that at most 256
+// workgroups share the columns.  Narrow slabs spread a step's rows over more
+// CUs; every workgroup reads all slabs' partial Y u.
+ChainSlabs chain_slabs(int dtype, int m, int64_t cols) {
+  const int epc = dtype == CABCD_F64 ? 2 : (dtype == CABCD_BF16 ? 8 : 16);
+  const int64_t chunks = cols / epc;
+  ChainSlabs s{};
+  s.lc = 4;
+  while (s.lc < 9 && chunks > (int64_t)256 << s.lc) s.lc = s.lc == 4 ? 6 : s.lc + 1;
+  s.tail = cols % epc != 0 ? 1 : 0;
+  s.nslab = (int)((chunks + (1 << s.lc) - 1) >> s.lc) + s.tail;
+  s.ps = 1;
+  while ((1 << s.ps) < m) ++s.ps;
+  s.partial = (size_t)s.nslab << s.ps;
+  return s;
+}
+
+hipError_t launch_chain_step(int dtype, const ChainStep& step, hipStream_t st) {
+  ChainStep a = step;
+  const int epc = dtype == CABCD_F64 ? 2 : (dtype == CABCD_BF16 ? 8 : 16);
+  if (a.m < 1 || a.m > kMaxRows || a.nsb > kMaxSuper || a.lc < 4 || a.lc == 5 || a.lc > 9 ||
+      a.ps < 1 || (1 << a.ps) < a.m || (1 << a.ps) > kStepThreads || a.cols < epc)
+    return hipErrorInvalidValue;
+  const unsigned grid = ((a.step && a.upd) || a.idx1 != nullptr ? a.nslab : 0) + 1 +
+                        (a.tri1 != nullptr ? kPrefetchWgs : 0);
+  const size_t lds = (size_t)step_lds(epc, 1 << a.lc, a.m) * sizeof(double);
+  a.bm = block_mul(a.b);
+  a.gbm = (65535 + a.gb) / a.gb;
+  const bool tall = a.m > kFewRows;
+  using Kern = void (*)(ChainStep);
+  const Kern kerns[3][2] = {
+      {chain_step_kernel<CABCD_F64, false>, chain_step_kernel<CABCD_F64, true>},
+      {chain_step_kernel<CABCD_BF16, false>, chain_step_kernel<CABCD_BF16, true>},
+      {chain_step_kernel<CABCD_FP8_E4M3, false>, chain_step_kernel<CABCD_FP8_E4M3, true>}};
+  const Kern kern = kerns[dtype == CABCD_F64 ? 0 : (dtype == CABCD_BF16 ? 1 : 2)][tall ? 1 : 0];
+  if (lds > 64 * 1024) {   // beyond the default limit (wide slabs of codes)
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL(kern, dim3(grid), dim3(kStepThreads), lds, st, a);
+  return hipGetLastError();
+}
+
+}  // namespace cabcd

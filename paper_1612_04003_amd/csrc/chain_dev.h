@@ -1,0 +1,32 @@
+// Device code shared by the kernels of the outer-step chain (chain.hip) and the
+// CSR updates that finish a chain step: the geometry of the block-triangular
+// inverse and the coordinate update x[idx] += delta.
+#pragma once
+
+#include "internal.h"
+
+namespace cabcd {
+namespace cdev {
+
+// Link word of row p of an outer step: bit 16 set when no earlier row has the
+// same index; low 16 bits: 1 + the next row with the same index (0: none).
+constexpr int kLinkFirst = 1 << 16;
+
+// x[idx] += delta for one step by one workgroup of T threads, a single writer
+// per coordinate: the first row of an index adds that index's rows in row order.
+template <int T>
+__device__ __forceinline__ void scatter_delta(const int32_t* __restrict__ idx,
+                                              const int* __restrict__ link, const double* delta,
+                                              int m, double* __restrict__ x) {
+  for (int p = threadIdx.x; p < m; p += T) {
+    int l = link[p];
+    if ((l & kLinkFirst) == 0) continue;
+    const int i = idx[p];
+    double v = x[i] + delta[p];
+    for (int q = (l & 0xFFFF) - 1; q >= 0; q = (link[q] & 0xFFFF) - 1) v += delta[q];
+    x[i] = v;
+  }
+}
+
+}  // namespace cdev
+}  // namespace cabcd

@@ -21,7 +21,7 @@
 // and the exact recomputations scatter into the columns of the gathered rows;
 // columns shared by several rows (popular features) meet in FP64 atomic adds,
 // so these results are reproducible up to the order of those additions.
-#include "internal.h"
+#include "chain_dev.h"
 
 #include <algorithm>
 
@@ -282,11 +282,16 @@ __global__ __launch_bounds__(kCsrThreads) void csr_gram_tile_kernel(
   }
 }
 
-// out[col] += gamma * v[p] * A[row(p)][col] for the entries of rows p < m.
+// out[col] += gamma * v[p] * A[row(p)][col] for the entries of rows p < m; with
+// xs.x the last workgroup does the step's x[idx] += delta instead.
 __global__ __launch_bounds__(kCsrThreads) void csr_scatter_kernel(
     const int64_t* __restrict__ rowptr, const int32_t* __restrict__ colidx,
     const double* __restrict__ vals, const int32_t* __restrict__ idx, int64_t m,
-    const double* __restrict__ v, double gamma, double* __restrict__ out) {
+    const double* __restrict__ v, double gamma, double* __restrict__ out, XScatter xs) {
+  if (xs.x != nullptr && blockIdx.x == gridDim.x - 1) {
+    cdev::scatter_delta<kCsrThreads>(xs.idx, xs.link, xs.delta, xs.m, xs.x);
+    return;
+  }
   const int lane = threadIdx.x & 63;
   const int64_t p = (int64_t)blockIdx.x * kCsrWaves + (threadIdx.x >> 6);
   if (p >= m) return;
@@ -406,10 +411,11 @@ hipError_t launch_csr_rowdot_rows(const CsrView& A, const int32_t* idx, int64_t 
 }
 
 hipError_t launch_csr_scatter(const CsrView& A, const int32_t* idx, int64_t m, const double* v,
-                              double gamma, double* out, hipStream_t st) {
+                              double gamma, double* out, const XScatter& xs, hipStream_t st) {
   if (m <= 0) return hipSuccess;
-  hipLaunchKernelGGL(csr_scatter_kernel, dim3((unsigned)((m + kCsrWaves - 1) / kCsrWaves)),
-                     dim3(kCsrThreads), 0, st, A.rowptr, A.colidx, A.vals, idx, m, v, gamma, out);
+  const unsigned grid = (unsigned)((m + kCsrWaves - 1) / kCsrWaves) + (xs.x != nullptr ? 1 : 0);
+  hipLaunchKernelGGL(csr_scatter_kernel, dim3(grid), dim3(kCsrThreads), 0, st, A.rowptr, A.colidx,
+                     A.vals, idx, m, v, gamma, out, xs);
   return hipGetLastError();
 }
 

@@ -30,7 +30,7 @@
 // Heavy slots are numbered in column order; the heavy columns are picked from
 // the column counts of a sample of the rows: any split gives the same Gram,
 // the choice only affects speed.
-#include "internal.h"
+#include "chain_dev.h"
 
 #include <algorithm>
 
@@ -712,12 +712,17 @@ struct UpdateArgs {
   double gamma;
   double* out;
   int bh, bs, bq;    // workgroups of the heavy, single and short parts (then long)
+  XScatter xs;       // with xs.x the last workgroup does x[idx] += delta
 };
 
 // One launch, four parts by workgroup range (each writes distinct columns).
 __global__ __launch_bounds__(kT) void split_update_kernel(UpdateArgs u) {
   const int lane = threadIdx.x & 63;
   int blk = blockIdx.x;
+  if (u.xs.x != nullptr && blk == (int)gridDim.x - 1) {
+    cdev::scatter_delta<kT>(u.xs.idx, u.xs.link, u.xs.delta, u.xs.m, u.xs.x);
+    return;
+  }
   if (blk < u.bh) {   // heavy: one wave per slot
     const int h = (int)(((int64_t)blk * kT + threadIdx.x) >> 6);
     if (h >= u.heavy) return;
@@ -764,7 +769,7 @@ __global__ __launch_bounds__(kT) void split_update_kernel(UpdateArgs u) {
     return;
   }
   blk -= u.bq;   // long lists: a wave each
-  const int64_t nw = ((int64_t)(gridDim.x - u.bh - u.bs - u.bq) * kT) >> 6;
+  const int64_t nw = ((int64_t)kUpdateGrid * kT) >> 6;
   const int nl = u.segn[1];
   for (int64_t i = ((int64_t)blk * kT + threadIdx.x) >> 6; i < nl; i += nw) {
     const Seg sg = u.lsegs[i];
@@ -899,7 +904,7 @@ SplitBufs split_bufs(const SplitLayout& L, const CsrSplitInfo& info, int m, int 
 hipError_t launch_csr_update_split(const CsrView& A, const CsrSplitInfo& info,
                                    const int32_t* idx, int m, int nsteps, int step,
                                    const double* delta, double gamma, double* out, double* dws,
-                                   int* iws, hipStream_t st) {
+                                   int* iws, const XScatter& xs, hipStream_t st) {
   if (m < 1 || m > kSplitMaxRows || step < 0 || step >= nsteps) return hipErrorInvalidValue;
   const SplitLayout L = csr_split_layout(info, A.cols, m, nsteps);
   const SplitBufs B = split_bufs(L, info, m, nsteps, dws, iws);
@@ -927,8 +932,10 @@ hipError_t launch_csr_update_split(const CsrView& A, const CsrSplitInfo& info,
   u.bh = (info.heavy + kT / 64 - 1) / (kT / 64);
   u.bs = (int)(((int64_t)m * u.nchunk * 64 + kT - 1) / kT);
   u.bq = kUpdateGrid;
-  hipLaunchKernelGGL(split_update_kernel, dim3(u.bh + u.bs + u.bq + kUpdateGrid), dim3(kT), 0,
-                     st, u);
+  u.xs = xs;
+  hipLaunchKernelGGL(split_update_kernel,
+                     dim3(u.bh + u.bs + u.bq + kUpdateGrid + (xs.x != nullptr ? 1 : 0)), dim3(kT),
+                     0, st, u);
   return hipGetLastError();
 }
 

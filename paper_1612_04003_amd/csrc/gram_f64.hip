@@ -75,7 +75,12 @@ __global__ __launch_bounds__(D16::THREADS) void gram_f64_dma16_upd_kernel(
 // each) for 1024 / GROUPS entries.  Many splits take 16 groups of 64 entries;
 // a few splits take one group, each thread summing all of its entry's splits.
 constexpr int kRedThreads = 1024;
-int red_groups(int nsplit) { return nsplit <= 4 ? 1 : 16; }
+// So does a launch of many entries with up to 16 splits: 16 groups of one split
+// each add in the same order, but load one value a thread (73 MB of 13 Grams'
+// partials: 2.3 TB/s).
+int red_groups(int nsplit, int64_t entries) {
+  return nsplit <= 4 || (nsplit <= 16 && entries >= (1 << 18)) ? 1 : 16;
+}
 
 // Partial set blockIdx.y: partials + set * nsplit * pstride.  MODE 0: the
 // Gram of step blockIdx.y (idx + step * m, G and add + step * m * m; Yu is
@@ -310,7 +315,7 @@ hipError_t launch_gram_reduce(const GramPlan& p, const double* partials, const i
                               int nsteps, const double* add) {
   if (nsteps < 1 || nsteps > 65535 || (nsteps > 1 && Yu != nullptr)) return hipErrorInvalidValue;
   const int64_t entries = (int64_t)p.nblk * 256 + 16 * p.nb;
-  const int groups = red_groups(p.nsplit);
+  const int groups = red_groups(p.nsplit, entries * nsteps);
   const int64_t blocks = (entries + kRedThreads / groups - 1) / (kRedThreads / groups);
   launch_reduce<0>(groups, dim3((unsigned)blocks, (unsigned)nsteps), st, partials, p.nsplit, p.nb,
                    idx, m, scale, shift, overlap ? 1 : 0, G, Yu, layout, rs, add, 1);
@@ -333,7 +338,7 @@ hipError_t launch_gram_reduce_big(const GramPlan& p, const double* partials, con
   if (p.nb != 16 || m <= 256 || m > 512 || ngram < 1 || (ngram > 1 && Yu != nullptr))
     return hipErrorInvalidValue;
   const int64_t entries = (int64_t)p.nblk * 256 + 16 * p.nb;
-  const int groups = red_groups(p.nsplit);
+  const int groups = red_groups(p.nsplit, entries * 2 * ngram);
   const int64_t blocks = (entries + kRedThreads / groups - 1) / (kRedThreads / groups);
   const size_t set = gram_partial_doubles(p);
   const int nc = big_cross_steps(m);

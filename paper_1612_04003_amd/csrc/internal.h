@@ -211,6 +211,75 @@ hipError_t launch_solve(const SolveArgs& a, hipStream_t st);
 // that is not positive sets *status to "not positive definite".
 hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, int* status, hipStream_t st);
 
+// ------------------------------------------------------------------ chain of steps
+// Outer steps whose Grams are computed ahead (chain.hip): the inverse of each
+// Gram's lower block triangle formed ahead, so a step's solves are one product.
+struct ChainPlan {
+  bool ok;            // b <= 16 and at most 32 superblocks
+  int gb, nsb;        // rows of a superblock (b floor(16 / b)), superblocks
+  size_t tri, dinv;   // doubles a step: the inverse, and its scratch
+};
+ChainPlan chain_plan(int m, int b);
+// From nsteps Grams (G + k m^2, indices idx + k m): the inverses (tri + k
+// p.tri), links of repeated indices (link + k m) and the pivot check; dinv
+// holds nsteps p.dinv doubles of scratch.
+hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
+                                const int32_t* idx, double* tri, double* dinv, int* link,
+                                int* status, hipStream_t st);
+// delta = T^-1 c of one step from its Y u (modes and scalars as SolveArgs).
+hipError_t launch_chain_delta(const ChainPlan& p, const double* tri, const double* Yu,
+                              const int32_t* idx, const double* x, const double* y, int m, int b,
+                              int mode, double lambda, double n, double* delta, int* status,
+                              hipStream_t st);
+// Column slabs of the dense step launches: 2^lc 16-byte chunks a slab, with
+// `tail` a last one of the columns past the whole chunks; partial Y u rows of
+// 2^ps >= m doubles a slab (`partial` doubles in all).
+struct ChainSlabs {
+  int lc, ps, nslab, tail;
+  size_t partial;
+};
+ChainSlabs chain_slabs(int dtype, int m, int64_t cols);
+// One launch of the dense chain.  step: delta of the step idx from its partial
+// Y u (P) and what its right-hand side takes at its indices (xg: m entries of x,
+// dual x + y, then for codes the m row scales), x[idx] += delta and, with upd, u
+// += gamma Y^T delta.  idx1 (may be NULL): the next step's P1 and xg1.
+// All pointers but idx1, rs and y must be readable in every launch.
+struct ChainStep {
+  const uint8_t* A;   // FP64 rows on 8-byte, codes on 16-byte boundaries; one chunk or more
+  int64_t ld, cols;
+  const float* rs;    // low precision: row scales (NULL = 1)
+  int m, b, gb, nsb;
+  int bm, gbm;        // set by the launcher: v / b and p / gb as products
+  int lc, ps, nslab, tail;
+  int step, upd;
+  const int32_t* ix;  // the indices of some step
+  const int32_t* idx;
+  const double* tri;
+  const int* link;
+  const double* P;
+  const double* xg;
+  const int32_t* idx1;
+  double* P1;
+  double* xg1;
+  const double* tri1;   // the next step's inverse, to be brought near (may be NULL)
+  double* u;
+  double* x;
+  const double* y;    // dual only
+  int mode;
+  double lambda, n, gamma;
+  int* status;
+};
+hipError_t launch_chain_step(int dtype, const ChainStep& a, hipStream_t st);
+// x[idx] += delta of a chain step, done by one more workgroup of a companion
+// update's launch (x NULL: none).
+struct XScatter {
+  const int32_t* idx;
+  const int* link;
+  const double* delta;
+  int m;
+  double* x;
+};
+
 // ------------------------------------------------------------------ low precision
 // Codes of A (rows x cols, FP64, ld lda) into Q (ld ldq elements) with FP32
 // row scales (FP8: amax/448; BF16: 1, row_scale may be NULL).
@@ -288,9 +357,9 @@ hipError_t launch_csr_gram_split(const CsrView& A, const CsrSplitInfo& info, con
 hipError_t launch_csr_update_split(const CsrView& A, const CsrSplitInfo& info,
                                    const int32_t* idx, int m, int nsteps, int step,
                                    const double* delta, double gamma, double* out, double* dws,
-                                   int* iws, hipStream_t st);
+                                   int* iws, const XScatter& xs, hipStream_t st);
 hipError_t launch_csr_scatter(const CsrView& A, const int32_t* idx, int64_t m, const double* v,
-                              double gamma, double* out, hipStream_t st);
+                              double gamma, double* out, const XScatter& xs, hipStream_t st);
 // out[p] = A[p] . v + beta * base[p] for every row.
 hipError_t launch_csr_rowdot(const CsrView& A, const double* v, const double* base, double beta,
                              double* out, hipStream_t st);

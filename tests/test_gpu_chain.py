@@ -1,0 +1,145 @@
+"""Outer steps whose Grams are computed ahead run as a chain: the inverse of each
+Gram's lower block triangle formed ahead, one launch per dense step.  Checked
+against the oracle (GPU) at the edges of its tiles: superblocks that the block
+size fills or pads, one to 32 of them, slabs of every width with ragged ends,
+rows on odd 8-byte boundaries, repeated indices, exact recomputations between
+steps, and the storage formats."""
+
+import numpy as np
+import pytest
+import scipy.sparse
+import torch
+
+import synth
+from oracle import bcd
+
+pytestmark = pytest.mark.gpu
+DEV = "cuda:0"
+
+
+def _rel(a, b):
+    a, b = np.asarray(a), np.asarray(b)
+    return np.linalg.norm(a - b) / np.linalg.norm(b)
+
+
+def _say(*a):
+    print("[chain]", *a, flush=True)
+
+
+# b, s: superblocks of 16 / b blocks: b = 1, 3 (15 rows), 6 (12), 9 (9), 16;
+# s b = 256 full, 9 x 28 = 252 in 28 superblocks, a partial last superblock
+@pytest.mark.parametrize("b,s", [(1, 1), (1, 37), (3, 17), (4, 64), (6, 25), (8, 32), (9, 28),
+                                 (12, 5), (16, 16), (7, 2)])
+@pytest.mark.parametrize("n,steps", [(1, 9), (31, 12), (257, 7), (2049, 37)])
+def test_primal_chain_matches_oracle(gpu_lib, b, s, n, steps):
+    """n = 1, 31: one slab, less than a chunk of it; 2049: a last slab of one
+    column; rows of n columns (odd: 8-byte boundaries)."""
+    d = max(40, b)
+    H = steps * s + s // 2
+    _say("primal", b, s, n, H)
+    X, y, _ = synth.gaussian_ridge(d, n, 10 * b + s + n)
+    w, r = gpu_lib.primal_bcd(X.to(DEV), y.to(DEV), 0.3, b, s, H, 5)
+    wo, zo = bcd.primal_bcd(X.numpy(), y.numpy(), 0.3, b, s, H, 5)
+    assert _rel(w.cpu(), wo) <= 1e-10
+    assert _rel(r.cpu(), zo - y.numpy()) <= 1e-10
+
+
+@pytest.mark.parametrize("d,b,s", [(30, 4, 8), (33, 5, 20), (1000, 8, 32), (4097, 2, 12),
+                                   (70001, 4, 3), (300001, 8, 2)])
+def test_dual_chain_matches_oracle(gpu_lib, d, b, s):
+    """Slabs of 32 to 1024 columns (and more slabs than 256)."""
+    n, H = 60, 21 * s
+    _say("dual", d, b, s)
+    X, y, _ = synth.gaussian_ridge(d, n, d + b)
+    a, w = gpu_lib.dual_bcd(X.t().contiguous().to(DEV), y.to(DEV), 1e-2, b, s, H, 6)
+    ao, wo = bcd.dual_bcd(X.numpy(), y.numpy(), 1e-2, b, s, H, 6)
+    assert _rel(a.cpu(), ao) <= 1e-10
+    assert _rel(w.cpu(), wo) <= 1e-10
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("n,pad,b,s", [(1000, True, 8, 12), (1001, False, 6, 5),
+                                       (20003, True, 4, 32), (600001, True, 4, 2)])
+def test_chain_codes(gpu_lib, dtype, n, pad, b, s):
+    """Stored codes, padded rows and rows on odd boundaries: the residual is that
+    of the iterate (FP64 passes over the codes), and the iterate is the FP64
+    run's on the dequantised matrix within the Gram's FP32 accumulation."""
+    d, steps = 64, 12
+    _say("codes", dtype, n, pad, b, s)
+    X, y, _ = synth.gaussian_ridge(d, n, n + b)
+    Q = gpu_lib.quantize(X.to(DEV), gpu_lib.BF16 if dtype == "bf16" else gpu_lib.FP8_E4M3)
+    Xh = Q.dequantize()
+    if not pad:
+        Q = gpu_lib.Quantized(Q.codes.contiguous(), Q.scales, Q.dtype)
+    yd = y.to(DEV)
+    w, r = gpu_lib.primal_bcd(Q, yd, 0.1, b, s, steps * s, 8)
+    assert _rel(r.cpu(), (Xh.t() @ w - yd).cpu()) <= 1e-11
+    wo, _ = bcd.primal_bcd(Xh.cpu().numpy(), y.numpy(), 0.1, b, s, steps * s, 8)
+    # each delta solves with a Gram of relative error 2^-24 sqrt(n) (FP8: 1e-5)
+    assert _rel(w.cpu(), wo) <= (1e-5 if dtype == "bf16" else 1e-3)
+
+
+def test_chain_repeated_indices_and_recomputation(gpu_lib):
+    """Blocks that repeat indices within a step many times over, with exact
+    recomputations between steps, monitor points, and the same run in calls."""
+    d, n, b, s, steps = 9, 515, 4, 16, 10
+    _say("repeats")
+    X, y, _ = synth.gaussian_ridge(d, n, 3)
+    rng = np.random.default_rng(1)
+    idx = np.concatenate([rng.permutation(d)[:b] for _ in range(steps * s)]).astype(np.int32)
+    Xd, yd = X.to(DEV), y.to(DEV)
+    ix = torch.tensor(idx, device=DEV)
+    wo, zo = bcd.primal_bcd(X.numpy(), y.numpy(), 0.2, b, s, steps * s, 0,
+                            explicit_idx=idx.reshape(-1, b))
+    w, r = gpu_lib.primal_bcd(Xd, yd, 0.2, b, s, steps * s, 0, explicit_idx=ix)
+    assert _rel(w.cpu(), wo) <= 1e-10 and _rel(r.cpu(), zo - y.numpy()) <= 1e-10
+    tr = torch.empty(5, dtype=torch.float64, device=DEV)
+    w2, r2 = gpu_lib.primal_bcd(Xd, yd, 0.2, b, s, steps * s, 0, explicit_idx=ix, resid_every=3,
+                                monitor_every=2, trace=tr)
+    assert _rel(w2.cpu(), wo) <= 1e-10 and _rel(r2.cpu(), zo - y.numpy()) <= 1e-10
+    w3 = torch.zeros(d, dtype=torch.float64, device=DEV)
+    r3 = -yd
+    for k0, k1 in ((0, 1), (1, 6), (6, 10)):
+        part = ix[k0 * s * b:k1 * s * b].contiguous()
+        gpu_lib.primal_bcd(Xd, yd, 0.2, b, s, (k1 - k0) * s, 0, w=w3, r=r3, explicit_idx=part,
+                           flags=gpu_lib.FLAG_STATE_VALID)
+    w4 = torch.zeros(d, dtype=torch.float64, device=DEV)
+    r4 = -yd
+    gpu_lib.primal_bcd(Xd, yd, 0.2, b, s, steps * s, 0, w=w4, r=r4, explicit_idx=ix,
+                       flags=gpu_lib.FLAG_STATE_VALID)
+    assert torch.equal(w3, w4) and torch.equal(r3, r4)
+
+
+def test_chain_short_workspace_and_pivot(gpu_lib):
+    """A caller workspace too small for the chain's buffers (but large enough for
+    the solves inside the steps) is accepted; a block that is not positive
+    definite is reported."""
+    d, n, b, s = 12, 300001, 4, 2
+    X, y, _ = synth.gaussian_ridge(d, n, 4)
+    Xd, yd = X.to(DEV), y.to(DEV)
+    w, r = gpu_lib.primal_bcd(Xd, yd, 0.1, b, s, 20 * s, 1)
+    ws = torch.empty(gpu_lib.workspace_bytes(Xd, b, s) // 3, dtype=torch.uint8, device=DEV)
+    w1, r1 = gpu_lib.primal_bcd(Xd, yd, 0.1, b, s, 20 * s, 1, workspace=ws)
+    assert _rel(w1.cpu(), w.cpu()) <= 1e-12 and _rel(r1.cpu(), r.cpu()) <= 1e-12
+    Xb = X.clone()
+    Xb[7] = float("nan")
+    with pytest.raises(gpu_lib.CabcdError) as e:
+        gpu_lib.primal_bcd(Xb.to(DEV), yd, 0.1, b, s, 20 * s, 1)
+    assert e.value.status == gpu_lib.ENOTSPD
+
+
+@pytest.mark.parametrize("b,s", [(16, 32), (9, 32), (8, 64), (5, 40), (16, 8), (4, 3), (1, 300)])
+def test_csr_chain_matches_oracle(gpu_lib, b, s):
+    """Sparse steps: the split Gram (s b >= 256) and the hash join, one to 32
+    superblocks, full and padded."""
+    n, d, H = 900, 700, 9 * s + 2
+    _say("csr", b, s)
+    rng = np.random.default_rng(b + s)
+    S = scipy.sparse.random(n, d, 0.03, format="csr", random_state=np.random.RandomState(b * s),
+                            data_rvs=rng.standard_normal)
+    y = rng.standard_normal(n)
+    a, w = gpu_lib.dual_bcd(gpu_lib.CSR.from_scipy(S, DEV), torch.tensor(y, device=DEV), 1e-2, b,
+                            s, H, 7)
+    ao, wo = bcd.dual_bcd(S.T.tocsc(), y, 1e-2, b, s, H, 7)
+    assert _rel(a.cpu(), ao) <= 1e-10
+    assert _rel(w.cpu(), wo) <= 1e-10
