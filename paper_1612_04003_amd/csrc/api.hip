@@ -231,7 +231,7 @@ hipError_t mat_scatter(const Mat& M, const int32_t* idx, int64_t m, const double
                        const XScatter& xs = XScatter{}) {
   if (M.lowp())
     return launch_gemv_t_lp(M.dtype, M.Q, M.ld, M.cols, M.rs, idx, m, v, gamma, base, beta,
-                            accumulate, out, st);
+                            accumulate, out, scratch, st);
   if (!M.csr)
     return launch_gemv_t(M.X, M.ld, M.cols, idx, m, v, gamma, base, beta, accumulate, out,
                          scratch, st);
@@ -255,6 +255,10 @@ hipError_t mat_rowdot(const Mat& M, const double* v, const double* base, double 
 size_t mat_scratch_doubles(const Mat& M, int64_t sb) {
   if (M.csr) return 1;
   size_t sc = std::max(gemv_t_scratch_doubles(sb, M.cols), gemv_t_scratch_doubles(M.rows, M.cols));
+  if (M.lowp()) {
+    sc = std::max(sc, gemv_t_lp_scratch_doubles(M.dtype, sb, M.cols));   // grows with the rows
+    sc = std::max(sc, gemv_t_lp_scratch_doubles(M.dtype, M.rows, M.cols));
+  }
   sc = std::max(sc, rowdot_scratch_doubles(M.rows, M.cols, M.dtype));
   sc = std::max(sc, rowdot_scratch_doubles(sb, M.cols, M.dtype));
   return std::max<size_t>(sc, 1);

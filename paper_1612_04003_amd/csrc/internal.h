@@ -296,10 +296,12 @@ hipError_t launch_gram_lp(const GramPlan& p, int dtype, const void* A, int64_t l
                           const int32_t* idx, int m, const double* u, double* partials,
                           hipStream_t st, int nsteps = 1);
 // out = [beta base | out] + gamma sum_p s[row(p)] v[p] decode(Q[row(p)]), FP64.
+// Needs a scratch of gemv_t_lp_scratch_doubles(dtype, m, cols) doubles (may be 0).
+size_t gemv_t_lp_scratch_doubles(int dtype, int64_t m, int64_t cols);
 hipError_t launch_gemv_t_lp(int dtype, const void* A, int64_t ld, int64_t cols, const float* rs,
                             const int32_t* idx, int64_t m, const double* v, double gamma,
                             const double* base, double beta, bool accumulate, double* out,
-                            hipStream_t st);
+                            double* scratch, hipStream_t st);
 
 // ------------------------------------------------------------------ CSR kernels
 struct CsrView {

@@ -441,43 +441,66 @@ hipError_t launch_lp_fmt(const GramPlan& p, const void* A, int64_t ld, int64_t c
 // ---------------------------------------------------------------- streaming pass
 // out[k] = (accumulate ? out[k] : beta base[k]) + gamma sum_p s[row(p)] v[p] dec(Q[row(p)][k])
 //
-// Each thread owns 16 bytes of codes per row (EPC columns); the RS threads of
-// a column chunk split the rows into RS consecutive ranges whose sums are
-// added in range order through LDS (deterministic).  FP8 takes two ranges: with
-// 16 columns per thread a pass over 2^20 columns has one wave per SIMD, too few
-// loads in flight to stream (3.6 TB/s; two ranges: 5.7 TB/s, four: 4.7).  BF16
-// (8 columns per thread) already has two waves per SIMD and streams best with
-// one range.  RIF rows are in flight per thread (16 measured slower).
-constexpr int kLvThreads = 256;
-template <int FMT> constexpr int kLvSlices = FMT == CABCD_BF16 ? 1 : 2;
+// Each lane owns 16 bytes of codes per row (EPC columns).  The rows are split
+// over the RS waves of a column group (ranges added in order through LDS) and,
+// where even sixteen waves leave CUs idle, over blockIdx.y (partial sums to
+// scratch, added in order by a second launch); deterministic.  lv_split picks
+// both: the pass streams from about 2048 waves on (FP8 over 2^20 columns, 4.3 GB:
+// one wave a column group 3.6 TB/s, two 6.0, four 4.7; BF16 has two waves a SIMD
+// with one), and columns alone give 16 codes x 64 lanes a wave: 2000 x 300001 FP8
+// took 0.65 ms with two waves a group (294 waves), 4187 x 618 BF16 one workgroup.
+// RIF rows are in flight per lane (16 measured slower).
 constexpr int kLvRif = 8;
 
+template <int RS>
+struct LvCfg {
+  static constexpr int CW = RS >= 4 ? 1 : 4 / RS;    // waves side by side
+  static constexpr int CPB = 64 * CW;                // column chunks per workgroup
+  static constexpr int THREADS = CPB * RS;
+};
+
+struct LvArgs {
+  const uint8_t* A;
+  int64_t ld, cols;
+  const float* rs;
+  const int32_t* idx;
+  int64_t m;
+  const double* v;
+  double gamma;
+  const double* base;
+  double beta;
+  int accumulate;
+  double* out;
+  double* scratch;   // groups x cols partial sums when the rows are split over the grid
+  int64_t rows_per_group;
+  int aligned;
+};
+
 template <int FMT, int RS>
-__global__ __launch_bounds__(kLvThreads) void gemv_t_lp_kernel(
-    const uint8_t* __restrict__ A, int64_t ld, int64_t cols, const float* __restrict__ rs,
-    const int32_t* __restrict__ idx, int64_t m, const double* __restrict__ v, double gamma,
-    const double* __restrict__ base, double beta, int accumulate, double* __restrict__ out,
-    int aligned) {
+__global__ __launch_bounds__(LvCfg<RS>::THREADS) void gemv_t_lp_kernel(LvArgs g) {
   constexpr int ES = FMT == CABCD_BF16 ? 2 : 1;
   constexpr int EPC = 16 / ES;
-  constexpr int CPB = kLvThreads / RS;   // column chunks per workgroup
+  constexpr int CPB = LvCfg<RS>::CPB, THREADS = LvCfg<RS>::THREADS;
   constexpr int RIF = kLvRif;
-  static_assert(CPB % 64 == 0, "a row range is a whole number of waves");
+  const gptr<const uint8_t> A = glb(g.A);
+  const int64_t ld = g.ld, cols = g.cols;
+  const int32_t* __restrict__ idx = g.idx;
+  const float* __restrict__ rs = g.rs;
+  const double* __restrict__ v = g.v;
+  extern __shared__ __attribute__((aligned(16))) double red[];   // [RS][EPC][CPB]
   const int tc = threadIdx.x % CPB;
   // the row range is uniform in a wave, so the row indices and coefficients
   // stay scalar loads; lanes past the last column load zeros (lp_load)
   const int sl = __builtin_amdgcn_readfirstlane(threadIdx.x / CPB);
   const int64_t k = ((int64_t)blockIdx.x * CPB + tc) * EPC;
-  const bool live = k < cols;
-  if constexpr (RS == 1) {
-    if (!live) return;
-  }
-  const int64_t per = (m + RS - 1) / RS;
-  const int64_t p1 = std::min<int64_t>(m, (sl + 1) * per);
+  const int64_t g0 = (int64_t)blockIdx.y * g.rows_per_group;
+  const int64_t g1 = std::min<int64_t>(g.m, g0 + g.rows_per_group);
+  const int64_t per = (g.rows_per_group + RS - 1) / RS;
+  const int64_t p1 = std::min<int64_t>(g1, g0 + (sl + 1) * per);
   double acc[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
-  int64_t p = sl * per;
+  int64_t p = g0 + sl * per;
   for (; p + RIF <= p1; p += RIF) {
     uint4 x[RIF];
     double c[RIF];
@@ -485,7 +508,7 @@ __global__ __launch_bounds__(kLvThreads) void gemv_t_lp_kernel(
     for (int q = 0; q < RIF; ++q) {
       const int64_t row = idx ? (int64_t)idx[p + q] : p + q;
       c[q] = v[p + q] * (rs ? (double)rs[row] : 1.0);
-      x[q] = lp_load<FMT>(A + row * ld * ES, k, cols, aligned != 0);
+      x[q] = lp_load<FMT>(A + row * ld * ES, k, cols, g.aligned != 0);
     }
 #pragma unroll
     for (int q = 0; q < RIF; ++q) {
@@ -498,32 +521,97 @@ __global__ __launch_bounds__(kLvThreads) void gemv_t_lp_kernel(
   for (; p < p1; ++p) {
     const int64_t row = idx ? (int64_t)idx[p] : p;
     const double cq = v[p] * (rs ? (double)rs[row] : 1.0);
-    const uint4 x = lp_load<FMT>(A + row * ld * ES, k, cols, aligned != 0);
+    const uint4 x = lp_load<FMT>(A + row * ld * ES, k, cols, g.aligned != 0);
     double dv[EPC];
     lp_decode_all<FMT>(x, dv);
 #pragma unroll
     for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], cq, acc[e]);
   }
-  if constexpr (RS > 1) {
-    __shared__ double red[RS - 1][EPC][CPB];
-    if (sl > 0) {
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) red[sl - 1][e][tc] = acc[e];
+  auto store = [&](int64_t kk, double s) {
+    if (kk >= cols) return;
+    if (g.scratch != nullptr) {
+      g.scratch[(int64_t)blockIdx.y * cols + kk] = s;
+    } else {
+      const double b0 = g.accumulate ? g.out[kk] : (g.base ? g.beta * g.base[kk] : 0.0);
+      g.out[kk] = b0 + g.gamma * s;
     }
+  };
+  if constexpr (RS == 1) {
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) store(k + e, acc[e]);
+  } else {
+#pragma unroll
+    for (int e = 0; e < EPC; ++e) red[(sl * EPC + e) * CPB + tc] = acc[e];
     __syncthreads();
-    if (sl > 0) return;
+    for (int q = threadIdx.x; q < EPC * CPB; q += THREADS) {   // element q % EPC of a chunk
+      const int e = q % EPC, ch = q / EPC;
+      double s = 0.0;
 #pragma unroll
-    for (int r = 0; r < RS - 1; ++r)
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] += red[r][e][tc];
-  }
-  if (!live) return;
-#pragma unroll
-  for (int e = 0; e < EPC; ++e) {
-    if (k + e < cols) {
-      const double b0 = accumulate ? out[k + e] : (base ? beta * base[k + e] : 0.0);
-      out[k + e] = b0 + gamma * acc[e];
+      for (int r = 0; r < RS; ++r) s += red[(r * EPC + e) * CPB + ch];
+      store(((int64_t)blockIdx.x * CPB + ch) * EPC + e, s);
     }
+  }
+}
+
+__global__ __launch_bounds__(256) void gemv_t_lp_combine_kernel(LvArgs g, int groups) {
+  const double* __restrict__ scratch = g.scratch;
+  const int64_t cols = g.cols;
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k >= cols) return;
+  double s = 0.0;
+  int r = 0;
+  for (; r + 8 <= groups; r += 8) {   // eight loads in flight
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) v[q] = scratch[(int64_t)(r + q) * cols + k];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) s += v[q];
+  }
+  for (; r < groups; ++r) s += scratch[(int64_t)r * cols + k];
+  const double b0 = g.accumulate ? g.out[k] : (g.base ? g.beta * g.base[k] : 0.0);
+  g.out[k] = b0 + g.gamma * s;
+}
+
+// The row split of a pass over m rows: rs waves a column group (a power of
+// two), of at least eight rows each, and groups of rows over the grid.
+struct LvSplit {
+  int rs, groups;
+};
+LvSplit lv_split(int dtype, int64_t m, int64_t cols) {
+  const int epc = dtype == CABCD_BF16 ? 8 : 16;
+  const int64_t cw = (cols + 64 * epc - 1) / (64 * epc);   // waves side by side
+  LvSplit s{1, 1};
+  while (s.rs < 16 && cw * s.rs < 2048 && m >= 16 * s.rs) s.rs *= 2;
+  // (a second launch costs about 4 us: only where it halves a pass or more)
+  if (s.rs == 16 && cw * s.rs < 1024)
+    s.groups = (int)std::max<int64_t>(1, std::min(2048 / (cw * s.rs), m / (16 * s.rs)));
+  return s;
+}
+
+template <int FMT, int RS>
+hipError_t launch_lv(const LvArgs& g, int groups, hipStream_t st) {
+  constexpr int EPC = FMT == CABCD_BF16 ? 8 : 16;
+  constexpr size_t lds = RS == 1 ? 0 : (size_t)RS * EPC * LvCfg<RS>::CPB * sizeof(double);
+  constexpr int64_t per_block = (int64_t)LvCfg<RS>::CPB * EPC;
+  if (lds > 64 * 1024) {
+    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gemv_t_lp_kernel<FMT, RS>),
+                                       hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
+    if (e != hipSuccess) return e;
+  }
+  hipLaunchKernelGGL((gemv_t_lp_kernel<FMT, RS>),
+                     dim3((unsigned)((g.cols + per_block - 1) / per_block), (unsigned)groups),
+                     dim3(LvCfg<RS>::THREADS), lds, st, g);
+  return hipGetLastError();
+}
+
+template <int FMT>
+hipError_t launch_lv_fmt(const LvArgs& g, const LvSplit& sp, hipStream_t st) {
+  switch (sp.rs) {
+    case 1: return launch_lv<FMT, 1>(g, sp.groups, st);
+    case 2: return launch_lv<FMT, 2>(g, sp.groups, st);
+    case 4: return launch_lv<FMT, 4>(g, sp.groups, st);
+    case 8: return launch_lv<FMT, 8>(g, sp.groups, st);
+    default: return launch_lv<FMT, 16>(g, sp.groups, st);
   }
 }
 
@@ -573,27 +661,40 @@ hipError_t launch_gram_lp(const GramPlan& p, int dtype, const void* A, int64_t l
   return launch_lp_fmt<CABCD_FP8_E4M3>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
 }
 
+size_t gemv_t_lp_scratch_doubles(int dtype, int64_t m, int64_t cols) {
+  const LvSplit s = lv_split(dtype, m, cols);
+  return s.groups > 1 ? (size_t)s.groups * (size_t)cols : 0;
+}
+
 hipError_t launch_gemv_t_lp(int dtype, const void* A, int64_t ld, int64_t cols, const float* rs,
                             const int32_t* idx, int64_t m, const double* v, double gamma,
                             const double* base, double beta, bool accumulate, double* out,
-                            hipStream_t st) {
+                            double* scratch, hipStream_t st) {
   if (cols <= 0) return hipSuccess;
   const int es = dtype == CABCD_BF16 ? 2 : 1;
-  const int epc = 16 / es;
-  const int aligned = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0);
-  const int slices = dtype == CABCD_BF16 ? kLvSlices<CABCD_BF16> : kLvSlices<CABCD_FP8_E4M3>;
-  const int64_t per_block = (int64_t)(kLvThreads / slices) * epc;
-  const int64_t blocks = (cols + per_block - 1) / per_block;
-  if (dtype == CABCD_BF16)
-    hipLaunchKernelGGL((gemv_t_lp_kernel<CABCD_BF16, kLvSlices<CABCD_BF16>>),
-                       dim3((unsigned)blocks), dim3(kLvThreads), 0, st,
-                       static_cast<const uint8_t*>(A), ld, cols, rs, idx, m, v, gamma, base, beta,
-                       accumulate ? 1 : 0, out, aligned);
-  else
-    hipLaunchKernelGGL((gemv_t_lp_kernel<CABCD_FP8_E4M3, kLvSlices<CABCD_FP8_E4M3>>),
-                       dim3((unsigned)blocks), dim3(kLvThreads), 0, st,
-                       static_cast<const uint8_t*>(A), ld, cols, rs, idx, m, v, gamma, base, beta,
-                       accumulate ? 1 : 0, out, aligned);
+  const LvSplit sp = lv_split(dtype, m, cols);
+  if (sp.groups > 1 && scratch == nullptr) return hipErrorInvalidValue;
+  LvArgs g{};
+  g.A = static_cast<const uint8_t*>(A);
+  g.ld = ld;
+  g.cols = cols;
+  g.rs = rs;
+  g.idx = idx;
+  g.m = m;
+  g.v = v;
+  g.gamma = gamma;
+  g.base = base;
+  g.beta = beta;
+  g.accumulate = accumulate ? 1 : 0;
+  g.out = out;
+  g.scratch = sp.groups > 1 ? scratch : nullptr;
+  g.rows_per_group = (m + sp.groups - 1) / sp.groups;
+  g.aligned = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0) ? 1 : 0;
+  hipError_t e = dtype == CABCD_BF16 ? launch_lv_fmt<CABCD_BF16>(g, sp, st)
+                                     : launch_lv_fmt<CABCD_FP8_E4M3>(g, sp, st);
+  if (e != hipSuccess || sp.groups == 1) return e;
+  hipLaunchKernelGGL(gemv_t_lp_combine_kernel, dim3((unsigned)((cols + 255) / 256)), dim3(256), 0,
+                     st, g, sp.groups);
   return hipGetLastError();
 }
 
