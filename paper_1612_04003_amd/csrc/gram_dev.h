@@ -920,23 +920,19 @@ __device__ __forceinline__ void store_entry(int64_t e, double t, int nblk, const
 // nc = 4 when m > 384, else 2) = idx[128 x .. 128 x + 128) followed by
 // ia[256 + 128 y .. 256 + 128 y + 128), x = t % 2, y = t / 2, whose 256-row
 // Gram holds the cross block of rows 256 + 128 y.. and columns 128 x.. .
-// Padding rows are multiplied and never stored.  Thread t of nthreads.
+// Padding rows are multiplied and never stored.  m may be below 256 (the ragged
+// last step of a batched problem): every row past m is idx[0], also in the first
+// half, whose entries past m are whatever the caller's list held before.  Thread
+// t of nthreads.
 __device__ __forceinline__ void big_lists(const int32_t* idx, int m, int32_t* ia, int32_t* ib,
                                           int t, int nthreads) {
   const int nc = m - 256 > 128 ? 4 : 2;
-  const int i0 = idx[0];
   for (int q = t; q < 512; q += nthreads) ia[q] = idx[q < m ? q : 0];
   for (int slot = t; slot < 256 * nc; slot += nthreads) {
     const int list = slot >> 8, pos = slot & 255;
     const int x = list & 1, y = list >> 1;
-    int v;
-    if (pos < 128) {
-      v = idx[128 * x + pos];
-    } else {
-      const int r = 256 + 128 * y + (pos - 128);
-      v = r < m ? idx[r] : i0;
-    }
-    ib[slot] = v;
+    const int r = pos < 128 ? 128 * x + pos : 256 + 128 * y + (pos - 128);
+    ib[slot] = idx[r < m ? r : 0];
   }
 }
 
