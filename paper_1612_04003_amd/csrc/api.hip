@@ -890,7 +890,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   const GramPlan fplan = plan_for(M, kGramRows);
   const bool fuse_kind = (o.flags & CABCD_FLAG_FOLD_UPDATE) != 0 && K == 1 && !M.csr &&
                          !M.lowp() && (int64_t)s * b == kGramRows &&
-                         gram_f64_takes_update(fplan, M.X, M.ld, kGramRows);
+                         gram_f64_takes_update(fplan, kGramRows);
   bool pending = false;
   const int32_t* pend_idx = nullptr;
   int ahead = 0, gslot = 0;                       // precomputed Grams left, next slot

@@ -98,8 +98,21 @@ __device__ __forceinline__ double slab_rows_dot(const double* __restrict__ A, in
                                                 int64_t k0, int64_t k1, const int32_t* rows,
                                                 const double* coef, int mq,
                                                 const double* __restrict__ base, double beta,
-                                                double* __restrict__ out, int aligned) {
+                                                double* __restrict__ out) {
   const gptr<const double> Ag = glb(A);
+  // columns k, k + 1 of a row, from any 8-byte boundary
+  auto pair = [&](gptr<const double> row, int64_t k) {
+    typedef double dv2u __attribute__((ext_vector_type(2), aligned(8)));
+    double2 v{0.0, 0.0};
+    if (k + 1 < k1) {
+      const dv2u t = *(gptr<const dv2u>)(row + k);
+      v.x = t.x;
+      v.y = t.y;
+    } else {
+      v.x = row[k];
+    }
+    return v;
+  };
   const gptr<const double> bg = glb(base);
   const gptr<double> og = glb(out);
   double ss = 0.0;
@@ -119,7 +132,7 @@ __device__ __forceinline__ double slab_rows_dot(const double* __restrict__ A, in
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
         const int64_t row = rows != nullptr ? rows[q + j] : q + j;
-        v[j] = gdev::load2(Ag + row * ld, k, k1, aligned != 0);
+        v[j] = pair(Ag + row * ld, k);
       }
 #pragma unroll
       for (int j = 0; j < 8; ++j) {
@@ -130,7 +143,7 @@ __device__ __forceinline__ double slab_rows_dot(const double* __restrict__ A, in
     }
     for (; q < mq; ++q) {
       const int64_t row = rows != nullptr ? rows[q] : q;
-      const double2 v = gdev::load2(Ag + row * ld, k, k1, aligned != 0);
+      const double2 v = pair(Ag + row * ld, k);
       a0 = fma(v.x, coef[q], a0);
       a1 = fma(v.y, coef[q], a1);
     }
@@ -206,7 +219,7 @@ __device__ __forceinline__ double rows_dot(const BProb& pr, int64_t k0, int64_t 
                                            const double* base, double beta) {
   if constexpr (FMT == CABCD_F64)
     return slab_rows_dot(static_cast<const double*>(pr.A), pr.ld, k0, k1, rows, coef, mq, base,
-                         beta, pr.r, pr.aligned);
+                         beta, pr.r);
   else
     return slab_rows_dot_lp<FMT>(static_cast<const uint8_t*>(pr.A), pr.ld, k0, k1, rows, coef,
                                  pr.rs, mq, base, beta, pr.r, pr.aligned);
@@ -247,7 +260,8 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
 // gets its own register allocation instead of one allocation over every
 // variant of the persistent loop.  They take the workgroup's dynamic LDS from
 // their own extern declaration, so their LDS accesses stay ds_* instructions.
-// Rows fed to LDS by DMA, one owned row per lane (16-byte aligned A, even ld).
+// Arguments of a non-inlined function are per-lane values to the compiler; the
+// tile loop's barriers need its bounds to be visibly uniform.
 __device__ __noinline__ void gram_call_dma16(const double* A, int64_t ld, int64_t k0,
                                              int64_t k1, const int32_t* idx, int m,
                                              const double* u, double* part) {
@@ -256,7 +270,6 @@ __device__ __noinline__ void gram_call_dma16(const double* A, int64_t ld, int64_
                         uni_ptr(u), uni_ptr(part), dyn_sm);
 }
 
-// NB <= 8 fed by LDS-DMA (16-byte aligned A, even ld).
 template <int NB>
 __device__ __noinline__ void gram_call_dma(const double* A, int64_t ld, int64_t k0, int64_t k1,
                                            const int32_t* idx, int m, const double* u,
@@ -264,17 +277,6 @@ __device__ __noinline__ void gram_call_dma(const double* A, int64_t ld, int64_t 
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
   gdev::gram_slab_dma<NB>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
                           uni_ptr(u), uni_ptr(part), dyn_sm);
-}
-
-template <int NB>
-__device__ __noinline__ void gram_call(const double* A, int64_t ld, int64_t k0, int64_t k1,
-                                       const int32_t* idx, int m, const double* u, double* part,
-                                       int aligned) {
-  extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  // Arguments of a non-inlined function are per-lane values to the compiler;
-  // the tile loop's barriers need its bounds to be visibly uniform.
-  gdev::gram_slab<NB, 2>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
-                         uni_ptr(u), uni_ptr(part), uni(aligned), dyn_sm);
 }
 
 template <int NB, int FMT>
@@ -293,28 +295,12 @@ __device__ __forceinline__ void gram_any(int nb, const void* A, int64_t ld, int6
                                          double* part, int aligned) {
   if constexpr (FMT == CABCD_F64) {
     const double* a = static_cast<const double*>(A);
-    const bool dma = uni(aligned) != 0;
     switch (nb) {
-      case 1:
-        if (dma) gram_call_dma<1>(a, ld, k0, k1, idx, m, u, part);
-        else gram_call<1>(a, ld, k0, k1, idx, m, u, part, aligned);
-        break;
-      case 2:
-        if (dma) gram_call_dma<2>(a, ld, k0, k1, idx, m, u, part);
-        else gram_call<2>(a, ld, k0, k1, idx, m, u, part, aligned);
-        break;
-      case 4:
-        if (dma) gram_call_dma<4>(a, ld, k0, k1, idx, m, u, part);
-        else gram_call<4>(a, ld, k0, k1, idx, m, u, part, aligned);
-        break;
-      case 8:
-        if (dma) gram_call_dma<8>(a, ld, k0, k1, idx, m, u, part);
-        else gram_call<8>(a, ld, k0, k1, idx, m, u, part, aligned);
-        break;
-      default:
-        if (uni(aligned)) gram_call_dma16(a, ld, k0, k1, idx, m, u, part);
-        else gram_call<16>(a, ld, k0, k1, idx, m, u, part, aligned);
-        break;
+      case 1: gram_call_dma<1>(a, ld, k0, k1, idx, m, u, part); break;
+      case 2: gram_call_dma<2>(a, ld, k0, k1, idx, m, u, part); break;
+      case 4: gram_call_dma<4>(a, ld, k0, k1, idx, m, u, part); break;
+      case 8: gram_call_dma<8>(a, ld, k0, k1, idx, m, u, part); break;
+      default: gram_call_dma16(a, ld, k0, k1, idx, m, u, part); break;
     }
   } else {
     const uint8_t* a = static_cast<const uint8_t*>(A);
@@ -946,8 +932,6 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->pool_doubles = pool;
   add(sizeof(double) * pool);
   if (B->dtype == CABCD_F64) {
-    area = std::max<int>(area, gdev::Cfg<16, 2>::LDS);
-    area = std::max<int>(area, gdev::Cfg<1, 2>::LDS);
     area = std::max<int>(area, gdev::D16::LDS);
     area = std::max<int>(area, std::max(gdev::DN<1>::LDS, gdev::DN<2>::LDS));
     area = std::max<int>(area, std::max(gdev::DN<4>::LDS, gdev::DN<8>::LDS));

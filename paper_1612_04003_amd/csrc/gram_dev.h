@@ -11,9 +11,10 @@
 //   workgroup each (split-K), so that hundreds of workgroups cover a thin
 //   m x m output with K in the hundreds of thousands.
 // * A workgroup streams its slab through LDS in KT-wide tiles: the m gathered
-//   rows are read with 16-byte coalesced loads, double-buffered, and Y u is
-//   accumulated in FP64 from the same registers while the tile is written to
-//   LDS, so Y is read from HBM exactly once.
+//   rows go from HBM straight into LDS (LDS-DMA of 16 bytes a lane, which needs
+//   dword alignment only, so rows may start on any 8-byte boundary: 6.0 TB/s
+//   from odd ones as from 16-byte ones), double-buffered, and Y u is accumulated
+//   in FP64 from the tile, so Y is read from HBM exactly once.
 // * The lower triangle of 16x16 output blocks is computed with
 //   v_mfma_f64_16x16x4_f64.  Each wave owns the blocks of two block rows
 //   (r, NB-1-r), so every wave has NB+1 accumulators and reads at most NB
@@ -37,273 +38,55 @@ namespace gdev {
 
 typedef double d4 __attribute__((ext_vector_type(4)));
 
-// Wave layouts.  RPW = block rows owned by one wave: 2 (rows r and NB-1-r, 8
-// waves, two per SIMD) or 4 (rows r, NB-1-r, NB/2-1-r, NB/2+r, 4 waves, one
-// per SIMD with the accumulators in AGPRs).  Either way every wave owns
-// the same number of lower blocks.  Waves that own the same rows (KG > 1, small
-// NB) split the k-steps of a tile instead.
-template <int NB, int RPW>
+// Wave layout: eight waves, two per SIMD, a wave owns block rows w and NB-1-w, so
+// every wave owns the same number of lower blocks.  Waves that own the same rows
+// (KG > 1, small NB) split the k-steps of a tile instead.
+template <int NB>
 struct Cfg {
   static constexpr int SBP = 16 * NB;                       // padded rows
   static constexpr int NBLK = NB * (NB + 1) / 2;            // lower 16x16 blocks
   static constexpr int KT = 256 / NB;                       // tile width: SBP*KT = 4096
-  static constexpr int RS = KT + 2;                         // LDS row stride (doubles)
   static constexpr int CH = KT / 2;                         // 16-byte chunks per row
-  static constexpr int R = NB >= RPW ? RPW : 1;             // rows per wave
-  static constexpr int BW = NB >= RPW ? NB / RPW : 1;       // waves splitting the blocks
-  static constexpr int WAVES = RPW == 2 ? 8 : 4;
-  static constexpr int KG = WAVES / BW;                     // waves splitting the k-steps
-  static constexpr int THREADS = 64 * WAVES;
+  static constexpr int BW = NB >= 2 ? NB / 2 : 1;           // waves splitting the blocks
+  static constexpr int KG = 8 / BW;                         // waves splitting the k-steps
+  static constexpr int THREADS = 512;
   static constexpr int NCH = SBP * CH / THREADS;            // chunks per thread per tile
   static constexpr int PAIRS = KT / 8;                      // 128-bit fragment reads per tile
-  static constexpr int NACC = NB >= RPW ? NBLK / BW : 1;    // accumulators per wave
-  static constexpr int TILE = SBP * RS;
+  static constexpr int NACC = NB >= 2 ? NBLK / BW : 1;      // accumulators per wave
   static constexpr int RED = (KG - 1) * NBLK * 256;
   static constexpr int YUS = SBP * CH;
-  static constexpr int LDS = std::max(std::max(2 * TILE, RED), YUS);
   static_assert(NCH * THREADS == SBP * CH, "tile must split evenly");
   static_assert(PAIRS % KG == 0, "k-steps must split evenly");
-  static_assert(NB < RPW || NACC * BW == NBLK, "blocks must split evenly");
+  static_assert(NB < 2 || NACC * BW == NBLK, "blocks must split evenly");
 };
 
 // Index of lower block (r, c) in row-major lower-triangular order.
 __host__ __device__ constexpr int blk_index(int r, int c) { return r * (r + 1) / 2 + c; }
 
 // i-th block row owned by wave w.
-__host__ __device__ constexpr int owned_row(int NB, int RPW, int w, int i) {
-  if (NB < RPW) return NB == 1 ? 0 : (i == 0 ? 0 : 1);
-  const int pair = RPW == 2 ? w : (i < 2 ? w : NB / 2 - 1 - w);
-  return (i % 2 == 0) ? pair : NB - 1 - pair;
+__host__ __device__ constexpr int owned_row(int NB, int w, int i) {
+  return NB == 1 ? 0 : (i == 0 ? w : NB - 1 - w);
 }
 
 // First accumulator of owned row i (accumulators of row r are its r+1 blocks).
-__host__ __device__ constexpr int acc_offset(int NB, int RPW, int w, int i) {
-  int off = 0;
-  for (int k = 0; k < i; ++k) off += owned_row(NB, RPW, w, k) + 1;
-  return off;
+__host__ __device__ constexpr int acc_offset(int NB, int w, int i) {
+  return i == 0 ? 0 : owned_row(NB, w, 0) + 1;
 }
 
 // Block index of accumulator a of wave bw.
-template <int NB, int RPW>
+template <int NB>
 __device__ __forceinline__ int acc_block(int bw, int a) {
-  using C = Cfg<NB, RPW>;
-  if (NB < RPW) return a;   // the whole (tiny) triangle, in row-major order
-  for (int i = 0; i < C::R; ++i) {
-    const int r = owned_row(NB, RPW, bw, i);
-    if (a <= r) return blk_index(r, a);
-    a -= r + 1;
-  }
-  return 0;
+  if (NB < 2) return 0;
+  return a <= bw ? blk_index(bw, a) : blk_index(NB - 1 - bw, a - bw - 1);
 }
 
 __device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
-template <int NB, int RPW, int W>
-__device__ __forceinline__ void mma_tile(const double* __restrict__ tile, int lane, int kg,
-                                         d4 (&acc)[Cfg<NB, RPW>::NACC]) {
-  using C = Cfg<NB, RPW>;
-  constexpr int NR = NB >= RPW ? C::R : (NB == 1 ? 1 : 2);
-  const double* base = tile + (lane & 15) * C::RS + 2 * (lane >> 4);
-#pragma unroll
-  for (int p = 0; p < C::PAIRS / C::KG; ++p) {
-    const int col = 8 * (kg + p * C::KG);
-    auto frag = [&](int r) {
-      return *reinterpret_cast<const double2*>(base + r * 16 * C::RS + col);
-    };
-    // The wave's own block rows stay in registers; the column fragments are
-    // streamed so only a few are live next to the accumulators.
-    double2 fo[NR];
-#pragma unroll
-    for (int i = 0; i < NR; ++i) fo[i] = frag(owned_row(NB, RPW, W, i));
-    constexpr int CMAX = NB >= RPW ? NB - 1 - W : NB - 1;   // largest owned row
-#pragma unroll
-    for (int c = 0; c <= CMAX; ++c) {
-      double2 fc = {0.0, 0.0};
-      bool own = false;
-#pragma unroll
-      for (int i = 0; i < NR; ++i)
-        if (owned_row(NB, RPW, W, i) == c) {
-          fc = fo[i];
-          own = true;
-        }
-      if (!own) fc = frag(c);
-#pragma unroll
-      for (int i = 0; i < NR; ++i) {
-        const int r = owned_row(NB, RPW, W, i);
-        if (c <= r) {
-          const int a = acc_offset(NB, RPW, W, i) + c;
-          acc[a] = mfma(fo[i].x, fc.x, acc[a]);
-          acc[a] = mfma(fo[i].y, fc.y, acc[a]);
-        }
-      }
-    }
-  }
-}
-
-template <int NB, int RPW, int W = 0>
-__device__ __forceinline__ void mma_dispatch(int bw, const double* __restrict__ tile, int lane,
-                                             int kg, d4 (&acc)[Cfg<NB, RPW>::NACC]) {
-  if constexpr (W < Cfg<NB, RPW>::BW) {
-    if (bw == W)
-      mma_tile<NB, RPW, W>(tile, lane, kg, acc);
-    else
-      mma_dispatch<NB, RPW, W + 1>(bw, tile, lane, kg, acc);
-  }
-}
-
-template <class PTR>
-__device__ __forceinline__ double2 load2(PTR p, int64_t k, int64_t k_end, bool aligned) {
-  double2 v;
-  if (k + 1 < k_end) {
-    if (aligned) {
-      typedef double dv2 __attribute__((ext_vector_type(2)));
-      const dv2 t = *reinterpret_cast<gptr<const dv2>>(p + k);
-      v.x = t.x;
-      v.y = t.y;
-    } else {
-      v.x = p[k];
-      v.y = p[k + 1];
-    }
-  } else {
-    v.x = k < k_end ? p[k] : 0.0;
-    v.y = 0.0;
-  }
-  return v;
-}
-
-// One workgroup's slab of the Gram: columns [k_begin, k_end) of the rows
-// idx[0..m) of A (m <= 16 NB; idx may point to LDS), u indexed by absolute
-// column (NULL: no Y u).  Writes the partial blocks and the partial Y u to
-// part[0 .. NBLK*256 + SBP).  lds holds Cfg::LDS doubles.  Every thread of the
-// workgroup must call it.
-template <int NB, int RPW>
-__device__ __forceinline__ void gram_slab(const double* __restrict__ A, int64_t ld,
-                                          int64_t k_begin, int64_t k_end, const int32_t* idx,
-                                          int m, const double* __restrict__ u,
-                                          double* __restrict__ part, int aligned, double* lds) {
-  using C = Cfg<NB, RPW>;
-
-  const int tid = threadIdx.x;
-  const int lane = tid & 63;
-  const int wave = tid >> 6;
-  const int bw = wave % C::BW;
-  const int kg = wave / C::BW;
-  const int c = tid % C::CH;
-  const int ntiles = (int)((k_end - k_begin + C::KT - 1) / C::KT);
-
-  int rho[C::NCH];
-  gptr<const double> rowp[C::NCH];
-  const gptr<const double> Ag = glb(A);
-  const gptr<const double> ug = glb(u);
-#pragma unroll
-  for (int i = 0; i < C::NCH; ++i) {
-    rho[i] = tid / C::CH + (C::THREADS / C::CH) * i;
-    rowp[i] = rho[i] < m ? Ag + (int64_t)idx[rho[i]] * ld : nullptr;
-  }
-  const bool want_u = u != nullptr;
-  const bool u_aligned = (reinterpret_cast<uintptr_t>(u) & 15) == 0;   // k is even
-  double yu[C::NCH];
-  double2 buf[C::NCH];
-  double2 ub = {0.0, 0.0};
-#pragma unroll
-  for (int i = 0; i < C::NCH; ++i) yu[i] = 0.0;
-
-  auto load_tile = [&](int t) {
-    const int64_t k = k_begin + (int64_t)t * C::KT + 2 * c;
-    if (want_u) ub = load2(ug, k, k_end, u_aligned);
-#pragma unroll
-    for (int i = 0; i < C::NCH; ++i) {
-      if (rowp[i] != nullptr) {
-        buf[i] = load2(rowp[i], k, k_end, aligned != 0);
-      } else {
-        buf[i].x = 0.0;
-        buf[i].y = 0.0;
-      }
-    }
-  };
-  auto store_tile = [&](int slot) {
-    double* T = lds + slot * C::TILE;
-#pragma unroll
-    for (int i = 0; i < C::NCH; ++i) {
-      *reinterpret_cast<double2*>(T + rho[i] * C::RS + 2 * c) = buf[i];
-      if (want_u) {
-        yu[i] = fma(buf[i].x, ub.x, yu[i]);
-        yu[i] = fma(buf[i].y, ub.y, yu[i]);
-      }
-    }
-  };
-
-  d4 acc[C::NACC];
-#pragma unroll
-  for (int a = 0; a < C::NACC; ++a) acc[a] = d4{0.0, 0.0, 0.0, 0.0};
-
-  load_tile(0);
-  store_tile(0);
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    const bool more = t + 1 < ntiles;
-    if (more) load_tile(t + 1);
-    mma_dispatch<NB, RPW>(bw, lds + (t & 1) * C::TILE, lane, kg, acc);
-    if (more) store_tile((t + 1) & 1);
-    __syncthreads();
-  }
-
-  // Sum the k-groups (waves with the same blocks) through LDS, in group order.
-  if constexpr (C::KG > 1) {
-    if (kg > 0) {
-#pragma unroll
-      for (int a = 0; a < C::NACC; ++a) {
-        double* dst = lds + ((kg - 1) * C::NBLK + acc_block<NB, RPW>(bw, a)) * 256 + lane;
-        dst[0] = acc[a][0];
-        dst[64] = acc[a][1];
-        dst[128] = acc[a][2];
-        dst[192] = acc[a][3];
-      }
-    }
-    __syncthreads();
-    if (kg == 0) {
-      for (int g = 1; g < C::KG; ++g) {
-#pragma unroll
-        for (int a = 0; a < C::NACC; ++a) {
-          const double* src = lds + ((g - 1) * C::NBLK + acc_block<NB, RPW>(bw, a)) * 256 + lane;
-          acc[a][0] += src[0];
-          acc[a][1] += src[64];
-          acc[a][2] += src[128];
-          acc[a][3] += src[192];
-        }
-      }
-    }
-  }
-  if (kg == 0) {
-#pragma unroll
-    for (int a = 0; a < C::NACC; ++a) {
-      gptr<double> dst = glb(part) + acc_block<NB, RPW>(bw, a) * 256 + lane;
-      dst[0] = acc[a][0];
-      dst[64] = acc[a][1];
-      dst[128] = acc[a][2];
-      dst[192] = acc[a][3];
-    }
-  }
-
-  if (want_u) {
-    __syncthreads();   // LDS is reused for the row sums of Y u
-#pragma unroll
-    for (int i = 0; i < C::NCH; ++i) lds[rho[i] * C::CH + c] = yu[i];
-    __syncthreads();
-    if (tid < C::SBP) {
-      double s = 0.0;
-      for (int q = 0; q < C::CH; ++q) s += lds[tid * C::CH + q];
-      glb(part)[C::NBLK * 256 + tid] = s;
-    }
-  }
-}
-
-
 // ---------------------------------------------------------------------------
-// NB <= 8 fed by LDS-DMA (the decomposition of gram_slab<NB, 2>: waves own
-// block-row pairs and split a tile's k-steps): a 32 KiB tile of SBP rows x
+// NB <= 8: waves own block-row pairs and split a tile's k-steps.  A 32 KiB tile of
+// SBP rows x
 // KT = 256 / NB columns goes from HBM straight into LDS, rows unpadded with the
 // 16-byte chunks of each aligned group of sixteen XOR-swizzled by the row
 // (chunk c of row r at c ^ (r & 15)), so the sixteen rows of a fragment read
@@ -312,7 +95,7 @@ __device__ __forceinline__ void gram_slab(const double* __restrict__ A, int64_t 
 // per tile keep the HBM pages busy.
 template <int NB>
 struct DN {
-  using C = Cfg<NB, 2>;
+  using C = Cfg<NB>;
   static constexpr int DMA_PER_WAVE = C::SBP * C::CH / 64 / 8;   // 4 instructions
   static constexpr int UDMA = (C::KT / 2 + 63) / 64;              // u slots, 64 a time
   static constexpr int TILE = C::SBP * C::KT + C::KT;            // doubles: rows, then u
@@ -321,8 +104,8 @@ struct DN {
 
 template <int NB, int W>
 __device__ __forceinline__ void mma_tile_dma(const double* __restrict__ tile, int lane, int kg,
-                                             d4 (&acc)[Cfg<NB, 2>::NACC]) {
-  using C = Cfg<NB, 2>;
+                                             d4 (&acc)[Cfg<NB>::NACC]) {
+  using C = Cfg<NB>;
   constexpr int NR = NB >= 2 ? 2 : 1;
   const int rl = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -332,7 +115,7 @@ __device__ __forceinline__ void mma_tile_dma(const double* __restrict__ tile, in
     auto frag = [&](int r) { return *reinterpret_cast<const double2*>(base + r * 16 * C::KT); };
     double2 fo[NR];
 #pragma unroll
-    for (int i = 0; i < NR; ++i) fo[i] = frag(owned_row(NB, 2, W, i));
+    for (int i = 0; i < NR; ++i) fo[i] = frag(owned_row(NB, W, i));
     constexpr int CMAX = NB >= 2 ? NB - 1 - W : 0;        // largest owned row
 #pragma unroll
     for (int c = 0; c <= CMAX; ++c) {
@@ -340,16 +123,16 @@ __device__ __forceinline__ void mma_tile_dma(const double* __restrict__ tile, in
       bool own = false;
 #pragma unroll
       for (int i = 0; i < NR; ++i)
-        if (owned_row(NB, 2, W, i) == c) {
+        if (owned_row(NB, W, i) == c) {
           fc = fo[i];
           own = true;
         }
       if (!own) fc = frag(c);
 #pragma unroll
       for (int i = 0; i < NR; ++i) {
-        const int r = owned_row(NB, 2, W, i);
+        const int r = owned_row(NB, W, i);
         if (c <= r) {
-          const int a = acc_offset(NB, 2, W, i) + c;
+          const int a = acc_offset(NB, W, i) + c;
           acc[a] = mfma(fo[i].x, fc.x, acc[a]);
           acc[a] = mfma(fo[i].y, fc.y, acc[a]);
         }
@@ -360,8 +143,8 @@ __device__ __forceinline__ void mma_tile_dma(const double* __restrict__ tile, in
 
 template <int NB, int W = 0>
 __device__ __forceinline__ void mma_dispatch_dma(int bw, const double* __restrict__ tile, int lane,
-                                                 int kg, d4 (&acc)[Cfg<NB, 2>::NACC]) {
-  if constexpr (W < Cfg<NB, 2>::BW) {
+                                                 int kg, d4 (&acc)[Cfg<NB>::NACC]) {
+  if constexpr (W < Cfg<NB>::BW) {
     if (bw == W)
       mma_tile_dma<NB, W>(tile, lane, kg, acc);
     else
@@ -369,14 +152,17 @@ __device__ __forceinline__ void mma_dispatch_dma(int bw, const double* __restric
   }
 }
 
-// The slab of gram_slab<NB, 2> on the DMA path (A 16-byte aligned with an even
-// ld); same arguments and partial layout.  lds holds DN<NB>::LDS doubles.
+// One workgroup's slab of the Gram: columns [k_begin, k_end) of the rows
+// idx[0..m) of A (m <= 16 NB; idx may point to LDS), u indexed by absolute
+// column (NULL: no Y u).  Writes the partial blocks and the partial Y u to
+// part[0 .. NBLK*256 + SBP).  lds holds DN<NB>::LDS doubles.  Every thread of the
+// workgroup must call it.
 template <int NB>
 __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int64_t ld,
                                               int64_t k_begin, int64_t k_end, const int32_t* idx,
                                               int m, const double* __restrict__ u,
                                               double* __restrict__ part, double* lds) {
-  using C = Cfg<NB, 2>;
+  using C = Cfg<NB>;
   using D = DN<NB>;
   typedef __attribute__((address_space(3))) void* lds_vptr;
   typedef __attribute__((address_space(1))) const void* glb_vptr;
@@ -411,7 +197,6 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
   }
   const bool want_u = u != nullptr;
   const gptr<const double> ug = glb(u);
-  const bool u_dma = want_u && (reinterpret_cast<uintptr_t>(u) & 15) == 0;
   auto issue = [&](int t, int slot) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
     double* T = lds + slot * D::TILE;
@@ -437,7 +222,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
         if (64 * j + lane < C::KT / 2) {
           double* dst = T + C::SBP * C::KT + 128 * j;
           const int64_t k = k0 + 2 * (64 * j + lane);
-          if (full && u_dma) {
+          if (full) {
             __builtin_amdgcn_global_load_lds((glb_vptr)(ug + k), (lds_vptr)dst, 16, 0, 0);
           } else {
             double2 v;
@@ -450,7 +235,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     }
   };
 
-  // Y u: chunk c of rows tid / CH + (THREADS / CH) i, as in gram_slab
+  // Y u: chunk c of rows tid / CH + (THREADS / CH) i
   const int c = tid % C::CH;
   int rho[C::NCH];
 #pragma unroll
@@ -490,7 +275,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     if (kg > 0) {
 #pragma unroll
       for (int a = 0; a < C::NACC; ++a) {
-        double* dst = lds + ((kg - 1) * C::NBLK + acc_block<NB, 2>(bw, a)) * 256 + lane;
+        double* dst = lds + ((kg - 1) * C::NBLK + acc_block<NB>(bw, a)) * 256 + lane;
         dst[0] = acc[a][0];
         dst[64] = acc[a][1];
         dst[128] = acc[a][2];
@@ -502,7 +287,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
       for (int g = 1; g < C::KG; ++g) {
 #pragma unroll
         for (int a = 0; a < C::NACC; ++a) {
-          const double* srcp = lds + ((g - 1) * C::NBLK + acc_block<NB, 2>(bw, a)) * 256 + lane;
+          const double* srcp = lds + ((g - 1) * C::NBLK + acc_block<NB>(bw, a)) * 256 + lane;
           acc[a][0] += srcp[0];
           acc[a][1] += srcp[64];
           acc[a][2] += srcp[128];
@@ -514,7 +299,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
   if (kg == 0) {
 #pragma unroll
     for (int a = 0; a < C::NACC; ++a) {
-      gptr<double> dst = glb(part) + acc_block<NB, 2>(bw, a) * 256 + lane;
+      gptr<double> dst = glb(part) + acc_block<NB>(bw, a) * 256 + lane;
       dst[0] = acc[a][0];
       dst[64] = acc[a][1];
       dst[128] = acc[a][2];
@@ -543,8 +328,8 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
 // c ^ ((r >> 1) & 7), so the sixteen rows of a fragment read fall in distinct
 // banks.  Y u is accumulated from the waves' own-row fragments (each block row
 // is owned by exactly one wave) and summed over the four lane groups at the
-// end.  Needs A 16-byte aligned with an even ld; chunks that cross the end of
-// the slab are written with ordinary LDS stores (zero-filled).
+// end.  Chunks that cross the end of the slab are written with ordinary LDS
+// stores (zero-filled).
 struct D16 {
   static constexpr int NB = 16, SBP = 256, NBLK = 136, KT = 16, CH = KT / 2;
   static constexpr int PP = KT / 8;                  // 128-bit fragment reads per tile
@@ -635,7 +420,6 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   }
   const bool want_u = MODE == 1 || u != nullptr;
   const gptr<const double> ug = glb(u);
-  const bool u_dma = MODE == 0 && want_u && (reinterpret_cast<uintptr_t>(u) & 15) == 0;
 
   // The previous step's rows (MODE 1 and 2): DMA instruction i of this wave
   // fills slots q = (4 W + i) * 64 + lane of an update buffer: row q / 8 =
@@ -644,7 +428,6 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   // addresses formed at each issue, to spare registers.
   int yrow[C::DMA_PER_WAVE];
   const gptr<double> rg = glb(up.r);
-  const bool r_dma = (reinterpret_cast<uintptr_t>(up.r) & 15) == 0;
   if constexpr (MODE != 0) {
 #pragma unroll
     for (int i = 0; i < C::DMA_PER_WAVE; ++i)
@@ -672,7 +455,7 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
     if (W == 7 && lane < C::CH) {
       double* dst = Y + C::SBP * C::KT;
       const int64_t k = k0 + 2 * lane;
-      if (r_dma && k + 1 < k_end) {
+      if (k + 1 < k_end) {
         __builtin_amdgcn_global_load_lds((glb_vptr)(rg + k), (lds_vptr)dst, 16, 0, 0);
       } else {
         double2 v;
@@ -751,7 +534,7 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
     if (MODE == 0 && W == 7 && lane < C::CH) {
       double* dst = T + C::SBP * C::KT;
       const int64_t k = k0 + 2 * lane;
-      if (u_dma && k + 1 < k_end) {
+      if (want_u && k + 1 < k_end) {
         __builtin_amdgcn_global_load_lds((glb_vptr)(ug + k), (lds_vptr)dst, 16, 0, 0);
       } else {
         double2 v;
@@ -850,8 +633,7 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   }
 }
 
-// The NB = 16 slab of gram_slab<16, 2> on the DMA path; same arguments and
-// partial layout (A must be 16-byte aligned with an even ld).
+// The NB = 16 slab; arguments and partial layout as gram_slab_dma.
 template <int MODE = 0>
 __device__ __forceinline__ void gram_slab_dma16(const double* __restrict__ A, int64_t ld,
                                                 int64_t k_begin, int64_t k_end,

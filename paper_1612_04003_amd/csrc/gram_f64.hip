@@ -5,7 +5,6 @@
 
 #include <algorithm>
 #include <cmath>
-#include <cstdlib>
 
 namespace cabcd {
 namespace {
@@ -14,27 +13,12 @@ using namespace gdev;
 
 // Several row lists per launch: step blockIdx.y reads idx + step * m and
 // writes its partials (and its Y u, when u is given) at partials + step * pstride.
-template <int NB, int RPW>
-__global__ __launch_bounds__((Cfg<NB, RPW>::THREADS)) void gram_f64_kernel(
-    const double* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
-    int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
-    int64_t pstride, int aligned) {
-  using C = Cfg<NB, RPW>;
-  __shared__ __attribute__((aligned(16))) double lds[C::LDS];
-  idx += (int64_t)blockIdx.y * m;
-  partials += (int64_t)blockIdx.y * pstride;
-  const int64_t k_begin = (int64_t)blockIdx.x * chunk;
-  const int64_t k_end = std::min(cols, k_begin + chunk);
-  gram_slab<NB, RPW>(A, ld, k_begin, k_end, idx, m, u,
-                     partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), aligned, lds);
-}
-
 template <int NB>
-__global__ __launch_bounds__((Cfg<NB, 2>::THREADS)) void gram_f64_dma_kernel(
+__global__ __launch_bounds__(Cfg<NB>::THREADS) void gram_f64_dma_kernel(
     const double* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
     int64_t pstride) {
-  using C = Cfg<NB, 2>;
+  using C = Cfg<NB>;
   __shared__ __attribute__((aligned(16))) double lds[DN<NB>::LDS];
   idx += (int64_t)blockIdx.y * m;
   partials += (int64_t)blockIdx.y * pstride;
@@ -161,33 +145,18 @@ __global__ __launch_bounds__(512) void big_index_kernel(const int32_t* __restric
                   ib + (int64_t)blockIdx.x * 256 * nc, threadIdx.x, 512);
 }
 
-bool d16_ok(const GramPlan& p, const double* A, int64_t ld) {
-  return p.nb == 16 && p.rpw == 1 && (reinterpret_cast<uintptr_t>(A) & 15) == 0 && (ld & 1) == 0;
-}
-
-template <int NB, int RPW>
+template <int NB>
 hipError_t launch_nb(const GramPlan& p, const double* A, int64_t ld, int64_t cols,
                      const int32_t* idx, int m, int nsteps, const double* u, double* partials,
                      hipStream_t st) {
-  const int aligned = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && (ld & 1) == 0) ? 1 : 0;
   const int64_t pstride = (int64_t)gram_partial_doubles(p);
   const dim3 grid((unsigned)p.nsplit, (unsigned)nsteps);
-  if constexpr (NB == 16) {
-    if (p.rpw == 1 && aligned) {
-      hipLaunchKernelGGL(gram_f64_dma16_kernel, grid, dim3(D16::THREADS), 0, st, A, ld, cols, idx,
-                         m, u, p.chunk, partials, pstride);
-      return hipGetLastError();
-    }
-  }
-  if constexpr (NB <= 8 && RPW == 2) {
-    if (p.rpw == 1 && aligned) {
-      hipLaunchKernelGGL((gram_f64_dma_kernel<NB>), grid, dim3(Cfg<NB, 2>::THREADS), 0, st, A,
-                         ld, cols, idx, m, u, p.chunk, partials, pstride);
-      return hipGetLastError();
-    }
-  }
-  hipLaunchKernelGGL((gram_f64_kernel<NB, RPW>), grid, dim3(Cfg<NB, RPW>::THREADS), 0, st, A, ld,
-                     cols, idx, m, u, p.chunk, partials, pstride, aligned);
+  if constexpr (NB == 16)
+    hipLaunchKernelGGL(gram_f64_dma16_kernel, grid, dim3(D16::THREADS), 0, st, A, ld, cols, idx, m,
+                       u, p.chunk, partials, pstride);
+  else
+    hipLaunchKernelGGL((gram_f64_dma_kernel<NB>), grid, dim3(Cfg<NB>::THREADS), 0, st, A, ld, cols,
+                       idx, m, u, p.chunk, partials, pstride);
   return hipGetLastError();
 }
 
@@ -244,13 +213,6 @@ GramPlan plan_gram_f64(int m, int64_t cols) {
   }
   p.chunk = best_chunk;
   p.nsplit = (int)((cols + best_chunk - 1) / best_chunk);
-  // Eight waves with two block rows each.  Four waves with four rows each (one
-  // wave per SIMD, accumulators in AGPRs) measured slower at nb = 8 (30.9 vs
-  // 38.3 TFLOP/s) and does not fit the registers at nb = 16.
-  // rpw = 1: the LDS-DMA variant of the same decomposition (aligned A only;
-  // CABCD_GRAM_DMA=0 selects the register-fed kernels instead).
-  const char* env = std::getenv("CABCD_GRAM_DMA");
-  p.rpw = (env != nullptr && std::atoi(env) == 0) ? 2 : 1;
   return p;
 }
 
@@ -263,23 +225,21 @@ hipError_t launch_gram_f64(const GramPlan& p, const double* A, int64_t ld, int64
                            hipStream_t st, int nsteps) {
   if (nsteps < 1 || nsteps > 65535) return hipErrorInvalidValue;
   switch (p.nb) {
-    case 1: return launch_nb<1, 2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
-    case 2: return launch_nb<2, 2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
-    case 4: return launch_nb<4, 2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
-    case 8: return launch_nb<8, 2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
-    case 16: return launch_nb<16, 2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 1: return launch_nb<1>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 2: return launch_nb<2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 4: return launch_nb<4>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 8: return launch_nb<8>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 16: return launch_nb<16>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
     default: return hipErrorInvalidValue;
   }
 }
 
-bool gram_f64_takes_update(const GramPlan& p, const double* A, int64_t ld, int m) {
-  return m == D16::SBP && d16_ok(p, A, ld);
-}
+bool gram_f64_takes_update(const GramPlan& p, int m) { return p.nb == 16 && m == D16::SBP; }
 
 hipError_t launch_gram_f64_upd(const GramPlan& p, const double* A, int64_t ld, int64_t cols,
                                const int32_t* idx, int m, double* partials, const D16Upd& up,
                                hipStream_t st) {
-  if (!gram_f64_takes_update(p, A, ld, m) || up.idx == nullptr || up.delta == nullptr ||
+  if (!gram_f64_takes_update(p, m) || up.idx == nullptr || up.delta == nullptr ||
       up.r == nullptr)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL((gram_f64_dma16_upd_kernel<1>), dim3((unsigned)p.nsplit), dim3(D16::THREADS),
@@ -289,7 +249,7 @@ hipError_t launch_gram_f64_upd(const GramPlan& p, const double* A, int64_t ld, i
 
 hipError_t launch_update_f64(const GramPlan& p, const double* A, int64_t ld, int64_t cols,
                              const D16Upd& up, hipStream_t st) {
-  if (!d16_ok(p, A, ld) || up.idx == nullptr || up.delta == nullptr || up.r == nullptr)
+  if (p.nb != 16 || up.idx == nullptr || up.delta == nullptr || up.r == nullptr)
     return hipErrorInvalidValue;
   hipLaunchKernelGGL((gram_f64_dma16_upd_kernel<2>), dim3((unsigned)p.nsplit), dim3(D16::THREADS),
                      0, st, A, ld, cols, nullptr, 0, p.chunk, nullptr, up);

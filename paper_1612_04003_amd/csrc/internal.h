@@ -115,7 +115,6 @@ struct GramPlan {
   int kt;          // columns per LDS tile
   int64_t chunk;   // columns per workgroup (multiple of kt)
   int nsplit;      // workgroups along the reduction dimension
-  int rpw;         // block rows per wave (2: eight waves, 4: four waves)
 };
 GramPlan plan_gram_f64(int m, int64_t cols);
 // The deferred companion update of the previous outer step (Alg. 2: r += gamma
@@ -130,9 +129,8 @@ struct D16Upd {
   double* r;
 };
 // The dense 256-row Gram can take the previous step's update along
-// (launch_gram_f64_upd) when its plan runs the LDS-DMA kernel: 16-byte
-// aligned rows with an even ld, m = 256.
-bool gram_f64_takes_update(const GramPlan& p, const double* A, int64_t ld, int m);
+// (launch_gram_f64_upd).
+bool gram_f64_takes_update(const GramPlan& p, int m);
 // The 256-row Gram (nsteps = 1) of gram_f64 with the previous step's update
 // applied to r first; the Y r partials use the updated r.
 hipError_t launch_gram_f64_upd(const GramPlan& p, const double* A, int64_t ld, int64_t cols,

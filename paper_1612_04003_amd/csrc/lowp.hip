@@ -625,7 +625,6 @@ GramPlan plan_gram_lp(int m, int64_t cols, int dtype) {
   p.nblk = nb * (nb + 1) / 2;
   const int es = dtype == CABCD_BF16 ? 2 : 1;
   p.kt = (2048 / nb) / es;
-  p.rpw = 2;
   if (nb == 16) {
     // the LDS-DMA kernel (aligned rows): one workgroup per CU, 256-byte tile
     // rows; its slabs also suit the register-fed kernel (a multiple of kt)

@@ -43,14 +43,16 @@ struct GemvT {
   double* out;
   double* scratch;   // rg x cols partials when the rows are split
   int64_t rows_per_group;
-  int aligned;
 };
 
-// VEC: 16-byte loads of column pairs (A 16-byte aligned, even ld).  Eight rows
+// 16-byte loads of column pairs, from any 8-byte boundary (the load needs dword
+// alignment only).  Eight rows
 // at a time: their indices and coefficients (the same for every thread) are
 // fetched first, then the eight loads go out together with no branch between
 // them, so each thread keeps eight loads in flight (sixteen measured the same).
-template <bool VEC>
+typedef double dv2 __attribute__((ext_vector_type(2)));
+typedef double dv2u __attribute__((ext_vector_type(2), aligned(8)));   // any 8-byte boundary
+
 __global__ __launch_bounds__(kVecThreads) void gemv_t_kernel(GemvT g) {
   constexpr int U = 8;
   const int64_t k = ((int64_t)blockIdx.x * kVecThreads + threadIdx.x) * 2;
@@ -58,9 +60,7 @@ __global__ __launch_bounds__(kVecThreads) void gemv_t_kernel(GemvT g) {
   const int64_t p1 = std::min(g.m, p0 + g.rows_per_group);
   if (k >= g.cols) return;
   const bool two = k + 1 < g.cols;
-  const bool vec = VEC && two;
   const gptr<const double> A = glb(g.A) + k;
-  typedef double dv2 __attribute__((ext_vector_type(2)));
   double s0 = 0.0, s1 = 0.0;
   int64_t p = p0;
   // the row of entry p: idx[p] (gathered rows) or p; one loop per case keeps
@@ -75,15 +75,12 @@ __global__ __launch_bounds__(kVecThreads) void gemv_t_kernel(GemvT g) {
         c[q] = g.v[p + q];
       }
       dv2 x[U];
-      if (vec) {
+      if (two) {
 #pragma unroll
-        for (int q = 0; q < U; ++q) x[q] = *reinterpret_cast<gptr<const dv2>>(A + off[q]);
+        for (int q = 0; q < U; ++q) x[q] = *(gptr<const dv2u>)(A + off[q]);
       } else {
 #pragma unroll
-        for (int q = 0; q < U; ++q) {
-          x[q].x = A[off[q]];
-          x[q].y = two ? A[off[q] + 1] : 0.0;
-        }
+        for (int q = 0; q < U; ++q) x[q] = dv2{A[off[q]], 0.0};
       }
 #pragma unroll
       for (int q = 0; q < U; ++q) {
@@ -154,7 +151,7 @@ struct RowDot {
   double* part;        // rows x parts partial sums when parts > 1
   int64_t chunk;       // elements per part
   int parts;
-  int vec;             // A rows and v 16-byte aligned
+  int vec;             // low precision: A rows 16-byte aligned
 };
 
 // Lane l of a wave reads the 16-byte chunks l, l + 64, ... of its row part,
@@ -174,7 +171,6 @@ __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
   const int64_t ar = g.idx ? (int64_t)g.idx[p] : p;   // row of A
   const gptr<const uint8_t> row = glb(g.A) + ar * g.ld * ES;
   const gptr<const double> v = glb(g.v);
-  typedef double dv2 __attribute__((ext_vector_type(2)));
   double acc = 0.0;
   auto chunk_dot = [&](const uint4& x, int64_t k) {
     double e[EPC];
@@ -186,7 +182,7 @@ __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
     double t = 0.0;
 #pragma unroll
     for (int j = 0; j < EPC; j += 2) {
-      const dv2 c = *(gptr<const dv2>)(v + k + j);
+      const dv2 c = *(gptr<const dv2u>)(v + k + j);
       t = fma(e[j], c.x, t);
       t = fma(e[j + 1], c.y, t);
     }
@@ -194,7 +190,8 @@ __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
   };
   int64_t k = k0 + (int64_t)lane * EPC;
   if (g.vec) {
-    typedef unsigned int uv4 __attribute__((ext_vector_type(4)));
+    // FP64 rows may start on any 8-byte boundary
+    typedef unsigned int uv4 __attribute__((ext_vector_type(4), aligned(8)));
     for (; k + (int64_t)(U - 1) * 64 * EPC + EPC <= k1; k += (int64_t)U * 64 * EPC) {
       uint4 x[U];
 #pragma unroll
@@ -210,7 +207,7 @@ __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
       acc += chunk_dot(make_uint4(t.x, t.y, t.z, t.w), k);
     }
   }
-  // element by element: unaligned rows, and the ragged end of the part
+  // element by element: codes on odd boundaries, and the ragged end of the part
   for (; k < k1; k += 64 * EPC) {
     const int64_t ke = std::min<int64_t>(k + EPC, k1);
     double t = 0.0;
@@ -397,8 +394,8 @@ static hipError_t launch_rowdot_any(int dtype, const void* A, int64_t ld, const 
   g.parts = rowdot_parts(rows, cols, es, &g.chunk);
   g.part = g.parts > 1 ? scratch : nullptr;
   if (g.parts > 1 && scratch == nullptr) return hipErrorInvalidValue;
-  g.vec = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0 &&
-           (reinterpret_cast<uintptr_t>(v) & 15) == 0)
+  g.vec = dtype == CABCD_F64 ||
+                  ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0)
               ? 1
               : 0;
   const int64_t waves = rows * g.parts;
@@ -451,18 +448,13 @@ hipError_t launch_gemv_t(const double* A, int64_t ld, int64_t cols, const int32_
   g.beta = beta;
   g.accumulate = accumulate ? 1 : 0;
   g.out = out;
-  g.aligned = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && (ld & 1) == 0) ? 1 : 0;
   const int rg = gemv_t_groups(m, cols);
   g.rows_per_group = (m + rg - 1) / rg;
   g.scratch = rg > 1 ? scratch : nullptr;
   if (rg > 1 && scratch == nullptr) return hipErrorInvalidValue;
   const int64_t tiles = (cols + kColsPerWG - 1) / kColsPerWG;
-  if (g.aligned)
-    hipLaunchKernelGGL(gemv_t_kernel<true>, dim3((unsigned)tiles, (unsigned)rg),
-                       dim3(kVecThreads), 0, st, g);
-  else
-    hipLaunchKernelGGL(gemv_t_kernel<false>, dim3((unsigned)tiles, (unsigned)rg),
-                       dim3(kVecThreads), 0, st, g);
+  hipLaunchKernelGGL(gemv_t_kernel, dim3((unsigned)tiles, (unsigned)rg), dim3(kVecThreads), 0, st,
+                     g);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess || rg == 1) return e;
   hipLaunchKernelGGL(gemv_t_combine_kernel,

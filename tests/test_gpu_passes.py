@@ -1,6 +1,6 @@
-"""The streaming passes over stored codes, at the edges of their splits (GPU): the
-exact residual X^T w - y and the map -X a / (lambda n) against FP64 products of
-the dequantised matrix.  Tolerance per entry: a sum of `rows` terms in FP64,
+"""The streaming passes, at the edges of their splits and on every boundary that a
+row may start on (GPU): the exact residual X^T w - y, the full residual and the map
+-X a / (lambda n) against FP64 products (codes: of the dequantised matrix).  Tolerance per entry: a sum of `rows` terms in FP64,
 2 rows u sum |terms|."""
 
 import pytest
@@ -37,3 +37,34 @@ def test_lowp_passes(gpu_lib, dtype, rows, cols, padded):
     want = (Xh.t() @ w) / (-0.5 * rows)
     mag = (Xh.abs().t() @ w.abs()) / (0.5 * rows)
     assert bool(((v - want).abs() <= 2 * (rows + 2) * U * mag).all())
+
+
+# rows that start on odd 8-byte boundaries (odd ld, odd first element) and on
+# 16-byte ones; one column, odd and even counts, several parts of a row
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (0, 1), (1, 1), (1, 2)])
+@pytest.mark.parametrize("rows,cols", [(3, 1), (40, 33), (257, 1030), (19, 20001), (900, 77)])
+def test_f64_rows_on_any_boundary(gpu_lib, rows, cols, off, pad):
+    print("[passes] f64", rows, cols, off, pad, flush=True)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + cols)
+    buf = torch.full((off + rows * (cols + pad) + 1,), float("nan"), device=DEV,
+                     dtype=torch.float64)
+    X = buf[off:off + rows * (cols + pad)].view(rows, cols + pad)[:, :cols]
+    X.copy_(torch.randn(rows, cols, generator=g, device=DEV, dtype=torch.float64))
+    vec = torch.randn(rows + 2 * cols + 3, generator=g, device=DEV, dtype=torch.float64)
+    w, y, u = vec[1:1 + rows], vec[1 + rows:1 + rows + cols], vec[-cols - 1:-1]
+    Xc = X.contiguous()
+    _, r = gpu_lib.primal_objective(X, y, 0.1, w)
+    want, mag = Xc.t() @ w - y, Xc.abs().t() @ w.abs() + y.abs()
+    assert bool(((r - want).abs() <= 2 * (rows + 2) * U * mag).all())
+    _, rho = gpu_lib.primal_residual(X, 0.1, w, u)
+    want, mag = -0.1 * w - (Xc @ u) / cols, 0.1 * w.abs() + (Xc.abs() @ u.abs()) / cols
+    assert bool(((rho - want).abs() <= 2 * (cols + 4) * U * mag).all())
+    for m in (1, 16, 31, 64, 100, 129, 256, 300):
+        idx = torch.randint(0, rows, (m,), generator=g, device=DEV, dtype=torch.int32)
+        G, Yu = gpu_lib.gram(X, idx, 1.0 / cols, 0.5, u)
+        Y = Xc[idx.long()]
+        want = Y @ Y.t() / cols + 0.5 * torch.eye(m, device=DEV, dtype=torch.float64)
+        mag = Y.abs() @ Y.abs().t() / cols + 0.5
+        assert bool(((G - want).abs() <= 2 * (cols + 4) * U * mag).all())
+        assert bool(((Yu - Y @ u).abs() <= 2 * (cols + 4) * U * (Y.abs() @ u.abs())).all())
