@@ -3,19 +3,22 @@
 //
 // A round is a work queue of column slabs (problem p, slab q).  A workgroup
 // that takes a slab
-//   1. draws the blocks of the problem's current outer step (the sampler is
-//      keyed by (seed, h), so every slab of the problem gets the same ones);
+//   1. loads the blocks of the problem's current outer step, drawn by the
+//      workgroup that finished the step before (drawing them in every slab took
+//      7 us an item);
 //   2. applies the problem's pending companion update r += Y_prev^T delta_prev
 //      on the slab's columns (the deferred residual update of the previous
 //      outer step, Alg. 2), so the update's HBM traffic lands in the same pass
 //      as the next Gram instead of a pass of its own;
 //   3. computes the slab's Gram partial and Y r partial (the split-K slab of the
 //      one-problem Gram kernel);
-//   4. counts its arrival; the workgroup that completes the problem's set of
-//      slabs sums the partials in slab order (deterministic), runs the fused
-//      solve of the s blocks (Gauss-Jordan block inverses, recurrence,
-//      w[idx] += delta) and records
-//      the step.  No workgroup ever waits for another.
+//   4. counts its arrival in its group of kBGroup slabs; the workgroup that
+//      completes a group sums the group's partials in slab order, and the one that
+//      completes the problem's groups sums those in order (deterministic), runs
+//      the fused solve of the s blocks (Gauss-Jordan block inverses, recurrence,
+//      w[idx] += delta), draws the next step's blocks and records the step.  No
+//      workgroup ever waits for another.  Partials travel at agent scope
+//      (gdev::put), so an arrival needs no fence.
 // A second persistent kernel evaluates f(w) every few rounds, either
 // recomputing r = X^T w - y exactly from X (the periodic full residual of the
 // paper's stopping discussion) or from the maintained residual after applying
@@ -40,6 +43,8 @@ constexpr int kBT = 512;           // threads of the batched kernels (8 waves)
 constexpr int kBMaxRows = 512;     // s*b of one problem (above 256: assembled Gram)
 constexpr int kBMaxB = 16;
 constexpr int kBMaxSlabs = 64;
+constexpr int kBGroup = 8;         // slabs whose partials one workgroup sums
+constexpr int kGroups = kBMaxSlabs / kBGroup;
 // Low-precision slabs stream tiles of 16 kBLpTile bytes (64 KiB; the
 // one-problem kernels use 32 KiB): a round's many problems fill the GPU
 // without narrow slabs, and the doubled bytes in flight per workgroup cut the
@@ -60,22 +65,25 @@ struct BProb {                     // constant per problem (device copy)
   int64_t chunk;                   // columns per slab
   int b, s, bp, nb;
   int nslab, aligned;
-  int sets, pad;                   // partial sets per slab (1; above 256 rows 4 or 6)
+  int sets;                        // partial sets per slab (1; above 256 rows 4 or 6)
+  int naux;                        // slabs of the monitor passes
+  int64_t achunk;                  // their columns
+  int32_t* ix;                     // 2 x s b: blocks of the step (parity of its number)
+  int* garrive;                    // slab arrivals by group in the current launch
   double* partials;                // nslab x sets x (nblk*256 + 16 nb)
   double* G;                       // (s b)^2
   double* Yu;                      // s b
   double* delta;                   // s b: the last step's delta
-  double* objp;                    // nslab partial sums of r^2
+  double* objp;                    // naux partial sums of r^2
 };
 
 struct BState {                    // mutable per problem
   int64_t h;                       // inner iterations done
-  int64_t h_prev;                  // first iteration of the step with a pending update
   int64_t steps;                   // outer steps done
   double obj;                      // f(w) at the last monitor point
   int m_prev;                      // rows of the pending companion update (0: none)
   int active;                      // still iterating
-  int arrive;                      // slab arrivals in the current launch
+  int arrive;                      // group (monitor passes: slab) arrivals in the launch
   int status;                      // DeviceStatus (sticky)
   int fresh;                       // 0: stale, 1: obj from the maintained r, 2: r exact
   int pad[3];
@@ -91,138 +99,129 @@ struct BQueue {
 
 // -------------------------------------------------------------- device helpers
 
-// out[k] = (base ? beta base[k] : out[k]) + sum_{q < mq} A[row(q)][k] coef[q],
-// k in [k0, k1), row(q) = rows ? rows[q] : q; the sum runs in q order.
-// Returns this thread's sum of the new out[k]^2.
-__device__ __forceinline__ double slab_rows_dot(const double* __restrict__ A, int64_t ld,
-                                                int64_t k0, int64_t k1, const int32_t* rows,
-                                                const double* coef, int mq,
-                                                const double* __restrict__ base, double beta,
-                                                double* __restrict__ out) {
-  const gptr<const double> Ag = glb(A);
-  // columns k, k + 1 of a row, from any 8-byte boundary
-  auto pair = [&](gptr<const double> row, int64_t k) {
-    typedef double dv2u __attribute__((ext_vector_type(2), aligned(8)));
-    double2 v{0.0, 0.0};
-    if (k + 1 < k1) {
-      const dv2u t = *(gptr<const dv2u>)(row + k);
-      v.x = t.x;
-      v.y = t.y;
-    } else {
-      v.x = row[k];
-    }
-    return v;
-  };
-  const gptr<const double> bg = glb(base);
-  const gptr<double> og = glb(out);
-  double ss = 0.0;
-  for (int64_t k = k0 + 2 * (int64_t)threadIdx.x; k < k1; k += 2 * kBT) {
-    const bool two = k + 1 < k1;
-    double a0, a1 = 0.0;
-    if (base != nullptr) {
-      a0 = beta * bg[k];
-      if (two) a1 = beta * bg[k + 1];
-    } else {
-      a0 = og[k];
-      if (two) a1 = og[k + 1];
-    }
-    int q = 0;
-    for (; q + 8 <= mq; q += 8) {
-      double2 v[8];
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const int64_t row = rows != nullptr ? rows[q + j] : q + j;
-        v[j] = pair(Ag + row * ld, k);
-      }
-#pragma unroll
-      for (int j = 0; j < 8; ++j) {
-        const double c = coef[q + j];
-        a0 = fma(v[j].x, c, a0);
-        a1 = fma(v[j].y, c, a1);
-      }
-    }
-    for (; q < mq; ++q) {
-      const int64_t row = rows != nullptr ? rows[q] : q;
-      const double2 v = pair(Ag + row * ld, k);
-      a0 = fma(v.x, coef[q], a0);
-      a1 = fma(v.y, coef[q], a1);
-    }
-    og[k] = a0;
-    if (two) og[k + 1] = a1;
-    ss += a0 * a0 + a1 * a1;
-  }
-  return ss;
-}
-
-// The same pass over stored BF16 / FP8 codes: rows decoded exactly to FP64 and
-// multiplied by coef[q] * rs[row(q)] (rs NULL: 1).  k0 is a multiple of the
-// 16-byte chunk.
+// out[k] = (base ? beta base[k] : out[k]) + sum_{q < mq} A[row(q)][k] coef[q] (codes:
+// times rs[row(q)], decoded exactly to FP64), k in [k0, k1), row(q) = rows ?
+// rows[q] : q, k0 a multiple of the 16-byte chunk.  Returns this thread's sum of the
+// new out[k]^2.
+//
+// A wave takes 64 chunks of columns (a unit) and one of R ranges of the rows at a
+// time, eight rows in flight; the ranges of a unit are added in order through LDS
+// (lds holds `cap` >= kDotLds doubles).  So a slab of any width keeps all waves
+// busy: 1152 columns as two passes of 1024 columns over all rows left the second
+// pass to two waves.  R follows from the row count alone, so every pass over a
+// problem's columns rounds alike however they are sliced.
 template <int FMT>
-__device__ __forceinline__ double slab_rows_dot_lp(const uint8_t* __restrict__ A, int64_t ld,
-                                                   int64_t k0, int64_t k1, const int32_t* rows,
-                                                   const double* coef, const float* rs, int mq,
-                                                   const double* __restrict__ base, double beta,
-                                                   double* __restrict__ out, int aligned) {
-  constexpr int ES = FMT == CABCD_BF16 ? 2 : 1;
-  constexpr int EPC = 16 / ES;
-  const gptr<const uint8_t> Ag = glb(A);
-  const gptr<const double> bg = glb(base);
-  const gptr<double> og = glb(out);
-  const gptr<const float> rg = glb(rs);
-  double ss = 0.0;
-  for (int64_t k = k0 + EPC * (int64_t)threadIdx.x; k < k1; k += (int64_t)EPC * kBT) {
-    double acc[EPC];
-#pragma unroll
-    for (int e = 0; e < EPC; ++e)
-      acc[e] = k + e < k1 ? (base != nullptr ? beta * bg[k + e] : og[k + e]) : 0.0;
-    int q = 0;
-    for (; q + 4 <= mq; q += 4) {
-      uint4 x[4];
-      double c[4];
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const int64_t row = rows != nullptr ? rows[q + j] : q + j;
-        c[j] = coef[q + j] * (rs != nullptr ? (double)rg[row] : 1.0);
-        x[j] = ldev::lp_load<FMT>(Ag + row * ld * ES, k, k1, aligned != 0);
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        double dv[EPC];
-        ldev::lp_decode_all<FMT>(x[j], dv);
-#pragma unroll
-        for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c[j], acc[e]);
-      }
-    }
-    for (; q < mq; ++q) {
-      const int64_t row = rows != nullptr ? rows[q] : q;
-      const double c = coef[q] * (rs != nullptr ? (double)rg[row] : 1.0);
-      double dv[EPC];
-      ldev::lp_decode_all<FMT>(ldev::lp_load<FMT>(Ag + row * ld * ES, k, k1, aligned != 0), dv);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
-    }
-#pragma unroll
-    for (int e = 0; e < EPC; ++e) {
-      if (k + e < k1) {
-        og[k + e] = acc[e];
-        ss += acc[e] * acc[e];
-      }
-    }
-  }
-  return ss;
-}
+constexpr int kDotUnit = FMT == CABCD_F64 ? 128 : FMT == CABCD_BF16 ? 512 : 1024;
+template <int FMT>
+constexpr int kDotLds = 8 * kDotUnit<FMT>;
 
-// Either pass, by storage format.
 template <int FMT>
 __device__ __forceinline__ double rows_dot(const BProb& pr, int64_t k0, int64_t k1,
                                            const int32_t* rows, const double* coef, int mq,
-                                           const double* base, double beta) {
-  if constexpr (FMT == CABCD_F64)
-    return slab_rows_dot(static_cast<const double*>(pr.A), pr.ld, k0, k1, rows, coef, mq, base,
-                         beta, pr.r);
-  else
-    return slab_rows_dot_lp<FMT>(static_cast<const uint8_t*>(pr.A), pr.ld, k0, k1, rows, coef,
-                                 pr.rs, mq, base, beta, pr.r, pr.aligned);
+                                           const double* base, double beta, double* lds,
+                                           int cap) {
+  constexpr int ES = FMT == CABCD_F64 ? 8 : (FMT == CABCD_BF16 ? 2 : 1);
+  constexpr int EPC = 16 / ES;
+  constexpr int UNIT = kDotUnit<FMT>;   // 64 EPC
+  constexpr int U = FMT == CABCD_FP8_E4M3 ? 4 : 8;   // rows in flight
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
+  const gptr<const uint8_t> A = glb(static_cast<const uint8_t*>(pr.A));
+  const gptr<const float> rg = glb(pr.rs);
+  const gptr<const double> bg = glb(base);
+  const gptr<double> og = glb(pr.r);
+  const int64_t ldb = pr.ld * ES;
+  int R = 8;
+  while (R > 1 && mq < 8 * R) R /= 2;
+  const int per = ((mq + R - 1) / R + U - 1) / U * U;
+  double ss = 0.0;
+  auto finish = [&](int64_t k, double s) {
+    const double v = (base != nullptr ? beta * bg[k] : og[k]) + s;
+    og[k] = v;
+    ss = fma(v, v, ss);
+  };
+  const int maxu = R > 1 ? cap / (R * UNIT) : INT_MAX;   // units of a pass
+  for (int64_t p0 = k0; p0 < k1; p0 += (int64_t)maxu * UNIT) {
+    const int nu = (int)std::min<int64_t>((k1 - p0 + UNIT - 1) / UNIT, maxu);
+    for (int task = wave; task < nu * R; task += kBT / 64) {
+      const int unit = task / R, part = task - unit * R;
+      const int q0 = part * per, q1 = std::min(mq, q0 + per);
+      const int64_t k = p0 + (int64_t)unit * UNIT + lane * EPC;
+      const bool full = k + EPC <= k1 && (FMT == CABCD_F64 || pr.aligned != 0);
+      double acc[EPC];
+#pragma unroll
+      for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
+      auto row_of = [&](int q) { return (int64_t)(rows != nullptr ? rows[q] : q); };
+      auto coef_of = [&](int q, int64_t row) {
+        return FMT != CABCD_F64 && pr.rs != nullptr ? coef[q] * (double)rg[row] : coef[q];
+      };
+      if (full) {   // 16-byte loads (FP64 rows: from any 8-byte boundary)
+        typedef unsigned int uv4 __attribute__((ext_vector_type(4), aligned(8)));
+        const gptr<const uint8_t> Ak = A + k * ES;
+        auto add = [&](uv4 w, double c) {
+          const uint4 x = make_uint4(w.x, w.y, w.z, w.w);
+          double dv[EPC];
+          if constexpr (FMT == CABCD_F64)
+            __builtin_memcpy(dv, &x, 16);
+          else
+            ldev::lp_decode_all<FMT>(x, dv);
+#pragma unroll
+          for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
+        };
+        int q = q0;
+        for (; q + U <= q1; q += U) {
+          uv4 x[U];
+          double c[U];
+#pragma unroll
+          for (int j = 0; j < U; ++j) {
+            const int64_t row = row_of(q + j);
+            c[j] = coef_of(q + j, row);
+            x[j] = *(gptr<const uv4>)(Ak + row * ldb);
+          }
+#pragma unroll
+          for (int j = 0; j < U; ++j) add(x[j], c[j]);
+        }
+        for (; q < q1; ++q) {
+          const int64_t row = row_of(q);
+          add(*(gptr<const uv4>)(Ak + row * ldb), coef_of(q, row));
+        }
+      } else if (k < k1) {   // the ragged end, and codes on odd boundaries
+        for (int q = q0; q < q1; ++q) {
+          const int64_t row = row_of(q);
+          const double c = coef_of(q, row);
+          if constexpr (FMT == CABCD_F64) {
+            acc[0] = fma(*(gptr<const double>)(A + row * ldb + k * ES), c, acc[0]);
+          } else {
+            double dv[EPC];
+            ldev::lp_decode_all<FMT>(ldev::lp_load<FMT>(A + row * ldb, k, k1, false), dv);
+#pragma unroll
+            for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
+          }
+        }
+      }
+      if (R == 1) {
+#pragma unroll
+        for (int e = 0; e < EPC; ++e)
+          if (k + e < k1) finish(k + e, acc[e]);
+      } else {
+        double* o = lds + (part * nu + unit) * UNIT + lane * EPC;
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) o[e] = acc[e];
+      }
+    }
+    if (R > 1) {
+      __syncthreads();
+      const int64_t p1 = std::min(k1, p0 + (int64_t)nu * UNIT);
+      for (int64_t k = p0 + threadIdx.x; k < p1; k += kBT) {
+        const double* v = lds + (k - p0);
+        double s = v[0];
+        for (int part = 1; part < R; ++part) s += v[part * nu * UNIT];
+        finish(k, s);
+      }
+      __syncthreads();   // lds is free again
+    }
+  }
+  return ss;
 }
 
 // Workgroup sum in a fixed order (valid in thread 0).
@@ -266,8 +265,8 @@ __device__ __noinline__ void gram_call_dma16(const double* A, int64_t ld, int64_
                                              int64_t k1, const int32_t* idx, int m,
                                              const double* u, double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  gdev::gram_slab_dma16(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
-                        uni_ptr(u), uni_ptr(part), dyn_sm);
+  gdev::gram_slab_dma16<0, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx),
+                                 uni(m), uni_ptr(u), uni_ptr(part), dyn_sm);
 }
 
 template <int NB>
@@ -275,8 +274,8 @@ __device__ __noinline__ void gram_call_dma(const double* A, int64_t ld, int64_t 
                                            const int32_t* idx, int m, const double* u,
                                            double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  gdev::gram_slab_dma<NB>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
-                          uni_ptr(u), uni_ptr(part), dyn_sm);
+  gdev::gram_slab_dma<NB, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx),
+                                uni(m), uni_ptr(u), uni_ptr(part), dyn_sm);
 }
 
 template <int NB, int FMT>
@@ -284,9 +283,10 @@ __device__ __noinline__ void gram_lp_call(const uint8_t* A, int64_t ld, int64_t 
                                           const int32_t* idx, int m, const double* u,
                                           double* part, int aligned) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  ldev::gram_lp_slab<NB, FMT, kBLpTile>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx),
-                                        uni(m), uni_ptr(u), uni_ptr(part), uni(aligned),
-                                        reinterpret_cast<uint8_t*>(dyn_sm));
+  ldev::gram_lp_slab<NB, FMT, kBLpTile, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1),
+                                              uni_ptr(idx), uni(m), uni_ptr(u), uni_ptr(part),
+                                              uni(aligned),
+                                              reinterpret_cast<uint8_t*>(dyn_sm));
 }
 
 template <int FMT>
@@ -357,16 +357,15 @@ __device__ __forceinline__ int next_item(BQueue* Q, int* slot) {
   return uni(*slot);
 }
 
-// Publish this workgroup's global writes and count its arrival at problem st;
-// true (in every thread) for the workgroup that completes the set of nslab.
-__device__ __forceinline__ bool arrive_last(BState* st, int nslab, int* slot) {
-  __threadfence();
+// Count this workgroup's arrival at a counter; true (in every thread) for the one
+// that completes the count of n.  What the others read afterwards was stored at
+// agent scope (gdev::put<true>): waiting for those stores publishes them.
+__device__ __forceinline__ bool arrive_last(int* counter, int n, int* slot) {
+  __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  if (threadIdx.x == 0) *slot = atomicAdd(&st->arrive, 1) == nslab - 1 ? 1 : 0;
+  if (threadIdx.x == 0) *slot = atomicAdd(counter, 1) == n - 1 ? 1 : 0;
   __syncthreads();
-  const bool last = uni(*slot) != 0;
-  if (last) __threadfence();   // acquire the other workgroups' writes
-  return last;
+  return uni(*slot) != 0;
 }
 
 // The last workgroup to leave resets the queue for the next launch.
@@ -382,16 +381,24 @@ __device__ __forceinline__ void queue_exit(BQueue* Q) {
 
 // ------------------------------------------------------------------- kernels
 
+// The blocks of outer step 0 (one workgroup per problem).
+__global__ __launch_bounds__(kBT) void batch_first_blocks_kernel(const BProb* __restrict__ P) {
+  const BProb& pr = P[blockIdx.x];
+  const int sk = (int)std::min((int64_t)pr.s, pr.H);
+  if ((int)threadIdx.x < sk)
+    smp::sample_block(pr.seed, threadIdx.x, pr.b, pr.d, pr.ix + threadIdx.x * pr.b);
+}
+
 template <int FMT>
 __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict__ P,
                                                          BState* __restrict__ S,
                                                          const BItem* __restrict__ items,
                                                          int nitems, BQueue* Q, int area) {
   extern __shared__ __attribute__((aligned(16))) double sm[];
-  int32_t* icur = reinterpret_cast<int32_t*>(sm + area);
+  double* dprev = sm + area;
+  int32_t* icur = reinterpret_cast<int32_t*>(dprev + kBMaxRows);
   int32_t* iprev = icur + kBMaxRows;
-  double* dprev = reinterpret_cast<double*>(iprev + kBMaxRows);
-  int* ctl = reinterpret_cast<int*>(dprev + kBMaxRows);
+  int* ctl = iprev + kBMaxRows;
   int32_t* ia = ctl + 4;           // index lists of a Gram above 256 rows
   int32_t* ib = ia + 512;
   const int tid = threadIdx.x;
@@ -402,51 +409,67 @@ __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict
     BState* st = S + item.prob;
     if (uni(st->active) == 0) break;
     const int64_t h = uni64(st->h);
-    const int64_t hp = uni64(st->h_prev);
+    const int64_t steps = uni64(st->steps);
     const int mp = uni(st->m_prev);
     const int sk = (int)std::min((int64_t)pr.s, pr.H - h);
-    const int m = sk * pr.b;
+    const int m = sk * pr.b, sb = pr.s * pr.b;
     const int64_t k0 = (int64_t)item.slab * pr.chunk;
     const int64_t k1 = std::min(pr.n, k0 + pr.chunk);
+    int32_t* const cur = pr.ix + (steps & 1) * sb;         // this step's blocks
+    int32_t* const other = pr.ix + ((steps + 1) & 1) * sb;   // the last one's, then the next's
 
-    if (tid < sk) smp::sample_block(pr.seed, h + tid, pr.b, pr.d, icur + tid * pr.b);
-    if (mp > 0) {
-      if (tid < mp / pr.b) smp::sample_block(pr.seed, hp + tid, pr.b, pr.d, iprev + tid * pr.b);
-      for (int q = tid; q < mp; q += kBT) dprev[q] = glb(pr.delta)[q];
+    if (tid < m) icur[tid] = glb(cur)[tid];
+    if (tid < mp) {
+      iprev[tid] = glb(other)[tid];
+      dprev[tid] = glb(pr.delta)[tid];
     }
     __syncthreads();
     if (mp > 0) {
       // deferred companion update of the previous outer step, this slab's columns
-      rows_dot<FMT>(pr, k0, k1, iprev, dprev, mp, nullptr, 0.0);
+      rows_dot<FMT>(pr, k0, k1, iprev, dprev, mp, nullptr, 0.0, sm, area);
       __syncthreads();   // the Gram below reads these r values back
     }
     const int64_t pstride = (int64_t)(pr.nb * (pr.nb + 1) / 2) * 256 + 16 * pr.nb;
     const int sets = uni(pr.sets);
+    const int64_t sstride = sets * pstride;   // doubles of a slab's partials
     // a problem above 256 rows: the Gram of every step assembled from 256-row
     // Grams (the two diagonal blocks, then 2 or 4 cross-block Grams)
     const int nsets = sets == 1 ? 1 : 2 + (m - 256 > 128 ? 4 : 2);
+    double* const part = pr.partials + item.slab * sstride;
     if (sets == 1) {
-      gram_any<FMT>(pr.nb, pr.A, pr.ld, k0, k1, icur, m, pr.r, pr.partials + item.slab * pstride,
-                    pr.aligned);
+      gram_any<FMT>(pr.nb, pr.A, pr.ld, k0, k1, icur, m, pr.r, part, pr.aligned);
     } else {
       gdev::big_lists(icur, m, ia, ib, tid, kBT);
       __syncthreads();
-      double* part = pr.partials + (int64_t)item.slab * sets * pstride;
       for (int g = 0; g < nsets; ++g)
         gram_any<FMT>(16, pr.A, pr.ld, k0, k1, g < 2 ? ia + 256 * g : ib + 256 * (g - 2), 256,
-                      g < 2 ? pr.r : nullptr, part + g * pstride, pr.aligned);
+                           g < 2 ? pr.r : nullptr, part + g * pstride, pr.aligned);
     }
-    if (!arrive_last(st, pr.nslab, ctl + 1)) break;
+    // the slab's group, then (with more than one group) the problem's groups
+    const int ngroup = (pr.nslab + kBGroup - 1) / kBGroup;
+    const int grp = item.slab / kBGroup;
+    const int gn = std::min(kBGroup, pr.nslab - grp * kBGroup);
+    if (!arrive_last(pr.garrive + grp, gn, ctl + 1)) break;
+    if (tid == 0) pr.garrive[grp] = 0;
+    int n = pr.nslab;
+    int64_t stride = sstride;
+    if (ngroup > 1) {
+      double* const gp = pr.partials + grp * kBGroup * sstride;
+      gdev::sum_sets<kBT>(gp, gn, sstride, nsets * pstride,
+                          [&](int64_t e, double s) { gdev::put<true>(glb(gp) + e, s); });
+      if (!arrive_last(&st->arrive, ngroup, ctl + 1)) break;
+      n = ngroup;
+      stride = kBGroup * sstride;
+    }
 
     // Last slab of this problem: Gov (overlap-augmented, Alg. 2 scale 1/n and
     // shift lambda), then the fused solve and w[idx] += delta.
     if (sets == 1)
-      gdev::reduce_wg<kBT>(pr.partials, pr.nslab, pr.nb, icur, m, 1.0 / (double)pr.n, pr.lambda,
+      gdev::reduce_wg<kBT>(pr.partials, n, stride, pr.nb, icur, m, 1.0 / (double)pr.n, pr.lambda,
                            pr.G, pr.Yu, FMT == CABCD_F64 ? 0 : 1, pr.rs);
     else
-      gdev::reduce_wg_big<kBT>(pr.partials, pr.nslab, sets * pstride, nsets, icur, m,
-                               1.0 / (double)pr.n, pr.lambda, pr.G, pr.Yu,
-                               FMT == CABCD_F64 ? 0 : 1, pr.rs);
+      gdev::reduce_wg_big<kBT>(pr.partials, n, stride, nsets, icur, m, 1.0 / (double)pr.n,
+                               pr.lambda, pr.G, pr.Yu, FMT == CABCD_F64 ? 0 : 1, pr.rs);
     __syncthreads();
     SolveArgs a;
     a.G = pr.G;
@@ -465,12 +488,15 @@ __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict
     a.pre_inverted = 0;
     solve_any(pr.bp, a);
     __syncthreads();
+    const int sn = (int)std::min((int64_t)pr.s, pr.H - h - sk);   // the next step's blocks
+    if (tid < sn) smp::sample_block(pr.seed, h + sk + tid, pr.b, pr.d, icur + tid * pr.b);
+    __syncthreads();
+    if (tid < sn * pr.b) glb(other)[tid] = icur[tid];
     if (tid == 0) {
       st->arrive = 0;
-      st->h_prev = h;
       st->m_prev = m;
       st->h = h + sk;
-      st->steps += 1;
+      st->steps = steps + 1;
       st->fresh = 0;
       if (h + sk >= pr.H) st->active = 0;
     }
@@ -484,6 +510,10 @@ __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict
 // MODE 2 (monitor): apply the pending update and evaluate f(w) from the
 //         maintained r (a pass over the pending rows and r only), retire as 0.
 constexpr int kAuxExact = 0, kAuxFlush = 1, kAuxMonitor = 2;
+// LDS of a monitor item's row ranges (rows_dot), in doubles: two units of columns
+// (FP8: one).
+template <int FMT>
+constexpr int kAuxLds = FMT == CABCD_FP8_E4M3 ? kDotLds<FMT> : 2 * kDotLds<FMT>;
 
 template <int MODE, int FMT>
 __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict__ P,
@@ -494,6 +524,7 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
   __shared__ double dprev[kBMaxRows];
   __shared__ double red[kBT / 64];
   __shared__ int ctl[2];
+  __shared__ __attribute__((aligned(16))) double part[kAuxLds<FMT>];
   const int tid = threadIdx.x;
 
   for (int it = next_item(Q, ctl); it < nitems; it = next_item(Q, ctl)) do {
@@ -503,26 +534,28 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
     const int fresh = uni(st->fresh);
     const int mp = uni(st->m_prev);
     if (MODE == kAuxExact ? fresh == 2 : MODE == kAuxFlush ? mp == 0 : fresh != 0) break;
-    const int64_t k0 = (int64_t)item.slab * pr.chunk;
-    const int64_t k1 = std::min(pr.n, k0 + pr.chunk);
+    const int64_t k0 = (int64_t)item.slab * pr.achunk;
+    const int64_t k1 = std::min(pr.n, k0 + pr.achunk);
     double ss = 0.0;
     if (MODE == kAuxExact) {
-      ss = rows_dot<FMT>(pr, k0, k1, nullptr, pr.w, (int)pr.d, pr.y, -1.0);
+      ss = rows_dot<FMT>(pr, k0, k1, nullptr, pr.w, (int)pr.d, pr.y, -1.0, part, kAuxLds<FMT>);
     } else if (mp > 0) {
-      const int64_t hp = uni64(st->h_prev);
-      if (tid < mp / pr.b) smp::sample_block(pr.seed, hp + tid, pr.b, pr.d, iprev + tid * pr.b);
-      for (int q = tid; q < mp; q += kBT) dprev[q] = glb(pr.delta)[q];
+      const int32_t* prev = pr.ix + ((uni64(st->steps) + 1) & 1) * pr.s * pr.b;
+      if (tid < mp) {
+        iprev[tid] = glb(prev)[tid];
+        dprev[tid] = glb(pr.delta)[tid];
+      }
       __syncthreads();
-      ss = rows_dot<FMT>(pr, k0, k1, iprev, dprev, mp, nullptr, 0.0);
+      ss = rows_dot<FMT>(pr, k0, k1, iprev, dprev, mp, nullptr, 0.0, part, kAuxLds<FMT>);
     } else {
       const gptr<const double> rg = glb(pr.r);
       for (int64_t k = k0 + tid; k < k1; k += kBT) ss = fma(rg[k], rg[k], ss);
     }
     if (MODE != kAuxFlush) {
       ss = block_sum(ss, red);
-      if (tid == 0) glb(pr.objp)[item.slab] = ss;
+      if (tid == 0) gdev::put<true>(glb(pr.objp) + item.slab, ss);
     }
-    if (!arrive_last(st, pr.nslab, ctl + 1)) break;
+    if (!arrive_last(&st->arrive, pr.naux, ctl + 1)) break;
     if (MODE != kAuxFlush) {
       double ww = 0.0;
       const gptr<const double> wg = glb(pr.w);
@@ -530,7 +563,12 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
       ww = block_sum(ww, red);
       if (tid == 0) {
         double rr = 0.0;
-        for (int q = 0; q < pr.nslab; ++q) rr += glb(pr.objp)[q];
+        for (int q = 0; q < pr.naux; q += 8) {   // eight loads in flight
+          double v[8];
+          for (int j = 0; j < 8; ++j)
+            v[j] = gdev::get_agent(glb(pr.objp) + std::min(q + j, pr.naux - 1));
+          for (int j = 0; j < 8; ++j) rr += q + j < pr.naux ? v[j] : 0.0;
+        }
         const double f = rr / (2.0 * (double)pr.n) + 0.5 * pr.lambda * ww;
         st->obj = f;
         if (!isfinite(f)) raise_status(&st->status, DEV_NONFINITE);
@@ -578,6 +616,9 @@ constexpr double kCuBw = 5.0e12 / 256;
 constexpr double kWgBw = 60e9;
 constexpr double kSolveBlock = 1.5e-6;
 constexpr double kRoundFixed = 10e-6;
+// Bytes of X in one item of an exact monitor (32 problems, 2.5 GB: 0.549 ms at 128
+// KiB, 0.512 at 256, 0.503 at 1 MiB, 0.568 at 4 MiB).
+constexpr int64_t kAuxBytes = 1 << 20;
 constexpr int kGraphMaxRounds = 64;   // rounds of one captured monitor period, at most
 constexpr int kReplanRounds = 32;     // rounds between checks for re-slicing, about
 
@@ -586,6 +627,14 @@ int elem_bytes(int dtype) { return dtype == CABCD_F64 ? 8 : dtype == CABCD_BF16 
 // Columns per LDS tile of the Gram slab (slab widths are multiples of it).
 int tile_cols(int nb, int dtype) {
   return dtype == CABCD_F64 ? 256 / nb : (kBLpTile / nb) / elem_bytes(dtype);
+}
+
+// Columns of a monitor item: units of 64 16-byte chunks, as many as kAuxBytes of the
+// d rows hold.  (With the step's slabs as items an exact monitor of 32 problems, 2.5
+// GB, took 0.97 ms: items of up to 17 MB, whose tail ran on a few CUs.)
+int64_t aux_chunk(int64_t d, int dtype) {
+  const int64_t unit = 64 * 16 / elem_bytes(dtype);
+  return unit * std::max<int64_t>(1, kAuxBytes / (d * 1024));
 }
 
 // CU-seconds of one problem's slabs in one round (Gram of the padded rows and
@@ -631,8 +680,8 @@ void slice(double wp, double target, int64_t n, int kt, int64_t& chunk_out, int&
 // Slab items per CU a round aims at: FP64 slabs carry matrix-core work and
 // balance best at four; low-precision slabs are pure streams, and fewer,
 // longer items cut their per-item overhead (BF16 batched to 1e-6: 0.153 s at
-// four, 0.141 s at two; FP64 0.334 s at four, 0.339 s at two, 0.374 s at
-// eight).
+// four, 0.141 s at two; a round of 32 FP64 problems 0.301 ms at four, 0.327 at
+// six, 0.370 at eight).
 double items_per_cu(int dtype) { return dtype == CABCD_F64 ? 4.0 : 2.0; }
 
 // (b, s) of every problem for a target of `rp` rounds per pass over the
@@ -697,10 +746,11 @@ struct cabcd_batch_plan {
   std::vector<cabcd::BProb> probs;
   cabcd::BProb* dP = nullptr;
   cabcd::BState* dS = nullptr;
-  cabcd::BItem* dI = nullptr;
+  cabcd::BItem* dI = nullptr;    // slabs of a round
+  cabcd::BItem* dIa = nullptr;   // slabs of a monitor pass
   cabcd::BQueue* dQ = nullptr;
   void* mem = nullptr;
-  int nitems = 0;
+  int nitems = 0, naux = 0;
   int area = 0;            // doubles of the step kernel's shared Gram/solve area
   size_t step_lds = 0;
   int grid_step = 1, grid_aux = 1;
@@ -718,7 +768,7 @@ struct cabcd_batch_plan {
   // re-slicing of the slabs as problems retire
   int cus = 1, occ_step = 1, occ_aux = 1;
   int items_cap = 0;       // capacity of dI
-  double* pool = nullptr;  // partials and objective partials of re-sliced plans
+  double* pool = nullptr;  // partials of re-sliced plans
   size_t pool_doubles = 0;
   int plan_active = 0;     // active problems when the slabs were last sliced
   int64_t replan_period = 0;
@@ -729,15 +779,15 @@ namespace {
 
 template <int FMT>
 hipError_t launch_step_t(cabcd_batch_plan* B, hipStream_t st) {
-  hipLaunchKernelGGL(batch_step_kernel<FMT>, dim3(B->grid_step), dim3(kBT), B->step_lds, st,
-                     B->dP, B->dS, B->dI, B->nitems, B->dQ, B->area);
+  hipLaunchKernelGGL(batch_step_kernel<FMT>, dim3(B->grid_step), dim3(kBT), B->step_lds,
+                     st, B->dP, B->dS, B->dI, B->nitems, B->dQ, B->area);
   return hipGetLastError();
 }
 
 template <int MODE, int FMT>
 hipError_t launch_aux_t(cabcd_batch_plan* B, hipStream_t st) {
   hipLaunchKernelGGL((batch_aux_kernel<MODE, FMT>), dim3(B->grid_aux), dim3(kBT), 0, st, B->dP,
-                     B->dS, B->dI, B->nitems, B->dQ);
+                     B->dS, B->dIa, B->naux, B->dQ);
   return hipGetLastError();
 }
 
@@ -771,6 +821,27 @@ const void* step_kernel_ptr(int dtype) {
     case CABCD_F64: return reinterpret_cast<const void*>(batch_step_kernel<CABCD_F64>);
     case CABCD_BF16: return reinterpret_cast<const void*>(batch_step_kernel<CABCD_BF16>);
     default: return reinterpret_cast<const void*>(batch_step_kernel<CABCD_FP8_E4M3>);
+  }
+}
+
+const void* aux_kernel_ptr(int dtype) {
+  switch (dtype) {
+    case CABCD_F64:
+      return reinterpret_cast<const void*>(batch_aux_kernel<kAuxExact, CABCD_F64>);
+    case CABCD_BF16:
+      return reinterpret_cast<const void*>(batch_aux_kernel<kAuxExact, CABCD_BF16>);
+    default: return reinterpret_cast<const void*>(batch_aux_kernel<kAuxExact, CABCD_FP8_E4M3>);
+  }
+}
+
+// LDS of the FP64 Gram slab with nb block rows, in doubles.
+int gram_lds(int nb) {
+  switch (nb) {
+    case 1: return gdev::DN<1>::LDS;
+    case 2: return gdev::DN<2>::LDS;
+    case 4: return gdev::DN<4>::LDS;
+    case 8: return gdev::DN<8>::LDS;
+    default: return gdev::D16::LDS;
   }
 }
 
@@ -905,6 +976,15 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->nitems = (int)items.size();
   B->cus = cus;
   B->items_cap = std::max(B->nitems, 4 * cus + 2 * P);
+  std::vector<BItem> aux;
+  std::vector<int64_t> achunk(P);
+  std::vector<int> naux(P);
+  for (int p : order) {
+    achunk[p] = aux_chunk(pb[p].X.rows, B->dtype);
+    naux[p] = (int)((pb[p].X.cols + achunk[p] - 1) / achunk[p]);
+    for (int q = 0; q < naux[p]; ++q) aux.push_back(BItem{p, q});
+  }
+  B->naux = (int)aux.size();
 
   // Workspace and device copies.  The pool holds the partials of re-sliced
   // plans: as much as the first plan's, plus the largest slab set of one
@@ -914,6 +994,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   add(sizeof(BProb) * P);
   add(sizeof(BState) * P);
   add(sizeof(BItem) * B->items_cap);
+  add(sizeof(BItem) * B->naux);
   add(sizeof(BQueue));
   int area = 0;
   size_t pool = 0;
@@ -924,24 +1005,23 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     add(sizeof(double) * sb * sb);
     add(sizeof(double) * sb);
     add(sizeof(double) * sb);
-    add(sizeof(double) * best[p].nslab);
+    add(sizeof(double) * naux[p]);
+    add(sizeof(int32_t) * 2 * sb);
+    add(sizeof(int) * kGroups);
     area = std::max<int>(area, (int)((solve_lds_bytes(sb, best[p].b) + 7) / 8));
-    pool += (size_t)best[p].nslab * (slab_doubles(sb) + 1) + 64;
+    if (B->dtype == CABCD_F64) area = std::max({area, gram_lds(nb), kDotLds<CABCD_F64>});
+    pool += (size_t)best[p].nslab * slab_doubles(sb) + 32;
   }
-  pool += (size_t)kBMaxSlabs * (slab_doubles(kBMaxRows) + 1) + 64;
+  pool += (size_t)kBMaxSlabs * slab_doubles(kBMaxRows) + 32;
   B->pool_doubles = pool;
   add(sizeof(double) * pool);
-  if (B->dtype == CABCD_F64) {
-    area = std::max<int>(area, gdev::D16::LDS);
-    area = std::max<int>(area, std::max(gdev::DN<1>::LDS, gdev::DN<2>::LDS));
-    area = std::max<int>(area, std::max(gdev::DN<4>::LDS, gdev::DN<8>::LDS));
-  } else {
+  if (B->dtype != CABCD_F64) {
     const int lp = B->dtype == CABCD_BF16
                        ? std::max(ldev::LpCfg<16, CABCD_BF16, kBLpTile>::LDS,
                                   ldev::LpCfg<1, CABCD_BF16, kBLpTile>::LDS)
                        : std::max(ldev::LpCfg<16, CABCD_FP8_E4M3, kBLpTile>::LDS,
                                   ldev::LpCfg<1, CABCD_FP8_E4M3, kBLpTile>::LDS);
-    area = std::max<int>(area, (lp + 7) / 8);
+    area = std::max<int>(area, (lp + 7) / 8);   // (kDotLds and more)
   }
   B->area = (area + 1) & ~1;
   B->step_lds = sizeof(double) * B->area + kBMaxRows * 2 * sizeof(int32_t) +
@@ -955,6 +1035,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->dP = ws.take<BProb>(P);
   B->dS = ws.take<BState>(P);
   B->dI = ws.take<BItem>(B->items_cap);
+  B->dIa = ws.take<BItem>(B->naux);
   B->dQ = ws.take<BQueue>(1);
   B->pool = ws.take<double>(B->pool_doubles);
   B->probs.resize(P);
@@ -981,7 +1062,8 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     o.bp = pow2_at_least(o.b);
     o.nb = nb_of(sb);
     o.sets = sets_of(sb);
-    o.pad = 0;
+    o.naux = naux[p];
+    o.achunk = achunk[p];
     o.nslab = best[p].nslab;
     o.aligned = ((reinterpret_cast<uintptr_t>(o.A) & 15) == 0 &&
                  ((o.ld * elem_bytes(B->dtype)) & 15) == 0)
@@ -991,7 +1073,10 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     o.G = ws.take<double>((size_t)sb * sb);
     o.Yu = ws.take<double>(sb);
     o.delta = ws.take<double>(sb);
-    o.objp = ws.take<double>(o.nslab);
+    o.objp = ws.take<double>(o.naux);
+    o.ix = ws.take<int32_t>(2 * sb);
+    o.garrive = ws.take<int>(kGroups);
+    BATCH_HIP(hipMemsetAsync(o.garrive, 0, sizeof(int) * kGroups, st));
     BState& s = S[p];
     std::memset(&s, 0, sizeof s);
     s.obj = NAN;
@@ -1000,6 +1085,8 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   BATCH_HIP(hipMemcpyAsync(B->dP, B->probs.data(), sizeof(BProb) * P, hipMemcpyHostToDevice, st));
   BATCH_HIP(hipMemcpyAsync(B->dS, S.data(), sizeof(BState) * P, hipMemcpyHostToDevice, st));
   BATCH_HIP(hipMemcpyAsync(B->dI, items.data(), sizeof(BItem) * items.size(),
+                           hipMemcpyHostToDevice, st));
+  BATCH_HIP(hipMemcpyAsync(B->dIa, aux.data(), sizeof(BItem) * aux.size(),
                            hipMemcpyHostToDevice, st));
   BQueue q0{0, 0};
   BATCH_HIP(hipMemcpyAsync(B->dQ, &q0, sizeof q0, hipMemcpyHostToDevice, st));
@@ -1012,12 +1099,13 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
                                                          B->step_lds));
   B->occ_step = std::max(occ, 1);
   B->grid_step = std::max(1, std::min(B->nitems, B->occ_step * cus));
-  BATCH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(
-      &occ, reinterpret_cast<const void*>(batch_aux_kernel<0, CABCD_F64>), kBT, 0));
+  BATCH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, aux_kernel_ptr(B->dtype), kBT, 0));
   B->occ_aux = std::max(occ, 1);
-  B->grid_aux = std::max(1, std::min(B->nitems, B->occ_aux * cus));
+  B->grid_aux = std::max(1, std::min(B->naux, B->occ_aux * cus));
   B->plan_active = P;
 
+  hipLaunchKernelGGL(batch_first_blocks_kernel, dim3(P), dim3(kBT), 0, st, B->dP);
+  BATCH_HIP(hipGetLastError());
   // r_0 = X^T w_0 - y and f(w_0).
   BATCH_HIP(launch_aux(B, kAuxExact, st));
   cabcd_status rc = sync_status(B, st, nullptr);
@@ -1069,9 +1157,9 @@ cabcd_status capture(cabcd_batch_plan* B) {
 // Re-slicing: once the active problems have halved since the slabs were last
 // cut, their slabs are cut again for the active problems alone (same (b, s),
 // the slab target recomputed from their work), so the GPU stays filled as
-// problems retire.  Runs between launches; the partials and objective
-// partials live only within a launch, so they move to the pool freely.  Only
-// the rounding order of the Gram sums changes (more, shorter slabs).
+// problems retire.  Runs between launches; the partials live only within a
+// launch, so they move to the pool freely.  Only the rounding order of the Gram
+// sums changes (more, shorter slabs).
 cabcd_status replan(cabcd_batch_plan* B, hipStream_t st) {
   std::vector<BState> S(B->P);
   BATCH_HIP(hipMemcpyAsync(S.data(), B->dS, sizeof(BState) * B->P, hipMemcpyDeviceToHost, st));
@@ -1096,7 +1184,7 @@ cabcd_status replan(cabcd_batch_plan* B, hipStream_t st) {
       const BProb& o = B->probs[act[i]];
       slice(wp[i], target, o.n, tile_cols(o.nb, B->dtype), chunk[i], nslab[i]);
       items += nslab[i];
-      doubles += (size_t)nslab[i] * (slab_doubles(o.b * o.s) + 1) + 64;
+      doubles += (size_t)nslab[i] * slab_doubles(o.b * o.s) + 32;
     }
     if (items <= (size_t)B->items_cap && doubles <= B->pool_doubles) break;
   }
@@ -1113,16 +1201,23 @@ cabcd_status replan(cabcd_batch_plan* B, hipStream_t st) {
     o.chunk = chunk[i];
     o.nslab = nslab[i];
     o.partials = ws.take<double>((size_t)o.nslab * slab_doubles(o.b * o.s));
-    o.objp = ws.take<double>(o.nslab);
     for (int q = 0; q < o.nslab; ++q) items.push_back(BItem{act[i], q});
   }
+  // monitor passes keep a retired problem while its last update is pending
+  std::vector<BItem> aux;
+  for (int p = 0; p < B->P; ++p)
+    if (S[p].active || S[p].m_prev > 0)
+      for (int q = 0; q < B->probs[p].naux; ++q) aux.push_back(BItem{p, q});
   B->nitems = (int)items.size();
+  B->naux = (int)aux.size();
   B->grid_step = std::max(1, std::min(B->nitems, B->occ_step * B->cus));
-  B->grid_aux = std::max(1, std::min(B->nitems, B->occ_aux * B->cus));
+  B->grid_aux = std::max(1, std::min(B->naux, B->occ_aux * B->cus));
   B->plan_active = (int)act.size();
   BATCH_HIP(hipMemcpyAsync(B->dP, B->probs.data(), sizeof(BProb) * B->P, hipMemcpyHostToDevice,
                            st));
   BATCH_HIP(hipMemcpyAsync(B->dI, items.data(), sizeof(BItem) * items.size(),
+                           hipMemcpyHostToDevice, st));
+  BATCH_HIP(hipMemcpyAsync(B->dIa, aux.data(), sizeof(BItem) * aux.size(),
                            hipMemcpyHostToDevice, st));
   BATCH_HIP(hipStreamSynchronize(st));
   return capture(B);

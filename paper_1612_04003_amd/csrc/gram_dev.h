@@ -84,6 +84,21 @@ __device__ __forceinline__ d4 mfma(double a, double b, d4 c) {
   return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0);
 }
 
+// Stores and loads of a slab's partial sums.  AGENT: at agent scope (written
+// through to, and read from, where every XCD sees them), for a reader in the same
+// launch, which then needs no fence: publishing ordinary stores with one writes
+// the XCD's whole L2 back, 37 us an item in the batched rounds.
+template <bool AGENT>
+__device__ __forceinline__ void put(gptr<double> p, double v) {
+  if constexpr (AGENT)
+    __hip_atomic_store((double*)p, v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  else
+    *p = v;
+}
+__device__ __forceinline__ double get_agent(gptr<const double> p) {
+  return __hip_atomic_load((const double*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 // ---------------------------------------------------------------------------
 // NB <= 8: waves own block-row pairs and split a tile's k-steps.  A 32 KiB tile of
 // SBP rows x
@@ -99,7 +114,11 @@ struct DN {
   static constexpr int DMA_PER_WAVE = C::SBP * C::CH / 64 / 8;   // 4 instructions
   static constexpr int UDMA = (C::KT / 2 + 63) / 64;              // u slots, 64 a time
   static constexpr int TILE = C::SBP * C::KT + C::KT;            // doubles: rows, then u
-  static constexpr int LDS = std::max(std::max(2 * TILE, C::RED), C::YUS);
+  // parts in which a wave's blocks meet the other k-groups' (NB = 8: 64.5 KiB
+  // of LDS instead of 72, so that two batched workgroups fit a CU)
+  static constexpr int HV = C::RED > 2 * TILE ? 2 : 1;
+  static constexpr int RED = (C::KG - 1) * C::BW * ((C::NACC + HV - 1) / HV) * 256;
+  static constexpr int LDS = std::max(std::max(2 * TILE, RED), C::YUS);
 };
 
 template <int NB, int W>
@@ -157,7 +176,7 @@ __device__ __forceinline__ void mma_dispatch_dma(int bw, const double* __restric
 // column (NULL: no Y u).  Writes the partial blocks and the partial Y u to
 // part[0 .. NBLK*256 + SBP).  lds holds DN<NB>::LDS doubles.  Every thread of the
 // workgroup must call it.
-template <int NB>
+template <int NB, bool AGENT = false>
 __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int64_t ld,
                                               int64_t k_begin, int64_t k_end, const int32_t* idx,
                                               int m, const double* __restrict__ u,
@@ -270,40 +289,39 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     __syncthreads();
   }
 
-  // Sum the k-groups (waves with the same blocks) through LDS, in group order.
+  // Sum the k-groups (waves with the same blocks) through LDS, in group order,
+  // a wave's blocks in HV parts so that they fit the tiles' space.
   if constexpr (C::KG > 1) {
-    if (kg > 0) {
+    constexpr int HA = (C::NACC + D::HV - 1) / D::HV;   // accumulators of a part
 #pragma unroll
-      for (int a = 0; a < C::NACC; ++a) {
-        double* dst = lds + ((kg - 1) * C::NBLK + acc_block<NB>(bw, a)) * 256 + lane;
-        dst[0] = acc[a][0];
-        dst[64] = acc[a][1];
-        dst[128] = acc[a][2];
-        dst[192] = acc[a][3];
+    for (int a0 = 0; a0 < C::NACC; a0 += HA) {
+      auto at = [&](int g, int a) {
+        return lds + (((g - 1) * C::BW + bw) * HA + (a - a0)) * 256 + lane;
+      };
+      if (kg > 0) {
+#pragma unroll
+        for (int a = a0; a < std::min(a0 + HA, C::NACC); ++a)
+#pragma unroll
+          for (int i = 0; i < 4; ++i) at(kg, a)[64 * i] = acc[a][i];
       }
-    }
-    __syncthreads();
-    if (kg == 0) {
-      for (int g = 1; g < C::KG; ++g) {
+      __syncthreads();
+      if (kg == 0) {
+        for (int g = 1; g < C::KG; ++g) {
 #pragma unroll
-        for (int a = 0; a < C::NACC; ++a) {
-          const double* srcp = lds + ((g - 1) * C::NBLK + acc_block<NB>(bw, a)) * 256 + lane;
-          acc[a][0] += srcp[0];
-          acc[a][1] += srcp[64];
-          acc[a][2] += srcp[128];
-          acc[a][3] += srcp[192];
+          for (int a = a0; a < std::min(a0 + HA, C::NACC); ++a)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) acc[a][i] += at(g, a)[64 * i];
         }
       }
+      if (a0 + HA < C::NACC) __syncthreads();
     }
   }
   if (kg == 0) {
 #pragma unroll
     for (int a = 0; a < C::NACC; ++a) {
       gptr<double> dst = glb(part) + acc_block<NB>(bw, a) * 256 + lane;
-      dst[0] = acc[a][0];
-      dst[64] = acc[a][1];
-      dst[128] = acc[a][2];
-      dst[192] = acc[a][3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) put<AGENT>(dst + 64 * i, acc[a][i]);
     }
   }
   if (want_u) {
@@ -314,7 +332,7 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     if (tid < C::SBP) {
       double sum = 0.0;
       for (int q = 0; q < C::CH; ++q) sum += lds[tid * C::CH + q];
-      glb(part)[C::NBLK * 256 + tid] = sum;
+      put<AGENT>(glb(part) + C::NBLK * 256 + tid, sum);
     }
   }
 }
@@ -392,7 +410,7 @@ __device__ __forceinline__ int d16_swz(int r) { return D16::CH == 8 ? (r >> 1) &
 // previous step's rows are DMA'd two tiles ahead, their chunks swizzled as
 // the Gram's tiles are ((r >> 1) & 7), so the column-pair reads of sixteen
 // consecutive rows fall in distinct banks.
-template <int W, int MODE>
+template <int W, int MODE, bool AGENT>
 __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t ld,
                                          int64_t k_begin, int64_t k_end, const int32_t* idx,
                                          int m, const double* __restrict__ u,
@@ -617,10 +635,8 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   for (int a = 0; a < 17; ++a) {
     const int blk = a <= R0 ? blk_index(R0, a) : blk_index(R1, a - R0 - 1);
     gptr<double> dst = pg + blk * 256 + lane;
-    dst[0] = acc[a][0];
-    dst[64] = acc[a][1];
-    dst[128] = acc[a][2];
-    dst[192] = acc[a][3];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) put<AGENT>(dst + 64 * i, acc[a][i]);
   }
   if (want_u) {   // Y u of the two owned block rows: sum the four lane groups
 #pragma unroll
@@ -628,13 +644,13 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
       double v = yua[i];
       v += __shfl_xor(v, 16, 64);
       v += __shfl_xor(v, 32, 64);
-      if (lane < 16) pg[C::NBLK * 256 + 16 * (i == 0 ? R0 : R1) + lane] = v;
+      if (lane < 16) put<AGENT>(pg + C::NBLK * 256 + 16 * (i == 0 ? R0 : R1) + lane, v);
     }
   }
 }
 
 // The NB = 16 slab; arguments and partial layout as gram_slab_dma.
-template <int MODE = 0>
+template <int MODE = 0, bool AGENT = false>
 __device__ __forceinline__ void gram_slab_dma16(const double* __restrict__ A, int64_t ld,
                                                 int64_t k_begin, int64_t k_end,
                                                 const int32_t* idx, int m,
@@ -642,14 +658,14 @@ __device__ __forceinline__ void gram_slab_dma16(const double* __restrict__ A, in
                                                 double* __restrict__ part, double* lds,
                                                 const D16Upd up = D16Upd{}) {
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: d16_slab<0, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 1: d16_slab<1, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 2: d16_slab<2, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 3: d16_slab<3, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 4: d16_slab<4, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 5: d16_slab<5, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 6: d16_slab<6, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    default: d16_slab<7, MODE>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 0: d16_slab<0, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 1: d16_slab<1, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 2: d16_slab<2, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 3: d16_slab<3, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 4: d16_slab<4, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 5: d16_slab<5, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 6: d16_slab<6, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    default: d16_slab<7, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
   }
 }
 
@@ -758,60 +774,56 @@ __device__ __forceinline__ void store_entry_big(int64_t e, double t, int set, in
   glb(G)[(int64_t)gc * m + gr] = v;
 }
 
-// The whole reduction by one workgroup of T threads: partial sets 0..nsplit-1
-// (stride nblk*256 + 16 nb) are added in set order for every entry.
-template <int T>
-__device__ __forceinline__ void reduce_wg(const double* __restrict__ partials, int nsplit, int nb,
-                                          const int32_t* idx, int m, double scale, double shift,
-                                          double* __restrict__ G, double* __restrict__ Yu,
-                                          int layout, const float* __restrict__ rs) {
-  const int nblk = nb * (nb + 1) / 2;
-  const int64_t pstride = (int64_t)nblk * 256 + 16 * nb;
-  for (int64_t e = threadIdx.x; e < pstride; e += T) {
-    const gptr<const double> p = glb(partials) + e;
+// out[e] = the sum over q < n of in[e + q stride], in q order, by T threads;
+// every value at agent scope (gdev::put<true>).
+template <int T, class Out>
+__device__ __forceinline__ void sum_sets(const double* __restrict__ in, int n, int64_t stride,
+                                         int64_t count, Out out) {
+  for (int64_t e = threadIdx.x; e < count; e += T) {
+    const gptr<const double> p = glb(in) + e;
     double s = 0.0;
-    int sp = 0;
-    for (; sp + 8 <= nsplit; sp += 8) {
+    for (int q = 0; q < n; q += 8) {
       double v[8];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) v[q] = p[(int64_t)(sp + q) * pstride];
+      for (int j = 0; j < 8; ++j) v[j] = get_agent(p + (int64_t)std::min(q + j, n - 1) * stride);
 #pragma unroll
-      for (int q = 0; q < 8; ++q) s += v[q];
+      for (int j = 0; j < 8; ++j) s += q + j < n ? v[j] : 0.0;
     }
-    for (; sp < nsplit; ++sp) s += p[(int64_t)sp * pstride];
-    store_entry(e, s, nblk, idx, m, scale, shift, 1, G, Yu, layout, rs);
+    out(e, s);
   }
 }
 
-// The reduction of a Gram of m <= 512 rows assembled from 256-row Grams, by
-// one workgroup of T threads: slab q's partial set g (g < 2: the diagonal
-// blocks, then the cross blocks; nsets = 2 + big_cross_steps(m)) is at
-// partials + q sstride + g pstride16; every entry sums its slabs in slab order
-// and is stored once (store_entry_big).
+// The whole reduction by one workgroup of T threads: n partial sets (stride
+// doubles apart) are added in set order for every entry.
 template <int T>
-__device__ __forceinline__ void reduce_wg_big(const double* __restrict__ partials, int nslab,
-                                              int64_t sstride, int nsets, const int32_t* idx,
+__device__ __forceinline__ void reduce_wg(const double* __restrict__ partials, int n,
+                                          int64_t stride, int nb, const int32_t* idx, int m,
+                                          double scale, double shift, double* __restrict__ G,
+                                          double* __restrict__ Yu, int layout,
+                                          const float* __restrict__ rs) {
+  const int nblk = nb * (nb + 1) / 2;
+  sum_sets<T>(partials, n, stride, (int64_t)nblk * 256 + 16 * nb, [&](int64_t e, double s) {
+    store_entry(e, s, nblk, idx, m, scale, shift, 1, G, Yu, layout, rs);
+  });
+}
+
+// The reduction of a Gram of m <= 512 rows assembled from 256-row Grams, by
+// one workgroup of T threads: set q's partial Gram g (g < 2: the diagonal
+// blocks, then the cross blocks; nsets = 2 + big_cross_steps(m)) is at
+// partials + q stride + g pstride16; every entry sums its sets in order and is
+// stored once (store_entry_big).
+template <int T>
+__device__ __forceinline__ void reduce_wg_big(const double* __restrict__ partials, int n,
+                                              int64_t stride, int nsets, const int32_t* idx,
                                               int m, double scale, double shift,
                                               double* __restrict__ G, double* __restrict__ Yu,
                                               int layout, const float* __restrict__ rs) {
   constexpr int64_t pstride = (int64_t)136 * 256 + 16 * 16;
-  for (int g = 0; g < nsets; ++g) {
-    const int cls = g < 2 ? 0 : 1, step = g < 2 ? g : g - 2;
-    for (int64_t e = threadIdx.x; e < pstride; e += T) {
-      const gptr<const double> p = glb(partials) + (int64_t)g * pstride + e;
-      double s = 0.0;
-      int q = 0;
-      for (; q + 8 <= nslab; q += 8) {
-        double v[8];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) v[j] = p[(int64_t)(q + j) * sstride];
-#pragma unroll
-        for (int j = 0; j < 8; ++j) s += v[j];
-      }
-      for (; q < nslab; ++q) s += p[(int64_t)q * sstride];
-      store_entry_big(e, s, cls, step, idx, m, scale, shift, 1, G, Yu, layout, rs, nullptr);
-    }
-  }
+  for (int g = 0; g < nsets; ++g)
+    sum_sets<T>(partials + g * pstride, n, stride, pstride, [&](int64_t e, double s) {
+      store_entry_big(e, s, g < 2 ? 0 : 1, g < 2 ? g : g - 2, idx, m, scale, shift, 1, G, Yu,
+                      layout, rs, nullptr);
+    });
 }
 
 }  // namespace gdev

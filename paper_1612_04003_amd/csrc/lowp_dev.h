@@ -5,7 +5,7 @@
 // blocks are stored in the FP32 MFMA output order.
 #pragma once
 
-#include "internal.h"
+#include "gram_dev.h"
 
 #include <algorithm>
 
@@ -173,7 +173,7 @@ __device__ __forceinline__ uint4 lp_load(PTR row, int64_t k, int64_t k_end, bool
 // the rows idx[0..m) of the stored codes A (ld in elements), FP32 MFMA
 // accumulation, partial blocks (FP32 MFMA output order) and partial Y u (FP64,
 // decoded codes, row scales not applied) to part.  lds holds LpCfg::LDS bytes.
-template <int NB, int FMT, int TB = 2048>
+template <int NB, int FMT, int TB = 2048, bool AGENT = false>
 __device__ __forceinline__ void gram_lp_slab(const uint8_t* __restrict__ A, int64_t ld,
                                              int64_t k_begin, int64_t k_end, const int32_t* idx,
                                              int m, const double* __restrict__ u,
@@ -271,10 +271,8 @@ __device__ __forceinline__ void gram_lp_slab(const uint8_t* __restrict__ A, int6
 #pragma unroll
     for (int a = 0; a < C::NACC; ++a) {
       gptr<double> dst = glb(part) + lp_acc_block<NB>(bw, a) * 256 + lane;
-      dst[0] = acc[a][0];
-      dst[64] = acc[a][1];
-      dst[128] = acc[a][2];
-      dst[192] = acc[a][3];
+#pragma unroll
+      for (int i = 0; i < 4; ++i) gdev::put<AGENT>(dst + 64 * i, (double)acc[a][i]);
     }
   }
   if (want_u) {
@@ -286,7 +284,7 @@ __device__ __forceinline__ void gram_lp_slab(const uint8_t* __restrict__ A, int6
     if (tid < C::SBP) {
       double s = 0.0;
       for (int q = 0; q < C::CH; ++q) s += ys[tid * C::CH + q];
-      glb(part)[C::NBLK * 256 + tid] = s;
+      gdev::put<AGENT>(glb(part) + C::NBLK * 256 + tid, s);
     }
   }
 }

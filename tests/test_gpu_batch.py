@@ -331,3 +331,38 @@ def test_batch_mixed_storage_types_rejected(gpu_lib):
     with pytest.raises(gpu_lib.CabcdError) as e:
         gpu_lib.Batch(probs)
     assert e.value.status == gpu_lib.EINVAL
+
+
+@pytest.mark.parametrize("b,s", [(1, 1), (5, 3), (4, 4), (8, 4), (9, 7), (16, 4), (16, 8)])
+def test_batch_update_row_ranges_and_slab_groups(gpu_lib, b, s):
+    """The update and the monitors split a slab's rows into 1, 2, 4 or 8 ranges
+    (from 16, 32 and 64 rows on) over units of 128 columns, and slabs are summed
+    in groups of eight: row counts at those lines, columns at the edges of a unit
+    and from one slab to several groups of them."""
+    _say("batch row ranges b=%d s=%d" % (b, s))
+    cases = [(max(b, 40), n, b, s, 5 * s + 1, 1e-2, 70 + i)
+             for i, n in enumerate((1, 127, 128, 129, 1025, 30011))]
+    probs = _problems(cases)
+    act, infos = _run(gpu_lib, probs, [3, 4])
+    assert act == 0
+    for q, (d, n, _, _, H, lam, seed), inf in zip(probs, cases, infos):
+        wo, _ = bcd.primal_bcd(q["Xc"], q["yc"], lam, b, s, H, seed)
+        w = q["w"].cpu().numpy()
+        assert np.linalg.norm(w - wo) <= 1e-10 * max(np.linalg.norm(wo), 1e-300)
+        ro = q["Xc"].T @ w - q["yc"]
+        assert np.linalg.norm(q["r"].cpu().numpy() - ro) <= 1e-10 * np.linalg.norm(q["yc"])
+        f = ro @ ro / (2 * n) + 0.5 * lam * (w @ w)
+        assert abs(inf["objective"] - f) <= 1e-10 * f
+    assert b * s < 32 or max(inf["nslab"] for inf in infos) > 8
+
+
+def test_batch_update_pending_at_retirement_is_applied_after_reslicing(gpu_lib):
+    """Without monitoring, problems whose budget ends before the slabs are cut
+    again still get their last update when the run ends."""
+    _say("batch retirement without monitoring")
+    cases = [(40, 3000, 4, 4, 16 if i else 800, 1e-2, 80 + i) for i in range(4)]
+    probs = _problems(cases)
+    _run(gpu_lib, probs, [100], monitor_every=0)
+    for q in probs:
+        ro = q["Xc"].T @ q["w"].cpu().numpy() - q["yc"]
+        assert np.linalg.norm(q["r"].cpu().numpy() - ro) <= 1e-10 * np.linalg.norm(q["yc"])
