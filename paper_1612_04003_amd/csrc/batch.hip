@@ -34,6 +34,7 @@
 #include <cmath>
 #include <cstring>
 #include <numeric>
+#include <type_traits>
 #include <vector>
 
 namespace cabcd {
@@ -64,10 +65,9 @@ struct BProb {                     // constant per problem (device copy)
   int64_t H;                       // inner-iteration budget (INT64_MAX: none)
   int64_t chunk;                   // columns per slab
   int b, s, bp, nb;
-  int nslab, aligned;
-  int sets;                        // partial sets per slab (1; above 256 rows 4 or 6)
-  int naux;                        // slabs of the monitor passes
-  int64_t achunk;                  // their columns
+  int nslab, naux;                 // slabs of a round, of the monitor passes
+  int sets, pad;                   // partial sets per slab (1; above 256 rows 4 or 6)
+  int64_t achunk;                  // columns of a monitor slab
   int32_t* ix;                     // 2 x s b: blocks of the step (parity of its number)
   int* garrive;                    // slab arrivals by group in the current launch
   double* partials;                // nslab x sets x (nblk*256 + 16 nb)
@@ -147,56 +147,56 @@ __device__ __forceinline__ double rows_dot(const BProb& pr, int64_t k0, int64_t 
       const int unit = task / R, part = task - unit * R;
       const int q0 = part * per, q1 = std::min(mq, q0 + per);
       const int64_t k = p0 + (int64_t)unit * UNIT + lane * EPC;
-      const bool full = k + EPC <= k1 && (FMT == CABCD_F64 || pr.aligned != 0);
       double acc[EPC];
 #pragma unroll
       for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
+      auto add = [&](const uint4& x, double c) {
+        double dv[EPC];
+        if constexpr (FMT == CABCD_F64)
+          __builtin_memcpy(dv, &x, 16);
+        else
+          ldev::lp_decode_all<FMT>(x, dv);
+#pragma unroll
+        for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
+      };
       auto row_of = [&](int q) { return (int64_t)(rows != nullptr ? rows[q] : q); };
       auto coef_of = [&](int q, int64_t row) {
         return FMT != CABCD_F64 && pr.rs != nullptr ? coef[q] * (double)rg[row] : coef[q];
       };
-      if (full) {   // 16-byte loads (FP64 rows: from any 8-byte boundary)
-        typedef unsigned int uv4 __attribute__((ext_vector_type(4), aligned(8)));
-        const gptr<const uint8_t> Ak = A + k * ES;
-        auto add = [&](uv4 w, double c) {
-          const uint4 x = make_uint4(w.x, w.y, w.z, w.w);
-          double dv[EPC];
-          if constexpr (FMT == CABCD_F64)
-            __builtin_memcpy(dv, &x, 16);
-          else
-            ldev::lp_decode_all<FMT>(x, dv);
+      // 16-byte loads from any boundary; a chunk past k1 as the last 16 bytes before
+      // it, shifted down (rows shorter than a chunk: element by element)
+      if (k1 >= EPC) {
+        const ldev::LpWindow<FMT> w(k, k1);
+        const gptr<const uint8_t> Ak = A + w.k * ES;
+        auto pass = [&](auto edge) {
+          int q = q0;
+          for (; q + U <= q1; q += U) {
+            uint4 x[U];
+            double c[U];
 #pragma unroll
-          for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
-        };
-        int q = q0;
-        for (; q + U <= q1; q += U) {
-          uv4 x[U];
-          double c[U];
+            for (int j = 0; j < U; ++j) {
+              const int64_t row = row_of(q + j);
+              c[j] = coef_of(q + j, row);
+              x[j] = ldev::lp_load16(Ak + row * ldb);
+            }
 #pragma unroll
-          for (int j = 0; j < U; ++j) {
-            const int64_t row = row_of(q + j);
-            c[j] = coef_of(q + j, row);
-            x[j] = *(gptr<const uv4>)(Ak + row * ldb);
+            for (int j = 0; j < U; ++j)
+              add(decltype(edge)::value ? ldev::lp_shift(x[j], w.sh) : x[j], c[j]);
           }
-#pragma unroll
-          for (int j = 0; j < U; ++j) add(x[j], c[j]);
-        }
-        for (; q < q1; ++q) {
-          const int64_t row = row_of(q);
-          add(*(gptr<const uv4>)(Ak + row * ldb), coef_of(q, row));
-        }
-      } else if (k < k1) {   // the ragged end, and codes on odd boundaries
+          for (; q < q1; ++q) {
+            const int64_t row = row_of(q);
+            const uint4 x = ldev::lp_load16(Ak + row * ldb);
+            add(decltype(edge)::value ? ldev::lp_shift(x, w.sh) : x, coef_of(q, row));
+          }
+        };
+        if (__any(w.sh != 0))
+          pass(std::true_type{});
+        else
+          pass(std::false_type{});
+      } else {
         for (int q = q0; q < q1; ++q) {
           const int64_t row = row_of(q);
-          const double c = coef_of(q, row);
-          if constexpr (FMT == CABCD_F64) {
-            acc[0] = fma(*(gptr<const double>)(A + row * ldb + k * ES), c, acc[0]);
-          } else {
-            double dv[EPC];
-            ldev::lp_decode_all<FMT>(ldev::lp_load<FMT>(A + row * ldb, k, k1, false), dv);
-#pragma unroll
-            for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
-          }
+          add(ldev::lp_load<FMT>(A + row * ldb, k, k1), coef_of(q, row));
         }
       }
       if (R == 1) {
@@ -281,18 +281,17 @@ __device__ __noinline__ void gram_call_dma(const double* A, int64_t ld, int64_t 
 template <int NB, int FMT>
 __device__ __noinline__ void gram_lp_call(const uint8_t* A, int64_t ld, int64_t k0, int64_t k1,
                                           const int32_t* idx, int m, const double* u,
-                                          double* part, int aligned) {
+                                          double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
   ldev::gram_lp_slab<NB, FMT, kBLpTile, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1),
                                               uni_ptr(idx), uni(m), uni_ptr(u), uni_ptr(part),
-                                              uni(aligned),
                                               reinterpret_cast<uint8_t*>(dyn_sm));
 }
 
 template <int FMT>
 __device__ __forceinline__ void gram_any(int nb, const void* A, int64_t ld, int64_t k0,
                                          int64_t k1, const int32_t* idx, int m, const double* u,
-                                         double* part, int aligned) {
+                                         double* part) {
   if constexpr (FMT == CABCD_F64) {
     const double* a = static_cast<const double*>(A);
     switch (nb) {
@@ -305,11 +304,11 @@ __device__ __forceinline__ void gram_any(int nb, const void* A, int64_t ld, int6
   } else {
     const uint8_t* a = static_cast<const uint8_t*>(A);
     switch (nb) {
-      case 1: gram_lp_call<1, FMT>(a, ld, k0, k1, idx, m, u, part, aligned); break;
-      case 2: gram_lp_call<2, FMT>(a, ld, k0, k1, idx, m, u, part, aligned); break;
-      case 4: gram_lp_call<4, FMT>(a, ld, k0, k1, idx, m, u, part, aligned); break;
-      case 8: gram_lp_call<8, FMT>(a, ld, k0, k1, idx, m, u, part, aligned); break;
-      default: gram_lp_call<16, FMT>(a, ld, k0, k1, idx, m, u, part, aligned); break;
+      case 1: gram_lp_call<1, FMT>(a, ld, k0, k1, idx, m, u, part); break;
+      case 2: gram_lp_call<2, FMT>(a, ld, k0, k1, idx, m, u, part); break;
+      case 4: gram_lp_call<4, FMT>(a, ld, k0, k1, idx, m, u, part); break;
+      case 8: gram_lp_call<8, FMT>(a, ld, k0, k1, idx, m, u, part); break;
+      default: gram_lp_call<16, FMT>(a, ld, k0, k1, idx, m, u, part); break;
     }
   }
 }
@@ -437,13 +436,13 @@ __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict
     const int nsets = sets == 1 ? 1 : 2 + (m - 256 > 128 ? 4 : 2);
     double* const part = pr.partials + item.slab * sstride;
     if (sets == 1) {
-      gram_any<FMT>(pr.nb, pr.A, pr.ld, k0, k1, icur, m, pr.r, part, pr.aligned);
+      gram_any<FMT>(pr.nb, pr.A, pr.ld, k0, k1, icur, m, pr.r, part);
     } else {
       gdev::big_lists(icur, m, ia, ib, tid, kBT);
       __syncthreads();
       for (int g = 0; g < nsets; ++g)
         gram_any<FMT>(16, pr.A, pr.ld, k0, k1, g < 2 ? ia + 256 * g : ib + 256 * (g - 2), 256,
-                           g < 2 ? pr.r : nullptr, part + g * pstride, pr.aligned);
+                           g < 2 ? pr.r : nullptr, part + g * pstride);
     }
     // the slab's group, then (with more than one group) the problem's groups
     const int ngroup = (pr.nslab + kBGroup - 1) / kBGroup;
@@ -1065,10 +1064,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     o.naux = naux[p];
     o.achunk = achunk[p];
     o.nslab = best[p].nslab;
-    o.aligned = ((reinterpret_cast<uintptr_t>(o.A) & 15) == 0 &&
-                 ((o.ld * elem_bytes(B->dtype)) & 15) == 0)
-                    ? 1
-                    : 0;
+    o.pad = 0;
     o.partials = ws.take<double>((size_t)o.nslab * slab_doubles(sb));
     o.G = ws.take<double>((size_t)sb * sb);
     o.Yu = ws.take<double>(sb);

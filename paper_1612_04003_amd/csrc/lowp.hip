@@ -14,6 +14,7 @@
 
 #include <algorithm>
 #include <cmath>
+#include <type_traits>
 
 namespace cabcd {
 namespace {
@@ -87,7 +88,7 @@ template <int NB, int FMT>
 __global__ __launch_bounds__(kLpThreads) void gram_lp_kernel(
     const uint8_t* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
-    int64_t pstride, int aligned) {
+    int64_t pstride) {
   using C = LpCfg<NB, FMT>;
   __shared__ __attribute__((aligned(16))) uint8_t lds[C::LDS];
   idx += (int64_t)blockIdx.y * m;            // several outer steps per launch
@@ -95,7 +96,7 @@ __global__ __launch_bounds__(kLpThreads) void gram_lp_kernel(
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   gram_lp_slab<NB, FMT>(A, ld, k_begin, k_end, idx, m, u,
-                        partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), aligned, lds);
+                        partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), lds);
 }
 
 // ---------------------------------------------------------------------------
@@ -189,7 +190,6 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int ntiles = (int)((k_end - k_begin + C::KT - 1) / C::KT);
-  const int64_t end_b = k_end * C::ES;   // row bytes in range
 
   // DMA instruction i of this wave fills tile bytes (8 W + i) KiB + 16 lane:
   // row 4 (8 W + i) + lane / 16, position lane % 16, chunk (lane % 16) ^ (row % 16).
@@ -210,8 +210,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   // the Y u threads of the sixteen chunks read a piece from consecutive slots.
   auto upiece = [](int slot) { return (C::EPC / 2) * (slot & 15) + (slot >> 4); };
   // A tile inside the slab is all DMA; the last tile of a slab that ends
-  // inside a tile is filled by a compact loop of ordinary loads (zeros past
-  // the end), kept out of line of the DMA path to keep the loop body small.
+  // inside a tile is filled by ordinary loads (zeros past the end).
   auto issue = [&](int t, int slot) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
     uint8_t* T = lds + slot * C::BUF;
@@ -238,20 +237,30 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
       }
       return;
     }
+    if (k_end >= C::EPC) {
 #pragma unroll
-    for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
-      const int64_t kb = k0 * C::ES + cof[i];
-      uint64_t lo = 0, hi = 0;
-#pragma clang loop unroll(disable)
-      for (int e = 0; e < 16; ++e) {
-        const uint64_t v = kb + e < end_b ? (uint64_t)src[i][kb + e] : 0;
-        if (e < 8)
-          lo |= v << (8 * e);
-        else
-          hi |= v << (8 * (e - 8));
+      for (int i0 = 0; i0 < C::DMA_PER_WAVE; i0 += 4) {   // four loads in flight
+        uint4 x[4];
+        int sh[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          const LpWindow<FMT> w(k0 + cof[i0 + i] / C::ES, k_end);
+          x[i] = lp_load16(src[i0 + i] + w.k * C::ES);
+          sh[i] = w.sh;
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          *reinterpret_cast<uint4*>(T + (C::DMA_PER_WAVE * W + i0 + i) * 1024 + 16 * lane) =
+              lp_shift(x[i], sh[i]);
       }
-      *reinterpret_cast<uint4*>(T + (C::DMA_PER_WAVE * W + i) * 1024 + 16 * lane) =
-          make_uint4((uint32_t)lo, (uint32_t)(lo >> 32), (uint32_t)hi, (uint32_t)(hi >> 32));
+    } else {   // a matrix narrower than a chunk
+#pragma clang loop unroll(disable)
+      for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
+        const int r = 4 * (C::DMA_PER_WAVE * W + i) + (lane >> 4);
+        const int c = (lane & 15) ^ (r & 15);
+        *reinterpret_cast<uint4*>(T + (C::DMA_PER_WAVE * W + i) * 1024 + 16 * lane) =
+            lp_load<FMT>(Ag + (int64_t)idx[r < m ? r : 0] * ld * C::ES, k0 + C::EPC * c, k_end);
+      }
     }
     if (want_u && W == 7) {
 #pragma clang loop unroll(disable)
@@ -412,15 +421,13 @@ hipError_t launch_lp_nb(const GramPlan& p, const void* A, int64_t ld, int64_t co
                         const int32_t* idx, int m, int nsteps, const double* u,
                         double* partials, hipStream_t st) {
   using C = LpCfg<NB, FMT>;
-  const int aligned =
-      ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * C::ES) & 15) == 0) ? 1 : 0;
-  if constexpr (NB == 16) {
-    if (aligned && p.chunk % LD16<FMT>::KT == 0)
+  if constexpr (NB == 16) {   // 16-byte aligned rows
+    if ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * C::ES) & 15) == 0 && p.chunk % LD16<FMT>::KT == 0)
       return launch_lp_dma16<FMT>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
   }
   hipLaunchKernelGGL((gram_lp_kernel<NB, FMT>), dim3((unsigned)p.nsplit, (unsigned)nsteps),
                      dim3(kLpThreads), 0, st, static_cast<const uint8_t*>(A), ld, cols, idx, m, u,
-                     p.chunk, partials, (int64_t)gram_partial_doubles(p), aligned);
+                     p.chunk, partials, (int64_t)gram_partial_doubles(p));
   return hipGetLastError();
 }
 
@@ -473,7 +480,6 @@ struct LvArgs {
   double* out;
   double* scratch;   // groups x cols partial sums when the rows are split over the grid
   int64_t rows_per_group;
-  int aligned;
 };
 
 template <int FMT, int RS>
@@ -490,7 +496,7 @@ __global__ __launch_bounds__(LvCfg<RS>::THREADS) void gemv_t_lp_kernel(LvArgs g)
   extern __shared__ __attribute__((aligned(16))) double red[];   // [RS][EPC][CPB]
   const int tc = threadIdx.x % CPB;
   // the row range is uniform in a wave, so the row indices and coefficients
-  // stay scalar loads; lanes past the last column load zeros (lp_load)
+  // stay scalar loads; lanes past the last column get zeros
   const int sl = __builtin_amdgcn_readfirstlane(threadIdx.x / CPB);
   const int64_t k = ((int64_t)blockIdx.x * CPB + tc) * EPC;
   const int64_t g0 = (int64_t)blockIdx.y * g.rows_per_group;
@@ -500,32 +506,47 @@ __global__ __launch_bounds__(LvCfg<RS>::THREADS) void gemv_t_lp_kernel(LvArgs g)
   double acc[EPC];
 #pragma unroll
   for (int e = 0; e < EPC; ++e) acc[e] = 0.0;
-  int64_t p = g0 + sl * per;
-  for (; p + RIF <= p1; p += RIF) {
-    uint4 x[RIF];
-    double c[RIF];
-#pragma unroll
-    for (int q = 0; q < RIF; ++q) {
-      const int64_t row = idx ? (int64_t)idx[p + q] : p + q;
-      c[q] = v[p + q] * (rs ? (double)rs[row] : 1.0);
-      x[q] = lp_load<FMT>(A + row * ld * ES, k, cols, g.aligned != 0);
-    }
-#pragma unroll
-    for (int q = 0; q < RIF; ++q) {
-      double dv[EPC];
-      lp_decode_all<FMT>(x[q], dv);
-#pragma unroll
-      for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c[q], acc[e]);
-    }
-  }
-  for (; p < p1; ++p) {
-    const int64_t row = idx ? (int64_t)idx[p] : p;
-    const double cq = v[p] * (rs ? (double)rs[row] : 1.0);
-    const uint4 x = lp_load<FMT>(A + row * ld * ES, k, cols, g.aligned != 0);
+  auto add = [&](const uint4& x, double c) {
     double dv[EPC];
     lp_decode_all<FMT>(x, dv);
 #pragma unroll
-    for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], cq, acc[e]);
+    for (int e = 0; e < EPC; ++e) acc[e] = fma(dv[e], c, acc[e]);
+  };
+  auto row_of = [&](int64_t p) { return idx ? (int64_t)idx[p] : p; };
+  auto coef = [&](int64_t p, int64_t row) { return v[p] * (rs ? (double)rs[row] : 1.0); };
+  const int64_t p0 = g0 + sl * per;
+  if (cols >= EPC) {
+    const LpWindow<FMT> w(k, cols);
+    const gptr<const uint8_t> Ak = A + w.k * ES;
+    auto rows = [&](auto edge) {   // edge: lanes of this wave run past the last column
+      int64_t p = p0;
+      for (; p + RIF <= p1; p += RIF) {
+        uint4 x[RIF];
+        double c[RIF];
+#pragma unroll
+        for (int q = 0; q < RIF; ++q) {
+          const int64_t row = row_of(p + q);
+          c[q] = coef(p + q, row);
+          x[q] = lp_load16(Ak + row * ld * ES);
+        }
+#pragma unroll
+        for (int q = 0; q < RIF; ++q) add(decltype(edge)::value ? lp_shift(x[q], w.sh) : x[q], c[q]);
+      }
+      for (; p < p1; ++p) {
+        const int64_t row = row_of(p);
+        const uint4 x = lp_load16(Ak + row * ld * ES);
+        add(decltype(edge)::value ? lp_shift(x, w.sh) : x, coef(p, row));
+      }
+    };
+    if (__any(w.sh != 0))
+      rows(std::true_type{});
+    else
+      rows(std::false_type{});
+  } else {
+    for (int64_t p = p0; p < p1; ++p) {
+      const int64_t row = row_of(p);
+      add(lp_load<FMT>(A + row * ld * ES, k, cols), coef(p, row));
+    }
   }
   auto store = [&](int64_t kk, double s) {
     if (kk >= cols) return;
@@ -670,7 +691,6 @@ hipError_t launch_gemv_t_lp(int dtype, const void* A, int64_t ld, int64_t cols, 
                             const double* base, double beta, bool accumulate, double* out,
                             double* scratch, hipStream_t st) {
   if (cols <= 0) return hipSuccess;
-  const int es = dtype == CABCD_BF16 ? 2 : 1;
   const LvSplit sp = lv_split(dtype, m, cols);
   if (sp.groups > 1 && scratch == nullptr) return hipErrorInvalidValue;
   LvArgs g{};
@@ -688,7 +708,6 @@ hipError_t launch_gemv_t_lp(int dtype, const void* A, int64_t ld, int64_t cols, 
   g.out = out;
   g.scratch = sp.groups > 1 ? scratch : nullptr;
   g.rows_per_group = (m + sp.groups - 1) / sp.groups;
-  g.aligned = ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0) ? 1 : 0;
   hipError_t e = dtype == CABCD_BF16 ? launch_lv_fmt<CABCD_BF16>(g, sp, st)
                                      : launch_lv_fmt<CABCD_FP8_E4M3>(g, sp, st);
   if (e != hipSuccess || sp.groups == 1) return e;

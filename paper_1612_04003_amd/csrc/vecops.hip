@@ -151,11 +151,10 @@ struct RowDot {
   double* part;        // rows x parts partial sums when parts > 1
   int64_t chunk;       // elements per part
   int parts;
-  int vec;             // low precision: A rows 16-byte aligned
 };
 
-// Lane l of a wave reads the 16-byte chunks l, l + 64, ... of its row part,
-// four in flight; the lane sums are combined by a butterfly.
+// Lane l of a wave reads the 16-byte chunks l, l + 64, ... of its row part (rows may
+// start on any boundary), four in flight; the lane sums are combined by a butterfly.
 template <int FMT>
 __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
   constexpr int ES = FMT == CABCD_F64 ? 8 : (FMT == CABCD_BF16 ? 2 : 1);
@@ -189,25 +188,15 @@ __global__ __launch_bounds__(kVecThreads) void rowdot_kernel(RowDot g) {
     return t;
   };
   int64_t k = k0 + (int64_t)lane * EPC;
-  if (g.vec) {
-    // FP64 rows may start on any 8-byte boundary
-    typedef unsigned int uv4 __attribute__((ext_vector_type(4), aligned(8)));
-    for (; k + (int64_t)(U - 1) * 64 * EPC + EPC <= k1; k += (int64_t)U * 64 * EPC) {
-      uint4 x[U];
+  for (; k + (int64_t)(U - 1) * 64 * EPC + EPC <= k1; k += (int64_t)U * 64 * EPC) {
+    uint4 x[U];
 #pragma unroll
-      for (int u = 0; u < U; ++u) {
-        const uv4 t = *(gptr<const uv4>)(row + (k + (int64_t)u * 64 * EPC) * ES);
-        x[u] = make_uint4(t.x, t.y, t.z, t.w);
-      }
+    for (int u = 0; u < U; ++u) x[u] = ldev::lp_load16(row + (k + (int64_t)u * 64 * EPC) * ES);
 #pragma unroll
-      for (int u = 0; u < U; ++u) acc += chunk_dot(x[u], k + (int64_t)u * 64 * EPC);
-    }
-    for (; k + EPC <= k1; k += 64 * EPC) {
-      const uv4 t = *(gptr<const uv4>)(row + k * ES);
-      acc += chunk_dot(make_uint4(t.x, t.y, t.z, t.w), k);
-    }
+    for (int u = 0; u < U; ++u) acc += chunk_dot(x[u], k + (int64_t)u * 64 * EPC);
   }
-  // element by element: codes on odd boundaries, and the ragged end of the part
+  for (; k + EPC <= k1; k += 64 * EPC) acc += chunk_dot(ldev::lp_load16(row + k * ES), k);
+  // element by element: the ragged end of the part
   for (; k < k1; k += 64 * EPC) {
     const int64_t ke = std::min<int64_t>(k + EPC, k1);
     double t = 0.0;
@@ -394,10 +383,6 @@ static hipError_t launch_rowdot_any(int dtype, const void* A, int64_t ld, const 
   g.parts = rowdot_parts(rows, cols, es, &g.chunk);
   g.part = g.parts > 1 ? scratch : nullptr;
   if (g.parts > 1 && scratch == nullptr) return hipErrorInvalidValue;
-  g.vec = dtype == CABCD_F64 ||
-                  ((reinterpret_cast<uintptr_t>(A) & 15) == 0 && ((ld * es) & 15) == 0)
-              ? 1
-              : 0;
   const int64_t waves = rows * g.parts;
   const int64_t per = kVecThreads / 64;
   const dim3 grid((unsigned)((waves + per - 1) / per));

@@ -68,3 +68,32 @@ def test_f64_rows_on_any_boundary(gpu_lib, rows, cols, off, pad):
         mag = Y.abs() @ Y.abs().t() / cols + 0.5
         assert bool(((G - want).abs() <= 2 * (cols + 4) * U * mag).all())
         assert bool(((Yu - Y @ u).abs() <= 2 * (cols + 4) * U * (Y.abs() @ u.abs())).all())
+
+
+# every remainder of a 16-byte chunk, rows shorter than one, one and several tiles,
+# each block count of the low-precision Gram; codes from an odd and an aligned byte on.
+# Entries are small whole numbers (times 64), so FP32 and FP64 sums are exact.
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("off,pad", [(0, 0), (1, 0), (0, 1)])
+@pytest.mark.parametrize("m", [3, 20, 60, 100, 200])
+def test_lowp_gram_ragged_ends(gpu_lib, dtype, m, off, pad):
+    print("[passes] lowp gram ends", dtype, m, off, pad, flush=True)
+    code = gpu_lib.BF16 if dtype == "bf16" else gpu_lib.FP8_E4M3
+    g = torch.Generator(device=DEV)
+    g.manual_seed(m)
+    idx = torch.randperm(m, generator=g, device=DEV).to(torch.int32)
+    for cols in list(range(1, 35)) + [256 + r for r in range(0, 16, 3)] + [4096 + 17]:
+        X = 64.0 * torch.randint(-7, 8, (m, cols), generator=g, device=DEV).to(torch.float64)
+        X[:, cols // 2] = 448.0     # FP8 row scale 1
+        Q = gpu_lib.quantize(X, code)
+        if off or pad:
+            ld = cols + pad
+            buf = torch.zeros(off + m * ld, device=DEV, dtype=Q.codes.dtype)
+            view = buf[off:].view(m, ld)[:, :cols]
+            view.copy_(Q.codes)
+            Q = gpu_lib.Quantized(view, Q.scales, Q.dtype)
+        u = torch.randint(-3, 4, (cols,), generator=g, device=DEV).to(torch.float64)
+        G, Yu = gpu_lib.gram(Q, idx, 1.0, 0.0, u)
+        Y = X[idx.long()].cpu()
+        assert torch.equal(G.cpu(), Y @ Y.t()), cols
+        assert torch.equal(Yu.cpu(), Y @ u.cpu()), cols
