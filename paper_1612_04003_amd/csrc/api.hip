@@ -216,9 +216,9 @@ size_t big_partials(const Mat& M) {
 size_t max_partials(const Mat& M, int sb_max) {
   if (M.csr) return 1;
   size_t best = 0;
-  for (int m = 1;; m = (m < 16 ? 16 : m * 2)) {
+  for (int m = 16;; m += 16) {
     best = std::max(best, gram_partial_doubles(plan_for(M, std::min(m, sb_max))));
-    if (m >= sb_max) break;
+    if (m >= std::min(sb_max, kGramRows)) break;
   }
   if (sb_max > kGramRows) best = std::max(best, big_partials(M));
   return best;
@@ -574,10 +574,10 @@ hipError_t mat_gram_steps(const Mat& M, const GramPlan& plan, const int32_t* idx
     return timer->run_on(st, CABCD_PHASE_GRAM, [&] {
       return launch_csr_gram_steps(M.C, idx, m, nsteps, scale, shift, true, G, st);
     });
-  // The 256-row kernels take a whole CU per workgroup: a launch that fills the
+  // The kernels above 128 rows take a whole CU per workgroup: a launch that fills the
   // GPU would keep the running steps' workgroups waiting for its own (52 us
   // instead of 16 for a dense dual step), so they go out half a GPU at a time.
-  const int per = plan.nb == 16 ? std::max(1, kHalfGpu / plan.nsplit) : nsteps;
+  const int per = plan.nb > 8 ? std::max(1, kHalfGpu / plan.nsplit) : nsteps;
   const size_t set = gram_partial_doubles(plan);
   hipError_t e = timer->run_on(st, CABCD_PHASE_GRAM, [&]() -> hipError_t {
     for (int k = 0; k < nsteps; k += per) {

@@ -261,12 +261,14 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
 // their own extern declaration, so their LDS accesses stay ds_* instructions.
 // Arguments of a non-inlined function are per-lane values to the compiler; the
 // tile loop's barriers need its bounds to be visibly uniform.
-__device__ __noinline__ void gram_call_dma16(const double* A, int64_t ld, int64_t k0,
+__device__ __noinline__ void gram_call_tri16(const double* A, int64_t ld, int64_t k0,
                                              int64_t k1, const int32_t* idx, int m,
                                              const double* u, double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  gdev::gram_slab_dma16<0, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx),
-                                 uni(m), uni_ptr(u), uni_ptr(part), dyn_sm);
+  constexpr int T = gdev::Tri<16>::TILE;
+  gdev::gram_slab_tri<16, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
+                                uni_ptr(u), uni_ptr(part),
+                                gdev::TriLds{dyn_sm, dyn_sm + T, dyn_sm + 2 * T});
 }
 
 template <int NB>
@@ -299,7 +301,7 @@ __device__ __forceinline__ void gram_any(int nb, const void* A, int64_t ld, int6
       case 2: gram_call_dma<2>(a, ld, k0, k1, idx, m, u, part); break;
       case 4: gram_call_dma<4>(a, ld, k0, k1, idx, m, u, part); break;
       case 8: gram_call_dma<8>(a, ld, k0, k1, idx, m, u, part); break;
-      default: gram_call_dma16(a, ld, k0, k1, idx, m, u, part); break;
+      default: gram_call_tri16(a, ld, k0, k1, idx, m, u, part); break;
     }
   } else {
     const uint8_t* a = static_cast<const uint8_t*>(A);
@@ -840,7 +842,7 @@ int gram_lds(int nb) {
     case 2: return gdev::DN<2>::LDS;
     case 4: return gdev::DN<4>::LDS;
     case 8: return gdev::DN<8>::LDS;
-    default: return gdev::D16::LDS;
+    default: return 3 * gdev::Tri<16>::TILE;
   }
 }
 

@@ -32,6 +32,7 @@
 #include "internal.h"
 
 #include <algorithm>
+#include <type_traits>
 
 namespace cabcd {
 namespace gdev {
@@ -99,6 +100,9 @@ __device__ __forceinline__ double get_agent(gptr<const double> p) {
   return __hip_atomic_load((const double*)p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// s_waitcnt immediate: no vector memory load outstanding (LDS and scalar counters free).
+constexpr int kWaitVm0 = 0x0F70;
+
 // ---------------------------------------------------------------------------
 // NB <= 8: waves own block-row pairs and split a tile's k-steps.  A 32 KiB tile of
 // SBP rows x
@@ -115,7 +119,7 @@ struct DN {
   static constexpr int UDMA = (C::KT / 2 + 63) / 64;              // u slots, 64 a time
   static constexpr int TILE = C::SBP * C::KT + C::KT;            // doubles: rows, then u
   // parts in which a wave's blocks meet the other k-groups' (NB = 8: 64.5 KiB
-  // of LDS instead of 72, so that two batched workgroups fit a CU)
+  // of LDS instead of 72)
   static constexpr int HV = C::RED > 2 * TILE ? 2 : 1;
   static constexpr int RED = (C::KG - 1) * C::BW * ((C::NACC + HV - 1) / HV) * 256;
   static constexpr int LDS = std::max(std::max(2 * TILE, RED), C::YUS);
@@ -338,32 +342,264 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
 }
 
 // ---------------------------------------------------------------------------
-// NB = 16 fed by LDS-DMA loads (gfx950 global_load_lds_dwordx4): the tile goes
-// from global memory straight into LDS, so there are no staging registers and
-// no ds_write instructions.  A DMA instruction writes 64 consecutive 16-byte
-// LDS slots (lane l at base + 16 l); the slots hold unpadded 128-byte rows
-// whose eight 16-byte chunks are XOR-swizzled, chunk c of row r at position
-// c ^ ((r >> 1) & 7), so the sixteen rows of a fragment read fall in distinct
-// banks.  Y u is accumulated from the waves' own-row fragments (each block row
-// is owned by exactly one wave) and summed over the four lane groups at the
-// end.  Chunks that cross the end of the slab are written with ordinary LDS
-// stores (zero-filled).
+// NB = 10, 12, 14, 16 (129 to 256 rows): the matrix cores bound it.  The lower 16x16
+// blocks are dealt to the eight waves in row-major runs of equal length, and a wave
+// runs through its blocks column by column, so that it holds few rows of fragments at
+// a time.  Tiles are 16 columns, three in LDS: one is computed, the next is in, the
+// one after is on its way.  Rows are unpadded 128-byte slots whose eight 16-byte
+// chunks are XOR-swizzled, chunk c of row r at c ^ ((r >> 1) & 7), so the sixteen rows
+// of a fragment read fall in distinct banks.
+//
+// The order of a tile is fixed by hand (sched_barrier): before each block the fragments
+// kTriLead ahead are read, at the end of a tile from the next one, so that the matrix
+// cores start on it straight after the barrier.  256 x 2^18 (17.2 GFLOP): 317 us as two
+// buffers whose reads the compiler let wait for the DMA into the other one, 296 with
+// that wait gone, 291 with the third buffer and the fixed order (250 us more for each
+// 2^18 columns more, the rest is writing 71 MB of partial sums at the end); 150 x 100003
+// as sixteen block rows 125 us, as ten 55.
+constexpr int kTriMin = 9;       // block rows from which on these kernels run
+constexpr int kTriLead = 4;
+constexpr int tri_rows(int nb) { return nb < kTriMin ? nb : (nb + 1) / 2 * 2; }
+
+template <int NB>
+struct Tri {
+  static constexpr int SBP = 16 * NB, NBLK = NB * (NB + 1) / 2, KT = 16, CH = KT / 2;
+  static constexpr int PP = KT / 8;                  // 128-bit fragment reads per tile
+  static constexpr int THREADS = 512;
+  static constexpr int TILE = SBP * KT + KT;         // doubles per buffer: rows, then u
+  static constexpr int DMA = SBP * CH / 64;          // instructions of 64 chunks a tile
+  static constexpr int MAXB = (NBLK + 7) / 8;        // blocks of a wave, at most
+};
+
+// Wave W's blocks (row r, column c, index q in row-major order) in the order they are
+// computed, the rows of fragments in the order they are first used, how many of them
+// block i needs, and the rows whose Y u is this wave's (its diagonal blocks').
+template <int NB, int W>
+struct TriWave {
+  int n = 0, nf = 0, nd = 0;
+  int r[17] = {}, c[17] = {}, q[17] = {}, need[17] = {};
+  int fr[16] = {};
+  int diag[16] = {};
+  constexpr TriWave() {
+    const int q0 = W * Tri<NB>::NBLK / 8, q1 = (W + 1) * Tri<NB>::NBLK / 8;
+    bool have[16] = {};
+    for (int col = 0; col < NB; ++col)
+      for (int row = col; row < NB; ++row) {
+        const int k = blk_index(row, col);
+        if (k < q0 || k >= q1) continue;
+        if (!have[row]) {
+          have[row] = true;
+          fr[nf++] = row;
+        }
+        if (!have[col]) {
+          have[col] = true;
+          fr[nf++] = col;
+        }
+        r[n] = row;
+        c[n] = col;
+        q[n] = k;
+        need[n] = nf;
+        ++n;
+        if (row == col) diag[nd++] = row;
+      }
+  }
+};
+
+// The three tile buffers (Tri<NB>::TILE doubles each).  In the one-problem kernels
+// each is a __shared__ array of its own and the tile loop is unrolled over the three,
+// which is what tells the compiler that a read of one need not wait for the DMA into
+// another.
+struct TriLds {
+  double *t0, *t1, *t2;
+};
+
+template <int I, int N, class F>
+__device__ __forceinline__ void static_for(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    static_for<I + 1, N>(f);
+  }
+}
+
+template <int NB, int W, bool AGENT>
+__device__ __forceinline__ void tri_slab(const double* __restrict__ A, int64_t ld,
+                                         int64_t k_begin, int64_t k_end, const int32_t* idx,
+                                         int m, const double* __restrict__ u,
+                                         double* __restrict__ part, const TriLds L) {
+  using C = Tri<NB>;
+  typedef __attribute__((address_space(3))) void* lds_vptr;
+  typedef __attribute__((address_space(1))) const void* glb_vptr;
+  constexpr TriWave<NB, W> T{};
+  constexpr int LEAD = T.nf < kTriLead ? T.nf : kTriLead;
+  constexpr int ND = (C::DMA - W + 7) / 8;   // this wave's DMA instructions: W + 8 i
+  const int lane = threadIdx.x & 63;
+  // The ragged tile of a slab that ends inside one comes first, by ordinary loads.
+  const int nfull = (int)((k_end - k_begin) / C::KT);
+  const bool ragged = k_begin + (int64_t)nfull * C::KT < k_end;
+  const int ntiles = nfull + (ragged ? 1 : 0);
+
+  // DMA instruction i of a wave fills slots (W + 8 i) * 64 + lane: row slot / 8,
+  // position slot % 8; rows past m: any valid row
+  auto slot_row = [&](int i) { return 8 * (W + 8 * i) + (lane >> 3); };
+  auto chunk_of = [&](int r) { return (lane & 7) ^ ((r >> 1) & 7); };
+  const gptr<const double> Ag = glb(A);
+  const bool want_u = u != nullptr;
+  const gptr<const double> ug = glb(u);
+  gptr<const double> src[ND];
+#pragma unroll
+  for (int i = 0; i < ND; ++i) {
+    const int r = slot_row(i);
+    src[i] = Ag + (int64_t)idx[r < m ? r : 0] * ld + k_begin + 2 * chunk_of(r);
+  }
+  // full tile f (columns k_begin + 16 f ..)
+  auto issue = [&](int f, double* B) {
+#pragma unroll
+    for (int i = 0; i < ND; ++i)
+      __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + (int64_t)f * C::KT),
+                                       (lds_vptr)(B + (W + 8 * i) * 128), 16, 0, 0);
+    if (W == 7 && want_u && lane < C::CH)   // the tile's u after the rows
+      __builtin_amdgcn_global_load_lds((glb_vptr)(ug + k_begin + (int64_t)f * C::KT + 2 * lane),
+                                       (lds_vptr)(B + C::SBP * C::KT), 16, 0, 0);
+  };
+  const int shift = ragged ? 1 : 0;   // tile t is full tile t - shift
+  if (ragged) {
+    const int64_t k0 = k_begin + (int64_t)nfull * C::KT;
+#pragma unroll
+    for (int i = 0; i < ND; ++i) {
+      const int64_t off = (int64_t)nfull * C::KT, k = k0 + 2 * chunk_of(slot_row(i));
+      double2 v;
+      v.x = k < k_end ? src[i][off] : 0.0;
+      v.y = k + 1 < k_end ? src[i][off + 1] : 0.0;
+      *reinterpret_cast<double2*>(L.t0 + (W + 8 * i) * 128 + 2 * lane) = v;
+    }
+    if (W == 7 && lane < C::KT)
+      L.t0[C::SBP * C::KT + lane] = want_u && k0 + lane < k_end ? ug[k0 + lane] : 0.0;
+  } else {
+    issue(0, L.t0);
+  }
+  if (ntiles > 1) issue(1 - shift, L.t1);
+
+  // fragment offsets of the two k-pairs: row lane % 16 of a block row, chunk 4 pp +
+  // lane / 16, swizzled
+  const int g = lane >> 4, rl = lane & 15;
+  int lane_off[C::PP];
+#pragma unroll
+  for (int pp = 0; pp < C::PP; ++pp)
+    lane_off[pp] = rl * C::KT + 2 * ((4 * pp + g) ^ ((rl >> 1) & 7));
+  auto frag = [&](const double* B, int pp, int r) {
+    return *reinterpret_cast<const double2*>(B + lane_off[pp] + r * 16 * C::KT);
+  };
+
+  d4 acc[T.n];
+#pragma unroll
+  for (int a = 0; a < T.n; ++a) acc[a] = d4{0.0, 0.0, 0.0, 0.0};
+  double yu[T.nd > 0 ? T.nd : 1];
+#pragma unroll
+  for (int a = 0; a < T.nd; ++a) yu[a] = 0.0;
+  double2 pre[LEAD];   // the next tile's first fragments
+
+  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
+  __syncthreads();
+#pragma unroll
+  for (int i = 0; i < LEAD; ++i) pre[i] = frag(L.t0, 0, T.fr[i]);
+
+  // Tile t in cur, tile t + 1 in nxt, tile t + 2 on its way into far.
+  auto step = [&](int t, const double* cur, const double* nxt, double* far) {
+    double2 F[C::PP][NB];
+    double2 ut[C::PP];
+    static_for<0, LEAD>([&](auto i) { F[0][T.fr[i]] = pre[i]; });
+    static_for<0, C::PP * T.n>([&](auto I) {
+      constexpr int pp = I / T.n, i = I % T.n;
+      // fragments read before this block: all that the one before it had asked for
+      constexpr int before =
+          I == 0 ? LEAD
+                 : std::max(LEAD, (I - 1) / T.n * T.nf + T.need[(I - 1) % T.n] + LEAD);
+      constexpr int after = std::max(before, pp * T.nf + T.need[i] + LEAD);
+      static_for<before, after>([&](auto l) {
+        constexpr int tile = l / (C::PP * T.nf), lp = l / T.nf % C::PP, f = l % T.nf;
+        if constexpr (tile == 0)
+          F[lp][T.fr[f]] = frag(cur, lp, T.fr[f]);
+        else
+          pre[f] = frag(nxt, 0, T.fr[f]);
+      });
+      if constexpr (T.nd > 0 && i == 0)   // u at the same two columns
+        ut[pp] = *reinterpret_cast<const double2*>(cur + C::SBP * C::KT + 8 * pp + 2 * g);
+      const double2 fr = F[pp][T.r[i]], fc = F[pp][T.c[i]];
+      acc[i] = mfma(fr.x, fc.x, acc[i]);
+      acc[i] = mfma(fr.y, fc.y, acc[i]);
+      if constexpr (i == T.n - 1)
+        static_for<0, T.nd>([&](auto d) {
+          yu[d] = fma(F[pp][T.diag[d]].x, ut[pp].x, yu[d]);
+          yu[d] = fma(F[pp][T.diag[d]].y, ut[pp].y, yu[d]);
+        });
+      __builtin_amdgcn_sched_barrier(0);
+      if constexpr (I == 1) {
+        if (t + 2 < ntiles) issue(t + 2 - shift, far);
+        __builtin_amdgcn_sched_barrier(0);
+      }
+    });
+    __builtin_amdgcn_s_waitcnt(kWaitVm0);   // tile t + 2 is in LDS
+    lds_barrier();
+  };
+  for (int t = 0; t < ntiles; t += 3) {
+    step(t, L.t0, L.t1, L.t2);
+    if (t + 1 < ntiles) step(t + 1, L.t1, L.t2, L.t0);
+    if (t + 2 < ntiles) step(t + 2, L.t2, L.t0, L.t1);
+  }
+
+  gptr<double> pg = glb(part);
+  static_for<0, T.n>([&](auto a) {
+    gptr<double> dst = pg + T.q[a] * 256 + lane;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) put<AGENT>(dst + 64 * i, acc[a][i]);
+  });
+  if (want_u) {   // Y u of the wave's diagonal rows: sum the four lane groups
+    static_for<0, T.nd>([&](auto d) {
+      double v = yu[d];
+      v += __shfl_xor(v, 16, 64);
+      v += __shfl_xor(v, 32, 64);
+      if (lane < 16) put<AGENT>(pg + C::NBLK * 256 + 16 * T.diag[d] + lane, v);
+    });
+  }
+}
+
+// The slab of NB block rows; arguments and partial layout as gram_slab_dma.
+template <int NB, bool AGENT = false>
+__device__ __forceinline__ void gram_slab_tri(const double* __restrict__ A, int64_t ld,
+                                              int64_t k_begin, int64_t k_end, const int32_t* idx,
+                                              int m, const double* __restrict__ u,
+                                              double* __restrict__ part, const TriLds L) {
+  switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
+    case 0: tri_slab<NB, 0, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 1: tri_slab<NB, 1, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 2: tri_slab<NB, 2, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 3: tri_slab<NB, 3, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 4: tri_slab<NB, 4, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 5: tri_slab<NB, 5, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 6: tri_slab<NB, 6, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    default: tri_slab<NB, 7, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+  }
+}
+
+// ---------------------------------------------------------------------------
+// The 256-row Gram with the previous step's companion update folded in
+// (CABCD_FLAG_FOLD_UPDATE), and that update alone.  Two tiles in LDS, rows as in Tri;
+// wave W owns block rows W and 15 - W.  Y u is accumulated from the waves' own-row
+// fragments and summed over the four lane groups at the end.
 struct D16 {
   static constexpr int NB = 16, SBP = 256, NBLK = 136, KT = 16, CH = KT / 2;
   static constexpr int PP = KT / 8;                  // 128-bit fragment reads per tile
   static constexpr int THREADS = 512;
   static constexpr int TILE = SBP * KT + KT;         // doubles per buffer: rows, then u
   static constexpr int DMA_PER_WAVE = SBP * CH / THREADS;   // 4 instructions
-  static constexpr int LDS = 2 * TILE;
-  // With the previous step's companion update folded in: two more buffers
-  // for the previous step's rows (and the tile's old companion entries), then
-  // gamma * delta of the previous step.
-  static constexpr int YT = SBP * KT + KT;           // doubles per update buffer
-  static constexpr int YOFF = 2 * TILE;
-  static constexpr int DOFF = 2 * TILE + 2 * YT;
-  static constexpr int LDS_UPD = DOFF + SBP;
 };
 
+// The folded slab's LDS: two tile buffers of D16::TILE doubles, two for the previous
+// step's rows (and the tile's old companion entries) and gamma * delta of the previous
+// step (D16::SBP), each a __shared__ array of its own (see TriLds).
+struct D16Lds {
+  double *t0, *t1, *y0, *y1, *dl;
+};
 
 // x of the lane N places along in the lane's row of sixteen (DPP row_ror),
 // as two 32-bit moves
@@ -396,9 +632,8 @@ __device__ __forceinline__ int d16_swz(int r) { return D16::CH == 8 ? (r >> 1) &
 // The whole slab for wave W (block rows W and 15 - W); gram_slab_dma16 picks
 // the instantiation once, so each wave's tile loop is one straight-line path
 // for the register allocator.
-// MODE 0: the Gram slab (and Y u with u given).  MODE 1: the same, with the
-// previous step's companion update applied to the slab's columns first; Y u
-// then uses the updated companion (u is ignored).  MODE 2: the update alone
+// MODE 1: the Gram slab with the previous step's companion update applied to the
+// slab's columns first; Y u uses the updated companion.  MODE 2: the update alone
 // (the last step of a call, or one followed by a check), by the same code, so
 // a column's update has the same rounding whichever way it runs.
 //
@@ -410,11 +645,10 @@ __device__ __forceinline__ int d16_swz(int r) { return D16::CH == 8 ? (r >> 1) &
 // previous step's rows are DMA'd two tiles ahead, their chunks swizzled as
 // the Gram's tiles are ((r >> 1) & 7), so the column-pair reads of sixteen
 // consecutive rows fall in distinct banks.
-template <int W, int MODE, bool AGENT>
+template <int W, int MODE>
 __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t ld,
                                          int64_t k_begin, int64_t k_end, const int32_t* idx,
-                                         int m, const double* __restrict__ u,
-                                         double* __restrict__ part, double* lds,
+                                         int m, double* __restrict__ part, const D16Lds L,
                                          const D16Upd up) {
   using C = D16;
   typedef __attribute__((address_space(3))) void* lds_vptr;
@@ -436,25 +670,20 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
     // rows past m: any valid row (MODE 2 reads no Gram rows)
     src[i] = MODE == 2 ? Ag : Ag + (int64_t)idx[r < m ? r : 0] * ld;
   }
-  const bool want_u = MODE == 1 || u != nullptr;
-  const gptr<const double> ug = glb(u);
 
-  // The previous step's rows (MODE 1 and 2): DMA instruction i of this wave
+  // The previous step's rows: DMA instruction i of this wave
   // fills slots q = (4 W + i) * 64 + lane of an update buffer: row q / 8 =
   // 8 (4 W + i) + lane / 8, chunk (q % 8) ^ ((row >> 1) & 7), the swizzle
   // being (4 i + lane / 16) & 7.  The rows are kept as indices and the
   // addresses formed at each issue, to spare registers.
   int yrow[C::DMA_PER_WAVE];
   const gptr<double> rg = glb(up.r);
-  if constexpr (MODE != 0) {
 #pragma unroll
-    for (int i = 0; i < C::DMA_PER_WAVE; ++i)
-      yrow[i] = up.idx[8 * (C::DMA_PER_WAVE * W + i) + (lane >> 3)];
-    if (tid < C::SBP) lds[C::DOFF + tid] = up.gamma * up.delta[tid];
-  }
-  auto issue_y = [&](int t, int slot) {
+  for (int i = 0; i < C::DMA_PER_WAVE; ++i)
+    yrow[i] = up.idx[8 * (C::DMA_PER_WAVE * W + i) + (lane >> 3)];
+  if (tid < C::SBP) L.dl[tid] = up.gamma * up.delta[tid];
+  auto issue_y = [&](int t, double* Y) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
-    double* Y = lds + C::YOFF + slot * C::YT;
 #pragma unroll
     for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
       double* dst = Y + (C::DMA_PER_WAVE * W + i) * 128;
@@ -483,11 +712,10 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
       }
     }
   };
-  // tile t's update from update buffer yslot; MODE 1 also fills the u slot
-  // of Gram buffer uslot
-  auto update = [&](int t, int yslot, int uslot) {
-    const double* Y = lds + C::YOFF + yslot * C::YT;
-    const double* dl = lds + C::DOFF;
+  // tile t's update from update buffer Y; MODE 1 also fills the u slot of Gram
+  // buffer T
+  auto update = [&](int t, const double* Y, double* T) {
+    const double* dl = L.dl;
     double p0 = 0.0, p1 = 0.0;
 #pragma unroll 2
     for (int j = 0; j < C::SBP / 64; ++j) {
@@ -512,54 +740,47 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
       if (k < k_end) rg[k] = n0;
       if (k + 1 < k_end) rg[k + 1] = n1;
       if constexpr (MODE == 1) {
-        double* us = lds + uslot * C::TILE + C::SBP * C::KT;
+        double* us = T + C::SBP * C::KT;
         us[2 * W] = k < k_end ? n0 : 0.0;
         us[2 * W + 1] = k + 1 < k_end ? n1 : 0.0;
       }
     }
   };
   if constexpr (MODE == 2) {
-    issue_y(0, 0);
-    __builtin_amdgcn_s_waitcnt(0);
-    __syncthreads();
-    for (int t = 0; t < ntiles; ++t) {
-      if (t + 1 < ntiles) issue_y(t + 1, (t + 1) & 1);
-      update(t, t & 1, -1);
+    auto step = [&](int t, const double* cur, double* nxt) {
+      if (t + 1 < ntiles) issue_y(t + 1, nxt);
+      update(t, cur, nullptr);
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
+    };
+    issue_y(0, L.y0);
+    __builtin_amdgcn_s_waitcnt(0);
+    __syncthreads();
+    for (int t = 0; t < ntiles; t += 2) {
+      step(t, L.y0, L.y1);
+      if (t + 1 < ntiles) step(t + 1, L.y1, L.y0);
     }
     return;
   }
 
-  auto issue = [&](int t, int slot) {
+  // tile t's rows (its u slot is the update's to fill)
+  auto issue = [&](int t, double* T) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
-    double* T = lds + slot * C::TILE;
+    if (k0 + C::KT <= k_end) {
+#pragma unroll
+      for (int i = 0; i < C::DMA_PER_WAVE; ++i)   // 64 slots of 2 doubles each
+        __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + (k0 + cofs[i])),
+                                         (lds_vptr)(T + (C::DMA_PER_WAVE * W + i) * 128), 16, 0,
+                                         0);
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
-      double* dst = T + (C::DMA_PER_WAVE * W + i) * 128;   // 64 slots of 2 doubles
       const int64_t k = k0 + cofs[i];
-      if (k + 1 < k_end) {
-        __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + k), (lds_vptr)dst, 16, 0, 0);
-      } else {
-        double2 v;
-        v.x = k < k_end ? src[i][k] : 0.0;
-        v.y = 0.0;
-        *reinterpret_cast<double2*>(dst + 2 * lane) = v;
-      }
-    }
-    // the tile's KT entries of u (zeros without u): lanes 0..CH-1 of wave 7
-    // (MODE 1: the update writes them)
-    if (MODE == 0 && W == 7 && lane < C::CH) {
-      double* dst = T + C::SBP * C::KT;
-      const int64_t k = k0 + 2 * lane;
-      if (want_u && k + 1 < k_end) {
-        __builtin_amdgcn_global_load_lds((glb_vptr)(ug + k), (lds_vptr)dst, 16, 0, 0);
-      } else {
-        double2 v;
-        v.x = want_u && k < k_end ? ug[k] : 0.0;
-        v.y = want_u && k + 1 < k_end ? ug[k + 1] : 0.0;
-        *reinterpret_cast<double2*>(dst + 2 * lane) = v;
-      }
+      double2 v;
+      v.x = k < k_end ? src[i][k] : 0.0;
+      v.y = k + 1 < k_end ? src[i][k + 1] : 0.0;
+      *reinterpret_cast<double2*>(T + (C::DMA_PER_WAVE * W + i) * 128 + 2 * lane) = v;
     }
   };
 
@@ -576,38 +797,26 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   for (int a = 0; a < 17; ++a) acc[a] = d4{0.0, 0.0, 0.0, 0.0};
   double yua[2] = {0.0, 0.0};
 
-  issue(0, 0);
-  if constexpr (MODE == 1) {
-    issue_y(0, 0);
-    if (ntiles > 1) issue_y(1, 1);
-  }
-  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
-  __syncthreads();
-  if constexpr (MODE == 1) {
-    update(0, 0, 0);
-    __syncthreads();
-  }
-  for (int t = 0; t < ntiles; ++t) {
-    if (t + 1 < ntiles) issue(t + 1, (t + 1) & 1);
-    if constexpr (MODE == 1) {
-      // update buffer t & 1 held tile t (updated during tile t - 1); tile t + 1
-      // arrived during tile t - 1.  Waves 0-3 update before their matrix
-      // instructions, waves 4-7 (the other wave of each SIMD) after them, so
-      // the update's latency runs beside the other wave's MFMA chain.
-      if (t + 2 < ntiles) issue_y(t + 2, t & 1);
-      if (W < 4 && t + 1 < ntiles) update(t + 1, (t + 1) & 1, (t + 1) & 1);
-    }
-    const double* tile = lds + (t & 1) * C::TILE;
+  // Tile t in cur while tile t + 1 is on its way into nxt, tile t + 1's update in
+  // ynxt, tile t + 2's update rows on their way into ycur.
+  auto step = [&](int t, const double* cur, double* nxt, double* ycur, const double* ynxt) {
+    if (t + 1 < ntiles) issue(t + 1, nxt);
+    // update buffer t & 1 held tile t (updated during tile t - 1); tile t + 1
+    // arrived during tile t - 1.  Waves 0-3 update before their matrix
+    // instructions, waves 4-7 (the other wave of each SIMD) after them, so
+    // the update's latency runs beside the other wave's MFMA chain.
+    if (t + 2 < ntiles) issue_y(t + 2, ycur);
+    if (W < 4 && t + 1 < ntiles) update(t + 1, ynxt, nxt);
 #pragma unroll
     for (int pp = 0; pp < C::PP; ++pp) {
-      const double* base = tile + lane_off[pp];
+      const double* base = cur + lane_off[pp];
       auto frag = [&](int r) {   // rows 16 r .. 16 r + 15, this lane's chunk of pair pp
         return *reinterpret_cast<const double2*>(base + r * 16 * C::KT);
       };
       const double2 f0 = frag(R0);
       const double2 f1 = frag(R1);
       const double2 ut =   // u at the same two columns (unswizzled, after the rows)
-          *reinterpret_cast<const double2*>(tile + C::SBP * C::KT + 8 * pp + 2 * g);
+          *reinterpret_cast<const double2*>(cur + C::SBP * C::KT + 8 * pp + 2 * g);
       yua[0] = fma(f0.x, ut.x, yua[0]);
       yua[0] = fma(f0.y, ut.y, yua[0]);
       yua[1] = fma(f1.x, ut.x, yua[1]);
@@ -623,11 +832,20 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
         acc[R0 + 1 + c] = mfma(f1.y, fc.y, acc[R0 + 1 + c]);
       }
     }
-    if constexpr (MODE == 1) {
-      if (W >= 4 && t + 1 < ntiles) update(t + 1, (t + 1) & 1, (t + 1) & 1);
-    }
+    if (W >= 4 && t + 1 < ntiles) update(t + 1, ynxt, nxt);
     __builtin_amdgcn_s_waitcnt(0);   // tile t + 1 is in LDS
     __syncthreads();
+  };
+  issue(0, L.t0);
+  issue_y(0, L.y0);
+  if (ntiles > 1) issue_y(1, L.y1);
+  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
+  __syncthreads();
+  update(0, L.y0, L.t0);
+  __syncthreads();
+  for (int t = 0; t < ntiles; t += 2) {
+    step(t, L.t0, L.t1, L.y0, L.y1);
+    if (t + 1 < ntiles) step(t + 1, L.t1, L.t0, L.y1, L.y0);
   }
 
   gptr<double> pg = glb(part);
@@ -636,36 +854,33 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
     const int blk = a <= R0 ? blk_index(R0, a) : blk_index(R1, a - R0 - 1);
     gptr<double> dst = pg + blk * 256 + lane;
 #pragma unroll
-    for (int i = 0; i < 4; ++i) put<AGENT>(dst + 64 * i, acc[a][i]);
+    for (int i = 0; i < 4; ++i) dst[64 * i] = acc[a][i];
   }
-  if (want_u) {   // Y u of the two owned block rows: sum the four lane groups
 #pragma unroll
-    for (int i = 0; i < 2; ++i) {
-      double v = yua[i];
-      v += __shfl_xor(v, 16, 64);
-      v += __shfl_xor(v, 32, 64);
-      if (lane < 16) put<AGENT>(pg + C::NBLK * 256 + 16 * (i == 0 ? R0 : R1) + lane, v);
-    }
+  for (int i = 0; i < 2; ++i) {   // Y u of the two owned block rows: sum the four lane groups
+    double v = yua[i];
+    v += __shfl_xor(v, 16, 64);
+    v += __shfl_xor(v, 32, 64);
+    if (lane < 16) pg[C::NBLK * 256 + 16 * (i == 0 ? R0 : R1) + lane] = v;
   }
 }
 
-// The NB = 16 slab; arguments and partial layout as gram_slab_dma.
-template <int MODE = 0, bool AGENT = false>
+// The folded slab (MODE 1) or its update alone (MODE 2); partial layout as gram_slab_dma.
+template <int MODE>
 __device__ __forceinline__ void gram_slab_dma16(const double* __restrict__ A, int64_t ld,
                                                 int64_t k_begin, int64_t k_end,
                                                 const int32_t* idx, int m,
-                                                const double* __restrict__ u,
-                                                double* __restrict__ part, double* lds,
-                                                const D16Upd up = D16Upd{}) {
+                                                double* __restrict__ part, const D16Lds L,
+                                                const D16Upd up) {
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: d16_slab<0, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 1: d16_slab<1, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 2: d16_slab<2, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 3: d16_slab<3, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 4: d16_slab<4, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 5: d16_slab<5, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    case 6: d16_slab<6, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
-    default: d16_slab<7, MODE, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, lds, up); break;
+    case 0: d16_slab<0, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 1: d16_slab<1, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 2: d16_slab<2, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 3: d16_slab<3, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 4: d16_slab<4, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 5: d16_slab<5, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 6: d16_slab<6, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    default: d16_slab<7, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
   }
 }
 

@@ -28,17 +28,19 @@ __global__ __launch_bounds__(Cfg<NB>::THREADS) void gram_f64_dma_kernel(
                     partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), lds);
 }
 
-__global__ __launch_bounds__(D16::THREADS) void gram_f64_dma16_kernel(
+template <int NB>
+__global__ __launch_bounds__(Tri<NB>::THREADS) void gram_f64_tri_kernel(
     const double* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
     int64_t pstride) {
-  __shared__ __attribute__((aligned(16))) double lds[D16::LDS];
+  using C = Tri<NB>;
+  __shared__ __attribute__((aligned(16))) double t0[C::TILE], t1[C::TILE], t2[C::TILE];
   idx += (int64_t)blockIdx.y * m;
   partials += (int64_t)blockIdx.y * pstride;
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
-  gram_slab_dma16(A, ld, k_begin, k_end, idx, m, u,
-                  partials + (int64_t)blockIdx.x * (D16::NBLK * 256 + D16::SBP), lds);
+  gram_slab_tri<NB>(A, ld, k_begin, k_end, idx, m, u,
+                    partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), TriLds{t0, t1, t2});
 }
 
 // MODE 1: the Gram with the previous step's update folded in; MODE 2: the
@@ -47,12 +49,14 @@ template <int MODE>
 __global__ __launch_bounds__(D16::THREADS) void gram_f64_dma16_upd_kernel(
     const double* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, int64_t chunk, double* __restrict__ partials, D16Upd up) {
-  __shared__ __attribute__((aligned(16))) double lds[D16::LDS_UPD];
+  __shared__ __attribute__((aligned(16))) double t0[D16::TILE], t1[D16::TILE];
+  __shared__ __attribute__((aligned(16))) double y0[D16::TILE], y1[D16::TILE], dl[D16::SBP];
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   double* part =
       MODE == 1 ? partials + (int64_t)blockIdx.x * (D16::NBLK * 256 + D16::SBP) : nullptr;
-  gram_slab_dma16<MODE>(A, ld, k_begin, k_end, idx, m, nullptr, part, lds, up);
+  gram_slab_dma16<MODE>(A, ld, k_begin, k_end, idx, m, part,
+                        D16Lds{t0, t1, y0, y1, dl}, up);
 }
 
 // A reduction workgroup has 1024 threads: GROUPS split groups (a wave or more
@@ -151,9 +155,9 @@ hipError_t launch_nb(const GramPlan& p, const double* A, int64_t ld, int64_t col
                      hipStream_t st) {
   const int64_t pstride = (int64_t)gram_partial_doubles(p);
   const dim3 grid((unsigned)p.nsplit, (unsigned)nsteps);
-  if constexpr (NB == 16)
-    hipLaunchKernelGGL(gram_f64_dma16_kernel, grid, dim3(D16::THREADS), 0, st, A, ld, cols, idx, m,
-                       u, p.chunk, partials, pstride);
+  if constexpr (NB >= kTriMin)
+    hipLaunchKernelGGL((gram_f64_tri_kernel<NB>), grid, dim3(Tri<NB>::THREADS), 0, st, A, ld, cols,
+                       idx, m, u, p.chunk, partials, pstride);
   else
     hipLaunchKernelGGL((gram_f64_dma_kernel<NB>), grid, dim3(Cfg<NB>::THREADS), 0, st, A, ld, cols,
                        idx, m, u, p.chunk, partials, pstride);
@@ -162,16 +166,25 @@ hipError_t launch_nb(const GramPlan& p, const double* A, int64_t ld, int64_t col
 
 }  // namespace
 
+// Block rows of a Gram of m <= 256 rows: a power of two up to 8 (the k-split kernels),
+// even numbers above (the matrix cores bound those, and 150 rows as sixteen block rows
+// were 136 blocks of work for 55; odd numbers would save 8 % more at most).
+int gram_f64_blocks(int m) {
+  int nb = 1;
+  while (16 * nb < m && nb < 8) nb *= 2;
+  return 16 * nb >= m ? nb : tri_rows((m + 15) / 16);
+}
+
 GramPlan plan_gram_f64(int m, int64_t cols) {
   GramPlan p{};
-  int nb = 1;
-  while (16 * nb < m) nb *= 2;
+  const int nb = gram_f64_blocks(m);
   p.nb = nb;
   p.nblk = nb * (nb + 1) / 2;
-  p.kt = 256 / nb;
+  const bool tri = nb >= kTriMin;
+  p.kt = tri ? 16 : 256 / nb;
   const int bw = nb >= 2 ? nb / 2 : 1;
-  const int kg = 8 / bw;
-  const int nacc = nb >= 2 ? nb + 1 : 1;
+  const int kg = tri ? 1 : 8 / bw;
+  const int nacc = tri ? (p.nblk + 7) / 8 : nb >= 2 ? nb + 1 : 1;
   // Cost model (alpha-beta-gamma style, eq. comm): matrix-core time of the
   // slowest round of workgroups, HBM time of the gathered rows, and the traffic
   // of writing and re-reading the partial Grams.  Pick the cheapest chunk.
@@ -229,6 +242,9 @@ hipError_t launch_gram_f64(const GramPlan& p, const double* A, int64_t ld, int64
     case 2: return launch_nb<2>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
     case 4: return launch_nb<4>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
     case 8: return launch_nb<8>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 10: return launch_nb<10>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 12: return launch_nb<12>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
+    case 14: return launch_nb<14>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
     case 16: return launch_nb<16>(p, A, ld, cols, idx, m, nsteps, u, partials, st);
     default: return hipErrorInvalidValue;
   }

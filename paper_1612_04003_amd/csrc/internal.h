@@ -110,12 +110,13 @@ hipError_t launch_sample(uint64_t seed, int64_t h0, int64_t count, int b, int64_
 // ------------------------------------------------------------------ dense FP64 Gram
 // Plan of one Gram launch over the gathered rows of a dense FP64 matrix.
 struct GramPlan {
-  int nb;          // 16-row blocks covering m rows (1, 2, 4, 8 or 16)
+  int nb;          // 16-row blocks covering m rows (1, 2, 4, 8 or 16; FP64 also 10, 12, 14)
   int nblk;        // lower-triangular 16x16 blocks: nb*(nb+1)/2
   int kt;          // columns per LDS tile
   int64_t chunk;   // columns per workgroup (multiple of kt)
   int nsplit;      // workgroups along the reduction dimension
 };
+int gram_f64_blocks(int m);
 GramPlan plan_gram_f64(int m, int64_t cols);
 // The deferred companion update of the previous outer step (Alg. 2: r += gamma
 // Y^T delta with the previous step's rows and delta; Alg. 4 the same for w):
