@@ -207,9 +207,12 @@ GramPlan plan_for(const Mat& M, int m) {
   return M.lowp() ? plan_gram_lp(m, M.cols, M.dtype) : plan_gram_f64(m, M.cols);
 }
 
-// A Gram of more than kGramRows rows: six partial sets of the 256-row plan
-// (two diagonal blocks, up to four cross blocks) and the two index lists.
-size_t big_partials(const Mat& M) {
+// A Gram of more than kGramRows rows, at most sb_max.  Low precision: six partial sets
+// of the 256-row plan (two diagonal blocks, up to four cross blocks) and the two index
+// lists.
+constexpr int kBigWgs = 256;   // workgroups: one a CU
+size_t big_partials(const Mat& M, int sb_max) {
+  if (!M.lowp()) return gram_big_doubles_max(sb_max, M.cols, kBigWgs);
   return 6 * gram_partial_doubles(plan_for(M, kGramRows)) + (512 + 4 * 256) / 2;
 }
 
@@ -220,7 +223,7 @@ size_t max_partials(const Mat& M, int sb_max) {
     best = std::max(best, gram_partial_doubles(plan_for(M, std::min(m, sb_max))));
     if (m >= std::min(sb_max, kGramRows)) break;
   }
-  if (sb_max > kGramRows) best = std::max(best, big_partials(M));
+  if (sb_max > kGramRows) best = std::max(best, big_partials(M, sb_max));
   return best;
 }
 
@@ -450,6 +453,20 @@ hipError_t mat_gram(const Mat& M, const int32_t* idx, int m, const double* u, do
     return timer ? timer->run(CABCD_PHASE_GRAM, f) : f();
   }
   if (m > kGramRows) {
+    hipError_t e;
+    if (!M.lowp()) {
+      const GramBig plan = plan_gram_big_f64(m, M.cols, kBigWgs);
+      auto g = [&] {
+        return launch_gram_big_f64(plan, M.X, M.ld, M.cols, idx, m, u, partials, st);
+      };
+      auto r = [&] {
+        return launch_gram_big_reduce_f64(plan, partials, idx, m, scale, shift, overlap, G,
+                                          u != nullptr ? Yu : nullptr, st);
+      };
+      e = timer ? timer->run(CABCD_PHASE_GRAM, g) : g();
+      if (e != hipSuccess) return e;
+      return timer ? timer->run(CABCD_PHASE_REDUCE, r) : r();
+    }
     // rows [0, 256) and [256, m): the two diagonal blocks as two 256-row
     // Grams (with Y u), the cross block from the 256-row Grams of pairs of
     // 128-row halves (their off-diagonal quarter)
@@ -459,24 +476,18 @@ hipError_t mat_gram(const Mat& M, const int32_t* idx, int m, const double* u, do
     int32_t* ib = ia + 512;
     const int nc = big_cross_steps(m);
     auto g = [&]() -> hipError_t {
-      hipError_t e = launch_big_index(idx, m, ia, ib, st);
-      if (e != hipSuccess) return e;
-      if (M.lowp()) {
-        e = launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, ia, kGramRows, u, partials, st, 2);
-        if (e != hipSuccess) return e;
-        return launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, ib, kGramRows, nullptr,
-                              partials + 2 * set, st, nc);
-      }
-      e = launch_gram_f64(plan, M.X, M.ld, M.cols, ia, kGramRows, u, partials, st, 2);
-      if (e != hipSuccess) return e;
-      return launch_gram_f64(plan, M.X, M.ld, M.cols, ib, kGramRows, nullptr, partials + 2 * set,
-                             st, nc);
+      hipError_t ge = launch_big_index(idx, m, ia, ib, st);
+      if (ge != hipSuccess) return ge;
+      ge = launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, ia, kGramRows, u, partials, st, 2);
+      if (ge != hipSuccess) return ge;
+      return launch_gram_lp(plan, M.dtype, M.Q, M.ld, M.cols, ib, kGramRows, nullptr,
+                            partials + 2 * set, st, nc);
     };
     auto r = [&] {
       return launch_gram_reduce_big(plan, partials, idx, m, scale, shift, overlap, G, Yu, st,
-                                    partial_layout(M, plan), M.lowp() ? M.rs : nullptr);
+                                    partial_layout(M, plan), M.rs);
     };
-    hipError_t e = timer ? timer->run(CABCD_PHASE_GRAM, g) : g();
+    e = timer ? timer->run(CABCD_PHASE_GRAM, g) : g();
     if (e != hipSuccess) return e;
     return timer ? timer->run(CABCD_PHASE_REDUCE, r) : r();
   }

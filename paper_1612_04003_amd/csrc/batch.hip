@@ -266,9 +266,9 @@ __device__ __noinline__ void gram_call_tri16(const double* A, int64_t ld, int64_
                                              const double* u, double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
   constexpr int T = gdev::Tri<16>::TILE;
-  gdev::gram_slab_tri<16, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
-                                uni_ptr(u), uni_ptr(part),
-                                gdev::TriLds{dyn_sm, dyn_sm + T, dyn_sm + 2 * T});
+  gdev::gram_slab_tri<gdev::Tri<16>, true>(
+      uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m), 0, uni_ptr(u),
+      uni_ptr(part), gdev::TriLds{dyn_sm, dyn_sm + T, dyn_sm + 2 * T});
 }
 
 template <int NB>

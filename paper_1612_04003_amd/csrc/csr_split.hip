@@ -851,21 +851,26 @@ SplitLayout csr_split_layout(const CsrSplitInfo& info, int64_t cols, int m, int 
   // workgroup.  The slabs (and so every sum's order) do not depend on how many
   // steps a launch actually takes: a run gives the same result however its
   // steps are batched or split between calls.
-  const int sets = m > 256 ? 2 + big_cross_steps(m) : 1;
-  L.plan = plan_gram_f64(std::min(m, 256), std::max(L.hp, 16));
-  const int kt = L.plan.kt;
   const int64_t width = std::max(L.hp, 16);
-  const int want = std::max(1, (256 + kPanelSteps * sets - 1) / (kPanelSteps * sets));
-  int64_t chunk = (width + want - 1) / want;
-  chunk = std::max<int64_t>(kt, (chunk + kt - 1) / kt * kt);
-  L.plan.chunk = chunk;
-  L.plan.nsplit = (int)((width + chunk - 1) / chunk);
-  L.doubles = (size_t)nsteps * ((size_t)m * L.hp + (size_t)m * m + (size_t)L.lcap) +
-              (size_t)nsteps * sets * gram_partial_doubles(L.plan);
+  const int want = (256 + kPanelSteps - 1) / kPanelSteps;
+  size_t partials;
+  if (m > 256) {
+    L.big = plan_gram_big_f64(m, width, want);
+    partials = (size_t)L.big.off[L.big.parts];
+  } else {
+    L.plan = plan_gram_f64(m, width);
+    const int kt = L.plan.kt;
+    int64_t chunk = (width + want - 1) / want;
+    chunk = std::max<int64_t>(kt, (chunk + kt - 1) / kt * kt);
+    L.plan.chunk = chunk;
+    L.plan.nsplit = (int)((width + chunk - 1) / chunk);
+    partials = gram_partial_doubles(L.plan);
+  }
+  L.doubles = (size_t)nsteps * ((size_t)m * L.hp + (size_t)m * m + (size_t)L.lcap + partials);
   L.doubles = (L.doubles + 31) / 32 * 32;   // the ints that follow start 256-byte aligned
   L.ints = (size_t)nsteps * (2 * (size_t)L.cs + 3 * (size_t)L.nblk + (size_t)L.lcap +
                              2 * (size_t)m * info.maxrow + 3 * (size_t)(L.lcap / 2 + 1) +
-                             3 * (size_t)(L.lcap / (kShortList + 1) + 1) + 2 + m + 512 + 4 * 256);
+                             3 * (size_t)(L.lcap / (kShortList + 1) + 1) + 2 + m);
   return L;
 }
 
@@ -875,7 +880,7 @@ struct SplitBufs {
   int *cnt, *off, *bsum, *lq, *ent, *rk, *segn;
   Seg *segs, *lsegs;
   int64_t segcap, lsegcap;
-  int32_t *iota, *ia, *ib;
+  int32_t* iota;
 };
 SplitBufs split_bufs(const SplitLayout& L, const CsrSplitInfo& info, int m, int nsteps,
                      double* dws, int* iws) {
@@ -896,8 +901,6 @@ SplitBufs split_bufs(const SplitLayout& L, const CsrSplitInfo& info, int m, int 
   B.lsegs = B.segs + (size_t)nsteps * B.segcap;
   B.segn = reinterpret_cast<int*>(B.lsegs + (size_t)nsteps * B.lsegcap);
   B.iota = B.segn + 2 * nsteps;
-  B.ia = B.iota + (size_t)nsteps * m;
-  B.ib = B.ia + (size_t)nsteps * 512;
   return B;
 }
 
@@ -954,7 +957,7 @@ hipError_t launch_csr_gram_split(const CsrView& A, const CsrSplitInfo& info, con
   int* segn = SB.segn;
   Seg *segs = SB.segs, *lsegs = SB.lsegs;
   const int64_t segcap = SB.segcap, lsegcap = SB.lsegcap;
-  int32_t *iota = SB.iota, *ia = SB.ia, *ib = SB.ib;
+  int32_t* iota = SB.iota;
 
   const int64_t waves = (int64_t)nsteps * m;
   const int wgrid = (int)((waves * 64 + kT - 1) / kT);
@@ -993,24 +996,17 @@ hipError_t launch_csr_gram_split(const CsrView& A, const CsrSplitInfo& info, con
   // the heavy part: the Gram of each step's m x Hp panel on the matrix cores
   // (rows k m .. k m + m - 1 of the stacked panels), plus the light rows
   hipLaunchKernelGGL(iota_steps_kernel, dim3(grid_for(waves)), dim3(kT), 0, st, iota, waves);
-  const GramPlan& P = L.plan;
-  if (m <= 256) {
-    e = launch_gram_f64(P, Dh, L.hp, L.hp, iota, m, nullptr, partials, st, nsteps);
+  if (m > 256) {
+    e = launch_gram_big_f64(L.big, Dh, L.hp, L.hp, iota, m, nullptr, partials, st, nsteps);
     if (e != hipSuccess) return e;
-    return launch_gram_reduce(P, partials, idx, m, scale, shift, overlap, G, nullptr, st, 0,
-                              nullptr, nsteps, Gl);
+    return launch_gram_big_reduce_f64(L.big, partials, idx, m, scale, shift, overlap, G, nullptr,
+                                      st, nsteps, Gl);
   }
-  const size_t set = gram_partial_doubles(P);
-  const int nc = big_cross_steps(m);
-  e = launch_big_index(iota, m, ia, ib, st, nsteps);
-  if (e == hipSuccess)
-    e = launch_gram_f64(P, Dh, L.hp, L.hp, ia, 256, nullptr, partials, st, 2 * nsteps);
-  if (e == hipSuccess)
-    e = launch_gram_f64(P, Dh, L.hp, L.hp, ib, 256, nullptr, partials + 2 * nsteps * set, st,
-                        nc * nsteps);
+  const GramPlan& P = L.plan;
+  e = launch_gram_f64(P, Dh, L.hp, L.hp, iota, m, nullptr, partials, st, nsteps);
   if (e != hipSuccess) return e;
-  return launch_gram_reduce_big(P, partials, idx, m, scale, shift, overlap, G, nullptr, st, 0,
-                                nullptr, nsteps, Gl);
+  return launch_gram_reduce(P, partials, idx, m, scale, shift, overlap, G, nullptr, st, 0, nullptr,
+                            nsteps, Gl);
 }
 
 }  // namespace cabcd

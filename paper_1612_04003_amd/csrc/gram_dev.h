@@ -361,51 +361,79 @@ constexpr int kTriMin = 9;       // block rows from which on these kernels run
 constexpr int kTriLead = 4;
 constexpr int tri_rows(int nb) { return nb < kTriMin ? nb : (nb + 1) / 2 * 2; }
 
-template <int NB>
-struct Tri {
-  static constexpr int SBP = 16 * NB, NBLK = NB * (NB + 1) / 2, KT = 16, CH = KT / 2;
+// A wave's blocks (block row r, block column c, index q in the partial) in the order
+// they are computed, the block rows in the order their fragments are first used, how
+// many of them block i needs, and the block rows whose Y u is this wave's (its diagonal
+// blocks').
+struct WaveBlocks {
+  int n = 0, nf = 0, nd = 0;
+  int r[17] = {}, c[17] = {}, q[17] = {}, need[17] = {};
+  int fr[24] = {}, diag[16] = {};
+  bool have[24] = {};
+  constexpr void add(int row, int col, int k) {
+    if (!have[row]) {
+      have[row] = true;
+      fr[nf++] = row;
+    }
+    if (!have[col]) {
+      have[col] = true;
+      fr[nf++] = col;
+    }
+    r[n] = row;
+    c[n] = col;
+    q[n] = k;
+    need[n] = nf;
+    ++n;
+    if (row == col) diag[nd++] = row;
+  }
+};
+
+// Block rows NR whose rows a tile holds, and blocks NBLK of the shape's partial.
+template <int NROWS, int NBLOCKS>
+struct SlabShape {
+  static constexpr int NR = NROWS, NBLK = NBLOCKS, SBP = 16 * NR, KT = 16, CH = KT / 2;
   static constexpr int PP = KT / 8;                  // 128-bit fragment reads per tile
   static constexpr int THREADS = 512;
   static constexpr int TILE = SBP * KT + KT;         // doubles per buffer: rows, then u
   static constexpr int DMA = SBP * CH / 64;          // instructions of 64 chunks a tile
-  static constexpr int MAXB = (NBLK + 7) / 8;        // blocks of a wave, at most
 };
 
-// Wave W's blocks (row r, column c, index q in row-major order) in the order they are
-// computed, the rows of fragments in the order they are first used, how many of them
-// block i needs, and the rows whose Y u is this wave's (its diagonal blocks').
-template <int NB, int W>
-struct TriWave {
-  int n = 0, nf = 0, nd = 0;
-  int r[17] = {}, c[17] = {}, q[17] = {}, need[17] = {};
-  int fr[16] = {};
-  int diag[16] = {};
-  constexpr TriWave() {
-    const int q0 = W * Tri<NB>::NBLK / 8, q1 = (W + 1) * Tri<NB>::NBLK / 8;
-    bool have[16] = {};
+// The lower triangle of NB block rows, rows base + r; wave W takes an eighth of the
+// row-major order.
+template <int NB>
+struct Tri : SlabShape<NB, NB * (NB + 1) / 2> {
+  static __device__ __forceinline__ int row(int base, int r) { return base + r; }
+  template <int W>
+  static constexpr WaveBlocks blocks() {
+    WaveBlocks b{};
+    const int n = NB * (NB + 1) / 2, q0 = W * n / 8, q1 = (W + 1) * n / 8;
     for (int col = 0; col < NB; ++col)
       for (int row = col; row < NB; ++row) {
         const int k = blk_index(row, col);
-        if (k < q0 || k >= q1) continue;
-        if (!have[row]) {
-          have[row] = true;
-          fr[nf++] = row;
-        }
-        if (!have[col]) {
-          have[col] = true;
-          fr[nf++] = col;
-        }
-        r[n] = row;
-        c[n] = col;
-        q[n] = k;
-        need[n] = nf;
-        ++n;
-        if (row == col) diag[nd++] = row;
+        if (k >= q0 && k < q1) b.add(row, col, k);
       }
+    return b;
   }
 };
 
-// The three tile buffers (Tri<NB>::TILE doubles each).  In the one-problem kernels
+// R block rows (rows base + r) against the first sixteen: block (i, j) at i * 16 + j; a
+// wave takes two block rows of R and 4 R / 4 block columns.
+template <int R>
+struct Rect : SlabShape<16 + R, 16 * R> {
+  static __device__ __forceinline__ int row(int base, int r) {
+    return r < 256 ? r : base + (r - 256);
+  }
+  template <int W>
+  static constexpr WaveBlocks blocks() {
+    WaveBlocks b{};
+    const int i0 = 2 * (W % (R / 2)), j0 = R * (W / (R / 2));
+    for (int j = j0; j < j0 + R; ++j)
+      for (int i = i0; i < i0 + 2; ++i) b.add(16 + i, j, i * 16 + j);
+    return b;
+  }
+};
+
+// The three tile buffers (a shape's TILE doubles each).  In the one-problem kernels
 // each is a __shared__ array of its own and the tile loop is unrolled over the three,
 // which is what tells the compiler that a read of one need not wait for the DMA into
 // another.
@@ -421,15 +449,14 @@ __device__ __forceinline__ void static_for(F&& f) {
   }
 }
 
-template <int NB, int W, bool AGENT>
+template <class C, int W, bool AGENT>
 __device__ __forceinline__ void tri_slab(const double* __restrict__ A, int64_t ld,
                                          int64_t k_begin, int64_t k_end, const int32_t* idx,
-                                         int m, const double* __restrict__ u,
+                                         int m, int base, const double* __restrict__ u,
                                          double* __restrict__ part, const TriLds L) {
-  using C = Tri<NB>;
   typedef __attribute__((address_space(3))) void* lds_vptr;
   typedef __attribute__((address_space(1))) const void* glb_vptr;
-  constexpr TriWave<NB, W> T{};
+  constexpr WaveBlocks T = C::template blocks<W>();
   constexpr int LEAD = T.nf < kTriLead ? T.nf : kTriLead;
   constexpr int ND = (C::DMA - W + 7) / 8;   // this wave's DMA instructions: W + 8 i
   const int lane = threadIdx.x & 63;
@@ -448,8 +475,8 @@ __device__ __forceinline__ void tri_slab(const double* __restrict__ A, int64_t l
   gptr<const double> src[ND];
 #pragma unroll
   for (int i = 0; i < ND; ++i) {
-    const int r = slot_row(i);
-    src[i] = Ag + (int64_t)idx[r < m ? r : 0] * ld + k_begin + 2 * chunk_of(r);
+    const int r = slot_row(i), p = C::row(base, r);
+    src[i] = Ag + (int64_t)idx[p < m ? p : 0] * ld + k_begin + 2 * chunk_of(r);
   }
   // full tile f (columns k_begin + 16 f ..)
   auto issue = [&](int f, double* B) {
@@ -505,15 +532,15 @@ __device__ __forceinline__ void tri_slab(const double* __restrict__ A, int64_t l
 
   // Tile t in cur, tile t + 1 in nxt, tile t + 2 on its way into far.
   auto step = [&](int t, const double* cur, const double* nxt, double* far) {
-    double2 F[C::PP][NB];
+    double2 F[C::PP][C::NR];
     double2 ut[C::PP];
     static_for<0, LEAD>([&](auto i) { F[0][T.fr[i]] = pre[i]; });
     static_for<0, C::PP * T.n>([&](auto I) {
       constexpr int pp = I / T.n, i = I % T.n;
       // fragments read before this block: all that the one before it had asked for
+      constexpr int last = I == 0 ? 0 : I - 1;
       constexpr int before =
-          I == 0 ? LEAD
-                 : std::max(LEAD, (I - 1) / T.n * T.nf + T.need[(I - 1) % T.n] + LEAD);
+          I == 0 ? LEAD : std::max(LEAD, last / T.n * T.nf + T.need[last % T.n] + LEAD);
       constexpr int after = std::max(before, pp * T.nf + T.need[i] + LEAD);
       static_for<before, after>([&](auto l) {
         constexpr int tile = l / (C::PP * T.nf), lp = l / T.nf % C::PP, f = l % T.nf;
@@ -563,21 +590,22 @@ __device__ __forceinline__ void tri_slab(const double* __restrict__ A, int64_t l
   }
 }
 
-// The slab of NB block rows; arguments and partial layout as gram_slab_dma.
-template <int NB, bool AGENT = false>
+// The slab of a shape (Tri: arguments and partial layout as gram_slab_dma; Rect: without
+// Y u): rows idx[C::row(base, .)], the m-th on replaced by the first.
+template <class C, bool AGENT = false>
 __device__ __forceinline__ void gram_slab_tri(const double* __restrict__ A, int64_t ld,
                                               int64_t k_begin, int64_t k_end, const int32_t* idx,
-                                              int m, const double* __restrict__ u,
+                                              int m, int base, const double* __restrict__ u,
                                               double* __restrict__ part, const TriLds L) {
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: tri_slab<NB, 0, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 1: tri_slab<NB, 1, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 2: tri_slab<NB, 2, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 3: tri_slab<NB, 3, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 4: tri_slab<NB, 4, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 5: tri_slab<NB, 5, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    case 6: tri_slab<NB, 6, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
-    default: tri_slab<NB, 7, AGENT>(A, ld, k_begin, k_end, idx, m, u, part, L); break;
+    case 0: tri_slab<C, 0, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 1: tri_slab<C, 1, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 2: tri_slab<C, 2, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 3: tri_slab<C, 3, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 4: tri_slab<C, 4, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 5: tri_slab<C, 5, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    case 6: tri_slab<C, 6, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
+    default: tri_slab<C, 7, AGENT>(A, ld, k_begin, k_end, idx, m, base, u, part, L); break;
   }
 }
 
@@ -928,7 +956,7 @@ __device__ __forceinline__ void store_entry(int64_t e, double t, int nblk, const
   }
 }
 
-// Index lists of a Gram of m in (256, 512] rows: ia = the m indices padded to
+// Index lists of a Gram of m in (256, 512] rows of codes or of a batched problem: ia = the m indices padded to
 // 512 with idx[0] (two 256-row Grams: the diagonal blocks); ib[t] (t < nc,
 // nc = 4 when m > 384, else 2) = idx[128 x .. 128 x + 128) followed by
 // ia[256 + 128 y .. 256 + 128 y + 128), x = t % 2, y = t / 2, whose 256-row
@@ -959,8 +987,7 @@ __device__ __forceinline__ void store_entry_big(int64_t e, double t, int set, in
                                                 const int32_t* idx, int m, double scale,
                                                 double shift, int overlap,
                                                 double* __restrict__ G, double* __restrict__ Yu,
-                                                int layout, const float* __restrict__ rs,
-                                                const double* __restrict__ add) {
+                                                int layout, const float* __restrict__ rs) {
   constexpr int kNblk = 136;
   if (e >= (int64_t)kNblk * 256) {          // the Y u entries follow the blocks
     const int p = 256 * step + (int)(e - (int64_t)kNblk * 256);
@@ -983,7 +1010,6 @@ __device__ __forceinline__ void store_entry_big(int64_t e, double t, int set, in
   if (gr >= m || gc >= m) return;
   const bool on = overlap ? (idx[gr] == idx[gc]) : (gr == gc);
   const double sc = rs ? scale * (double)glb(rs)[idx[gr]] * (double)glb(rs)[idx[gc]] : scale;
-  if (add != nullptr) t += glb(add)[(int64_t)gr * m + gc];
   const double v = sc * t + (on ? shift : 0.0);
   glb(G)[(int64_t)gr * m + gc] = v;
   glb(G)[(int64_t)gc * m + gr] = v;
@@ -1037,7 +1063,7 @@ __device__ __forceinline__ void reduce_wg_big(const double* __restrict__ partial
   for (int g = 0; g < nsets; ++g)
     sum_sets<T>(partials + g * pstride, n, stride, pstride, [&](int64_t e, double s) {
       store_entry_big(e, s, g < 2 ? 0 : 1, g < 2 ? g : g - 2, idx, m, scale, shift, 1, G, Yu,
-                      layout, rs, nullptr);
+                      layout, rs);
     });
 }
 

@@ -164,22 +164,43 @@ hipError_t launch_gram_reduce(const GramPlan& p, const double* partials, const i
                               double* Yu, hipStream_t st, int layout = 0,
                               const float* rs = nullptr, int nsteps = 1,
                               const double* add = nullptr);
-// Grams of m in (256, 512] rows from 256-row Grams (plan p of 256 rows, nb 16),
-// for ngram row lists idx + k m: launch_big_index builds per Gram the index
-// lists ia (512: the rows padded with the first) and ib (nc = big_cross_steps(m)
-// lists of 256: half-bands [rows 128 x.. ; rows 256 + 128 y..]); the Gram
-// launches then write 2 ngram partial sets (ia as 2 ngram steps, with Y u for
-// a single Gram) followed by nc ngram sets (ib), each of
-// gram_partial_doubles(p), which launch_gram_reduce_big sums into G + k m^2
-// (adding add + k m^2 when given) and Y u.
-hipError_t launch_big_index(const int32_t* idx, int m, int32_t* ia, int32_t* ib, hipStream_t st,
-                            int ngram = 1);
+// FP64 Grams of m in (256, 512] rows in parts, each its own share of the workgroups of
+// one launch: the triangles of rows [0, 256) and [256, m) (with Y u) and the rectangles
+// of the rows from 256 on, up to 128 at a time, against the first 256.
+struct GramBig {
+  static constexpr int kParts = 4;
+  int parts;
+  int kind[kParts];        // block rows of a triangle; -R: a rectangle of R block rows
+  int base[kParts];        // its first row
+  int wg[kParts + 1];      // its first workgroup; the number of workgroups last
+  int64_t chunk[kParts];   // columns of a slab
+  int64_t entry[kParts + 1];   // its first entry in the reduction's order
+  int64_t off[kParts + 1];     // its first partial (doubles); a Gram's partials last
+};
+// wgs: workgroups a Gram, about.
+GramBig plan_gram_big_f64(int m, int64_t cols, int wgs);
+// Largest partials (doubles) of any m in (256, m_max].
+size_t gram_big_doubles_max(int m_max, int64_t cols, int wgs);
+// ngram Grams of rows idx + k m, partials at k p.off[parts]; Y u (and u) with one Gram
+// only; add as in launch_gram_reduce.
+hipError_t launch_gram_big_f64(const GramBig& p, const double* A, int64_t ld, int64_t cols,
+                               const int32_t* idx, int m, const double* u, double* partials,
+                               hipStream_t st, int ngram = 1);
+hipError_t launch_gram_big_reduce_f64(const GramBig& p, const double* partials,
+                                      const int32_t* idx, int m, double scale, double shift,
+                                      bool overlap, double* G, double* Yu, hipStream_t st,
+                                      int ngram = 1, const double* add = nullptr);
+// Low-precision Grams of m in (256, 512] rows from 256-row Grams (plan p of 256 rows, nb
+// 16): launch_big_index builds the index lists ia (512: the rows padded with the first)
+// and ib (nc = big_cross_steps(m) lists of 256: half-bands [rows 128 x.. ; rows 256 +
+// 128 y..]); the Gram launches then write 2 partial sets (ia as 2 steps, with Y u)
+// followed by nc sets (ib), each of gram_partial_doubles(p), which
+// launch_gram_reduce_big sums into G and Y u.
+hipError_t launch_big_index(const int32_t* idx, int m, int32_t* ia, int32_t* ib, hipStream_t st);
 int big_cross_steps(int m);
 hipError_t launch_gram_reduce_big(const GramPlan& p, const double* partials, const int32_t* idx,
                                   int m, double scale, double shift, bool overlap, double* G,
-                                  double* Yu, hipStream_t st, int layout = 0,
-                                  const float* rs = nullptr, int ngram = 1,
-                                  const double* add = nullptr);
+                                  double* Yu, hipStream_t st, int layout, const float* rs);
 
 // ------------------------------------------------------------------ fused solve
 // One outer step's s block solves through the unrolled recurrence, followed by
@@ -342,7 +363,8 @@ struct SplitLayout {
   int nblk;          // scan workgroups over the columns
   int64_t cs;        // per-step column-table stride (nblk whole scan workgroups)
   int64_t lcap;      // light list capacity per step
-  GramPlan plan;     // the panel Gram's plan
+  GramPlan plan;     // the panel Gram's plan, up to 256 rows
+  GramBig big;       // and above
   size_t doubles, ints;   // scratch of one launch
 };
 size_t csr_split_prepare_ints(const CsrView& A);

@@ -12,7 +12,7 @@ U = 2.0 ** -53
 
 
 @pytest.mark.parametrize("m", [1, 16, 17, 33, 65, 128, 129, 144, 145, 160, 161, 176, 192, 193,
-                               208, 224, 225, 240, 255, 256])
+                               208, 224, 225, 240, 255, 256, 257, 320, 321, 384, 385, 449, 512])
 @pytest.mark.parametrize("cols", [1, 15, 16, 17, 31, 49, 4096 + 5, 33000])
 def test_f64_gram_block_counts(gpu_lib, m, cols):
     print("[gram] f64", m, cols, flush=True)
