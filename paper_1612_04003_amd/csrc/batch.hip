@@ -261,23 +261,27 @@ __device__ __forceinline__ T* uni_ptr(T* p) {
 // their own extern declaration, so their LDS accesses stay ds_* instructions.
 // Arguments of a non-inlined function are per-lane values to the compiler; the
 // tile loop's barriers need its bounds to be visibly uniform.
+// The FP64 tile buffers are __shared__ arrays of their own (see gdev::TriLds), the third
+// one of a 256-row Gram lies in the dynamic LDS.
+constexpr int kTile = std::max({gdev::DN<1>::TILE, gdev::DN<2>::TILE, gdev::DN<4>::TILE,
+                                gdev::DN<8>::TILE, gdev::Tri<16>::TILE});
+__shared__ __attribute__((aligned(16))) double tile0[kTile], tile1[kTile];
+
 __device__ __noinline__ void gram_call_tri16(const double* A, int64_t ld, int64_t k0,
                                              int64_t k1, const int32_t* idx, int m,
                                              const double* u, double* part) {
   extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  constexpr int T = gdev::Tri<16>::TILE;
   gdev::gram_slab_tri<gdev::Tri<16>, true>(
       uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m), 0, uni_ptr(u),
-      uni_ptr(part), gdev::TriLds{dyn_sm, dyn_sm + T, dyn_sm + 2 * T});
+      uni_ptr(part), gdev::TriLds{tile0, tile1, dyn_sm});
 }
 
 template <int NB>
 __device__ __noinline__ void gram_call_dma(const double* A, int64_t ld, int64_t k0, int64_t k1,
                                            const int32_t* idx, int m, const double* u,
                                            double* part) {
-  extern __shared__ __attribute__((aligned(16))) double dyn_sm[];
-  gdev::gram_slab_dma<NB, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx),
-                                uni(m), uni_ptr(u), uni_ptr(part), dyn_sm);
+  gdev::gram_slab_dma<NB, true>(uni_ptr(A), uni64(ld), uni64(k0), uni64(k1), uni_ptr(idx), uni(m),
+                                uni_ptr(u), uni_ptr(part), tile0, tile1);
 }
 
 template <int NB, int FMT>
@@ -835,17 +839,6 @@ const void* aux_kernel_ptr(int dtype) {
   }
 }
 
-// LDS of the FP64 Gram slab with nb block rows, in doubles.
-int gram_lds(int nb) {
-  switch (nb) {
-    case 1: return gdev::DN<1>::LDS;
-    case 2: return gdev::DN<2>::LDS;
-    case 4: return gdev::DN<4>::LDS;
-    case 8: return gdev::DN<8>::LDS;
-    default: return 3 * gdev::Tri<16>::TILE;
-  }
-}
-
 #define BATCH_HIP(call)                                                     \
   do {                                                                      \
     hipError_t e_ = (call);                                                 \
@@ -1010,7 +1003,8 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     add(sizeof(int32_t) * 2 * sb);
     add(sizeof(int) * kGroups);
     area = std::max<int>(area, (int)((solve_lds_bytes(sb, best[p].b) + 7) / 8));
-    if (B->dtype == CABCD_F64) area = std::max({area, gram_lds(nb), kDotLds<CABCD_F64>});
+    if (B->dtype == CABCD_F64)
+      area = std::max({area, nb == 16 ? gdev::Tri<16>::TILE : 0, kDotLds<CABCD_F64>});
     pool += (size_t)best[p].nslab * slab_doubles(sb) + 32;
   }
   pool += (size_t)kBMaxSlabs * slab_doubles(kBMaxRows) + 32;

@@ -54,7 +54,6 @@ struct Cfg {
   static constexpr int NCH = SBP * CH / THREADS;            // chunks per thread per tile
   static constexpr int PAIRS = KT / 8;                      // 128-bit fragment reads per tile
   static constexpr int NACC = NB >= 2 ? NBLK / BW : 1;      // accumulators per wave
-  static constexpr int RED = (KG - 1) * NBLK * 256;
   static constexpr int YUS = SBP * CH;
   static_assert(NCH * THREADS == SBP * CH, "tile must split evenly");
   static_assert(PAIRS % KG == 0, "k-steps must split evenly");
@@ -118,11 +117,10 @@ struct DN {
   static constexpr int DMA_PER_WAVE = C::SBP * C::CH / 64 / 8;   // 4 instructions
   static constexpr int UDMA = (C::KT / 2 + 63) / 64;              // u slots, 64 a time
   static constexpr int TILE = C::SBP * C::KT + C::KT;            // doubles: rows, then u
-  // parts in which a wave's blocks meet the other k-groups' (NB = 8: 64.5 KiB
-  // of LDS instead of 72)
-  static constexpr int HV = C::RED > 2 * TILE ? 2 : 1;
-  static constexpr int RED = (C::KG - 1) * C::BW * ((C::NACC + HV - 1) / HV) * 256;
-  static constexpr int LDS = std::max(std::max(2 * TILE, RED), C::YUS);
+  // accumulators a wave brings to the other k-groups' at a time: what a tile buffer holds
+  static constexpr int HA =
+      C::KG > 1 ? std::min(C::NACC, TILE / ((C::KG - 1) * C::BW * 256)) : C::NACC;
+  static_assert(HA >= 1 && C::YUS <= TILE, "the sums fit a tile buffer");
 };
 
 template <int NB, int W>
@@ -178,13 +176,15 @@ __device__ __forceinline__ void mma_dispatch_dma(int bw, const double* __restric
 // One workgroup's slab of the Gram: columns [k_begin, k_end) of the rows
 // idx[0..m) of A (m <= 16 NB; idx may point to LDS), u indexed by absolute
 // column (NULL: no Y u).  Writes the partial blocks and the partial Y u to
-// part[0 .. NBLK*256 + SBP).  lds holds DN<NB>::LDS doubles.  Every thread of the
-// workgroup must call it.
+// part[0 .. NBLK*256 + SBP).  t0 and t1: the tile buffers (DN<NB>::TILE doubles),
+// __shared__ arrays of their own, as in TriLds: with both in one array every tile waited
+// for the next one's DMA before its first read.  Every thread of the workgroup must
+// call it.
 template <int NB, bool AGENT = false>
 __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int64_t ld,
                                               int64_t k_begin, int64_t k_end, const int32_t* idx,
                                               int m, const double* __restrict__ u,
-                                              double* __restrict__ part, double* lds) {
+                                              double* __restrict__ part, double* t0, double* t1) {
   using C = Cfg<NB>;
   using D = DN<NB>;
   typedef __attribute__((address_space(3))) void* lds_vptr;
@@ -212,49 +212,52 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     live[i] = r < m;
     src[i] = Ag + (int64_t)idx[r < m ? r : 0] * ld;
     if (!live[i]) {
-#pragma unroll
-      for (int sl = 0; sl < 2; ++sl)
-        *reinterpret_cast<double2*>(lds + sl * D::TILE + (D::DMA_PER_WAVE * wave + i) * 128 +
-                                    2 * lane) = double2{0.0, 0.0};
+      const int at = (D::DMA_PER_WAVE * wave + i) * 128 + 2 * lane;
+      *reinterpret_cast<double2*>(t0 + at) = double2{0.0, 0.0};
+      *reinterpret_cast<double2*>(t1 + at) = double2{0.0, 0.0};
     }
   }
   const bool want_u = u != nullptr;
   const gptr<const double> ug = glb(u);
-  auto issue = [&](int t, int slot) {
+  // (padding rows stay zero; u: the tile's KT entries, unswizzled after the rows)
+  auto issue = [&](int t, double* T) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
-    double* T = lds + slot * D::TILE;
-    const bool full = k0 + C::KT <= k_end;
+    double* const ud = T + C::SBP * C::KT;
+    const bool u_wave = want_u && wave == 7;
+    if (k0 + C::KT <= k_end) {
+#pragma unroll
+      for (int i = 0; i < D::DMA_PER_WAVE; ++i)   // 64 slots of 2 doubles each
+        if (live[i])
+          __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + (k0 + cofs[i])),
+                                           (lds_vptr)(T + (D::DMA_PER_WAVE * wave + i) * 128), 16,
+                                           0, 0);
+      if (u_wave) {
+#pragma unroll
+        for (int j = 0; j < D::UDMA; ++j)
+          if (64 * j + lane < C::KT / 2)
+            __builtin_amdgcn_global_load_lds((glb_vptr)(ug + (k0 + 2 * (64 * j + lane))),
+                                             (lds_vptr)(ud + 128 * j), 16, 0, 0);
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < D::DMA_PER_WAVE; ++i) {
-      double* dst = T + (D::DMA_PER_WAVE * wave + i) * 128;   // 64 slots of 2 doubles
       const int64_t k = k0 + cofs[i];
-      if (!live[i]) {
-        // padding row: stays zero
-      } else if (full) {
-        __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + k), (lds_vptr)dst, 16, 0, 0);
-      } else {
-        double2 v;
-        v.x = k < k_end ? src[i][k] : 0.0;
-        v.y = k + 1 < k_end ? src[i][k + 1] : 0.0;
-        *reinterpret_cast<double2*>(dst + 2 * lane) = v;
-      }
+      double2 v;
+      v.x = live[i] && k < k_end ? src[i][k] : 0.0;
+      v.y = live[i] && k + 1 < k_end ? src[i][k + 1] : 0.0;
+      *reinterpret_cast<double2*>(T + (D::DMA_PER_WAVE * wave + i) * 128 + 2 * lane) = v;
     }
-    if (want_u && wave == 7) {   // the tile's KT entries of u, unswizzled after the rows
+    if (u_wave) {
 #pragma unroll
-      for (int j = 0; j < D::UDMA; ++j) {
+      for (int j = 0; j < D::UDMA; ++j)
         if (64 * j + lane < C::KT / 2) {
-          double* dst = T + C::SBP * C::KT + 128 * j;
           const int64_t k = k0 + 2 * (64 * j + lane);
-          if (full) {
-            __builtin_amdgcn_global_load_lds((glb_vptr)(ug + k), (lds_vptr)dst, 16, 0, 0);
-          } else {
-            double2 v;
-            v.x = k < k_end ? ug[k] : 0.0;
-            v.y = k + 1 < k_end ? ug[k + 1] : 0.0;
-            *reinterpret_cast<double2*>(dst + 2 * lane) = v;
-          }
+          double2 v;
+          v.x = k < k_end ? ug[k] : 0.0;
+          v.y = k + 1 < k_end ? ug[k + 1] : 0.0;
+          *reinterpret_cast<double2*>(ud + 128 * j + 2 * lane) = v;
         }
-      }
     }
   };
 
@@ -271,12 +274,8 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
 #pragma unroll
   for (int a = 0; a < C::NACC; ++a) acc[a] = d4{0.0, 0.0, 0.0, 0.0};
 
-  issue(0, 0);
-  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    if (t + 1 < ntiles) issue(t + 1, (t + 1) & 1);
-    const double* tile = lds + (t & 1) * D::TILE;
+  auto step = [&](int t, const double* tile, double* next) {
+    if (t + 1 < ntiles) issue(t + 1, next);
     mma_dispatch_dma<NB>(bw, tile, lane, kg, acc);
     if (want_u) {
       const double2 ub = *reinterpret_cast<const double2*>(tile + C::SBP * C::KT + 2 * c);
@@ -291,20 +290,26 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
     }
     __builtin_amdgcn_s_waitcnt(0);   // tile t + 1 is in LDS
     __syncthreads();
+  };
+  issue(0, t0);
+  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
+  __syncthreads();
+  for (int t = 0; t < ntiles; t += 2) {
+    step(t, t0, t1);
+    if (t + 1 < ntiles) step(t + 1, t1, t0);
   }
 
   // Sum the k-groups (waves with the same blocks) through LDS, in group order,
-  // a wave's blocks in HV parts so that they fit the tiles' space.
+  // HA of a wave's blocks at a time.
   if constexpr (C::KG > 1) {
-    constexpr int HA = (C::NACC + D::HV - 1) / D::HV;   // accumulators of a part
 #pragma unroll
-    for (int a0 = 0; a0 < C::NACC; a0 += HA) {
+    for (int a0 = 0; a0 < C::NACC; a0 += D::HA) {
       auto at = [&](int g, int a) {
-        return lds + (((g - 1) * C::BW + bw) * HA + (a - a0)) * 256 + lane;
+        return t0 + (((g - 1) * C::BW + bw) * D::HA + (a - a0)) * 256 + lane;
       };
       if (kg > 0) {
 #pragma unroll
-        for (int a = a0; a < std::min(a0 + HA, C::NACC); ++a)
+        for (int a = a0; a < std::min(a0 + D::HA, C::NACC); ++a)
 #pragma unroll
           for (int i = 0; i < 4; ++i) at(kg, a)[64 * i] = acc[a][i];
       }
@@ -312,12 +317,12 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
       if (kg == 0) {
         for (int g = 1; g < C::KG; ++g) {
 #pragma unroll
-          for (int a = a0; a < std::min(a0 + HA, C::NACC); ++a)
+          for (int a = a0; a < std::min(a0 + D::HA, C::NACC); ++a)
 #pragma unroll
             for (int i = 0; i < 4; ++i) acc[a][i] += at(g, a)[64 * i];
         }
       }
-      if (a0 + HA < C::NACC) __syncthreads();
+      if (a0 + D::HA < C::NACC) __syncthreads();
     }
   }
   if (kg == 0) {
@@ -331,11 +336,11 @@ __device__ __forceinline__ void gram_slab_dma(const double* __restrict__ A, int6
   if (want_u) {
     __syncthreads();   // LDS is reused for the row sums of Y u
 #pragma unroll
-    for (int i = 0; i < C::NCH; ++i) lds[rho[i] * C::CH + c] = yu[i];
+    for (int i = 0; i < C::NCH; ++i) t0[rho[i] * C::CH + c] = yu[i];
     __syncthreads();
     if (tid < C::SBP) {
       double sum = 0.0;
-      for (int q = 0; q < C::CH; ++q) sum += lds[tid * C::CH + q];
+      for (int q = 0; q < C::CH; ++q) sum += t0[tid * C::CH + q];
       put<AGENT>(glb(part) + C::NBLK * 256 + tid, sum);
     }
   }

@@ -19,13 +19,13 @@ __global__ __launch_bounds__(Cfg<NB>::THREADS) void gram_f64_dma_kernel(
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
     int64_t pstride) {
   using C = Cfg<NB>;
-  __shared__ __attribute__((aligned(16))) double lds[DN<NB>::LDS];
+  __shared__ __attribute__((aligned(16))) double t0[DN<NB>::TILE], t1[DN<NB>::TILE];
   idx += (int64_t)blockIdx.y * m;
   partials += (int64_t)blockIdx.y * pstride;
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   gram_slab_dma<NB>(A, ld, k_begin, k_end, idx, m, u,
-                    partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), lds);
+                    partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP), t0, t1);
 }
 
 template <int NB>

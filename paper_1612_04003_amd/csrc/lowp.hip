@@ -124,7 +124,6 @@ struct LD16 {
   static constexpr int TILE = SBP * RB;                  // 64 KiB of codes
   static constexpr int UB = KT * 8;                      // the tile's u segment
   static constexpr int BUF = TILE + UB;
-  static constexpr int LDS = 2 * BUF;
   static constexpr int DMA_PER_WAVE = TILE / 1024 / 8;   // 8 instructions of 1 KiB
   static constexpr int UDMA = UB / 1024;                 // 1 (BF16) or 2 (FP8)
 };
@@ -146,9 +145,14 @@ __host__ __device__ constexpr int lp16_sb_block(int W, int a) {
   return blk_index16(4 * d + r, 4 * d + t - r * (r + 1) / 2);
 }
 
-// One k-step of wave W's blocks: frag(r) gives the fragment of block row r,
-// mma(row, col, acc) one matrix instruction.
-template <int W, class Frag, class Mma>
+// Super-block row of accumulator a of wave W; its rows are 64 I and on.
+__host__ __device__ constexpr int lp16_sb_row(int W, int a) {
+  return W < 6 ? kSbI[W] : a < 10 ? (W == 6 ? 0 : 1) : (W == 6 ? 3 : 2);
+}
+
+// One k-step of wave W's blocks (of its part P): frag(r) gives the fragment of block
+// row r, mma(row, col, acc) one matrix instruction.
+template <int W, int P, class Frag, class Mma>
 __device__ __forceinline__ void lp16_sb_step(Frag frag, Mma mma, f4 (&acc)[20]) {
   if constexpr (W < 6) {
     constexpr int I = kSbI[W], J = kSbJ[W];
@@ -162,20 +166,17 @@ __device__ __forceinline__ void lp16_sb_step(Frag frag, Mma mma, f4 (&acc)[20]) 
 #pragma unroll
       for (int b = 0; b < 4; ++b) acc[4 * a + b] = mma(rf[a], cf[b], acc[4 * a + b]);
   } else {
+    constexpr int d = lp16_sb_row(W, 10 * P);
+    decltype(frag(0)) f[4];
 #pragma unroll
-    for (int di = 0; di < 2; ++di) {
-      const int d = di == 0 ? (W == 6 ? 0 : 1) : (W == 6 ? 3 : 2);
-      decltype(frag(0)) f[4];
+    for (int a = 0; a < 4; ++a) f[a] = frag(4 * d + a);
 #pragma unroll
-      for (int a = 0; a < 4; ++a) f[a] = frag(4 * d + a);
+    for (int r = 0; r < 4; ++r)
 #pragma unroll
-      for (int r = 0; r < 4; ++r)
-#pragma unroll
-        for (int c = 0; c <= r; ++c) {
-          const int i = 10 * di + r * (r + 1) / 2 + c;
-          acc[i] = mma(f[r], f[c], acc[i]);
-        }
-    }
+      for (int c = 0; c <= r; ++c) {
+        const int i = 10 * P + r * (r + 1) / 2 + c;
+        acc[i] = mma(f[r], f[c], acc[i]);
+      }
   }
 }
 
@@ -183,13 +184,14 @@ template <int FMT, int W>
 __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t ld,
                                           int64_t k_begin, int64_t k_end, const int32_t* idx,
                                           int m, const double* __restrict__ u,
-                                          double* __restrict__ part, uint8_t* lds) {
+                                          double* __restrict__ part, uint8_t* t0, uint8_t* t1) {
   using C = LD16<FMT>;
   typedef __attribute__((address_space(3))) void* lds_vptr;
   typedef __attribute__((address_space(1))) const void* glb_vptr;
   const int tid = threadIdx.x;
   const int lane = tid & 63;
   const int ntiles = (int)((k_end - k_begin + C::KT - 1) / C::KT);
+  const int nfull = (int)((k_end - k_begin) / C::KT);
 
   // DMA instruction i of this wave fills tile bytes (8 W + i) KiB + 16 lane:
   // row 4 (8 W + i) + lane / 16, position lane % 16, chunk (lane % 16) ^ (row % 16).
@@ -209,34 +211,37 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   // (EPC / 2) c + q of the segment (the q-th pair of u values of chunk c), so
   // the Y u threads of the sixteen chunks read a piece from consecutive slots.
   auto upiece = [](int slot) { return (C::EPC / 2) * (slot & 15) + (slot >> 4); };
-  // A tile inside the slab is all DMA; the last tile of a slab that ends
-  // inside a tile is filled by ordinary loads (zeros past the end).
-  auto issue = [&](int t, int slot) {
+  // A tile inside the slab is all DMA (rows that no block of this m reads are left
+  // out); the last tile of a slab that ends inside a tile is filled by ordinary loads
+  // (zeros past the end).
+  const bool rows_on = 8 * C::DMA_PER_WAVE / 2 * W < (m + 63) / 64 * 64;
+  auto issue = [&](int t, uint8_t* T) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
-    uint8_t* T = lds + slot * C::BUF;
-    if (k0 + C::KT <= k_end) {
+    if (rows_on) {
 #pragma unroll
       for (int i = 0; i < C::DMA_PER_WAVE; ++i)
         __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + k0 * C::ES + cof[i]),
                                          (lds_vptr)(T + (C::DMA_PER_WAVE * W + i) * 1024), 16,
                                          0, 0);
-      if (want_u && W == 7) {   // the tile's u segment after the rows, pieces transposed
+    }
+    if (want_u && W == 7) {   // the tile's u segment after the rows, pieces transposed
 #pragma unroll
-        for (int j = 0; j < C::UDMA; ++j) {
-          uint8_t* dst = T + C::TILE + j * 1024;
-          const int64_t ku = k0 + 2 * upiece(64 * j + lane);
-          if (u_dma) {
-            __builtin_amdgcn_global_load_lds((glb_vptr)(ug + ku), (lds_vptr)dst, 16, 0, 0);
-          } else {
-            double2 v;
-            v.x = ug[ku];
-            v.y = ug[ku + 1];
-            *reinterpret_cast<double2*>(dst + 16 * lane) = v;
-          }
+      for (int j = 0; j < C::UDMA; ++j) {
+        uint8_t* dst = T + C::TILE + j * 1024;
+        const int64_t ku = k0 + 2 * upiece(64 * j + lane);
+        if (u_dma) {
+          __builtin_amdgcn_global_load_lds((glb_vptr)(ug + ku), (lds_vptr)dst, 16, 0, 0);
+        } else {
+          double2 v;
+          v.x = ug[ku];
+          v.y = ug[ku + 1];
+          *reinterpret_cast<double2*>(dst + 16 * lane) = v;
         }
       }
-      return;
     }
+  };
+  auto fill = [&](int t, uint8_t* T) {
+    const int64_t k0 = k_begin + (int64_t)t * C::KT;
     if (k_end >= C::EPC) {
 #pragma unroll
       for (int i0 = 0; i0 < C::DMA_PER_WAVE; i0 += 4) {   // four loads in flight
@@ -298,31 +303,32 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
 #pragma unroll
   for (int j = 0; j < 16; ++j) yu[j] = 0.0;
 
-  issue(0, 0);
-  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
-  __syncthreads();
-  for (int t = 0; t < ntiles; ++t) {
-    if (t + 1 < ntiles) issue(t + 1, (t + 1) & 1);
-    const uint8_t* tile = lds + (t & 1) * C::BUF;
-    // 4 windows (BF16, K = 32) or 2 halves (FP8, K = 128) per tile
+  auto compute = [&](const uint8_t* tile) {
+    // 4 windows (BF16, K = 32) or 2 halves (FP8, K = 128) per tile; super-blocks whose
+    // rows are all past m are left out
+    auto blocks = [&](auto P) {
+      if (64 * lp16_sb_row(W, 10 * P) >= m) return;
 #pragma unroll
-    for (int h = 0; h < (FMT == CABCD_BF16 ? 4 : 2); ++h) {
-      if constexpr (FMT == CABCD_BF16) {
-        const uint8_t* base = tile + lane_off[h];
-        lp16_sb_step<W>([&](int r) {
-          return *reinterpret_cast<const uint4*>(base + r * 16 * C::RB);
-        }, [](const uint4& x, const uint4& y, f4 c) { return lp_mma_bf16(x, y, c); }, acc);
-      } else {
-        const uint8_t* b0 = tile + lane_off[2 * h];
-        const uint8_t* b1 = tile + lane_off[2 * h + 1];
-        lp16_sb_step<W>([&](int r) {   // 32 codes of row r: two 16-byte chunks
-          const uint4 x = *reinterpret_cast<const uint4*>(b0 + r * 16 * C::RB);
-          const uint4 y = *reinterpret_cast<const uint4*>(b1 + r * 16 * C::RB);
-          return lp_i8v{(int)x.x, (int)x.y, (int)x.z, (int)x.w, (int)y.x, (int)y.y, (int)y.z,
-                        (int)y.w};
-        }, [](const lp_i8v& x, const lp_i8v& y, f4 c) { return lp_mma_k128(x, y, c); }, acc);
+      for (int h = 0; h < (FMT == CABCD_BF16 ? 4 : 2); ++h) {
+        if constexpr (FMT == CABCD_BF16) {
+          const uint8_t* base = tile + lane_off[h];
+          lp16_sb_step<W, P>([&](int r) {
+            return *reinterpret_cast<const uint4*>(base + r * 16 * C::RB);
+          }, [](const uint4& x, const uint4& y, f4 c) { return lp_mma_bf16(x, y, c); }, acc);
+        } else {
+          const uint8_t* b0 = tile + lane_off[2 * h];
+          const uint8_t* b1 = tile + lane_off[2 * h + 1];
+          lp16_sb_step<W, P>([&](int r) {   // 32 codes of row r: two 16-byte chunks
+            const uint4 x = *reinterpret_cast<const uint4*>(b0 + r * 16 * C::RB);
+            const uint4 y = *reinterpret_cast<const uint4*>(b1 + r * 16 * C::RB);
+            return lp_i8v{(int)x.x, (int)x.y, (int)x.z, (int)x.w, (int)y.x, (int)y.y, (int)y.z,
+                          (int)y.w};
+          }, [](const lp_i8v& x, const lp_i8v& y, f4 c) { return lp_mma_k128(x, y, c); }, acc);
+        }
       }
-    }
+    };
+    blocks(std::integral_constant<int, 0>{});
+    if constexpr (W >= 6) blocks(std::integral_constant<int, 1>{});
     if (want_u) {
       // the 16-byte pieces of chunk yc sit 256 bytes apart, so the sixteen
       // chunks' reads of one piece fall in distinct banks
@@ -335,17 +341,39 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
         ub[2 * q + 1] = v.y;
       }
 #pragma unroll
-      for (int j = 0; j < YJ; ++j) {
-        const int r = yr0 + 16 * j;
-        const uint4 v = *reinterpret_cast<const uint4*>(tile + r * C::RB + 16 * (yc ^ (r & 15)));
-        double dv[C::EPC];
-        lp_decode_all<FMT>(v, dv);
+      for (int j0 = 0; j0 < YJ; j0 += 4) {
+        if (16 * j0 >= m) break;
 #pragma unroll
-        for (int e = 0; e < C::EPC; ++e) yu[j] = fma(dv[e], ub[e], yu[j]);
+        for (int j = j0; j < j0 + 4; ++j) {
+          const int r = yr0 + 16 * j;
+          const uint4 v =
+              *reinterpret_cast<const uint4*>(tile + r * C::RB + 16 * (yc ^ (r & 15)));
+          double dv[C::EPC];
+          lp_decode_all<FMT>(v, dv);
+#pragma unroll
+          for (int e = 0; e < C::EPC; ++e) yu[j] = fma(dv[e], ub[e], yu[j]);
+        }
       }
     }
+  };
+  auto step = [&](int t, const uint8_t* tile, uint8_t* next) {
+    if (t + 1 < nfull)
+      issue(t + 1, next);
+    else if (t + 1 < ntiles)
+      fill(t + 1, next);
+    compute(tile);
     __builtin_amdgcn_s_waitcnt(0);   // tile t + 1 is in LDS
     __syncthreads();
+  };
+  if (nfull > 0)
+    issue(0, t0);
+  else
+    fill(0, t0);
+  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
+  __syncthreads();
+  for (int t = 0; t < ntiles; t += 2) {
+    step(t, t0, t1);
+    if (t + 1 < ntiles) step(t + 1, t1, t0);
   }
 
   // partial blocks as FP32 (what the accumulators hold; half the bytes of
@@ -354,6 +382,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   const gptr<float> pf = (gptr<float>)pg;
 #pragma unroll
   for (int a = 0; a < lp16_sb_nacc(W); ++a) {
+    if (64 * lp16_sb_row(W, a) >= m) continue;
     gptr<float> dst = pf + lp16_sb_block(W, a) * 256 + lane;
     dst[0] = acc[a][0];
     dst[64] = acc[a][1];
@@ -361,7 +390,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
     dst[192] = acc[a][3];
   }
   if (want_u) {   // the sixteen chunk sums of each row, in chunk order
-    double* ys = reinterpret_cast<double*>(lds);
+    double* ys = reinterpret_cast<double*>(t0);
 #pragma unroll
     for (int j = 0; j < YJ; ++j) ys[(yr0 + 16 * j) * 16 + yc] = yu[j];
     __syncthreads();
@@ -380,21 +409,22 @@ __global__ __launch_bounds__(kLpThreads) void gram_lp_dma16_kernel(
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
     int64_t pstride) {
   using C = LD16<FMT>;
-  extern __shared__ __attribute__((aligned(16))) uint8_t dyn_lds[];
+  // (arrays of their own: the reads of one must not wait for the DMA into the other)
+  __shared__ __attribute__((aligned(16))) uint8_t t0[C::BUF], t1[C::BUF];
   idx += (int64_t)blockIdx.y * m;            // several outer steps per launch
   partials += (int64_t)blockIdx.y * pstride;
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   double* part = partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP);
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: lp16_slab<FMT, 0>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 1: lp16_slab<FMT, 1>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 2: lp16_slab<FMT, 2>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 3: lp16_slab<FMT, 3>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 4: lp16_slab<FMT, 4>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 5: lp16_slab<FMT, 5>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    case 6: lp16_slab<FMT, 6>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
-    default: lp16_slab<FMT, 7>(A, ld, k_begin, k_end, idx, m, u, part, dyn_lds); break;
+    case 0: lp16_slab<FMT, 0>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 1: lp16_slab<FMT, 1>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 2: lp16_slab<FMT, 2>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 3: lp16_slab<FMT, 3>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 4: lp16_slab<FMT, 4>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 5: lp16_slab<FMT, 5>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 6: lp16_slab<FMT, 6>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    default: lp16_slab<FMT, 7>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
   }
 }
 
@@ -402,17 +432,9 @@ template <int FMT>
 hipError_t launch_lp_dma16(const GramPlan& p, const void* A, int64_t ld, int64_t cols,
                            const int32_t* idx, int m, int nsteps, const double* u,
                            double* partials, hipStream_t st) {
-  using C = LD16<FMT>;
-  static bool attr_set = false;
-  if (!attr_set) {
-    hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(gram_lp_dma16_kernel<FMT>),
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, C::LDS);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
   hipLaunchKernelGGL((gram_lp_dma16_kernel<FMT>), dim3((unsigned)p.nsplit, (unsigned)nsteps),
-                     dim3(kLpThreads), C::LDS, st, static_cast<const uint8_t*>(A), ld, cols, idx,
-                     m, u, p.chunk, partials, (int64_t)gram_partial_doubles(p));
+                     dim3(kLpThreads), 0, st, static_cast<const uint8_t*>(A), ld, cols, idx, m, u,
+                     p.chunk, partials, (int64_t)gram_partial_doubles(p));
   return hipGetLastError();
 }
 
