@@ -160,7 +160,8 @@ typedef struct cabcd_opts {
                                 /* triangles (or diagonal blocks) of Grams        */
                                 /* computed ahead; a dense step of such a Gram    */
                                 /* (b <= 16) is one launch, counted here, with    */
-                                /* its companion update and the next step's Y u   */
+                                /* its companion update and the next step's Y u,  */
+                                /* or, with short rows, part of a run's launch    */
 #define CABCD_PHASE_UPDATE 4    /* companion update with Y^T delta (counted only   */
                                 /* when launched: not when it is left to the next */
                                 /* step's Gram or made moot by the exact          */

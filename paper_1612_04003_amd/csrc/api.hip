@@ -967,6 +967,9 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   // Dense chains: P[par] and xg[par] hold the partial Y u of the coming step and
   // x at its indices while have_dots.
   const ChainSlabs slabs = chain && !M.csr ? chain_slabs(M.dtype, s * b, cols) : ChainSlabs{};
+  // FP64 steps small enough for one workgroup: whole runs of them in one launch
+  const int solo =
+      chain && !M.csr && !M.lowp() ? chain_solo_lc(s * b, cols, ah.chain.nsb) : -1;
   int par = 0;
   bool have_dots = false;
   ChainStep cs{};
@@ -1059,11 +1062,51 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
       HIP_TRY(
           mat_gram(M, idx, m, comp, scale, shift, true, B.G[0], B.Yu, B.partials[0], st, &timer));
     }
-    const bool fresh_next = o.resid_every > 0 && (k + 1) % o.resid_every == 0;
+    bool fresh_next = o.resid_every > 0 && (k + 1) % o.resid_every == 0;
     const double* tri =
         from_ahead && chain ? B.tri[cur] + (size_t)(gslot - 1) * ah.chain.tri : nullptr;
     const int* link = from_ahead && chain ? B.link[cur] + (size_t)(gslot - 1) * m : nullptr;
-    if (from_ahead && chain && !M.csr) {
+    if (from_ahead && solo >= 0) {
+      // as many steps of the batch as nothing looks in on
+      int run = 1;
+      auto stops = [&](int64_t k1) {   // something reads the companion after step k1
+        return (o.resid_every > 0 && k1 % o.resid_every == 0) ||
+               (o.monitor_every > 0 && k1 % o.monitor_every == 0 && slot < o.trace_len) ||
+               (checks && k1 % o.check_every == 0);
+      };
+      while (ahead > 0 && !stops(k + run)) {
+        ++run;
+        ++gslot;
+        --ahead;
+      }
+      h += (int64_t)(run - 1) * s;
+      k += run - 1;
+      fresh_next = o.resid_every > 0 && (k + 1) % o.resid_every == 0;
+      ChainSolo so{};
+      so.A = M.X;
+      so.ld = M.ld;
+      so.cols = cols;
+      so.m = m;
+      so.b = b;
+      so.gb = ah.chain.gb;
+      so.nsb = ah.chain.nsb;
+      so.steps = run;
+      so.lc = solo;
+      so.idx = idx;
+      so.tri = tri;
+      so.tri_stride = (int64_t)ah.chain.tri;
+      so.link = link;
+      so.u = comp;
+      so.x = coord;
+      so.y = y;
+      so.mode = dual ? 1 : 0;
+      so.last_upd = fresh_next ? 0 : 1;   // an exact recomputation would overwrite the update
+      so.lambda = lambda;
+      so.n = n;
+      so.gamma = gamma;
+      so.status = B.status;
+      HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] { return launch_chain_solo(so, st); }));
+    } else if (from_ahead && chain && !M.csr) {
       cs.ix = idx;
       cs.idx = idx;
       cs.tri = tri;

@@ -724,6 +724,247 @@ __global__ __launch_bounds__(kStepThreads, TALL ? 2 : 4) void chain_step_kernel(
   }
 }
 
+// ------------------------------------------------------------- few and short rows
+// Runs of steps in one launch by one workgroup, where a step's rows fit its registers
+// (32 elements a thread: 128 KiB) and T^-1 has at most a row of superblocks a wave.  The
+// companion stays in LDS and a thread holds its elements of the step's rows from the
+// products with u to the update; the next step's come from the L2 after that.  What
+// bounds a step is one chain of latencies (rows, sums over the wave and the workgroup,
+// T^-1 c, the sums of the update) and, towards 128 KiB, the 50 GB/s or so that a CU
+// reads.  A launch a step also waits for its own start and for the other XCDs' partial
+// sums.  Marginal time of a step, launches -> here (us): dense dual b s = 32, d = 64:
+// 8.1 -> 3.8; 64, 128: 9.2 -> 5.3; 32, 512: 8.4 -> 6.7; 64, 256: 9.2 -> 7.2; primal d =
+// 64, n = 256, b s = 32: 8.3 -> 4.9.  With 64 elements a thread (256 KiB) 32, 1024 was 8.4
+// -> 8.4 and 64, 512 9.5 -> 10.7, so the line is at half of that; rows asked for a step
+// ahead into registers of their own gained nothing.
+//
+// Column c + LC j (c = thread % LC) and row rg + RG q (rg = thread / LC, RG = 512 / LC)
+// is slot q CJ + j; LC is a power of two from 64 on, CJ = columns / LC, so a wave's 64
+// lanes lie in one row.
+constexpr int kSoloThreads = 512;
+constexpr int kSoloSlots = 32;                 // elements a thread holds
+constexpr int kSoloSuper = 8;                  // superblocks of T^-1, at most: one a wave
+// Columns a thread holds of a row: a power of two.
+int solo_cj(int64_t cols) {
+  int cj = 1;
+  while (cj * kSoloThreads < cols) cj *= 2;
+  return cj;
+}
+
+typedef unsigned int u32x2 __attribute__((ext_vector_type(2)));
+template <bool HALF32>   // swaps halves of 32 lanes, or neighbouring rows of 16
+__device__ __forceinline__ double swap_add(double a, double b) {
+  const unsigned alo = __double2loint(a), ahi = __double2hiint(a);
+  const unsigned blo = __double2loint(b), bhi = __double2hiint(b);
+  u32x2 lo, hi;
+  if constexpr (HALF32) {
+    const auto l = __builtin_amdgcn_permlane32_swap(alo, blo, false, false);
+    const auto h = __builtin_amdgcn_permlane32_swap(ahi, bhi, false, false);
+    lo = u32x2{l[0], l[1]};
+    hi = u32x2{h[0], h[1]};
+  } else {
+    const auto l = __builtin_amdgcn_permlane16_swap(alo, blo, false, false);
+    const auto h = __builtin_amdgcn_permlane16_swap(ahi, bhi, false, false);
+    lo = u32x2{l[0], l[1]};
+    hi = u32x2{h[0], h[1]};
+  }
+  return __hiloint2double((int)hi[0], (int)lo[0]) + __hiloint2double((int)hi[1], (int)lo[1]);
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double x) {
+  const int lo = __builtin_amdgcn_update_dpp(0, __double2loint(x), CTRL, 0xF, 0xF, false);
+  const int hi = __builtin_amdgcn_update_dpp(0, __double2hiint(x), CTRL, 0xF, 0xF, false);
+  return __hiloint2double(hi, lo);
+}
+// The sums over a wave of its lanes' sixteen values; lane l gets that of value l / 4.
+// Every exchange halves the values a lane holds, so sixteen sums take 15 + 2 additions.
+__device__ __forceinline__ double wave_sums16(double (&v)[16], int lane) {
+  double a[8], b[4];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) a[i] = swap_add<true>(v[i], v[i + 8]);
+#pragma unroll
+  for (int i = 0; i < 4; ++i) b[i] = swap_add<false>(a[i], a[i + 4]);
+  const bool b3 = (lane & 8) != 0, b2 = (lane & 4) != 0;
+  const double c0 = (b3 ? b[2] : b[0]) + dpp<0x128>(b3 ? b[0] : b[2]);   // row_ror:8
+  const double c1 = (b3 ? b[3] : b[1]) + dpp<0x128>(b3 ? b[1] : b[3]);
+  double d = (b2 ? c1 : c0) + dpp<0x141>(b2 ? c0 : c1);                  // row_half_mirror
+  d += dpp<0xB1>(d);   // the four lanes of a quad
+  d += dpp<0x4E>(d);
+  return d;
+}
+
+template <int CJ>
+__global__ __launch_bounds__(kSoloThreads) void chain_solo_kernel(ChainSolo a,
+                                                                 const int32_t* __restrict__ idx) {
+  constexpr int QN = kSoloSlots / CJ;   // rows a thread holds
+  extern __shared__ __attribute__((aligned(16))) double sm[];
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int m = a.m, cols = (int)a.cols, LC = 1 << a.lc, RG = kSoloThreads >> a.lc;
+  const int cp = tid & (LC - 1), rg = __builtin_amdgcn_readfirstlane(tid >> a.lc);
+  const int W = LC / 64, wq = wave & (W - 1);   // waves side by side in a row
+  double* c = sm;                               // kMaxSuper * 16
+  double* dl = c + kMaxSuper * 16;              // kMaxRows
+  double* red = dl + kMaxRows;                  // kSoloThreads CJ, at least W m
+  double* us = red + kSoloThreads * CJ;         // LC CJ
+  const bool owner = wave * 64 < m;             // holds rows of x
+
+  const gptr<const double> A = glb(a.A);
+  double x[kSoloSlots];                         // the step's rows
+  // (opaque: keeps the places of a step's rows out of the registers between steps)
+  auto first_row = [&] {
+    int r = rg;
+    asm volatile("" : "+s"(r));
+    return r;
+  };
+  // lane q holds the index of the wave's row q, a step ahead of its rows
+  auto load_index = [&](int step) {
+    return glb(idx)[(int64_t)min(step, a.steps - 1) * m + min(rg + lane * RG, m - 1)];
+  };
+  // eight rows at a time (spares registers), as far as there are rows
+  constexpr int B = QN < 8 ? QN : 8;
+  auto load_rows = [&](int ix) {
+    gdev::static_for<0, QN / B>([&](auto g) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (B * g * RG < m) {
+#pragma unroll
+        for (int q = B * g; q < B * g + B; ++q) {
+          const gptr<const double> row = A + (int64_t)__builtin_amdgcn_readlane(ix, q) * a.ld;
+#pragma unroll
+          for (int j = 0; j < CJ; ++j) x[q * CJ + j] = row[min(cp + j * LC, cols - 1)];
+        }
+      }
+    });
+  };
+#pragma unroll
+  for (int q = 0; q < kSoloSlots; ++q) x[q] = 0.0;
+  load_rows(load_index(0));
+  int nidx = load_index(1);
+  c[tid] = 0.0;
+  for (int k = tid; k < LC * CJ; k += kSoloThreads) us[k] = k < cols ? glb(a.u)[k] : 0.0;
+  const int sb = (tid * a.gbm) >> 16;           // tid / gb
+  const int cat = 16 * sb + tid - sb * a.gb;
+  const int diag = diag_mask(a.bm, lane);
+  __syncthreads();
+
+  for (int step = 0; step < a.steps; ++step) {
+    const int32_t* ix = idx + (int64_t)step * m;
+    const gptr<const double> T = glb(a.tri) + step * a.tri_stride;
+    double xi = 0.0;
+    if (tid < m) {   // (the dual's right-hand side takes x + y)
+      const int i = ix[tid];
+      xi = a.mode != 0 ? glb(a.x)[i] + glb(a.y)[i] : glb(a.x)[i];
+    }
+    // this wave's row of superblocks of T^-1
+    double tr[kSoloSuper][4];
+    const int I = min(wave, a.nsb - 1);
+#pragma unroll
+    for (int J = 0; J < kSoloSuper; ++J)
+      tri_load(T + (int64_t)tri_block(I, min(J, I)) * 256, lane, tr[J]);
+    // ---- Y u
+    {
+      double ul[CJ];
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) ul[j] = us[cp + j * LC];
+      constexpr int G = QN < 16 ? QN : 16;
+      gdev::static_for<0, QN / G>([&](auto g) {
+        constexpr int q0 = g * G;
+        __builtin_amdgcn_sched_barrier(0);
+        if (q0 * RG < m) {   // uniform
+          double t[16];
+#pragma unroll
+          for (int q = 0; q < 16; ++q) {
+            t[q] = 0.0;
+            if (q < G) {
+#pragma unroll
+              for (int j = 0; j < CJ; ++j) t[q] = fma(x[(q0 + q) * CJ + j], ul[j], t[q]);
+            }
+          }
+          const double s = wave_sums16(t, lane);
+          const int p = rg + (q0 + (lane >> 2)) * RG;
+          if ((lane & 3) == 0 && (lane >> 2) < G && p < m) red[wq * m + p] = s;
+        }
+      });
+    }
+    lds_barrier();
+    if (tid < m) {
+      double v[8], s = 0.0;
+#pragma unroll
+      for (int w = 0; w < 8; ++w) v[w] = red[min(w, W - 1) * m + tid];
+#pragma unroll
+      for (int w = 0; w < 8; ++w) s += w < W ? v[w] : 0.0;
+      c[cat] = rhs_of(a.mode, a.lambda, a.n, s, xi, 0.0);
+    }
+    lds_barrier();
+    // ---- delta = T^-1 c
+    if (wave < a.nsb) {
+      double acc[4] = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+      for (int J = 0; J < kSoloSuper; ++J)
+        if (J <= I) tri_fma(tr[J], c[J * 16 + (lane & 15)], J == I, diag, acc);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const double s = d16_row_sum(acc[i]);
+        const int row = 4 * i + (lane >> 4);
+        if ((lane & 15) == 0 && row < a.gb && I * a.gb + row < m) dl[I * a.gb + row] = s;
+      }
+    }
+    lds_barrier();
+    // ---- u += gamma Y^T delta
+    if (step + 1 < a.steps || a.last_upd) {
+      double acc[CJ];
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) acc[j] = 0.0;
+      const int r0 = first_row();
+      gdev::static_for<0, QN / B>([&](auto g) {
+        __builtin_amdgcn_sched_barrier(0);
+        if (B * g * RG < m) {
+#pragma unroll
+          for (int q = B * g; q < B * g + B; ++q) {
+            const int p = r0 + q * RG;
+            const double d = dl[min(p, m - 1)];
+#pragma unroll
+            for (int j = 0; j < CJ; ++j) acc[j] = p < m ? fma(x[q * CJ + j], d, acc[j]) : acc[j];
+          }
+        }
+      });
+#pragma unroll
+      for (int j = 0; j < CJ; ++j) {
+        if (RG > 1)
+          red[rg * LC + cp] = acc[j];   // (CJ = 1)
+        else if (cp + j * LC < cols)   // (u stays 0 past the last column)
+          us[cp + j * LC] += a.gamma * acc[j];
+      }
+    }
+    // ---- x[idx] += delta: one writer per coordinate
+    if (tid < m) {
+      if (!isfinite(dl[tid])) raise_status(a.status, DEV_NONFINITE);
+      cdev::scatter_delta<kSoloThreads>(ix, a.link + (int64_t)step * m, dl, m, a.x);
+    }
+    if (owner) __builtin_amdgcn_s_waitcnt(0);   // x is read again after the barrier
+    asm volatile("" ::: "memory");
+    lds_barrier();
+    asm volatile("" ::: "memory");
+    load_rows(nidx);
+    nidx = load_index(step + 2);
+    if (RG > 1 && (step + 1 < a.steps || a.last_upd)) {
+      if (tid < cols) {
+        double v[8], s = 0.0;
+#pragma unroll
+        for (int g = 0; g < 8; ++g) v[g] = red[min(g, RG - 1) * LC + tid];
+#pragma unroll
+        for (int g = 0; g < 8; ++g) s += g < RG ? v[g] : 0.0;
+        us[tid] += a.gamma * s;
+      }
+      lds_barrier();
+    }
+  }
+  if (a.steps > 1 || a.last_upd) {
+    __syncthreads();
+    for (int k = tid; k < cols; k += kSoloThreads) glb(a.u)[k] = us[k];
+  }
+}
+
 }  // namespace
 
 ChainPlan chain_plan(int m, int b) {
@@ -811,6 +1052,44 @@ hipError_t launch_chain_step(int dtype, const ChainStep& step, hipStream_t st) {
   }
   hipLaunchKernelGGL(kern, dim3(grid), dim3(kStepThreads), lds, st, a);
   return hipGetLastError();
+}
+
+// Column lanes (log2) of chain_solo_kernel for m rows of cols FP64 columns with nsb
+// superblocks, or -1 where a launch a step is the way (see there).
+int chain_solo_lc(int m, int64_t cols, int nsb) {
+  if (nsb > kSoloSuper || cols > 8 * kSoloThreads) return -1;
+  int lc = 6;
+  while ((1 << lc) < cols && lc < 9) ++lc;
+  const int64_t cj = solo_cj(cols);
+  return cj * ((m + (kSoloThreads >> lc) - 1) / (kSoloThreads >> lc)) <= kSoloSlots ? lc : -1;
+}
+
+hipError_t launch_chain_solo(const ChainSolo& args, hipStream_t st) {
+  ChainSolo a = args;
+  if (a.steps < 1 || chain_solo_lc(a.m, a.cols, a.nsb) != a.lc || a.lc < 0)
+    return hipErrorInvalidValue;
+  a.bm = block_mul(a.b);
+  a.gbm = (65535 + a.gb) / a.gb;
+  const int cj = solo_cj(a.cols);
+  const size_t lds = sizeof(double) *
+                     (kMaxSuper * 16 + kMaxRows + (size_t)kSoloThreads * cj + ((size_t)cj << a.lc));
+  auto go = [&](auto kernel) -> hipError_t {
+    if (lds > 64 * 1024) {
+      const hipError_t e = hipFuncSetAttribute(reinterpret_cast<const void*>(kernel),
+                                               hipFuncAttributeMaxDynamicSharedMemorySize,
+                                               (int)lds);
+      if (e != hipSuccess) return e;
+    }
+    hipLaunchKernelGGL(kernel, dim3(1), dim3(kSoloThreads), lds, st, a, a.idx);
+    return hipGetLastError();
+  };
+  switch (cj) {
+    case 1: return go(chain_solo_kernel<1>);
+    case 2: return go(chain_solo_kernel<2>);
+    case 4: return go(chain_solo_kernel<4>);
+    case 8: return go(chain_solo_kernel<8>);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 }  // namespace cabcd

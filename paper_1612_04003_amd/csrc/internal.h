@@ -290,6 +290,27 @@ struct ChainStep {
   int* status;
 };
 hipError_t launch_chain_step(int dtype, const ChainStep& a, hipStream_t st);
+// `steps` chain steps of FP64 rows in one launch by one workgroup, from step 0's rows
+// idx; step k's rows are idx + k m, its inverse tri + k tri_stride, its links link + k m.
+// The last step leaves u as it is unless last_upd.
+struct ChainSolo {
+  const double* A;
+  int64_t ld, cols;
+  int m, b, gb, nsb, steps, lc;
+  int bm, gbm;        // set by the launcher
+  const int32_t* idx;
+  const double* tri;
+  int64_t tri_stride;
+  const int* link;
+  double* u;
+  double* x;
+  const double* y;    // dual only
+  int mode, last_upd;
+  double lambda, n, gamma;
+  int* status;
+};
+int chain_solo_lc(int m, int64_t cols, int nsb);
+hipError_t launch_chain_solo(const ChainSolo& a, hipStream_t st);
 // x[idx] += delta of a chain step, done by one more workgroup of a companion
 // update's launch (x NULL: none).
 struct XScatter {

@@ -143,3 +143,30 @@ def test_csr_chain_matches_oracle(gpu_lib, b, s):
     ao, wo = bcd.dual_bcd(S.T.tocsc(), y, 1e-2, b, s, H, 7)
     assert _rel(a.cpu(), ao) <= 1e-10
     assert _rel(w.cpu(), wo) <= 1e-10
+
+
+# one workgroup for runs of steps: one column lane to eight columns a lane, as many rows
+# as its registers hold and one less, one to eight superblocks
+@pytest.mark.parametrize("d,b,s", [(1, 1, 1), (63, 8, 16), (64, 1, 127), (65, 16, 8), (128, 4, 32),
+                                   (129, 7, 9), (257, 16, 2), (512, 8, 4), (513, 4, 4),
+                                   (1024, 5, 3), (1025, 8, 1), (2048, 2, 4), (2049, 2, 2),
+                                   (4096, 1, 4)])
+def test_dual_short_steps_in_one_workgroup(gpu_lib, d, b, s):
+    """Against the oracle, and the same bits when the run is split, monitored
+    steps and exact recomputations in between; rows on odd 8-byte boundaries."""
+    n = max(50, b)            # repeated coordinates from step to step
+    H = 23 * s + s // 2
+    _say("short dual steps", d, b, s)
+    X, y, _ = synth.gaussian_ridge(d, n, d + b + s)
+    buf = torch.full((1 + n * (d + 1),), float("nan"), dtype=torch.float64, device=DEV)
+    A = buf[1:].view(n, d + 1)[:, :d]
+    A.copy_(X.t())
+    a, w = gpu_lib.dual_bcd(A, y.to(DEV), 1e-2, b, s, H, 6, resid_every=7)
+    ao, wo = bcd.dual_bcd(X.numpy(), y.numpy(), 1e-2, b, s, H, 6)
+    assert _rel(a.cpu(), ao) <= 1e-10
+    assert _rel(w.cpu(), wo) <= 1e-10
+    a1, w1 = gpu_lib.dual_bcd(A, y.to(DEV), 1e-2, b, s, H, 6)
+    a2, w2 = gpu_lib.dual_bcd(A, y.to(DEV), 1e-2, b, s, 9 * s, 6)
+    a2, w2 = gpu_lib.dual_bcd(A, y.to(DEV), 1e-2, b, s, H - 9 * s, 6, alpha=a2, w=w2,
+                              h0=9 * s, flags=gpu_lib.FLAG_STATE_VALID)
+    assert torch.equal(a1, a2) and torch.equal(w1, w2)
