@@ -472,7 +472,7 @@ hipError_t launch_lp_fmt(const GramPlan& p, const void* A, int64_t ld, int64_t c
 //
 // Each lane owns 16 bytes of codes per row (EPC columns).  The rows are split
 // over the RS waves of a column group (ranges added in order through LDS) and,
-// where even sixteen waves leave CUs idle, over blockIdx.y (partial sums to
+// where those leave CUs idle, over blockIdx.y (partial sums to
 // scratch, added in order by a second launch); deterministic.  lv_split picks
 // both: the pass streams from about 2048 waves on (FP8 over 2^20 columns, 4.3 GB:
 // one wave a column group 3.6 TB/s, two 6.0, four 4.7; BF16 has two waves a SIMD
@@ -615,19 +615,29 @@ __global__ __launch_bounds__(256) void gemv_t_lp_combine_kernel(LvArgs g, int gr
   g.out[k] = b0 + g.gamma * s;
 }
 
-// The row split of a pass over m rows: rs waves a column group (a power of
-// two), of at least eight rows each, and groups of rows over the grid.
+// The row split of a pass over m rows: rs waves a column group (a power of two), of at
+// least eight rows each, and groups of rows over the grid, whose second launch costs
+// about 4 us and its sums.  A pass of kLvLong bytes or more takes up to four waves and
+// groups from there on: small workgroups fill the CUs evenly, where eight or sixteen
+// waves made 1.1 or 0.8 workgroups a CU (calls, us: 2000 x 300001 FP8 156 -> 138, 8192 x
+// 65536 FP8 234 -> 116, 16384 x 30000 FP8 150 -> 104, 4096 x 100003 BF16 191 -> 169; 1024 x
+// 500000 FP8, four waves 102, in two groups 115).  130 x 300001 FP8: eight waves 31.9, four
+// in two groups 33.1.
+constexpr int64_t kLvLong = 128 << 20;
 struct LvSplit {
   int rs, groups;
 };
 LvSplit lv_split(int dtype, int64_t m, int64_t cols) {
   const int epc = dtype == CABCD_BF16 ? 8 : 16;
   const int64_t cw = (cols + 64 * epc - 1) / (64 * epc);   // waves side by side
+  const bool lng = m * cols * (16 / epc) >= kLvLong;
+  const int rs_max = lng ? 4 : 16;
   LvSplit s{1, 1};
-  while (s.rs < 16 && cw * s.rs < 2048 && m >= 16 * s.rs) s.rs *= 2;
-  // (a second launch costs about 4 us: only where it halves a pass or more)
-  if (s.rs == 16 && cw * s.rs < 1024)
-    s.groups = (int)std::max<int64_t>(1, std::min(2048 / (cw * s.rs), m / (16 * s.rs)));
+  while (s.rs < rs_max && cw * s.rs < 2048 && m >= 16 * s.rs) s.rs *= 2;
+  const int64_t waves = cw * s.rs;
+  if (s.rs == rs_max && waves < (lng ? 1500 : 1024))
+    s.groups = (int)std::max<int64_t>(
+        1, std::min(lng ? (2048 + waves - 1) / waves : 2048 / waves, m / (16 * s.rs)));
   return s;
 }
 

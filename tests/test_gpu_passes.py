@@ -15,7 +15,8 @@ U = 2.0 ** -53
 # ragged last chunks and single columns
 @pytest.mark.parametrize("rows,cols", [(1, 1), (5, 100), (17, 515), (40, 1000), (64, 33001),
                                        (130, 300001), (300, 70001), (513, 600), (5000, 31),
-                                       (4187, 618), (2001, 20001)])
+                                       (4187, 618), (2001, 20001), (1025, 140001),
+                                       (2300, 131072)])
 @pytest.mark.parametrize("dtype", ["bf16", "fp8"])
 @pytest.mark.parametrize("padded", [True, False])
 def test_lowp_passes(gpu_lib, dtype, rows, cols, padded):
