@@ -970,6 +970,25 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   // FP64 steps small enough for one workgroup: whole runs of them in one launch
   const int solo =
       chain && !M.csr && !M.lowp() ? chain_solo_lc(s * b, cols, ah.chain.nsb) : -1;
+  const bool csr_fused = chain && M.csr && !split && csr_step_fused(s * b);
+  CsrStep cr{};
+  if (csr_fused) {
+    cr.rowptr = M.C.rowptr;
+    cr.colidx = M.C.colidx;
+    cr.vals = M.C.vals;
+    cr.m = s * b;
+    cr.b = b;
+    cr.gb = ah.chain.gb;
+    cr.mode = dual ? 1 : 0;
+    cr.y = y;
+    cr.c = B.Yu;
+    cr.u = comp;
+    cr.x = coord;
+    cr.lambda = lambda;
+    cr.n = n;
+    cr.gamma = gamma;
+    cr.status = B.status;
+  }
   int par = 0;
   bool have_dots = false;
   ChainStep cs{};
@@ -1044,7 +1063,12 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
       Gk = B.G[cur] + (size_t)gslot * m * m;
       ++gslot;
       --ahead;
-      if (!chain || M.csr)
+      if (csr_fused) {
+        cr.idx = idx;
+        cr.tri = B.tri[cur] + (size_t)(gslot - 1) * ah.chain.tri;
+        cr.link = B.link[cur] + (size_t)(gslot - 1) * m;
+        HIP_TRY(timer.run(CABCD_PHASE_YU, [&] { return launch_csr_rhs(cr, st); }));
+      } else if (!chain || M.csr)
         HIP_TRY(timer.run(CABCD_PHASE_YU, [&] {
           return mat_rows_dot(M, idx, m, comp, B.Yu, B.scratch, st);
         }));
@@ -1066,7 +1090,10 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
     const double* tri =
         from_ahead && chain ? B.tri[cur] + (size_t)(gslot - 1) * ah.chain.tri : nullptr;
     const int* link = from_ahead && chain ? B.link[cur] + (size_t)(gslot - 1) * m : nullptr;
-    if (from_ahead && solo >= 0) {
+    if (from_ahead && csr_fused) {
+      cr.upd = fresh_next ? 0 : 1;   // an exact recomputation would overwrite the update
+      HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] { return launch_csr_step_update(cr, st); }));
+    } else if (from_ahead && solo >= 0) {
       // as many steps of the batch as nothing looks in on
       int run = 1;
       auto stops = [&](int64_t k1) {   // something reads the companion after step k1

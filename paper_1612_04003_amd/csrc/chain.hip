@@ -52,15 +52,11 @@ namespace cabcd {
 namespace {
 
 using cdev::kLinkFirst;
+using cdev::rhs_of;
+using cdev::tri_at;
+using cdev::tri_block;
 using gdev::d16_row_sum;
 using gdev::d4;
-
-__host__ __device__ constexpr int tri_block(int i, int j) { return i * (i + 1) / 2 + j; }
-
-// Place of item i of a lane in a stored superblock.
-__host__ __device__ constexpr int tri_at(int i, int lane) {
-  return (i >> 1) * 128 + 2 * lane + (i & 1);
-}
 
 // v / b for v < 16, 1 <= b <= 16, as a product with bm = block_mul(b).
 __host__ __device__ constexpr int block_mul(int b) { return (255 + b) / b; }
@@ -233,12 +229,6 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
 }
 
 // ------------------------------------------------------------------ delta = T^-1 c
-
-// c_p of the step's right-hand side (solve_dev.h) from Y u and x at its index.
-__device__ __forceinline__ double rhs_of(int mode, double lambda, double n, double yu, double xi,
-                                         double yi) {
-  return mode == 0 ? (-lambda * xi - yu / n) : ((yu - xi - yi) / n);
-}
 
 // This lane's items of the stored superblock at t.
 __device__ __forceinline__ void tri_load(gptr<const double> t, int lane, double (&v)[4]) {

@@ -28,5 +28,18 @@ __device__ __forceinline__ void scatter_delta(const int32_t* __restrict__ idx,
   }
 }
 
+// Right-hand side of a row of an outer step from its Y u (mode 0 primal, 1 dual).
+__device__ __forceinline__ double rhs_of(int mode, double lambda, double n, double yu, double xi,
+                                         double yi) {
+  return mode == 0 ? (-lambda * xi - yu / n) : ((yu - xi - yi) / n);
+}
+
+// T^-1 of a step: superblock (i, j) of 256 doubles, and the place of item i of a lane in
+// one (row 4 i + lane / 16, column lane % 16).
+__host__ __device__ constexpr int tri_block(int i, int j) { return i * (i + 1) / 2 + j; }
+__host__ __device__ constexpr int tri_at(int i, int lane) {
+  return (i >> 1) * 128 + 2 * lane + (i & 1);
+}
+
 }  // namespace cdev
 }  // namespace cabcd

@@ -336,6 +336,136 @@ __global__ __launch_bounds__(kCsrThreads) void csr_rowdot_kernel(
   if (lane == 0) out[p] = t + (base ? beta * base[p] : 0.0);
 }
 
+// A chain step of up to kFusedRows rows in two launches instead of three: the row
+// products leave the step's right-hand side c instead of Y u, and in the update a wave
+// forms its own row's delta, its row of T^-1 times c, while the row's entries are on
+// their way.  The workgroup that updates x forms all of them, and bounds the launch from
+// about 64 rows on.  (x is read by the first launch and written by the second.)
+// Marginal time of a step (100000 columns, 200 entries a row), three launches -> two: 16
+// rows 10.4 -> 7.8 us, 32 11.0 -> 8.5, 64 12.0 -> 11.2; 128 rows (480 entries) 16.5 -> 18.
+constexpr int kFusedRows = 64;
+
+__global__ __launch_bounds__(kCsrThreads) void csr_rhs_kernel(CsrStep a) {
+  const int lane = threadIdx.x & 63;
+  const int p = (int)blockIdx.x * kCsrWaves + (threadIdx.x >> 6);
+  if (p >= a.m) return;
+  const int64_t r = a.idx[p];
+  const double xi = a.x[r], yi = a.mode == 0 ? 0.0 : a.y[r];
+  const int64_t end = a.rowptr[r + 1];
+  double t = 0.0;
+  for (int64_t k0 = a.rowptr[r] + lane; k0 < end; k0 += 64 * kProbeU) {   // as csr_rowdot_kernel
+    int col[kProbeU];
+    double val[kProbeU];
+#pragma unroll
+    for (int u = 0; u < kProbeU; ++u) {
+      const int64_t k = k0 + 64 * u;
+      col[u] = k < end ? a.colidx[k] : -1;
+      val[u] = k < end ? a.vals[k] : 0.0;
+    }
+    double v[kProbeU];
+#pragma unroll
+    for (int u = 0; u < kProbeU; ++u) v[u] = col[u] >= 0 ? a.u[col[u]] : 0.0;
+#pragma unroll
+    for (int u = 0; u < kProbeU; ++u)
+      if (col[u] >= 0) t = fma(val[u], v[u], t);
+  }
+  t = wave_sum(t);
+  if (lane == 0) a.c[p] = cdev::rhs_of(a.mode, a.lambda, a.n, t, xi, yi);
+}
+
+// This lane's columns of T^-1 and of c: lane + 64 t, in superblock column J at cc.
+struct StepCols {
+  int J[kFusedRows / 64], cc[kFusedRows / 64];
+  double c[kFusedRows / 64];
+  __device__ __forceinline__ StepCols(const CsrStep& a, int lane) {
+#pragma unroll
+    for (int t = 0; t < kFusedRows / 64; ++t) {
+      const int q = min(lane + 64 * t, a.m - 1);
+      J[t] = (q * a.gbm) >> 16;   // q / gb
+      cc[t] = q - J[t] * a.gb;
+      c[t] = a.c[q];
+    }
+  }
+};
+
+// delta of the rows p, p + kCsrWaves, ... (N of them, those below m) in every lane of a
+// wave: row p of T^-1 up to the end of its block, the loads of all N rows in flight.
+template <int N>
+__device__ __forceinline__ void chain_row_delta(const CsrStep& a, int p0, int lane,
+                                                const StepCols& s, double (&d)[N]) {
+  constexpr int T = kFusedRows / 64;
+  double v[N][T];
+  int end[N];
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    const int p = __builtin_amdgcn_readfirstlane(min(p0 + k * kCsrWaves, a.m - 1));
+    const int I = (p * a.gbm) >> 16, r = p - I * a.gb;
+    end[k] = min(a.m, (((p * a.bm) >> 16) + 1) * a.b);
+    const gptr<const double> row = glb(a.tri) + cdev::tri_block(I, 0) * 256 +
+                                   cdev::tri_at(r >> 2, 16 * (r & 3));
+#pragma unroll
+    for (int t = 0; t < T; ++t) v[k][t] = row[min(s.J[t], I) * 256 + 2 * s.cc[t]];
+  }
+#pragma unroll
+  for (int k = 0; k < N; ++k) {
+    double x = 0.0;
+#pragma unroll
+    for (int t = 0; t < T; ++t) x = lane + 64 * t < end[k] ? fma(v[k][t], s.c[t], x) : x;
+    d[k] = wave_sum(x);
+  }
+}
+
+__global__ __launch_bounds__(kCsrThreads) void csr_step_update_kernel(CsrStep a) {
+  const int lane = threadIdx.x & 63;
+  const int wave = threadIdx.x >> 6;
+  const StepCols sc(a, lane);
+  if (blockIdx.x == gridDim.x - 1) {
+    __shared__ double dl[kFusedRows];
+    constexpr int N = 8;
+    for (int p0 = wave; p0 < a.m; p0 += N * kCsrWaves) {
+      double d[N];
+      chain_row_delta<N>(a, p0, lane, sc, d);
+#pragma unroll
+      for (int k = 0; k < N; ++k) {
+        const int p = p0 + k * kCsrWaves;
+        if (lane == k && p < a.m) {
+          dl[p] = d[k];
+          if (!isfinite(d[k])) raise_status(a.status, DEV_NONFINITE);
+        }
+      }
+    }
+    __syncthreads();
+    cdev::scatter_delta<kCsrThreads>(a.idx, a.link, dl, a.m, a.x);
+    return;
+  }
+  const int p = (int)blockIdx.x * kCsrWaves + wave;
+  if (p >= a.m) return;
+  const int64_t row = a.idx[p];
+  const int64_t k0 = a.rowptr[row], end = a.rowptr[row + 1];
+  int col[kProbeU];
+  double val[kProbeU];
+  auto load = [&](int64_t k) {
+#pragma unroll
+    for (int u = 0; u < kProbeU; ++u) {
+      const bool in = k + 64 * u < end;
+      col[u] = in ? a.colidx[k + 64 * u] : -1;
+      val[u] = in ? a.vals[k + 64 * u] : 0.0;
+    }
+  };
+  load(k0 + lane);
+  double dp[1];
+  chain_row_delta<1>(a, p, lane, sc, dp);
+  const double d = a.gamma * dp[0];
+  if (d == 0.0) return;
+  for (int64_t k = k0 + lane; k < end;) {
+#pragma unroll
+    for (int u = 0; u < kProbeU; ++u)
+      if (col[u] >= 0) unsafeAtomicAdd(a.u + col[u], d * val[u]);
+    k += 64 * kProbeU;
+    if (k < end) load(k);
+  }
+}
+
 __global__ void fill_kernel(double* __restrict__ out, int64_t n, const double* __restrict__ base,
                             double beta) {
   const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
@@ -416,6 +546,25 @@ hipError_t launch_csr_scatter(const CsrView& A, const int32_t* idx, int64_t m, c
   const unsigned grid = (unsigned)((m + kCsrWaves - 1) / kCsrWaves) + (xs.x != nullptr ? 1 : 0);
   hipLaunchKernelGGL(csr_scatter_kernel, dim3(grid), dim3(kCsrThreads), 0, st, A.rowptr, A.colidx,
                      A.vals, idx, m, v, gamma, out, xs);
+  return hipGetLastError();
+}
+
+bool csr_step_fused(int m) { return m <= kFusedRows; }
+
+hipError_t launch_csr_rhs(const CsrStep& a, hipStream_t st) {
+  if (a.m < 1 || !csr_step_fused(a.m)) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(csr_rhs_kernel, dim3((unsigned)((a.m + kCsrWaves - 1) / kCsrWaves)),
+                     dim3(kCsrThreads), 0, st, a);
+  return hipGetLastError();
+}
+
+hipError_t launch_csr_step_update(const CsrStep& step, hipStream_t st) {
+  CsrStep a = step;
+  if (a.m < 1 || !csr_step_fused(a.m)) return hipErrorInvalidValue;
+  a.bm = (65535 + a.b) / a.b;
+  a.gbm = (65535 + a.gb) / a.gb;
+  const unsigned rows = a.upd ? (unsigned)((a.m + kCsrWaves - 1) / kCsrWaves) : 0;
+  hipLaunchKernelGGL(csr_step_update_kernel, dim3(rows + 1), dim3(kCsrThreads), 0, st, a);
   return hipGetLastError();
 }
 

@@ -402,6 +402,25 @@ hipError_t launch_csr_update_split(const CsrView& A, const CsrSplitInfo& info,
                                    const int32_t* idx, int m, int nsteps, int step,
                                    const double* delta, double gamma, double* out, double* dws,
                                    int* iws, const XScatter& xs, hipStream_t st);
+// A chain step of few rows (csr_step_fused) in two launches: c from the rows' products
+// with u, then u += gamma Y^T delta (with upd) and x[idx] += delta, delta = T^-1 c.
+struct CsrStep {
+  const int64_t* rowptr;
+  const int32_t* colidx;
+  const double* vals;
+  const int32_t* idx;
+  int m, b, gb, mode, upd;
+  int bm, gbm;        // set by the launcher: p / b and p / gb as products
+  const double* tri;
+  const int* link;
+  const double* y;    // dual only
+  double *c, *u, *x;
+  double lambda, n, gamma;
+  int* status;
+};
+bool csr_step_fused(int m);
+hipError_t launch_csr_rhs(const CsrStep& a, hipStream_t st);
+hipError_t launch_csr_step_update(const CsrStep& step, hipStream_t st);
 hipError_t launch_csr_scatter(const CsrView& A, const int32_t* idx, int64_t m, const double* v,
                               double gamma, double* out, const XScatter& xs, hipStream_t st);
 // out[p] = A[p] . v + beta * base[p] for every row.

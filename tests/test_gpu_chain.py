@@ -170,3 +170,33 @@ def test_dual_short_steps_in_one_workgroup(gpu_lib, d, b, s):
     a2, w2 = gpu_lib.dual_bcd(A, y.to(DEV), 1e-2, b, s, H - 9 * s, 6, alpha=a2, w=w2,
                               h0=9 * s, flags=gpu_lib.FLAG_STATE_VALID)
     assert torch.equal(a1, a2) and torch.equal(w1, w2)
+
+
+# sparse steps in two launches up to 64 rows, in three from there on
+@pytest.mark.parametrize("b,s", [(1, 1), (1, 64), (1, 65), (3, 21), (5, 7), (7, 9), (8, 8), (16, 4),
+                                 (13, 5)])
+@pytest.mark.parametrize("kind", ["dual", "primal"])
+def test_sparse_steps_of_few_rows(gpu_lib, kind, b, s):
+    """Rows without entries, coordinates repeated inside and across steps, exact
+    recomputations in between."""
+    rows, cols = 70, 900
+    _say("sparse few rows", kind, b, s)
+    rng = np.random.default_rng(b * s)
+    S = scipy.sparse.random(rows, cols, 0.05, random_state=rng, format="csr")
+    S.data = rng.standard_normal(S.nnz)
+    S = scipy.sparse.csr_matrix(S.multiply((np.arange(rows) % 9 != 4)[:, None]))
+    S.eliminate_zeros()
+    S.sort_indices()
+    H = 13 * s + s // 2
+    y = rng.standard_normal(rows if kind == "dual" else cols)
+    A = gpu_lib.CSR.from_scipy(S, DEV)
+    yd = torch.tensor(y, device=DEV)
+    if kind == "dual":
+        x, u = gpu_lib.dual_bcd(A, yd, 1e-2, b, s, H, 8, resid_every=5)
+        xo, uo = bcd.dual_bcd(S.T.tocsc(), y, 1e-2, b, s, H, 8)
+    else:
+        x, u = gpu_lib.primal_bcd(A, yd, 1e-2, b, s, H, 8, resid_every=5)
+        xo, uo = bcd.primal_bcd(S, y, 1e-2, b, s, H, 8)
+        uo = uo - y
+    assert _rel(x.cpu(), xo) <= 1e-10
+    assert _rel(u.cpu(), uo) <= 1e-10
