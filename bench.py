@@ -266,7 +266,7 @@ def headline(args, cabcd, torch, synth):
         out["folded_update"] = {
             "ms_per_step": round(el_f / args.steps * 1e3, 4),
             "value": round(gram_flops * args.steps / el_f / 1e12, 3),
-            "kernel": "gram_f64_dma16_upd_kernel<1> (the call's first step: gram_f64_dma16_kernel)",
+            "kernel": "gram_f64_dma16_upd_kernel<1> (the call's first step: gram_f64_tri_kernel)",
             "gram_ms": round(gf_ms, 4),
             "gram_frac": round(gram_flops / (gf_ms * 1e-3) / 1e12 / PEAK_FP64_MATRIX_TFLOPS, 4),
             "gram_bytes": 2 * ybytes + 16 * n}

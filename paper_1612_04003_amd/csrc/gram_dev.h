@@ -625,13 +625,13 @@ struct D16 {
   static constexpr int THREADS = 512;
   static constexpr int TILE = SBP * KT + KT;         // doubles per buffer: rows, then u
   static constexpr int DMA_PER_WAVE = SBP * CH / THREADS;   // 4 instructions
-};
-
-// The folded slab's LDS: two tile buffers of D16::TILE doubles, two for the previous
-// step's rows (and the tile's old companion entries) and gamma * delta of the previous
-// step (D16::SBP), each a __shared__ array of its own (see TriLds).
-struct D16Lds {
-  double *t0, *t1, *y0, *y1, *dl;
+  // two more buffers for the previous step's rows (and the tile's old companion
+  // entries), then gamma * delta of the previous step; one array (as arrays of their
+  // own with the tile loop unrolled over them a step took 0.388 ms, not 0.371)
+  static constexpr int YT = SBP * KT + KT;           // doubles per update buffer
+  static constexpr int YOFF = 2 * TILE;
+  static constexpr int DOFF = 2 * TILE + 2 * YT;
+  static constexpr int LDS_UPD = DOFF + SBP;
 };
 
 // x of the lane N places along in the lane's row of sixteen (DPP row_ror),
@@ -681,7 +681,7 @@ __device__ __forceinline__ int d16_swz(int r) { return D16::CH == 8 ? (r >> 1) &
 template <int W, int MODE>
 __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t ld,
                                          int64_t k_begin, int64_t k_end, const int32_t* idx,
-                                         int m, double* __restrict__ part, const D16Lds L,
+                                         int m, double* __restrict__ part, double* lds,
                                          const D16Upd up) {
   using C = D16;
   typedef __attribute__((address_space(3))) void* lds_vptr;
@@ -714,9 +714,10 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
 #pragma unroll
   for (int i = 0; i < C::DMA_PER_WAVE; ++i)
     yrow[i] = up.idx[8 * (C::DMA_PER_WAVE * W + i) + (lane >> 3)];
-  if (tid < C::SBP) L.dl[tid] = up.gamma * up.delta[tid];
-  auto issue_y = [&](int t, double* Y) {
+  if (tid < C::SBP) lds[C::DOFF + tid] = up.gamma * up.delta[tid];
+  auto issue_y = [&](int t, int slot) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
+    double* Y = lds + C::YOFF + slot * C::YT;
 #pragma unroll
     for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
       double* dst = Y + (C::DMA_PER_WAVE * W + i) * 128;
@@ -745,10 +746,11 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
       }
     }
   };
-  // tile t's update from update buffer Y; MODE 1 also fills the u slot of Gram
-  // buffer T
-  auto update = [&](int t, const double* Y, double* T) {
-    const double* dl = L.dl;
+  // tile t's update from update buffer yslot; MODE 1 also fills the u slot
+  // of Gram buffer uslot
+  auto update = [&](int t, int yslot, int uslot) {
+    const double* Y = lds + C::YOFF + yslot * C::YT;
+    const double* dl = lds + C::DOFF;
     double p0 = 0.0, p1 = 0.0;
 #pragma unroll 2
     for (int j = 0; j < C::SBP / 64; ++j) {
@@ -773,47 +775,40 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
       if (k < k_end) rg[k] = n0;
       if (k + 1 < k_end) rg[k + 1] = n1;
       if constexpr (MODE == 1) {
-        double* us = T + C::SBP * C::KT;
+        double* us = lds + uslot * C::TILE + C::SBP * C::KT;
         us[2 * W] = k < k_end ? n0 : 0.0;
         us[2 * W + 1] = k + 1 < k_end ? n1 : 0.0;
       }
     }
   };
   if constexpr (MODE == 2) {
-    auto step = [&](int t, const double* cur, double* nxt) {
-      if (t + 1 < ntiles) issue_y(t + 1, nxt);
-      update(t, cur, nullptr);
-      __builtin_amdgcn_s_waitcnt(0);
-      __syncthreads();
-    };
-    issue_y(0, L.y0);
+    issue_y(0, 0);
     __builtin_amdgcn_s_waitcnt(0);
     __syncthreads();
-    for (int t = 0; t < ntiles; t += 2) {
-      step(t, L.y0, L.y1);
-      if (t + 1 < ntiles) step(t + 1, L.y1, L.y0);
+    for (int t = 0; t < ntiles; ++t) {
+      if (t + 1 < ntiles) issue_y(t + 1, (t + 1) & 1);
+      update(t, t & 1, -1);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
     }
     return;
   }
 
-  // tile t's rows (its u slot is the update's to fill)
-  auto issue = [&](int t, double* T) {
+  auto issue = [&](int t, int slot) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
-    if (k0 + C::KT <= k_end) {
-#pragma unroll
-      for (int i = 0; i < C::DMA_PER_WAVE; ++i)   // 64 slots of 2 doubles each
-        __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + (k0 + cofs[i])),
-                                         (lds_vptr)(T + (C::DMA_PER_WAVE * W + i) * 128), 16, 0,
-                                         0);
-      return;
-    }
+    double* T = lds + slot * C::TILE;
 #pragma unroll
     for (int i = 0; i < C::DMA_PER_WAVE; ++i) {
+      double* dst = T + (C::DMA_PER_WAVE * W + i) * 128;   // 64 slots of 2 doubles
       const int64_t k = k0 + cofs[i];
-      double2 v;
-      v.x = k < k_end ? src[i][k] : 0.0;
-      v.y = k + 1 < k_end ? src[i][k + 1] : 0.0;
-      *reinterpret_cast<double2*>(T + (C::DMA_PER_WAVE * W + i) * 128 + 2 * lane) = v;
+      if (k + 1 < k_end) {
+        __builtin_amdgcn_global_load_lds((glb_vptr)(src[i] + k), (lds_vptr)dst, 16, 0, 0);
+      } else {
+        double2 v;
+        v.x = k < k_end ? src[i][k] : 0.0;
+        v.y = 0.0;
+        *reinterpret_cast<double2*>(dst + 2 * lane) = v;
+      }
     }
   };
 
@@ -830,26 +825,32 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
   for (int a = 0; a < 17; ++a) acc[a] = d4{0.0, 0.0, 0.0, 0.0};
   double yua[2] = {0.0, 0.0};
 
-  // Tile t in cur while tile t + 1 is on its way into nxt, tile t + 1's update in
-  // ynxt, tile t + 2's update rows on their way into ycur.
-  auto step = [&](int t, const double* cur, double* nxt, double* ycur, const double* ynxt) {
-    if (t + 1 < ntiles) issue(t + 1, nxt);
+  issue(0, 0);
+  issue_y(0, 0);
+  if (ntiles > 1) issue_y(1, 1);
+  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
+  __syncthreads();
+  update(0, 0, 0);
+  __syncthreads();
+  for (int t = 0; t < ntiles; ++t) {
+    if (t + 1 < ntiles) issue(t + 1, (t + 1) & 1);
     // update buffer t & 1 held tile t (updated during tile t - 1); tile t + 1
     // arrived during tile t - 1.  Waves 0-3 update before their matrix
     // instructions, waves 4-7 (the other wave of each SIMD) after them, so
     // the update's latency runs beside the other wave's MFMA chain.
-    if (t + 2 < ntiles) issue_y(t + 2, ycur);
-    if (W < 4 && t + 1 < ntiles) update(t + 1, ynxt, nxt);
+    if (t + 2 < ntiles) issue_y(t + 2, t & 1);
+    if (W < 4 && t + 1 < ntiles) update(t + 1, (t + 1) & 1, (t + 1) & 1);
+    const double* tile = lds + (t & 1) * C::TILE;
 #pragma unroll
     for (int pp = 0; pp < C::PP; ++pp) {
-      const double* base = cur + lane_off[pp];
+      const double* base = tile + lane_off[pp];
       auto frag = [&](int r) {   // rows 16 r .. 16 r + 15, this lane's chunk of pair pp
         return *reinterpret_cast<const double2*>(base + r * 16 * C::KT);
       };
       const double2 f0 = frag(R0);
       const double2 f1 = frag(R1);
       const double2 ut =   // u at the same two columns (unswizzled, after the rows)
-          *reinterpret_cast<const double2*>(cur + C::SBP * C::KT + 8 * pp + 2 * g);
+          *reinterpret_cast<const double2*>(tile + C::SBP * C::KT + 8 * pp + 2 * g);
       yua[0] = fma(f0.x, ut.x, yua[0]);
       yua[0] = fma(f0.y, ut.y, yua[0]);
       yua[1] = fma(f1.x, ut.x, yua[1]);
@@ -865,20 +866,9 @@ __device__ __forceinline__ void d16_slab(const double* __restrict__ A, int64_t l
         acc[R0 + 1 + c] = mfma(f1.y, fc.y, acc[R0 + 1 + c]);
       }
     }
-    if (W >= 4 && t + 1 < ntiles) update(t + 1, ynxt, nxt);
+    if (W >= 4 && t + 1 < ntiles) update(t + 1, (t + 1) & 1, (t + 1) & 1);
     __builtin_amdgcn_s_waitcnt(0);   // tile t + 1 is in LDS
     __syncthreads();
-  };
-  issue(0, L.t0);
-  issue_y(0, L.y0);
-  if (ntiles > 1) issue_y(1, L.y1);
-  __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
-  __syncthreads();
-  update(0, L.y0, L.t0);
-  __syncthreads();
-  for (int t = 0; t < ntiles; t += 2) {
-    step(t, L.t0, L.t1, L.y0, L.y1);
-    if (t + 1 < ntiles) step(t + 1, L.t1, L.t0, L.y1, L.y0);
   }
 
   gptr<double> pg = glb(part);
@@ -903,17 +893,17 @@ template <int MODE>
 __device__ __forceinline__ void gram_slab_dma16(const double* __restrict__ A, int64_t ld,
                                                 int64_t k_begin, int64_t k_end,
                                                 const int32_t* idx, int m,
-                                                double* __restrict__ part, const D16Lds L,
+                                                double* __restrict__ part, double* lds,
                                                 const D16Upd up) {
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: d16_slab<0, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 1: d16_slab<1, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 2: d16_slab<2, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 3: d16_slab<3, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 4: d16_slab<4, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 5: d16_slab<5, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    case 6: d16_slab<6, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
-    default: d16_slab<7, MODE>(A, ld, k_begin, k_end, idx, m, part, L, up); break;
+    case 0: d16_slab<0, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 1: d16_slab<1, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 2: d16_slab<2, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 3: d16_slab<3, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 4: d16_slab<4, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 5: d16_slab<5, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    case 6: d16_slab<6, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
+    default: d16_slab<7, MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up); break;
   }
 }
 

@@ -83,14 +83,12 @@ template <int MODE>
 __global__ __launch_bounds__(D16::THREADS) void gram_f64_dma16_upd_kernel(
     const double* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, int64_t chunk, double* __restrict__ partials, D16Upd up) {
-  __shared__ __attribute__((aligned(16))) double t0[D16::TILE], t1[D16::TILE];
-  __shared__ __attribute__((aligned(16))) double y0[D16::TILE], y1[D16::TILE], dl[D16::SBP];
+  __shared__ __attribute__((aligned(16))) double lds[D16::LDS_UPD];
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   double* part =
       MODE == 1 ? partials + (int64_t)blockIdx.x * (D16::NBLK * 256 + D16::SBP) : nullptr;
-  gram_slab_dma16<MODE>(A, ld, k_begin, k_end, idx, m, part,
-                        D16Lds{t0, t1, y0, y1, dl}, up);
+  gram_slab_dma16<MODE>(A, ld, k_begin, k_end, idx, m, part, lds, up);
 }
 
 // A reduction workgroup has 1024 threads: GROUPS split groups (a wave or more
