@@ -631,7 +631,7 @@ struct StepBuffers {
   double* rnorm;     // its norm
   // the chain of steps whose Grams are computed ahead
   double* tri[2];    // slots inverses of the Grams' block triangles
-  double* dinv;      // scratch of one launch
+  double* work;      // scratch of one launch
   int* link[2];      // slots x sb links of repeated indices
   double* P[2];      // dense: partial Y u of a step and of the next one
   double* xg[2];     // dense: x (and y, row scales) at their indices
@@ -659,7 +659,7 @@ size_t layout(Carve& c, StepBuffers& B, const Mat& M, const Ahead& ah, int b, in
   B.rho = c.take<double>(checks ? M.rows : 1);
   B.rnorm = c.take<double>(1);
   if (ah.chain.ok) {
-    B.dinv = c.take<double>(slots * ah.chain.dinv);
+    B.work = c.take<double>(slots * ah.chain.work);
     const size_t pd = M.csr ? 1 : chain_slabs(M.dtype, sb, M.cols).partial;
     for (int q = 0; q < 2; ++q) {
       B.tri[q] = c.take<double>(slots * ah.chain.tri);
@@ -959,7 +959,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
       });
     if (chain)
       he = timer.run_on(bs, CABCD_PHASE_SOLVE, [&] {
-        return launch_chain_prepare(ah.chain, B.G[buf], nst, mb, b, ib, B.tri[buf], B.dinv,
+        return launch_chain_prepare(ah.chain, B.G[buf], nst, mb, b, ib, B.tri[buf], B.work,
                                     B.link[buf], B.status, bs);
       });
     return he;

@@ -13,11 +13,26 @@
 //   * chain_diag_kernel: the superblocks on the diagonal (block lower triangular
 //     inside) by Gauss-Jordan elimination, one row per lane; their pivots are
 //     those of the b x b blocks Gamma_j, so a pivot <= 0 is reported as before;
-//   * chain_panel_kernel: one workgroup per superblock column J runs the forward
-//     substitution Z_IJ = -D_I^-1 sum_{J<=t<I} G_It Z_tJ on the FP64 matrix
-//     cores.  An FP64 MFMA result holds item i at row 4 i + lane / 16, which is
-//     the operand layout of k-slice i, so Z feeds the next product from the
-//     registers it was written from (kept in LDS).
+//   * chain_panel_kernel: a first inverse Z by rows, Z_IJ = -(sum_{J<t<=I} Z_It T_tJ)
+//     D_J^-1, one workgroup per superblock row I on the FP64 matrix cores, which
+//     work on Z transposed: an FP64 MFMA result holds item i at row 4 i + lane /
+//     16, which is the operand layout of k-slice i, so Z feeds the next product
+//     from the registers it was written from (kept in LDS);
+//   * chain_resid_kernel, chain_refine_kernel: T^-1 = Z + (I - Z T) Z for the rows
+//     that need it, the residual summed in twice the working precision.
+// The order and the refinement are for accuracy.  With c = T delta the product Z c
+// is off by (Z T - I) delta, which the substitution has no counterpart to: where
+// the rows are nearly collinear, c is far smaller than |T| |delta|.  An inverse by
+// columns keeps T Z - I small and leaves Z T - I large: w of 256 x 4096, b = 8, s =
+// 32, row correlation 0.9999, lambda 1e-5, was off by 5.3e-7 where the substitution
+// is off by 8.7e-12.  By rows w is right, but the errors of a step's deltas are
+// independent of each other, where later blocks of the substitution make up for
+// those of earlier ones, and the companion takes them up: on the CPU a dual w of 300
+// x 600, b = s = 16, was off by 4.3e-10, against 1.5e-11.  The refined inverse is
+// exact to the rounding of its entries, and Z c to the rounding of the product, which
+// c scales: w and r of that primal run are off by 1.1e-11 and 1.2e-11, by substitution
+// by 8.7e-12 and 1.0e-11.  Refining every row adds 2 us to a step of 256 rows and 11 to
+// one of 512; where none is refined there are two short launches a batch more.
 // T^-1 is stored as its lower 16 x 16 superblocks in that result layout, items
 // 2 i and 2 i + 1 of a lane side by side (256 doubles each, row-major over the
 // block triangle), which the product reads with two 16-byte loads a lane.
@@ -88,31 +103,40 @@ __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict
   if (bad) raise_status(status, DEV_NOTSPD);
   if (I >= nsb) return;
   double* t = tri + (int64_t)tri_block(I, I) * 256;
-  double* d = dinv + (int64_t)I * 256 + u;   // the matrix-core operand order: k-slice, lane
-#pragma unroll
+  double* d = dinv + (int64_t)I * 256 + (u >> 2) * 64 + (u & 3) * 16;   // transposed operand:
+#pragma unroll                                                           // k-slice, lane
   for (int v = 0; v < 16; ++v) {
     t[tri_at(u >> 2, (u & 3) * 16 + v)] = e[v];
-    d[(v >> 2) * 64 + (v & 3) * 16] = e[v];
+    d[v] = e[v];
   }
 }
 
-// Workgroup x < gridDim.x - 1: superblock column J = x of step blockIdx.y by
-// four waves; the last workgroup builds the step's links.  FULL: gb = 16 and m a
-// multiple of 16.
+// Workgroup x < gridDim.x - 1: superblock row I = nsb - 1 - x of step blockIdx.y by
+// four waves (the longest rows first); the last workgroup builds the step's links.
+// FULL: gb = 16 and m a multiple of 16.  Z to `tri`, and to `out` too where the row needs
+// no refinement, which `need` notes.
 //
-// A column is a chain over its rows: row R (superblock J + R) needs Z of every
-// row before it.  Wave w holds the rows r = w mod 4 and adds their products to
-// its part of row R; the parts meet in LDS and wave R mod 4, the only one that
-// reads Z_R afterwards, finishes the row.  So the other waves run ahead into
-// the next row meanwhile (the parts are double-buffered), and one barrier a row
+// A row is a chain over its columns: column R (superblock I - R) needs Z of every
+// column before it.  Wave w holds the columns r = w mod 4 and adds their products to
+// its part of column R; the parts meet in LDS and wave R mod 4, the only one that
+// reads Z_R afterwards, finishes it.  So the other waves run ahead into
+// the next column meanwhile (the parts are double-buffered), and one barrier a column
 // is enough.  PF operand blocks a wave are in flight; Z goes to memory at the
 // end (stores in the loop made the loads after them wait: 50 us for 13 steps of
-// 256 rows with one wave a column and stores in the loop, 190 us for 16 of 512).
+// 256 rows with one wave a row and stores in the loop, 190 us for 16 of 512).
+//
+// A row needs none where |Z_rk| sqrt(T_kk T_rr), which bounds the amplification |Z| |T|
+// whatever the scales of the rows, is at most kRefineFrom: in CPU runs of 160 steps of
+// all block sizes, correlations 0 to 0.999 and lambda 1e-6 to 0.1, Z as it is then came
+// within 10 % of the substitution (mean error of x and of the companion; 25 % above 32, 37 %
+// from 128 on).
 constexpr int kPanelWaves = 4;
+constexpr double kRefineFrom = 16.0;
 template <bool FULL>
 __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
     const double* __restrict__ G, int m, int gb, int nsb, double* __restrict__ tri,
-    const double* __restrict__ dinv, const int32_t* __restrict__ idx, int* __restrict__ link) {
+    const double* __restrict__ dinv, const int32_t* __restrict__ idx, int* __restrict__ link,
+    double* __restrict__ out, int* __restrict__ need) {
   extern __shared__ __attribute__((aligned(16))) double zs[];
   const int64_t step = blockIdx.y;
   if (blockIdx.x == gridDim.x - 1) {
@@ -135,20 +159,21 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l15 = lane & 15, l16 = lane >> 4;
-  const int J = blockIdx.x, nr = nsb - J;
+  const int I = nsb - 1 - (int)blockIdx.x, nr = I + 1;
   const gptr<const double> Gs = glb(G) + step * m * m;
   const gptr<double> T = glb(tri) + step * tri_block(nsb, 0) * 256;
-  const gptr<const double> D = glb(dinv) + (step * nsb + J) * 256 + lane;
-  double* part = zs + lane;                           // two sets of four parts
-  double* Z = zs + 2 * kPanelWaves * 256 + lane;      // Z of row r at r * 256
+  const gptr<const double> D = glb(dinv) + step * nsb * 256 + lane;
+  double* part = zs + lane;                       // two sets of four parts
+  double* Zs = zs + 2 * kPanelWaves * 256;        // Z of column r, transposed, at r * 256
+  double* Z = Zs + lane;
 
-  // operand block (R, r): rows of superblock J + R against columns of J + r,
-  // read as its transpose (G is symmetric): 16 consecutive doubles a row
+  // operand block (R, r): rows of superblock I - r of T in the columns of I - R,
+  // transposed: 16 consecutive doubles a row
   auto load = [&](int R, int r, double(&a)[4]) {
-    const int col = (J + R) * gb + l15;
+    const int col = (I - R) * gb + l15;
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      const int kk = 4 * s + l16, row = (J + r) * gb + kk;
+      const int kk = 4 * s + l16, row = (I - r) * gb + kk;
       if constexpr (FULL) {
         a[s] = Gs[(int64_t)row * m + col];
       } else {
@@ -167,21 +192,23 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
     Rn += end ? 1 : 0;
     rn = end ? w : rn;
   };
-  int Rd = w == 0 ? kPanelWaves : w;   // the next row this wave finishes
+  int Rd = w == 0 ? kPanelWaves : w;   // the next column this wave finishes
   auto load_d = [&] {
 #pragma unroll
-    for (int s = 0; s < 4; ++s) da[s] = D[(int64_t)min(Rd, nr - 1) * 256 + 64 * s];
+    for (int s = 0; s < 4; ++s) da[s] = D[(int64_t)(I - min(Rd, nr - 1)) * 256 + 64 * s];
   };
 #pragma unroll
   for (int q = 0; q < PF; ++q) next_load(ring[q]);
   load_d();
   if (w == 0) {
 #pragma unroll
-    for (int i = 0; i < 4; ++i) Z[64 * i] = T[(int64_t)tri_block(J, J) * 256 + tri_at(i, lane)];
+    for (int i = 0; i < 4; ++i)
+      Z[64 * i] =
+          T[(int64_t)tri_block(I, I) * 256 + tri_at(l15 >> 2, (l15 & 3) * 16 + 4 * i + l16)];
   }
   int R = 1, r = w;
   d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
-  auto end_row = [&] {
+  auto end_column = [&] {
     double* set = part + (R & 1) * kPanelWaves * 256;
     const d4 sum = acc[0] + acc[1];
     acc[0] = acc[1] = d4{0.0, 0.0, 0.0, 0.0};
@@ -210,7 +237,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
   while (R < nr) {
 #pragma unroll
     for (int q = 0; q < PF; ++q) {
-      while (R < nr && r >= R) end_row();   // uniform
+      while (R < nr && r >= R) end_column();   // uniform
       if (R < nr) {
         const double* z = Z + r * 256;
 #pragma unroll
@@ -220,15 +247,43 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
       }
     }
   }
-  // wave w wrote the rows R = w mod 4
-  for (int R1 = Rd - kPanelWaves; R1 > 0; R1 -= kPanelWaves) {
-    const gptr<double> to = T + (int64_t)tri_block(J + R1, J) * 256;
+  // wave w wrote the columns R = w mod 4
+  double* gd = zs;                       // the diagonal of G up to this row (kMaxRows at most)
+  double* top = zs + kPanelWaves * 256;   // a wave's largest |Z_rk|^2 T_kk T_rr
+  lds_barrier();
+  for (int p = threadIdx.x; p < nr * gb; p += 64 * kPanelWaves) {
+    const double v = Gs[(int64_t)min(p, m - 1) * (m + 1)];
+    gd[p] = p < m ? v : 0.0;
+  }
+  lds_barrier();
+  double big = 0.0;
+  for (int R1 = w; R1 < nr; R1 += kPanelWaves) {
+    const double* z = Zs + R1 * 256 + 16 * l15 + l16;
+    const double gk = l15 < gb ? gd[(I - R1) * gb + l15] : 0.0;
 #pragma unroll
-    for (int s = 0; s < 4; ++s) to[tri_at(s, lane)] = Z[R1 * 256 + 64 * s];
+    for (int s = 0; s < 4; ++s) {
+      const double gr = 4 * s + l16 < gb ? gd[I * gb + 4 * s + l16] : 0.0;
+      const double v = z[4 * s] * z[4 * s] * gk * gr;
+      big = fmax(big, v >= 0.0 ? v : __builtin_inf());
+    }
+  }
+  for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+  if (lane == 0) top[w] = big;
+  lds_barrier();
+  const bool refine =
+      fmax(fmax(top[0], top[1]), fmax(top[2], top[3])) > kRefineFrom * kRefineFrom;
+  if (threadIdx.x == 0) need[step * nsb + I] = refine ? 1 : 0;
+  const gptr<double> To = glb(out) + step * tri_block(nsb, 0) * 256;
+  for (int R1 = w; R1 < nr; R1 += kPanelWaves) {
+    const int64_t at = (int64_t)tri_block(I, I - R1) * 256;
+    const double* z = Zs + R1 * 256 + 16 * l15 + l16;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      if (R1 > 0) T[at + tri_at(s, lane)] = z[4 * s];
+      if (!refine) To[at + tri_at(s, lane)] = z[4 * s];
+    }
   }
 }
-
-// ------------------------------------------------------------------ delta = T^-1 c
 
 // This lane's items of the stored superblock at t.
 __device__ __forceinline__ void tri_load(gptr<const double> t, int lane, double (&v)[4]) {
@@ -239,6 +294,151 @@ __device__ __forceinline__ void tri_load(gptr<const double> t, int lane, double 
   v[2] = y.x;
   v[3] = y.y;
 }
+
+// Superblock (I, J) of the block triangle that is number x in it.
+__device__ __forceinline__ void tri_place(int x, int& I, int& J) {
+  I = 0;
+  while (tri_block(I + 1, 0) <= x) ++I;
+  J = x - tri_block(I, 0);
+}
+
+// h + l += a b in twice the working precision: the rounding errors of the product and
+// of the sum (TwoProduct and TwoSum; Ogita, Rump and Oishi, SIAM J. Sci. Comput. 2005,
+// algorithm Dot2).
+__device__ __forceinline__ void dot2(double a, double b, double& h, double& l) {
+#pragma clang fp contract(off)   // (h + p must round p)
+  const double p = a * b, e = fma(a, b, -p);
+  const double q = h + p, z = q - h;
+  l += ((h - (q - z)) + (p - z)) + e;
+  h = q;
+}
+
+// Superblock (I, J) of I - Z T (Z at `tri`) of step blockIdx.y, to `res` in the matrix
+// cores' operand order, for the rows in need.  Wave w adds the products t = J + w mod 4, a lane rows 4 (lane /
+// 16) .. + 3 of column lane % 16.  The vector units bound it: ten FP64 operations an
+// element product, one product's loads ahead.
+constexpr int kResWaves = 4;
+template <bool FULL>
+__global__ __launch_bounds__(64 * kResWaves) void chain_resid_kernel(
+    const double* __restrict__ G, int m, int b, int gb, int nsb, const double* __restrict__ tri,
+    const int* __restrict__ need, double* __restrict__ res) {
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  constexpr int ZS = 18;   // (16-byte pieces of a row stay aligned; two-way bank conflicts)
+  __shared__ __attribute__((aligned(16))) double zt[kResWaves][16 * ZS];   // Z_It, transposed
+  __shared__ double tt[kResWaves][256];                                    // T_tJ
+  __shared__ double part[kResWaves][2][256];
+  const int lane = threadIdx.x & 63;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l15 = lane & 15, l16 = lane >> 4;
+  const int64_t step = blockIdx.y;
+  int I, J;
+  tri_place((int)(gridDim.x - 1 - blockIdx.x), I, J);   // (the longest first)
+  if (need[step * nsb + I] == 0) return;
+  const gptr<const double> Gs = glb(G) + step * m * m;
+  const gptr<const double> Zr = glb(tri) + (step * tri_block(nsb, 0) + tri_block(I, 0)) * 256;
+  const int bm = block_mul(b);
+  const int col = J * gb + l15;
+  double zv[4], tv[4], h[4], l[4];
+  auto load = [&](int t) {
+    t = min(t, I);
+    tri_load(Zr + (int64_t)t * 256, lane, zv);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const int kk = 4 * s + l16, row = t * gb + kk;
+      const bool in = FULL || (kk < gb && l15 < gb && row < m && col < m);
+      const bool ok = in && (t != J || block_of(l15, bm) <= block_of(kk, bm));
+      const double v = Gs[ok ? (int64_t)row * m + col : 0];
+      tv[s] = ok ? v : (t == J && kk == l15 ? 1.0 : 0.0);
+    }
+  };
+#pragma unroll
+  for (int s = 0; s < 4; ++s) h[s] = l[s] = 0.0;
+  load(J + w);
+  for (int t0 = J; t0 <= I; t0 += kResWaves) {   // uniform
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      zt[w][l15 * ZS + 4 * s + l16] = zv[s];
+      tt[w][64 * s + lane] = tv[s];
+    }
+    lds_barrier();
+    load(t0 + kResWaves + w);
+    if (t0 + w <= I) {   // uniform in a wave
+#pragma unroll
+      for (int k = 0; k < 16; ++k) {
+        const double t = tt[w][16 * k + l15];
+        const dv2 z0 = *reinterpret_cast<const dv2*>(&zt[w][k * ZS + 4 * l16]);
+        const dv2 z1 = *reinterpret_cast<const dv2*>(&zt[w][k * ZS + 4 * l16 + 2]);
+        dot2(z0.x, t, h[0], l[0]);
+        dot2(z0.y, t, h[1], l[1]);
+        dot2(z1.x, t, h[2], l[2]);
+        dot2(z1.y, t, h[3], l[3]);
+      }
+    }
+  }
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    part[w][0][64 * s + lane] = h[s];
+    part[w][1][64 * s + lane] = l[s];
+  }
+  __syncthreads();
+  const int at = threadIdx.x, row = 4 * l16 + (at >> 6);   // (column l15)
+  double sh = I == J && row == l15 ? -1.0 : 0.0, sl = 0.0;
+#pragma unroll
+  for (int q = 0; q < kResWaves; ++q) {
+    const double p = part[q][0][at], s = sh + p, d = s - sh;
+    sl += ((sh - (s - d)) + (p - d)) + part[q][1][at];
+    sh = s;
+  }
+  res[(step * tri_block(nsb, 0) + tri_block(I, J)) * 256 + (l15 >> 2) * 64 + (l15 & 3) * 16 + row] =
+      -(sh + sl);
+}
+
+// T^-1 = Z + R Z from Z (`tri`) and the residual R for the rows in need: superblock 4 x +
+// wave of step blockIdx.y, to `out`.
+__global__ __launch_bounds__(256) void chain_refine_kernel(int nsb, const double* __restrict__ tri,
+                                                           const int* __restrict__ need,
+                                                           const double* __restrict__ res,
+                                                           double* __restrict__ out) {
+  typedef double dv2 __attribute__((ext_vector_type(2)));
+  const int n = tri_block(nsb, 0);
+  const int lane = threadIdx.x & 63;
+  const int x = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+  if (x >= n) return;
+  int I, J;
+  tri_place(n - 1 - x, I, J);   // (the longest first)
+  const int64_t step = blockIdx.y;
+  if (need[step * nsb + I] == 0) return;
+  const gptr<const double> Z = glb(tri) + step * n * 256;
+  const gptr<const double> R = glb(res) + (step * n + tri_block(I, 0)) * 256 + lane;
+  constexpr int U = 4;   // products in flight
+  double a[U][4], z[U][4], z0[4];
+  auto load = [&](int t, int q) {
+    t = min(t, I);
+#pragma unroll
+    for (int s = 0; s < 4; ++s) a[q][s] = R[(int64_t)t * 256 + 64 * s];
+    tri_load(Z + (int64_t)tri_block(t, J) * 256, lane, z[q]);
+  };
+  tri_load(Z + (int64_t)tri_block(I, J) * 256, lane, z0);
+#pragma unroll
+  for (int q = 0; q < U; ++q) load(J + q, q);
+  d4 acc[2] = {d4{0.0, 0.0, 0.0, 0.0}, d4{0.0, 0.0, 0.0, 0.0}};
+  for (int t0 = J; t0 <= I; t0 += U) {
+#pragma unroll
+    for (int q = 0; q < U; ++q) {
+      if (t0 + q <= I) {   // uniform
+#pragma unroll
+        for (int s = 0; s < 4; ++s) acc[s & 1] = gdev::mfma(a[q][s], z[q][s], acc[s & 1]);
+      }
+      load(t0 + U + q, q);
+    }
+  }
+  const d4 c = acc[0] + acc[1];
+  const gptr<double> o = glb(out) + (step * n + tri_block(I, J)) * 256;
+  *(gptr<dv2>)(o + 2 * lane) = dv2{z0[0] + c[0], z0[1] + c[1]};
+  *(gptr<dv2>)(o + 128 + 2 * lane) = dv2{z0[2] + c[2], z0[3] + c[3]};
+}
+
+// ------------------------------------------------------------------ delta = T^-1 c
 
 // Bit i: item i of this lane in a diagonal superblock is in the lower block
 // triangle.
@@ -964,16 +1164,22 @@ ChainPlan chain_plan(int m, int b) {
   p.nsb = (m + p.gb - 1) / p.gb;
   p.ok = p.nsb <= kMaxSuper;
   p.tri = (size_t)tri_block(p.nsb, 0) * 256;
-  p.dinv = (size_t)p.nsb * 256;
+  p.refined = m > b;
+  p.work = (size_t)p.nsb * 256 + (p.refined ? 2 * p.tri + (p.nsb + 1) / 2 : 0);
   return p;
 }
 
 hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
-                                const int32_t* idx, double* tri, double* dinv, int* link,
+                                const int32_t* idx, double* tri, double* work, int* link,
                                 int* status, hipStream_t st) {
   if (!p.ok || nsteps < 1 || nsteps > 65535) return hipErrorInvalidValue;
+  // one block a step (refined = false): its inverse is what the solve uses too
+  double* dinv = work;
+  double* raw = p.refined ? dinv + (size_t)nsteps * p.nsb * 256 : tri;
+  double* res = raw + (size_t)nsteps * p.tri;
+  int* need = reinterpret_cast<int*>(res + (size_t)nsteps * p.tri);
   hipLaunchKernelGGL(chain_diag_kernel, dim3((unsigned)((p.nsb + 3) / 4), (unsigned)nsteps),
-                     dim3(64), 0, st, G, m, b, p.gb, p.nsb, tri, dinv, status);
+                     dim3(64), 0, st, G, m, b, p.gb, p.nsb, raw, dinv, status);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = std::max((size_t)(2 * kPanelWaves + p.nsb) * 256 * sizeof(double),
@@ -985,8 +1191,19 @@ hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps,
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb, (unsigned)nsteps), dim3(64 * kPanelWaves), lds,
-                     st, G, m, p.gb, p.nsb, tri, dinv, idx, link);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb + (p.refined ? 1 : 0), (unsigned)nsteps),
+                     dim3(64 * kPanelWaves), lds, st, G, m, p.gb, p.nsb, raw, dinv, idx, link, tri,
+                     need);
+  e = hipGetLastError();
+  if (e != hipSuccess || !p.refined) return e;
+  const unsigned n = (unsigned)tri_block(p.nsb, 0);
+  hipLaunchKernelGGL(full ? chain_resid_kernel<true> : chain_resid_kernel<false>,
+                     dim3(n, (unsigned)nsteps), dim3(64 * kResWaves), 0, st, G, m, b, p.gb, p.nsb,
+                     raw, need, res);
+  e = hipGetLastError();
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(chain_refine_kernel, dim3((n + 3) / 4, (unsigned)nsteps), dim3(256), 0, st,
+                     p.nsb, raw, need, res, tri);
   return hipGetLastError();
 }
 

@@ -237,14 +237,15 @@ hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, int* status, 
 struct ChainPlan {
   bool ok;            // b <= 16 and at most 32 superblocks
   int gb, nsb;        // rows of a superblock (b floor(16 / b)), superblocks
-  size_t tri, dinv;   // doubles a step: the inverse, and its scratch
+  bool refined;       // the inverse is refined (more than one block a step)
+  size_t tri, work;   // doubles a step: the inverse, and its scratch
 };
 ChainPlan chain_plan(int m, int b);
 // From nsteps Grams (G + k m^2, indices idx + k m): the inverses (tri + k
-// p.tri), links of repeated indices (link + k m) and the pivot check; dinv
-// holds nsteps p.dinv doubles of scratch.
+// p.tri), links of repeated indices (link + k m) and the pivot check; work
+// holds nsteps p.work doubles of scratch.
 hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
-                                const int32_t* idx, double* tri, double* dinv, int* link,
+                                const int32_t* idx, double* tri, double* work, int* link,
                                 int* status, hipStream_t st);
 // delta = T^-1 c of one step from its Y u (modes and scalars as SolveArgs).
 hipError_t launch_chain_delta(const ChainPlan& p, const double* tri, const double* Yu,
