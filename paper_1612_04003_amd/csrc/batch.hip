@@ -446,9 +446,11 @@ __global__ __launch_bounds__(kBT) void batch_step_kernel(const BProb* __restrict
     } else {
       gdev::big_lists(icur, m, ia, ib, tid, kBT);
       __syncthreads();
-      for (int g = 0; g < nsets; ++g)
+      for (int g = 0; g < nsets; ++g) {
         gram_any<FMT>(16, pr.A, pr.ld, k0, k1, g < 2 ? ia + 256 * g : ib + 256 * (g - 2), 256,
-                           g < 2 ? pr.r : nullptr, part + g * pstride);
+                      g < 2 ? pr.r : nullptr, part + g * pstride);
+        __syncthreads();   // the next one fills the LDS that waves still sum Y u from
+      }
     }
     // the slab's group, then (with more than one group) the problem's groups
     const int ngroup = (pr.nslab + kBGroup - 1) / kBGroup;

@@ -212,7 +212,8 @@ __device__ __forceinline__ uint4 lp_load(gptr<const uint8_t> row, int64_t k, int
 // the rows idx[0..m) of the stored codes A (ld in elements), FP32 MFMA
 // accumulation, partial blocks (FP32 MFMA output order) and partial Y u (FP64,
 // decoded codes, row scales not applied) to part.  Rows past m are fed from the first
-// one (their entries are never read).  lds holds LpCfg::LDS bytes.
+// one (their entries are never read).  lds holds LpCfg::LDS bytes, which some waves may
+// still read when others return: a barrier comes before their next use.
 template <int NB, int FMT, int TB = 2048, bool AGENT = false>
 __device__ __forceinline__ void gram_lp_slab(const uint8_t* __restrict__ A, int64_t ld,
                                              int64_t k_begin, int64_t k_end, const int32_t* idx,

@@ -366,3 +366,33 @@ def test_batch_update_pending_at_retirement_is_applied_after_reslicing(gpu_lib):
     for q in probs:
         ro = q["Xc"].T @ q["w"].cpu().numpy() - q["yc"]
         assert np.linalg.norm(q["r"].cpu().numpy() - ro) <= 1e-10 * np.linalg.norm(q["yc"])
+
+
+@pytest.mark.parametrize("dtype", ["bf16", "fp8"])
+@pytest.mark.parametrize("n", [64, 2000, 20011])
+def test_batch_lowp_steps_above_256_rows_exact_sums(gpu_lib, dtype, n):
+    """One step of 257 to 512 rows over whole-number codes (every sum of the Grams and
+    of Y u is exact) ends at the oracle's w to the rounding of its solves; four problems,
+    so that workgroups go from Gram to Gram and from problem to problem."""
+    _say("batch lowp above 256 rows", dtype, n)
+    rng = np.random.default_rng(n)
+    probs = []
+    for b, s in ((16, 32), (16, 17), (8, 48), (12, 25)):
+        d = b * s + 5
+        X = rng.integers(-3, 4, (d, n)).astype(np.float64)
+        y = rng.integers(-8, 9, n).astype(np.float64)
+        code = gpu_lib.BF16 if dtype == "bf16" else gpu_lib.FP8_E4M3
+        view = torch.bfloat16 if dtype == "bf16" else torch.float8_e4m3fn
+        codes = torch.tensor(X, dtype=torch.float32, device=DEV).to(view).contiguous()
+        codes = codes.view(torch.int16 if dtype == "bf16" else torch.uint8)
+        Q = gpu_lib.Quantized(codes, torch.ones(d, dtype=torch.float32, device=DEV), code)
+        assert np.array_equal(Q.dequantize().cpu().numpy(), X)
+        probs.append(dict(X=Q, y=torch.tensor(y, device=DEV), lam=1.0, b=b, s=s, seed=n + b,
+                          H=s, Xc=X, yc=y))
+    act, infos = _run(gpu_lib, probs, [1], monitor_every=0)
+    assert act == 0
+    for q in probs:
+        wo, zo = bcd.primal_bcd(q["Xc"], q["yc"], q["lam"], q["b"], q["s"], q["H"], q["seed"])
+        assert np.linalg.norm(q["w"].cpu().numpy() - wo) <= 1e-11 * np.linalg.norm(wo)
+        ro = zo - q["yc"]
+        assert np.linalg.norm(q["r"].cpu().numpy() - ro) <= 1e-11 * np.linalg.norm(ro)
