@@ -773,13 +773,16 @@ __global__ __launch_bounds__(kStepThreads, TALL ? 2 : 4) void chain_step_kernel(
   // ---- the ragged columns: thread p holds row p's elements
   if (twg) {
     const int rem = (int)(a.cols - nchunk * EPC);
+    // (u is read once, into LDS: the barriers below do not order global memory)
+    if (tid < rem) us[tid] = glb(a.u)[nchunk * EPC + tid];
+    lds_barrier();
     const gptr<const uint8_t> At = glb(a.A);
     const gptr<const uint8_t> row0 = At + (int64_t)ixa[pt] * a.ld * ES;
     const gptr<const uint8_t> row1 = At + (int64_t)ixb[pt] * a.ld * ES;
     double t1 = 0.0;
     for (int e = 0; e < rem; ++e) {
       const int64_t k = nchunk * EPC + e;
-      double un = glb(a.u)[k];
+      double un = us[e];
       if (upd) {
         const double d = tid < m ? dl[tid] : 0.0;
         const double x = tid < m ? C::one(row0, k) : 0.0;

@@ -79,6 +79,35 @@ def test_chain_codes(gpu_lib, dtype, n, pad, b, s):
     assert _rel(w.cpu(), wo) <= (1e-5 if dtype == "bf16" else 1e-3)
 
 
+@pytest.mark.parametrize("dtype,n", [("f64", 3001), ("bf16", 3001), ("bf16", 3007),
+                                     ("fp8", 3009), ("fp8", 3023)])
+@pytest.mark.parametrize("b,s", [(4, 2), (8, 8)])
+def test_chain_ragged_columns(gpu_lib, dtype, n, b, s):
+    """The columns past the last 16-byte chunk (1 to 15 of them): the residual of every
+    one is the iterate's after many steps, in one call and in calls of a step, to the same
+    bits."""
+    d, steps = 48, 30
+    _say("ragged columns", dtype, n, b, s)
+    X, y, _ = synth.gaussian_ridge(d, n, n)
+    A, yd = X.to(DEV), y.to(DEV)
+    Xh = A
+    if dtype != "f64":
+        A = gpu_lib.quantize(A, gpu_lib.BF16 if dtype == "bf16" else gpu_lib.FP8_E4M3)
+        Xh = A.dequantize()
+    w, r = gpu_lib.primal_bcd(A, yd, 0.1, b, s, steps * s, 8)
+    exact = (Xh.t() @ w - yd).cpu()
+    k = n // 16 * 16
+    assert _rel(r[k:].cpu(), exact[k:]) <= 1e-11 and _rel(r.cpu(), exact) <= 1e-11
+    w1, r1 = torch.zeros_like(w), -yd
+    for i in range(steps):
+        gpu_lib.primal_bcd(A, yd, 0.1, b, s, s, 8, w=w1, r=r1, h0=i * s,
+                           flags=gpu_lib.FLAG_STATE_VALID)
+    w2, r2 = torch.zeros_like(w), -yd
+    gpu_lib.primal_bcd(A, yd, 0.1, b, s, steps * s, 8, w=w2, r=r2,
+                       flags=gpu_lib.FLAG_STATE_VALID)
+    assert torch.equal(w1, w2) and torch.equal(r1, r2)
+
+
 def test_chain_repeated_indices_and_recomputation(gpu_lib):
     """Blocks that repeat indices within a step many times over, with exact
     recomputations between steps, monitor points, and the same run in calls."""
