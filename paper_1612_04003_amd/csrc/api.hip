@@ -955,12 +955,12 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
     // their diagonal blocks inverted together, off the solves' chains
     if (pre_inv)
       he = timer.run_on(bs, CABCD_PHASE_SOLVE, [&] {
-        return launch_invert_diag(B.G[buf], nst, mb, b, B.status, bs);
+        return launch_invert_diag(B.G[buf], nst, mb, b, bs);
       });
     if (chain)
       he = timer.run_on(bs, CABCD_PHASE_SOLVE, [&] {
         return launch_chain_prepare(ah.chain, B.G[buf], nst, mb, b, ib, B.tri[buf], B.work,
-                                    B.link[buf], B.status, bs);
+                                    B.link[buf], bs);
       });
     return he;
   };
@@ -1179,7 +1179,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
       sa.pre_inverted = from_ahead && pre_inv ? 1 : 0;
       XScatter xs{};
       if (from_ahead && chain) {
-        xs = XScatter{idx, link, B.delta, m, coord};
+        xs = XScatter{idx, link, B.delta, m, coord, B.status};
         HIP_TRY(timer.run(CABCD_PHASE_SOLVE, [&] {
           return launch_chain_delta(ah.chain, tri, B.Yu, idx, coord, y, m, b, sa.mode, lambda, n,
                                     B.delta, B.status, st);

@@ -12,7 +12,8 @@
 // 16 with the identity:
 //   * chain_diag_kernel: the superblocks on the diagonal (block lower triangular
 //     inside) by Gauss-Jordan elimination, one row per lane; their pivots are
-//     those of the b x b blocks Gamma_j, so a pivot <= 0 is reported as before;
+//     those of the b x b blocks Gamma_j, and a pivot <= 0 or NaN is noted in the
+//     step's links, which report it when the step is run;
 //   * chain_panel_kernel: a first inverse Z by rows, Z_IJ = -(sum_{J<t<=I} Z_It T_tJ)
 //     D_J^-1, one workgroup per superblock row I on the FP64 matrix cores, which
 //     work on Z transposed: an FP64 MFMA result holds item i at row 4 i + lane /
@@ -66,6 +67,7 @@
 namespace cabcd {
 namespace {
 
+using cdev::kLinkBad;
 using cdev::kLinkFirst;
 using cdev::rhs_of;
 using cdev::tri_at;
@@ -82,7 +84,8 @@ __device__ __forceinline__ int block_of(int v, int bm) { return (v * bm) >> 8; }
 // Superblock I of step blockIdx.y: four per wave, one row per lane.
 __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict__ G, int m, int b,
                                                         int gb, int nsb, double* __restrict__ tri,
-                                                        double* __restrict__ dinv, int* status) {
+                                                        double* __restrict__ dinv,
+                                                        int* __restrict__ bad_block) {
   G += (int64_t)blockIdx.y * m * m;
   tri += (int64_t)blockIdx.y * tri_block(nsb, 0) * 256;
   dinv += (int64_t)blockIdx.y * nsb * 256;
@@ -100,8 +103,8 @@ __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict
     e[v] = live && block_of(v, bm) <= bu && v < gb && r0 + v < m ? e[v] : (u == v ? 1.0 : 0.0);
   bool bad = false;
   sdev::gj_rows16<0>(e, u, bad);   // every lane takes part in the row broadcasts
-  if (bad) raise_status(status, DEV_NOTSPD);
   if (I >= nsb) return;
+  if (u == 0) bad_block[(int)blockIdx.y * nsb + I] = bad ? 1 : 0;   // (the same in every lane)
   double* t = tri + (int64_t)tri_block(I, I) * 256;
   double* d = dinv + (int64_t)I * 256 + (u >> 2) * 64 + (u & 3) * 16;   // transposed operand:
 #pragma unroll                                                           // k-slice, lane
@@ -136,7 +139,7 @@ template <bool FULL>
 __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
     const double* __restrict__ G, int m, int gb, int nsb, double* __restrict__ tri,
     const double* __restrict__ dinv, const int32_t* __restrict__ idx, int* __restrict__ link,
-    double* __restrict__ out, int* __restrict__ need) {
+    const int* __restrict__ bad_block, double* __restrict__ out, int* __restrict__ need) {
   extern __shared__ __attribute__((aligned(16))) double zs[];
   const int64_t step = blockIdx.y;
   if (blockIdx.x == gridDim.x - 1) {
@@ -151,7 +154,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
       for (int q = 0; q < p; ++q) first &= ix[q] != i;
       int next = 0;
       for (int q = m - 1; q > p; --q) next = ix[q] == i ? q + 1 : next;
-      link[p] = (first ? kLinkFirst : 0) | next;
+      link[p] = (first ? kLinkFirst : 0) | next |
+                (bad_block[step * nsb + p / gb] != 0 ? kLinkBad : 0);
     }
     return;
   }
@@ -755,7 +759,7 @@ __global__ __launch_bounds__(kStepThreads, TALL ? 2 : 4) void chain_step_kernel(
   if (xwg) {
     if (a.step) {
       if (tid < m && !isfinite(dl[tid])) raise_status(a.status, DEV_NONFINITE);
-      cdev::scatter_delta<kStepThreads>(a.idx, a.link, dl, m, a.x);
+      cdev::scatter_delta<kStepThreads>(a.idx, a.link, dl, m, a.x, a.status);
       __syncthreads();
     }
     if (dots && tid < m) {   // (the dual's right-hand side takes x + y)
@@ -1132,7 +1136,7 @@ __global__ __launch_bounds__(kSoloThreads) void chain_solo_kernel(ChainSolo a,
     // ---- x[idx] += delta: one writer per coordinate
     if (tid < m) {
       if (!isfinite(dl[tid])) raise_status(a.status, DEV_NONFINITE);
-      cdev::scatter_delta<kSoloThreads>(ix, a.link + (int64_t)step * m, dl, m, a.x);
+      cdev::scatter_delta<kSoloThreads>(ix, a.link + (int64_t)step * m, dl, m, a.x, a.status);
     }
     if (owner) __builtin_amdgcn_s_waitcnt(0);   // x is read again after the barrier
     asm volatile("" ::: "memory");
@@ -1168,21 +1172,22 @@ ChainPlan chain_plan(int m, int b) {
   p.ok = p.nsb <= kMaxSuper;
   p.tri = (size_t)tri_block(p.nsb, 0) * 256;
   p.refined = m > b;
-  p.work = (size_t)p.nsb * 256 + (p.refined ? 2 * p.tri + (p.nsb + 1) / 2 : 0);
+  p.work = (size_t)p.nsb * 257 + (p.refined ? 2 * p.tri : 0);
   return p;
 }
 
 hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
                                 const int32_t* idx, double* tri, double* work, int* link,
-                                int* status, hipStream_t st) {
+                                hipStream_t st) {
   if (!p.ok || nsteps < 1 || nsteps > 65535) return hipErrorInvalidValue;
   // one block a step (refined = false): its inverse is what the solve uses too
   double* dinv = work;
-  double* raw = p.refined ? dinv + (size_t)nsteps * p.nsb * 256 : tri;
+  int* bad_block = reinterpret_cast<int*>(dinv + (size_t)nsteps * p.nsb * 256);
+  int* need = bad_block + (size_t)nsteps * p.nsb;
+  double* raw = p.refined ? dinv + (size_t)nsteps * p.nsb * 257 : tri;
   double* res = raw + (size_t)nsteps * p.tri;
-  int* need = reinterpret_cast<int*>(res + (size_t)nsteps * p.tri);
   hipLaunchKernelGGL(chain_diag_kernel, dim3((unsigned)((p.nsb + 3) / 4), (unsigned)nsteps),
-                     dim3(64), 0, st, G, m, b, p.gb, p.nsb, raw, dinv, status);
+                     dim3(64), 0, st, G, m, b, p.gb, p.nsb, raw, dinv, bad_block);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = std::max((size_t)(2 * kPanelWaves + p.nsb) * 256 * sizeof(double),
@@ -1195,8 +1200,8 @@ hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps,
     if (e != hipSuccess) return e;
   }
   hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb + (p.refined ? 1 : 0), (unsigned)nsteps),
-                     dim3(64 * kPanelWaves), lds, st, G, m, p.gb, p.nsb, raw, dinv, idx, link, tri,
-                     need);
+                     dim3(64 * kPanelWaves), lds, st, G, m, p.gb, p.nsb, raw, dinv, idx, link,
+                     bad_block, tri, need);
   e = hipGetLastError();
   if (e != hipSuccess || !p.refined) return e;
   const unsigned n = (unsigned)tri_block(p.nsb, 0);

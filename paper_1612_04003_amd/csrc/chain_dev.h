@@ -9,17 +9,21 @@ namespace cabcd {
 namespace cdev {
 
 // Link word of row p of an outer step: bit 16 set when no earlier row has the
-// same index; low 16 bits: 1 + the next row with the same index (0: none).
-constexpr int kLinkFirst = 1 << 16;
+// same index; bit 17 when a block of its superblock is not positive definite; low 16
+// bits: 1 + the next row with the same index (0: none).
+constexpr int kLinkFirst = 1 << 16, kLinkBad = 1 << 17;
 
 // x[idx] += delta for one step by one workgroup of T threads, a single writer
 // per coordinate: the first row of an index adds that index's rows in row order.
+// What the inversions ahead found in the step's blocks is reported here, as a run
+// may stop before a step whose Gram was computed ahead.
 template <int T>
 __device__ __forceinline__ void scatter_delta(const int32_t* __restrict__ idx,
                                               const int* __restrict__ link, const double* delta,
-                                              int m, double* __restrict__ x) {
+                                              int m, double* __restrict__ x, int* status) {
   for (int p = threadIdx.x; p < m; p += T) {
     int l = link[p];
+    if ((l & kLinkBad) != 0) raise_status(status, DEV_NOTSPD);
     if ((l & kLinkFirst) == 0) continue;
     const int i = idx[p];
     double v = x[i] + delta[p];

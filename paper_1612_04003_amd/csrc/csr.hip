@@ -289,7 +289,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_scatter_kernel(
     const double* __restrict__ vals, const int32_t* __restrict__ idx, int64_t m,
     const double* __restrict__ v, double gamma, double* __restrict__ out, XScatter xs) {
   if (xs.x != nullptr && blockIdx.x == gridDim.x - 1) {
-    cdev::scatter_delta<kCsrThreads>(xs.idx, xs.link, xs.delta, xs.m, xs.x);
+    cdev::scatter_delta<kCsrThreads>(xs.idx, xs.link, xs.delta, xs.m, xs.x, xs.status);
     return;
   }
   const int lane = threadIdx.x & 63;
@@ -435,7 +435,7 @@ __global__ __launch_bounds__(kCsrThreads) void csr_step_update_kernel(CsrStep a)
       }
     }
     __syncthreads();
-    cdev::scatter_delta<kCsrThreads>(a.idx, a.link, dl, a.m, a.x);
+    cdev::scatter_delta<kCsrThreads>(a.idx, a.link, dl, a.m, a.x, a.status);
     return;
   }
   const int p = (int)blockIdx.x * kCsrWaves + wave;

@@ -720,7 +720,7 @@ __global__ __launch_bounds__(kT) void split_update_kernel(UpdateArgs u) {
   const int lane = threadIdx.x & 63;
   int blk = blockIdx.x;
   if (u.xs.x != nullptr && blk == (int)gridDim.x - 1) {
-    cdev::scatter_delta<kT>(u.xs.idx, u.xs.link, u.xs.delta, u.xs.m, u.xs.x);
+    cdev::scatter_delta<kT>(u.xs.idx, u.xs.link, u.xs.delta, u.xs.m, u.xs.x, u.xs.status);
     return;
   }
   if (blk < u.bh) {   // heavy: one wave per slot

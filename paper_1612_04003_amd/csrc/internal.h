@@ -227,9 +227,9 @@ constexpr size_t kSolveMaxLds = 160 * 1024;
 size_t solve_lds_bytes(int m, int b);   // dynamic LDS of one solve launch
 hipError_t launch_solve(const SolveArgs& a, hipStream_t st);
 // Inverts in place the diagonal b x b blocks (Gamma_j, b <= 16) of nsteps
-// consecutive m x m Grams (s = m / b blocks each), as the solve would; a pivot
-// that is not positive sets *status to "not positive definite".
-hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, int* status, hipStream_t st);
+// consecutive m x m Grams (s = m / b blocks each), as the solve would; a block with a
+// pivot that is not positive gets a NaN first entry, which the solve reports.
+hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, hipStream_t st);
 
 // ------------------------------------------------------------------ chain of steps
 // Outer steps whose Grams are computed ahead (chain.hip): the inverse of each
@@ -242,11 +242,11 @@ struct ChainPlan {
 };
 ChainPlan chain_plan(int m, int b);
 // From nsteps Grams (G + k m^2, indices idx + k m): the inverses (tri + k
-// p.tri), links of repeated indices (link + k m) and the pivot check; work
-// holds nsteps p.work doubles of scratch.
+// p.tri) and links of repeated indices with the pivot check (link + k m); work holds
+// nsteps p.work doubles of scratch.
 hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps, int m, int b,
                                 const int32_t* idx, double* tri, double* work, int* link,
-                                int* status, hipStream_t st);
+                                hipStream_t st);
 // delta = T^-1 c of one step from its Y u (modes and scalars as SolveArgs).
 hipError_t launch_chain_delta(const ChainPlan& p, const double* tri, const double* Yu,
                               const int32_t* idx, const double* x, const double* y, int m, int b,
@@ -320,6 +320,7 @@ struct XScatter {
   const double* delta;
   int m;
   double* x;
+  int* status;
 };
 
 // ------------------------------------------------------------------ low precision

@@ -60,10 +60,11 @@ hipError_t launch_t(const SolveArgs& a, hipStream_t st) {
 
 // The diagonal blocks of nsteps Grams inverted ahead of their solves, with the
 // solve's own Gauss-Jordan code and padding: BP <= 8 one block per lane,
-// BP = 16 four blocks per wave (one row per lane).
+// BP = 16 four blocks per wave (one row per lane).  A run may stop before a step whose
+// Gram was computed ahead, so a bad pivot is left to the step's solve to report: the
+// inverse gets a NaN first entry.
 template <int BP>
-__global__ __launch_bounds__(64) void invert_diag_kernel(double* G, int m, int b, int s,
-                                                          int* status) {
+__global__ __launch_bounds__(64) void invert_diag_kernel(double* G, int m, int b, int s) {
   G += (int64_t)blockIdx.y * m * m;
   const int lane = threadIdx.x;
   bool bad = false;
@@ -79,6 +80,7 @@ __global__ __launch_bounds__(64) void invert_diag_kernel(double* G, int m, int b
 #pragma unroll
         for (int v = 0; v < BP; ++v) e[u][v] = u < b && v < b ? at(j, u, v) : (u == v ? 1.0 : 0.0);
       gj_lane<BP>(e, bad);
+      if (bad) e[0][0] = __builtin_nan("");
 #pragma unroll
       for (int u = 0; u < BP; ++u)
 #pragma unroll
@@ -94,7 +96,8 @@ __global__ __launch_bounds__(64) void invert_diag_kernel(double* G, int m, int b
     double e[16];
 #pragma unroll
     for (int v = 0; v < 16; ++v) e[v] = live && v < b ? at(j, u, v) : (u == v ? 1.0 : 0.0);
-    gj_rows16<0>(e, u, bad);
+    gj_rows16<0>(e, u, bad);   // bad: the same in a block's sixteen lanes
+    if (bad && u == 0) e[0] = __builtin_nan("");
     if (live) {
 #pragma unroll
       for (int v = 0; v < 16; ++v)
@@ -103,29 +106,28 @@ __global__ __launch_bounds__(64) void invert_diag_kernel(double* G, int m, int b
   } else {
     static_assert(BP <= 16, "blocks up to 16 x 16");
   }
-  if (bad) raise_status(status, DEV_NOTSPD);
 }
 
 template <int BP>
-hipError_t launch_inv(double* G, int nsteps, int m, int b, int s, int* status, hipStream_t st) {
+hipError_t launch_inv(double* G, int nsteps, int m, int b, int s, hipStream_t st) {
   const int per = BP <= 8 ? 64 : 4;   // blocks per workgroup
   hipLaunchKernelGGL(invert_diag_kernel<BP>, dim3((unsigned)((s + per - 1) / per), (unsigned)nsteps),
-                     dim3(64), 0, st, G, m, b, s, status);
+                     dim3(64), 0, st, G, m, b, s);
   return hipGetLastError();
 }
 
 }  // namespace
 
-hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, int* status, hipStream_t st) {
+hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, hipStream_t st) {
   if (nsteps < 1 || nsteps > 65535 || b < 1 || b > 16 || m % b != 0)
     return hipErrorInvalidValue;
   const int s = m / b;
   switch (pow2_at_least(b)) {
-    case 1: return launch_inv<1>(G, nsteps, m, b, s, status, st);
-    case 2: return launch_inv<2>(G, nsteps, m, b, s, status, st);
-    case 4: return launch_inv<4>(G, nsteps, m, b, s, status, st);
-    case 8: return launch_inv<8>(G, nsteps, m, b, s, status, st);
-    default: return launch_inv<16>(G, nsteps, m, b, s, status, st);
+    case 1: return launch_inv<1>(G, nsteps, m, b, s, st);
+    case 2: return launch_inv<2>(G, nsteps, m, b, s, st);
+    case 4: return launch_inv<4>(G, nsteps, m, b, s, st);
+    case 8: return launch_inv<8>(G, nsteps, m, b, s, st);
+    default: return launch_inv<16>(G, nsteps, m, b, s, st);
   }
 }
 

@@ -345,10 +345,12 @@ __device__ __forceinline__ void solve_block(const SolveArgs& a, double* sm) {
   // chains are independent, so their latencies overlap.  Larger blocks have
   // enough independent work per round and no registers to spare.
   // PRE: launch_invert_diag has inverted them already (a compile-time choice:
-  // a runtime branch here changed the register allocation of the chain)
+  // a runtime branch here changed the register allocation of the chain), a NaN first
+  // entry where a pivot was bad
   bool bad = false;
-  if constexpr (PRE)
-    ;
+  if constexpr (PRE) {
+    for (int j = tid; j < s; j += THREADS) bad |= isnan(Gi[(size_t)j * C::GS]);
+  }
   else if constexpr (BP <= 8 && THREADS <= 256)
     invert_per_lane<BP, THREADS>(Gi, s, tid, bad);
   else if constexpr (BP == 16)

@@ -288,3 +288,46 @@ def test_nearly_collinear_rows(gpu_lib, kind, rows, cols, b, s, steps, rho, lam)
     _say("  " + ", ".join(f"{e:.1e} = {e / unit:.1f} x {unit:.1e}" for e, unit in errs))
     for e, unit in errs:
         assert e <= 20 * unit
+
+
+# one workgroup for runs of steps, a launch a step (8 MiB of rows and less, and more), sparse
+# steps in two launches and three, the split Gram, and the solves with blocks inverted ahead
+# (codes on odd boundaries)
+@pytest.mark.parametrize("kind,n,b,s", [("dense", 256, 4, 8), ("dense", 1024, 8, 1),
+                                        ("dense", 1024, 16, 8), ("dense", 40000, 4, 8),
+                                        ("csr", 1024, 4, 8), ("csr", 1024, 8, 16),
+                                        ("csr", 1024, 8, 32), ("bf16", 1001, 4, 8),
+                                        ("bf16", 1001, 16, 4)])
+def test_block_of_a_step_that_is_not_run(gpu_lib, kind, n, b, s):
+    """Rows 62 and 63 make a block that is not positive definite.  A run that its tolerance
+    stops before the step that draws it ends well, though that step's Gram was
+    computed ahead; a run that reaches it reports the block."""
+    _say("block not run", kind, n, b, s)
+    d, steps = 64, 4
+    rng = np.random.default_rng(4)
+    X = rng.standard_normal((d, n))
+    y = rng.standard_normal(n)
+    # their Gram overflows; nothing else has anything in column 0
+    X[:, 0] = y[0] = 0.0
+    X[62, 0], X[63, 0] = (1e30, -1e30) if kind == "bf16" else (1e200, -1e200)
+    idx = np.concatenate([rng.permutation(62)[:b] for _ in range(steps * s)]).astype(np.int32)
+    idx = idx.reshape(-1, b)
+    idx[2 * s, :min(b, 2)] = (62, 63)[:min(b, 2)]
+    if kind == "csr":
+        A = gpu_lib.CSR.from_scipy(scipy.sparse.csr_matrix(X), DEV)
+    elif kind == "bf16":
+        Q = gpu_lib.quantize(torch.tensor(X, device=DEV), gpu_lib.BF16)
+        A = gpu_lib.Quantized(Q.codes.contiguous(), Q.scales, Q.dtype)
+    else:
+        A = torch.tensor(X, device=DEV)
+    ix, yd = torch.tensor(idx.ravel(), device=DEV), torch.tensor(y, device=DEV)
+    stats = {}
+    w, r = gpu_lib.primal_bcd(A, yd, 0.1, b, s, steps * s, 0, explicit_idx=ix, tol=1e6,
+                              check_every=2, stats=stats)
+    assert stats["h"] == 2 * s
+    Xd = X[:62] if kind != "bf16" else Q.dequantize().cpu().numpy()[:62]
+    wo, _ = bcd.primal_bcd(Xd, y, 0.1, b, s, 2 * s, 0, explicit_idx=idx)
+    assert _rel(w[:62].cpu(), wo) <= (1e-10 if kind != "bf16" else 1e-4)
+    with pytest.raises(gpu_lib.CabcdError) as e:
+        gpu_lib.primal_bcd(A, yd, 0.1, b, s, steps * s, 0, explicit_idx=ix)
+    assert e.value.status == gpu_lib.ENOTSPD
