@@ -33,8 +33,15 @@
  * Workspace.  Scratch memory is taken from a per-device pool that the library
  * grows with hipMalloc and keeps until process exit, unless opts->workspace is
  * given (then nothing is allocated and a too small workspace is CABCD_ENOMEM;
- * cabcd_workspace_bytes() gives the size).  Concurrent calls on one device
- * that use the library pool must be serialised by the caller.
+ * cabcd_workspace_bytes() gives the size).  Some smaller workspaces are enough
+ * for other forms of the same steps, with other rounding: below that size the
+ * block solves of steps whose Grams are computed ahead run inside the steps,
+ * and CSR steps of 256 to 512 rows take the split Gram (and the solves inside
+ * the steps) where its scratch fits past the step buffers, else the row-pair one;
+ * a workspace of that size or more holds the block inverses too, and the split
+ * Gram's scratch past them or, if only one of the two fits, that scratch.
+ * Concurrent calls on one device that use the library pool must be serialised
+ * by the caller.
  *
  * Errors.  Every entry point returns a cabcd_status; argument errors are found
  * before anything is enqueued.  cabcd_last_error() returns a thread-local

@@ -824,10 +824,26 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
     if (sbytes > kSplitBudget) {
       split = false;   // rows too long for the per-step entry tables
     } else if (o.workspace != nullptr) {
-      // the split scratch starts at the first 256-byte boundary past `need`
-      const uintptr_t w0 = reinterpret_cast<uintptr_t>(o.workspace);
-      const uintptr_t s0 = (w0 + need + 255) & ~(uintptr_t)255;
-      if (s0 + 2 * sbytes <= w0 + o.workspace_bytes) sp = reinterpret_cast<void*>(s0);
+      // the split scratch starts at the first 256-byte boundary past the step buffers
+      auto place = [&](size_t used) -> void* {
+        const uintptr_t w0 = reinterpret_cast<uintptr_t>(o.workspace);
+        const uintptr_t s0 = (w0 + used + 255) & ~(uintptr_t)255;
+        return s0 + 2 * sbytes <= w0 + o.workspace_bytes ? reinterpret_cast<void*>(s0) : nullptr;
+      };
+      sp = place(need);
+      if (sp == nullptr && ah.chain.ok) {
+        // room for the chain's buffers or the split Gram's, not for both: the split Gram
+        // (its updates have one writer a column, the row-pair path's are atomic).  What
+        // csr_split_prepare wrote stays: it is first in either layout.
+        const Ahead plain = plan_ahead(M, b, sb_full, false);
+        StepBuffers P{};
+        Carve again{static_cast<char*>(ws)};
+        sp = place(layout(again, P, M, plain, b, s, rtmp_len, checks));
+        if (sp != nullptr) {
+          ah = plain;
+          B = P;
+        }
+      }
       split = sp != nullptr;
     } else {
       e = pool_get(2 * sbytes, &sp, 1);

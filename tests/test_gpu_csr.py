@@ -273,3 +273,24 @@ def test_csr_dual_bench_size(gpu_lib, zipf_bench, s, H):
     e_a, e_w = _rel(a.cpu(), ao), _rel(w.cpu(), wo)
     _say(f"  rel err alpha {e_a:.2e}, w {e_w:.2e}")
     assert e_a <= 1e-10 and e_w <= 1e-10
+
+
+@pytest.mark.parametrize("b,s", [(16, 16), (8, 32)])
+def test_csr_workspace_for_the_chain_or_the_split_gram(gpu_lib, b, s):
+    """A caller workspace of cabcd_workspace_bytes has room for the block inverses or for
+    the split Gram's scratch, not for both: the steps keep the split Gram, whose updates
+    are the same bits in every run (the row-pair path adds them with atomics)."""
+    _say("csr workspace", b, s)
+    rng = np.random.default_rng(b)
+    n, d, H = 900, 48, 6 * s   # (few columns: the split scratch is the smaller one)
+    S = scipy.sparse.random(n, d, 0.4, format="csr", random_state=np.random.RandomState(b),
+                            data_rvs=rng.standard_normal)
+    y = rng.standard_normal(n)
+    A, yd = gpu_lib.CSR.from_scipy(S, DEV), torch.tensor(y, device=DEV)
+    ws = torch.empty(gpu_lib.workspace_bytes(A, b, s), dtype=torch.uint8, device=DEV)
+    runs = [gpu_lib.dual_bcd(A, yd, 1e-2, b, s, H, 3, workspace=ws) for _ in range(4)]
+    ao, wo = bcd.dual_bcd(S.T.tocsc(), y, 1e-2, b, s, H, 3)
+    for a, w in runs:
+        assert np.linalg.norm(a.cpu().numpy() - ao) <= 1e-10 * np.linalg.norm(ao)
+        assert np.linalg.norm(w.cpu().numpy() - wo) <= 1e-10 * np.linalg.norm(wo)
+        assert torch.equal(a, runs[0][0]) and torch.equal(w, runs[0][1])
