@@ -65,16 +65,17 @@ struct BProb {                     // constant per problem (device copy)
   int64_t H;                       // inner-iteration budget (INT64_MAX: none)
   int64_t chunk;                   // columns per slab
   int b, s, bp, nb;
-  int nslab, naux;                 // slabs of a round, of the monitor passes
-  int sets, pad;                   // partial sets per slab (1; above 256 rows 4 or 6)
-  int64_t achunk;                  // columns of a monitor slab
+  int nslab, sets;                 // slabs of a round, partial sets per slab (1; above 256
+                                   // rows 4 or 6)
+  int naux[2];                     // slabs of the exact monitors and of the other passes
+  int64_t achunk[2];               // their columns
   int32_t* ix;                     // 2 x s b: blocks of the step (parity of its number)
   int* garrive;                    // slab arrivals by group in the current launch
   double* partials;                // nslab x sets x (nblk*256 + 16 nb)
   double* G;                       // (s b)^2
   double* Yu;                      // s b
   double* delta;                   // s b: the last step's delta
-  double* objp;                    // naux partial sums of r^2
+  double* objp;                    // partial sums of r^2, one a monitor slab
 };
 
 struct BState {                    // mutable per problem
@@ -532,6 +533,7 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
   __shared__ double red[kBT / 64];
   __shared__ int ctl[2];
   __shared__ __attribute__((aligned(16))) double part[kAuxLds<FMT>];
+  constexpr int L = MODE == kAuxExact ? 0 : 1;   // which slabs
   const int tid = threadIdx.x;
 
   for (int it = next_item(Q, ctl); it < nitems; it = next_item(Q, ctl)) do {
@@ -541,8 +543,8 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
     const int fresh = uni(st->fresh);
     const int mp = uni(st->m_prev);
     if (MODE == kAuxExact ? fresh == 2 : MODE == kAuxFlush ? mp == 0 : fresh != 0) break;
-    const int64_t k0 = (int64_t)item.slab * pr.achunk;
-    const int64_t k1 = std::min(pr.n, k0 + pr.achunk);
+    const int64_t k0 = (int64_t)item.slab * pr.achunk[L];
+    const int64_t k1 = std::min(pr.n, k0 + pr.achunk[L]);
     double ss = 0.0;
     if (MODE == kAuxExact) {
       ss = rows_dot<FMT>(pr, k0, k1, nullptr, pr.w, (int)pr.d, pr.y, -1.0, part, kAuxLds<FMT>);
@@ -562,20 +564,16 @@ __global__ __launch_bounds__(kBT) void batch_aux_kernel(const BProb* __restrict_
       ss = block_sum(ss, red);
       if (tid == 0) gdev::put<true>(glb(pr.objp) + item.slab, ss);
     }
-    if (!arrive_last(&st->arrive, pr.naux, ctl + 1)) break;
+    if (!arrive_last(&st->arrive, pr.naux[L], ctl + 1)) break;
     if (MODE != kAuxFlush) {
       double ww = 0.0;
       const gptr<const double> wg = glb(pr.w);
       for (int64_t i = tid; i < pr.d; i += kBT) ww = fma(wg[i], wg[i], ww);
       ww = block_sum(ww, red);
+      double rr = 0.0;   // by the whole workgroup: there may be thousands of slabs
+      for (int q = tid; q < pr.naux[L]; q += kBT) rr += gdev::get_agent(glb(pr.objp) + q);
+      rr = block_sum(rr, red);
       if (tid == 0) {
-        double rr = 0.0;
-        for (int q = 0; q < pr.naux; q += 8) {   // eight loads in flight
-          double v[8];
-          for (int j = 0; j < 8; ++j)
-            v[j] = gdev::get_agent(glb(pr.objp) + std::min(q + j, pr.naux - 1));
-          for (int j = 0; j < 8; ++j) rr += q + j < pr.naux ? v[j] : 0.0;
-        }
         const double f = rr / (2.0 * (double)pr.n) + 0.5 * pr.lambda * ww;
         st->obj = f;
         if (!isfinite(f)) raise_status(&st->status, DEV_NONFINITE);
@@ -626,6 +624,14 @@ constexpr double kRoundFixed = 10e-6;
 // Bytes of X in one item of an exact monitor (32 problems, 2.5 GB: 0.549 ms at 128
 // KiB, 0.512 at 256, 0.503 at 1 MiB, 0.568 at 4 MiB).
 constexpr int64_t kAuxBytes = 1 << 20;
+// Of the step's rows and r in one item of the other passes: eight items a CU, within
+// these.  An item costs some microseconds beside its bytes.  (Eight rounds with a
+// maintained monitor each, us: 4 problems of 1024 x 2^19, 8 rows, items of 256 KiB 983,
+// 512 KiB 910, 1 MiB 851, as the exact monitors' items 5908; 32 of 512 x 65536, 128
+// rows, 256 KiB 12618, 1 MiB 9611; 3 of 100 x 2^20, 256 rows, 256 KiB 45127, 1 MiB 39723,
+// 2.6 MB 38826.)
+constexpr int64_t kAuxStepMin = 512 << 10, kAuxStepMax = 4 << 20;
+constexpr int kAuxItemsPerCu = 8;
 constexpr int kGraphMaxRounds = 64;   // rounds of one captured monitor period, at most
 constexpr int kReplanRounds = 32;     // rounds between checks for re-slicing, about
 
@@ -636,12 +642,15 @@ int tile_cols(int nb, int dtype) {
   return dtype == CABCD_F64 ? 256 / nb : (kBLpTile / nb) / elem_bytes(dtype);
 }
 
-// Columns of a monitor item: units of 64 16-byte chunks, as many as kAuxBytes of the
-// d rows hold.  (With the step's slabs as items an exact monitor of 32 problems, 2.5
-// GB, took 0.97 ms: items of up to 17 MB, whose tail ran on a few CUs.)
-int64_t aux_chunk(int64_t d, int dtype) {
+// Columns of a monitor item of n columns of `col_bytes`: units of 64 16-byte chunks, as
+// many as `bytes` hold, of equal items.  (With the step's slabs as items an exact monitor
+// of 32 problems, 2.5 GB, took 0.97 ms: items of up to 17 MB, whose tail ran on a few
+// CUs.)
+int64_t aux_chunk(int64_t n, int64_t col_bytes, int dtype, int64_t bytes) {
   const int64_t unit = 64 * 16 / elem_bytes(dtype);
-  return unit * std::max<int64_t>(1, kAuxBytes / (d * 1024));
+  const int64_t most = unit * std::max<int64_t>(1, bytes / (col_bytes * unit));
+  const int64_t slabs = (n + most - 1) / most;
+  return (n + slabs * unit - 1) / (slabs * unit) * unit;
 }
 
 // CU-seconds of one problem's slabs in one round (Gram of the padded rows and
@@ -754,13 +763,13 @@ struct cabcd_batch_plan {
   cabcd::BProb* dP = nullptr;
   cabcd::BState* dS = nullptr;
   cabcd::BItem* dI = nullptr;    // slabs of a round
-  cabcd::BItem* dIa = nullptr;   // slabs of a monitor pass
+  cabcd::BItem* dIa[2] = {};     // slabs of an exact monitor, of the other passes
   cabcd::BQueue* dQ = nullptr;
   void* mem = nullptr;
-  int nitems = 0, naux = 0;
+  int nitems = 0, naux[2] = {};
   int area = 0;            // doubles of the step kernel's shared Gram/solve area
   size_t step_lds = 0;
-  int grid_step = 1, grid_aux = 1;
+  int grid_step = 1, grid_aux[2] = {1, 1};
   int monitor_every = 4;
   int cheap_monitors = 0;  // maintained-residual monitor points between exact ones
   uint32_t flags = 0;
@@ -793,8 +802,9 @@ hipError_t launch_step_t(cabcd_batch_plan* B, hipStream_t st) {
 
 template <int MODE, int FMT>
 hipError_t launch_aux_t(cabcd_batch_plan* B, hipStream_t st) {
-  hipLaunchKernelGGL((batch_aux_kernel<MODE, FMT>), dim3(B->grid_aux), dim3(kBT), 0, st, B->dP,
-                     B->dS, B->dIa, B->naux, B->dQ);
+  constexpr int L = MODE == kAuxExact ? 0 : 1;
+  hipLaunchKernelGGL((batch_aux_kernel<MODE, FMT>), dim3(B->grid_aux[L]), dim3(kBT), 0, st,
+                     B->dP, B->dS, B->dIa[L], B->naux[L], B->dQ);
   return hipGetLastError();
 }
 
@@ -972,15 +982,27 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->nitems = (int)items.size();
   B->cus = cus;
   B->items_cap = std::max(B->nitems, 4 * cus + 2 * P);
-  std::vector<BItem> aux;
-  std::vector<int64_t> achunk(P);
-  std::vector<int> naux(P);
-  for (int p : order) {
-    achunk[p] = aux_chunk(pb[p].X.rows, B->dtype);
-    naux[p] = (int)((pb[p].X.cols + achunk[p] - 1) / achunk[p]);
-    for (int q = 0; q < naux[p]; ++q) aux.push_back(BItem{p, q});
+  std::vector<BItem> aux[2];
+  std::vector<int64_t> achunk[2];
+  std::vector<int> naux[2];
+  const int es = elem_bytes(B->dtype);
+  auto step_bytes = [&](int p) { return (int64_t)best[p].b * best[p].s * es + 16; };   // a column
+  int64_t all = 0;
+  for (int p = 0; p < P; ++p) all += pb[p].X.cols * step_bytes(p);
+  const int64_t step_item =
+      std::min(kAuxStepMax, std::max(kAuxStepMin, all / (kAuxItemsPerCu * (int64_t)cus)));
+  for (int l = 0; l < 2; ++l) {
+    achunk[l].resize(P);
+    naux[l].resize(P);
+    for (int p : order) {
+      const int64_t n = pb[p].X.cols;
+      achunk[l][p] = l == 0 ? aux_chunk(n, pb[p].X.rows * es, B->dtype, kAuxBytes)
+                            : aux_chunk(n, step_bytes(p), B->dtype, step_item);
+      naux[l][p] = (int)((pb[p].X.cols + achunk[l][p] - 1) / achunk[l][p]);
+      for (int q = 0; q < naux[l][p]; ++q) aux[l].push_back(BItem{p, q});
+    }
+    B->naux[l] = (int)aux[l].size();
   }
-  B->naux = (int)aux.size();
 
   // Workspace and device copies.  The pool holds the partials of re-sliced
   // plans: as much as the first plan's, plus the largest slab set of one
@@ -990,7 +1012,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   add(sizeof(BProb) * P);
   add(sizeof(BState) * P);
   add(sizeof(BItem) * B->items_cap);
-  add(sizeof(BItem) * B->naux);
+  for (int l = 0; l < 2; ++l) add(sizeof(BItem) * B->naux[l]);
   add(sizeof(BQueue));
   int area = 0;
   size_t pool = 0;
@@ -1001,7 +1023,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     add(sizeof(double) * sb * sb);
     add(sizeof(double) * sb);
     add(sizeof(double) * sb);
-    add(sizeof(double) * naux[p]);
+    add(sizeof(double) * std::max(naux[0][p], naux[1][p]));
     add(sizeof(int32_t) * 2 * sb);
     add(sizeof(int) * kGroups);
     area = std::max<int>(area, (int)((solve_lds_bytes(sb, best[p].b) + 7) / 8));
@@ -1032,7 +1054,7 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->dP = ws.take<BProb>(P);
   B->dS = ws.take<BState>(P);
   B->dI = ws.take<BItem>(B->items_cap);
-  B->dIa = ws.take<BItem>(B->naux);
+  for (int l = 0; l < 2; ++l) B->dIa[l] = ws.take<BItem>(B->naux[l]);
   B->dQ = ws.take<BQueue>(1);
   B->pool = ws.take<double>(B->pool_doubles);
   B->probs.resize(P);
@@ -1059,15 +1081,16 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
     o.bp = pow2_at_least(o.b);
     o.nb = nb_of(sb);
     o.sets = sets_of(sb);
-    o.naux = naux[p];
-    o.achunk = achunk[p];
+    for (int l = 0; l < 2; ++l) {
+      o.naux[l] = naux[l][p];
+      o.achunk[l] = achunk[l][p];
+    }
     o.nslab = best[p].nslab;
-    o.pad = 0;
     o.partials = ws.take<double>((size_t)o.nslab * slab_doubles(sb));
     o.G = ws.take<double>((size_t)sb * sb);
     o.Yu = ws.take<double>(sb);
     o.delta = ws.take<double>(sb);
-    o.objp = ws.take<double>(o.naux);
+    o.objp = ws.take<double>(std::max(o.naux[0], o.naux[1]));
     o.ix = ws.take<int32_t>(2 * sb);
     o.garrive = ws.take<int>(kGroups);
     BATCH_HIP(hipMemsetAsync(o.garrive, 0, sizeof(int) * kGroups, st));
@@ -1080,8 +1103,9 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   BATCH_HIP(hipMemcpyAsync(B->dS, S.data(), sizeof(BState) * P, hipMemcpyHostToDevice, st));
   BATCH_HIP(hipMemcpyAsync(B->dI, items.data(), sizeof(BItem) * items.size(),
                            hipMemcpyHostToDevice, st));
-  BATCH_HIP(hipMemcpyAsync(B->dIa, aux.data(), sizeof(BItem) * aux.size(),
-                           hipMemcpyHostToDevice, st));
+  for (int l = 0; l < 2; ++l)
+    BATCH_HIP(hipMemcpyAsync(B->dIa[l], aux[l].data(), sizeof(BItem) * aux[l].size(),
+                             hipMemcpyHostToDevice, st));
   BQueue q0{0, 0};
   BATCH_HIP(hipMemcpyAsync(B->dQ, &q0, sizeof q0, hipMemcpyHostToDevice, st));
 
@@ -1095,7 +1119,8 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   B->grid_step = std::max(1, std::min(B->nitems, B->occ_step * cus));
   BATCH_HIP(hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, aux_kernel_ptr(B->dtype), kBT, 0));
   B->occ_aux = std::max(occ, 1);
-  B->grid_aux = std::max(1, std::min(B->naux, B->occ_aux * cus));
+  for (int l = 0; l < 2; ++l)
+    B->grid_aux[l] = std::max(1, std::min(B->naux[l], B->occ_aux * cus));
   B->plan_active = P;
 
   hipLaunchKernelGGL(batch_first_blocks_kernel, dim3(P), dim3(kBT), 0, st, B->dP);
@@ -1198,21 +1223,24 @@ cabcd_status replan(cabcd_batch_plan* B, hipStream_t st) {
     for (int q = 0; q < o.nslab; ++q) items.push_back(BItem{act[i], q});
   }
   // monitor passes keep a retired problem while its last update is pending
-  std::vector<BItem> aux;
-  for (int p = 0; p < B->P; ++p)
-    if (S[p].active || S[p].m_prev > 0)
-      for (int q = 0; q < B->probs[p].naux; ++q) aux.push_back(BItem{p, q});
+  std::vector<BItem> aux[2];
+  for (int l = 0; l < 2; ++l) {
+    for (int p = 0; p < B->P; ++p)
+      if (S[p].active || S[p].m_prev > 0)
+        for (int q = 0; q < B->probs[p].naux[l]; ++q) aux[l].push_back(BItem{p, q});
+    B->naux[l] = (int)aux[l].size();
+    B->grid_aux[l] = std::max(1, std::min(B->naux[l], B->occ_aux * B->cus));
+  }
   B->nitems = (int)items.size();
-  B->naux = (int)aux.size();
   B->grid_step = std::max(1, std::min(B->nitems, B->occ_step * B->cus));
-  B->grid_aux = std::max(1, std::min(B->naux, B->occ_aux * B->cus));
   B->plan_active = (int)act.size();
   BATCH_HIP(hipMemcpyAsync(B->dP, B->probs.data(), sizeof(BProb) * B->P, hipMemcpyHostToDevice,
                            st));
   BATCH_HIP(hipMemcpyAsync(B->dI, items.data(), sizeof(BItem) * items.size(),
                            hipMemcpyHostToDevice, st));
-  BATCH_HIP(hipMemcpyAsync(B->dIa, aux.data(), sizeof(BItem) * aux.size(),
-                           hipMemcpyHostToDevice, st));
+  for (int l = 0; l < 2; ++l)
+    BATCH_HIP(hipMemcpyAsync(B->dIa[l], aux[l].data(), sizeof(BItem) * aux[l].size(),
+                             hipMemcpyHostToDevice, st));
   BATCH_HIP(hipStreamSynchronize(st));
   return capture(B);
 }

@@ -396,3 +396,24 @@ def test_batch_lowp_steps_above_256_rows_exact_sums(gpu_lib, dtype, n):
         assert np.linalg.norm(q["w"].cpu().numpy() - wo) <= 1e-11 * np.linalg.norm(wo)
         ro = zo - q["yc"]
         assert np.linalg.norm(q["r"].cpu().numpy() - ro) <= 1e-11 * np.linalg.norm(ro)
+
+
+@pytest.mark.parametrize("d,n,b,s", [(1024, 66001, 8, 16), (12, 400001, 4, 2), (300, 30001, 16, 16)])
+def test_batch_monitors_of_many_slabs(gpu_lib, d, n, b, s):
+    """Objectives of exact and maintained monitor points whose slabs are more than a
+    workgroup's threads or only a few, and of a run that ends on a pending update."""
+    _say("batch monitor slabs", d, n, b, s)
+    X, y, _ = synth.gaussian_ridge(d, n, n)
+    Xd, yd = X.to(DEV), y.to(DEV)
+    q = dict(X=Xd, y=yd, lam=0.05, b=b, s=s, seed=5, H=0)
+    with gpu_lib.Batch([q], monitor_every=1, cheap_monitors=2) as B:
+        for _ in range(4):
+            B.run(1)
+            r = Xd.t() @ q["w"] - yd
+            f = float(r @ r) / (2 * n) + 0.025 * float(q["w"] @ q["w"])
+            assert abs(B.info(0)["objective"] - f) <= 1e-12 * f
+            assert float((q["r"] - r).norm()) <= 1e-12 * float(r.norm())
+    with gpu_lib.Batch([q], monitor_every=0) as B:
+        B.run(3)
+    r = Xd.t() @ q["w"] - yd
+    assert float((q["r"] - r).norm()) <= 1e-12 * float(r.norm())
