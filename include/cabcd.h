@@ -254,7 +254,10 @@ cabcd_status cabcd_gram_noalloc(const cabcd_matrix* A, const int32_t* idx, int32
  * opts->resid_every to recompute r exactly every few outer steps) or CSR F64.
  * 1 <= b <= min(d, 32), s >= 1, s*b <= 512 dense / 1024 CSR (512 when
  * b > 16), H >= 0, lambda > 0; a larger s*b is CABCD_EUNSUPPORTED.
- * Results are reproducible bit for bit for dense storage.  For CSR, the
+ * Results are reproducible bit for bit for dense storage, also when the run is
+ * split into calls of whole outer steps, except that steps of at most 32 long
+ * rows (8 to 40 MiB a step, or 2^17 columns and more) round differently in calls
+ * of few steps.  For CSR, the
  * outer steps of 256 to 512 gathered rows whose Grams are computed ahead
  * update r (w for the dual) with one writer per column and are reproducible
  * too, also when the run is split into several calls (opts->h0); other CSR

@@ -46,6 +46,7 @@ constexpr int kFirstBatch = 6;              // steps of a chain's first batch (a
 constexpr int kChainAhead = 32;             // dense steps of a chain: Grams per launch (max)
 constexpr int kChainFewRows = 32;           // steps of so few rows are a chain up to
 constexpr int64_t kChainRowBytes = 40 << 20;   // so many gathered bytes
+constexpr int64_t kChainCallBytes = 48 << 20;  // (what their first step costs a call)
 constexpr int kSplitMinRows = 256;          // CSR: the split Gram from this many rows a step
 constexpr int kSplitMaxRows = 512;
 constexpr int kSplitAhead = 16;             // steps per split Gram launch (at most)
@@ -515,7 +516,11 @@ hipError_t mat_gram(const Mat& M, const int32_t* idx, int m, const double* u, do
 // and a dense step is one launch.  That saves the reduction, the solve and the
 // launches of a step, about 16 us, against the second pass, so steps of at most
 // kChainFewRows rows (whose Gram is no more work than that pass) are a chain
-// up to kChainRowBytes.
+// up to kChainRowBytes, in calls of enough steps to make up for the first one, whose
+// Gram, inverse and products come one after the other, about 30 us more: a step gains
+// what kChainRowBytes is more than its bytes, and kChainCallBytes is to be gained.  (Calls,
+// in one Gram a step and as a chain, us: 8 rows, 16 MiB, 1 step 63, 90; 2 steps 104, 101; 32
+// steps 906, 592; 32 rows, 32 MiB, 1 step 69, 101; 4 steps 163, 174; 16 steps 525, 504.)
 struct Ahead {
   int slots = 1;          // Grams per launch
   ChainPlan chain{};      // chain.ok: the steps are a chain
@@ -537,7 +542,8 @@ GramPlan plan_ahead_f64(int m, int64_t cols) {
   return p;
 }
 
-Ahead plan_ahead(const Mat& M, int b, int64_t sb, bool chain = true) {
+// steps: full outer steps of the call.
+Ahead plan_ahead(const Mat& M, int b, int64_t sb, int64_t steps, bool chain = true) {
   Ahead a;
   if (chain) a.chain = chain_plan((int)sb, b);
   if (!M.csr) {   // whole 16-byte chunks, on their boundaries for codes
@@ -555,7 +561,8 @@ Ahead plan_ahead(const Mat& M, int b, int64_t sb, bool chain = true) {
   a.plan = plan_for(M, (int)sb);
   const int64_t elem = M.dtype == CABCD_F64 ? 8 : (M.dtype == CABCD_BF16 ? 2 : 1);
   const int64_t bytes = sb * M.cols * elem;
-  const bool few = a.chain.ok && sb <= kChainFewRows && bytes <= kChainRowBytes;
+  const bool few = a.chain.ok && sb <= kChainFewRows && bytes < kChainRowBytes &&
+                   steps >= (kChainCallBytes + kChainRowBytes - bytes - 1) / (kChainRowBytes - bytes);
   if (sb > kGramRows || (!few && (bytes > kAheadRowBytes || a.plan.nsplit >= kDenseFill))) {
     a.chain.ok = false;
     return a;
@@ -771,13 +778,13 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   const int64_t rtmp_len = o.monitor_every > 0 ? (dual ? rows : cols) : 1;
   StepBuffers B{};
   const bool checks = o.check_every > 0;
-  Ahead ah = plan_ahead(M, b, (int64_t)s * b);
+  Ahead ah = plan_ahead(M, b, (int64_t)s * b, H / s);
   Carve probe{nullptr};
   size_t need = layout(probe, B, M, ah, b, s, rtmp_len, checks);
   if (ah.chain.ok && o.workspace != nullptr && o.workspace_bytes < need) {
     // a caller workspace without room for the chain's buffers: the solves stay
     // with their steps
-    ah = plan_ahead(M, b, (int64_t)s * b, false);
+    ah = plan_ahead(M, b, (int64_t)s * b, H / s, false);
     Carve again{nullptr};
     need = layout(again, B, M, ah, b, s, rtmp_len, checks);
   }
@@ -835,7 +842,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
         // room for the chain's buffers or the split Gram's, not for both: the split Gram
         // (its updates have one writer a column, the row-pair path's are atomic).  What
         // csr_split_prepare wrote stays: it is first in either layout.
-        const Ahead plain = plan_ahead(M, b, sb_full, false);
+        const Ahead plain = plan_ahead(M, b, sb_full, H / s, false);
         StepBuffers P{};
         Carve again{static_cast<char*>(ws)};
         sp = place(layout(again, P, M, plain, b, s, rtmp_len, checks));
@@ -937,15 +944,8 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   bool pf_ready = false;                          // next batch launched on the side stream
   int64_t pf_h = -1;
   int pf_nst = 0;
-  hipStream_t side = nullptr;
+  hipStream_t side = nullptr;                     // (with its events, when first needed)
   StreamEvents ev;
-  if (K > 1) {
-    side = side_stream();
-    if (side == nullptr || ev.create() != hipSuccess) {
-      set_error("creating the second stream or its events failed");
-      return CABCD_EHIP;
-    }
-  }
   // steps of the batch starting at iteration hb whose indices are at hand (0: none)
   auto batch_steps = [&](int64_t hb) -> int {
     int64_t avail = (H - hb) / s;
@@ -1067,6 +1067,13 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
         const int64_t h2 = h + (int64_t)ahead * s;
         const int n2 = batch_steps(h2);
         if (n2 > 0) {
+          if (side == nullptr) {
+            side = side_stream();
+            if (side == nullptr || ev.create() != hipSuccess) {
+              set_error("creating the second stream or its events failed");
+              return CABCD_EHIP;
+            }
+          }
           HIP_TRY(hipEventRecord(ev.issued, st));
           HIP_TRY(hipStreamWaitEvent(side, ev.issued, 0));
           HIP_TRY(launch_batch(h2, n2, cur ^ 1, side));
@@ -1549,8 +1556,9 @@ size_t cabcd_workspace_bytes(const cabcd_matrix* A, int32_t b, int32_t s) {
   if (b < 1 || s < 1 || (int64_t)s * b > max_rows_per_gram(M)) return 0;
   StepBuffers B{};
   Carve probe{nullptr};
-  return layout(probe, B, M, plan_ahead(M, b, (int64_t)s * b), b, s, std::max(A->rows, A->cols),
-                true);
+  // (calls of any number of steps: a chain needs no less than one Gram a step)
+  return layout(probe, B, M, plan_ahead(M, b, (int64_t)s * b, INT64_MAX), b, s,
+                std::max(A->rows, A->cols), true);
 }
 
 }  // extern "C"

@@ -21,7 +21,7 @@
 //     from the registers it was written from (kept in LDS);
 //   * chain_resid_kernel, chain_refine_kernel: T^-1 = Z + (I - Z T) Z for the rows
 //     that need it, the residual summed in twice the working precision.
-// The order and the refinement are for accuracy.  With c = T delta the product Z c
+// (chain_small_kernel does all of it for up to four superblocks.)  The order and the refinement are for accuracy.  With c = T delta the product Z c
 // is off by (Z T - I) delta, which the substitution has no counterpart to: where
 // the rows are nearly collinear, c is far smaller than |T| |delta|.  An inverse by
 // columns keeps T Z - I small and leaves Z T - I large: w of 256 x 4096, b = 8, s =
@@ -81,6 +81,24 @@ __device__ __forceinline__ int block_of(int v, int bm) { return (v * bm) >> 8; }
 
 // ------------------------------------------------------------------ T^-1
 
+// Row u of the inverse of superblock I (a group of sixteen lanes holds one), the
+// identity past nsb; true when a pivot is not positive (the same in the group).
+__device__ __forceinline__ bool diag_inverse(const double* __restrict__ G, int m, int b, int gb,
+                                             int nsb, int I, int u, double (&e)[16]) {
+  const int r0 = I * gb;
+  const bool live = I < nsb && u < gb && r0 + u < m;
+  // unconditional loads at clamped places, so that they go out together
+#pragma unroll
+  for (int v = 0; v < 16; ++v) e[v] = G[(int64_t)min(r0 + v, m - 1) * m + min(r0 + u, m - 1)];
+  const int bm = block_mul(b), bu = block_of(u, bm);
+#pragma unroll
+  for (int v = 0; v < 16; ++v)
+    e[v] = live && block_of(v, bm) <= bu && v < gb && r0 + v < m ? e[v] : (u == v ? 1.0 : 0.0);
+  bool bad = false;
+  sdev::gj_rows16<0>(e, u, bad);   // every lane takes part in the row broadcasts
+  return bad;
+}
+
 // Superblock I of step blockIdx.y: four per wave, one row per lane.
 __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict__ G, int m, int b,
                                                         int gb, int nsb, double* __restrict__ tri,
@@ -91,33 +109,72 @@ __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict
   dinv += (int64_t)blockIdx.y * nsb * 256;
   const int I = blockIdx.x * 4 + (threadIdx.x >> 4);
   const int u = threadIdx.x & 15;
-  const int r0 = I * gb;
-  const bool live = I < nsb && u < gb && r0 + u < m;
-  // unconditional loads at clamped places, so that they go out together
   double e[16];
-#pragma unroll
-  for (int v = 0; v < 16; ++v) e[v] = G[(int64_t)min(r0 + v, m - 1) * m + min(r0 + u, m - 1)];
-  const int bm = block_mul(b), bu = block_of(u, bm);
-#pragma unroll
-  for (int v = 0; v < 16; ++v)
-    e[v] = live && block_of(v, bm) <= bu && v < gb && r0 + v < m ? e[v] : (u == v ? 1.0 : 0.0);
-  bool bad = false;
-  sdev::gj_rows16<0>(e, u, bad);   // every lane takes part in the row broadcasts
+  const bool bad = diag_inverse(G, m, b, gb, nsb, I, u, e);
   if (I >= nsb) return;
-  if (u == 0) bad_block[(int)blockIdx.y * nsb + I] = bad ? 1 : 0;   // (the same in every lane)
+  if (u == 0) bad_block[(int)blockIdx.y * nsb + I] = bad ? 1 : 0;
   double* t = tri + (int64_t)tri_block(I, I) * 256;
-  double* d = dinv + (int64_t)I * 256 + (u >> 2) * 64 + (u & 3) * 16;   // transposed operand:
-#pragma unroll                                                           // k-slice, lane
+  double* d = dinv + (int64_t)I * 256 + 16 * u;   // the transposed operand: k-slice, lane
+#pragma unroll
   for (int v = 0; v < 16; ++v) {
     t[tri_at(u >> 2, (u & 3) * 16 + v)] = e[v];
     d[v] = e[v];
   }
 }
 
+// Rows of superblock t of T in the columns of superblock J < t, transposed, as an operand:
+// 16 consecutive doubles a row.  FULL: gb = 16 and m a multiple of 16.
+template <bool FULL>
+__device__ __forceinline__ void load_t(gptr<const double> Gs, int m, int gb, int t, int J,
+                                       int lane, double (&a)[4]) {
+  const int l15 = lane & 15, l16 = lane >> 4, col = J * gb + l15;
+#pragma unroll
+  for (int s = 0; s < 4; ++s) {
+    const int kk = 4 * s + l16, row = t * gb + kk;
+    if constexpr (FULL) {
+      a[s] = Gs[(int64_t)row * m + col];
+    } else {
+      const bool ok = kk < gb && l15 < gb && row < m && col < m;
+      const double v = Gs[ok ? (int64_t)row * m + col : 0];
+      a[s] = ok ? v : 0.0;
+    }
+  }
+}
+
+// -D_J^-1 from the right to the sum v, all transposed (da: the operand of D_J^-1).
+__device__ __forceinline__ d4 times_dinv(const double (&da)[4], const double (&v)[4]) {
+  d4 z0 = {0.0, 0.0, 0.0, 0.0}, z1 = {0.0, 0.0, 0.0, 0.0};
+  z0 = gdev::mfma(da[0], -v[0], z0);
+  z1 = gdev::mfma(da[1], -v[1], z1);
+  z0 = gdev::mfma(da[2], -v[2], z0);
+  z1 = gdev::mfma(da[3], -v[3], z1);
+  return z0 + z1;
+}
+
+// Link word of row p of the m rows ix; sb_bad: whether its superblock is.
+__device__ __forceinline__ int link_word(const int* ix, int m, int p, int sb_bad) {
+  const int i = ix[p];
+  bool first = true;
+  for (int q = 0; q < p; ++q) first &= ix[q] != i;
+  int next = 0;
+  for (int q = m - 1; q > p; --q) next = ix[q] == i ? q + 1 : next;
+  return (first ? kLinkFirst : 0) | next | (sb_bad != 0 ? kLinkBad : 0);
+}
+
+// A row needs no refinement where |Z_rk| sqrt(T_kk T_rr), which bounds the amplification
+// |Z| |T| whatever the scales of the rows, is at most kRefineFrom: in CPU runs of 160 steps
+// of all block sizes, correlations 0 to 0.999 and lambda 1e-6 to 0.1, Z as it is then came
+// within 10 % of the substitution (mean error of x and of the companion; 25 % above 32, 37 %
+// from 128 on).
+constexpr double kRefineFrom = 16.0;
+__device__ __forceinline__ double amplified(double z, double gk, double gr) {
+  const double v = z * z * gk * gr;
+  return v >= 0.0 ? v : __builtin_inf();
+}
+
 // Workgroup x < gridDim.x - 1: superblock row I = nsb - 1 - x of step blockIdx.y by
 // four waves (the longest rows first); the last workgroup builds the step's links.
-// FULL: gb = 16 and m a multiple of 16.  Z to `tri`, and to `out` too where the row needs
-// no refinement, which `need` notes.
+// Z to `tri`, and to `out` too where the row needs no refinement, which `need` notes.
 //
 // A row is a chain over its columns: column R (superblock I - R) needs Z of every
 // column before it.  Wave w holds the columns r = w mod 4 and adds their products to
@@ -127,14 +184,7 @@ __global__ __launch_bounds__(64) void chain_diag_kernel(const double* __restrict
 // is enough.  PF operand blocks a wave are in flight; Z goes to memory at the
 // end (stores in the loop made the loads after them wait: 50 us for 13 steps of
 // 256 rows with one wave a row and stores in the loop, 190 us for 16 of 512).
-//
-// A row needs none where |Z_rk| sqrt(T_kk T_rr), which bounds the amplification |Z| |T|
-// whatever the scales of the rows, is at most kRefineFrom: in CPU runs of 160 steps of
-// all block sizes, correlations 0 to 0.999 and lambda 1e-6 to 0.1, Z as it is then came
-// within 10 % of the substitution (mean error of x and of the companion; 25 % above 32, 37 %
-// from 128 on).
 constexpr int kPanelWaves = 4;
-constexpr double kRefineFrom = 16.0;
 template <bool FULL>
 __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
     const double* __restrict__ G, int m, int gb, int nsb, double* __restrict__ tri,
@@ -148,15 +198,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
     link += step * m;
     for (int p = threadIdx.x; p < m; p += blockDim.x) ix[p] = idx[p];
     __syncthreads();
-    for (int p = threadIdx.x; p < m; p += blockDim.x) {
-      const int i = ix[p];
-      bool first = true;
-      for (int q = 0; q < p; ++q) first &= ix[q] != i;
-      int next = 0;
-      for (int q = m - 1; q > p; --q) next = ix[q] == i ? q + 1 : next;
-      link[p] = (first ? kLinkFirst : 0) | next |
-                (bad_block[step * nsb + p / gb] != 0 ? kLinkBad : 0);
-    }
+    for (int p = threadIdx.x; p < m; p += blockDim.x)
+      link[p] = link_word(ix, m, p, bad_block[step * nsb + p / gb]);
     return;
   }
   constexpr int PF = 4;
@@ -171,22 +214,8 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
   double* Zs = zs + 2 * kPanelWaves * 256;        // Z of column r, transposed, at r * 256
   double* Z = Zs + lane;
 
-  // operand block (R, r): rows of superblock I - r of T in the columns of I - R,
-  // transposed: 16 consecutive doubles a row
-  auto load = [&](int R, int r, double(&a)[4]) {
-    const int col = (I - R) * gb + l15;
-#pragma unroll
-    for (int s = 0; s < 4; ++s) {
-      const int kk = 4 * s + l16, row = (I - r) * gb + kk;
-      if constexpr (FULL) {
-        a[s] = Gs[(int64_t)row * m + col];
-      } else {
-        const bool ok = kk < gb && l15 < gb && row < m && col < m;
-        const double v = Gs[ok ? (int64_t)row * m + col : 0];
-        a[s] = ok ? v : 0.0;
-      }
-    }
-  };
+  // operand block (R, r): rows of superblock I - r of T in the columns of I - R
+  auto load = [&](int R, int r, double(&a)[4]) { load_t<FULL>(Gs, m, gb, I - r, I - R, lane, a); };
   double ring[PF][4], da[4];
   int Rn = w + 1, rn = w;   // the next block to load (clamped past the last)
   auto next_load = [&](double(&a)[4]) {
@@ -224,14 +253,9 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
 #pragma unroll
       for (int s = 0; s < 4; ++s)
         v[s] = (set[64 * s] + set[256 + 64 * s]) + (set[512 + 64 * s] + set[768 + 64 * s]);
-      d4 z0 = {0.0, 0.0, 0.0, 0.0}, z1 = {0.0, 0.0, 0.0, 0.0};
-      z0 = gdev::mfma(da[0], -v[0], z0);
-      z1 = gdev::mfma(da[1], -v[1], z1);
-      z0 = gdev::mfma(da[2], -v[2], z0);
-      z1 = gdev::mfma(da[3], -v[3], z1);
-      z0 += z1;
+      const d4 z = times_dinv(da, v);
 #pragma unroll
-      for (int s = 0; s < 4; ++s) Z[R * 256 + 64 * s] = z0[s];
+      for (int s = 0; s < 4; ++s) Z[R * 256 + 64 * s] = z[s];
       Rd += kPanelWaves;
       load_d();
     }
@@ -253,7 +277,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
   }
   // wave w wrote the columns R = w mod 4
   double* gd = zs;                       // the diagonal of G up to this row (kMaxRows at most)
-  double* top = zs + kPanelWaves * 256;   // a wave's largest |Z_rk|^2 T_kk T_rr
+  double* top = zs + kPanelWaves * 256;   // a wave's largest amplification
   lds_barrier();
   for (int p = threadIdx.x; p < nr * gb; p += 64 * kPanelWaves) {
     const double v = Gs[(int64_t)min(p, m - 1) * (m + 1)];
@@ -267,8 +291,7 @@ __global__ __launch_bounds__(64 * kPanelWaves) void chain_panel_kernel(
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const double gr = 4 * s + l16 < gb ? gd[I * gb + 4 * s + l16] : 0.0;
-      const double v = z[4 * s] * z[4 * s] * gk * gr;
-      big = fmax(big, v >= 0.0 ? v : __builtin_inf());
+      big = fmax(big, amplified(z[4 * s], gk, gr));
     }
   }
   for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
@@ -317,29 +340,26 @@ __device__ __forceinline__ void dot2(double a, double b, double& h, double& l) {
   h = q;
 }
 
-// Superblock (I, J) of I - Z T (Z at `tri`) of step blockIdx.y, to `res` in the matrix
-// cores' operand order, for the rows in need.  Wave w adds the products t = J + w mod 4, a lane rows 4 (lane /
-// 16) .. + 3 of column lane % 16.  The vector units bound it: ten FP64 operations an
-// element product, one product's loads ahead.
+// Superblock (I, J) of I - Z T by a workgroup of kResWaves waves, to `out` in the matrix
+// cores' operand order (Zr: row I of Z).  Wave w adds the products t = J + w mod 4, a lane
+// rows 4 (lane / 16) .. + 3 of column lane % 16.  The vector units bound it: ten FP64
+// operations an element product, one product's loads ahead.
 constexpr int kResWaves = 4;
+struct ResLds {
+  static constexpr int ZS = 18;   // (16-byte pieces of a row aligned; two-way bank conflicts)
+  __attribute__((aligned(16))) double zt[kResWaves][16 * ZS];   // Z_It, transposed
+  double tt[kResWaves][256];                                    // T_tJ
+  double part[kResWaves][2][256];
+};
 template <bool FULL>
-__global__ __launch_bounds__(64 * kResWaves) void chain_resid_kernel(
-    const double* __restrict__ G, int m, int b, int gb, int nsb, const double* __restrict__ tri,
-    const int* __restrict__ need, double* __restrict__ res) {
+__device__ __forceinline__ void resid_block(gptr<const double> Gs, int m, int b, int gb,
+                                            gptr<const double> Zr, int I, int J, ResLds& L,
+                                            gptr<double> out) {
   typedef double dv2 __attribute__((ext_vector_type(2)));
-  constexpr int ZS = 18;   // (16-byte pieces of a row stay aligned; two-way bank conflicts)
-  __shared__ __attribute__((aligned(16))) double zt[kResWaves][16 * ZS];   // Z_It, transposed
-  __shared__ double tt[kResWaves][256];                                    // T_tJ
-  __shared__ double part[kResWaves][2][256];
+  constexpr int ZS = ResLds::ZS;
   const int lane = threadIdx.x & 63;
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int l15 = lane & 15, l16 = lane >> 4;
-  const int64_t step = blockIdx.y;
-  int I, J;
-  tri_place((int)(gridDim.x - 1 - blockIdx.x), I, J);   // (the longest first)
-  if (need[step * nsb + I] == 0) return;
-  const gptr<const double> Gs = glb(G) + step * m * m;
-  const gptr<const double> Zr = glb(tri) + (step * tri_block(nsb, 0) + tri_block(I, 0)) * 256;
   const int bm = block_mul(b);
   const int col = J * gb + l15;
   double zv[4], tv[4], h[4], l[4];
@@ -361,17 +381,17 @@ __global__ __launch_bounds__(64 * kResWaves) void chain_resid_kernel(
   for (int t0 = J; t0 <= I; t0 += kResWaves) {   // uniform
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
-      zt[w][l15 * ZS + 4 * s + l16] = zv[s];
-      tt[w][64 * s + lane] = tv[s];
+      L.zt[w][l15 * ZS + 4 * s + l16] = zv[s];
+      L.tt[w][64 * s + lane] = tv[s];
     }
     lds_barrier();
     load(t0 + kResWaves + w);
     if (t0 + w <= I) {   // uniform in a wave
 #pragma unroll
       for (int k = 0; k < 16; ++k) {
-        const double t = tt[w][16 * k + l15];
-        const dv2 z0 = *reinterpret_cast<const dv2*>(&zt[w][k * ZS + 4 * l16]);
-        const dv2 z1 = *reinterpret_cast<const dv2*>(&zt[w][k * ZS + 4 * l16 + 2]);
+        const double t = L.tt[w][16 * k + l15];
+        const dv2 z0 = *reinterpret_cast<const dv2*>(&L.zt[w][k * ZS + 4 * l16]);
+        const dv2 z1 = *reinterpret_cast<const dv2*>(&L.zt[w][k * ZS + 4 * l16 + 2]);
         dot2(z0.x, t, h[0], l[0]);
         dot2(z0.y, t, h[1], l[1]);
         dot2(z1.x, t, h[2], l[2]);
@@ -381,45 +401,47 @@ __global__ __launch_bounds__(64 * kResWaves) void chain_resid_kernel(
   }
 #pragma unroll
   for (int s = 0; s < 4; ++s) {
-    part[w][0][64 * s + lane] = h[s];
-    part[w][1][64 * s + lane] = l[s];
+    L.part[w][0][64 * s + lane] = h[s];
+    L.part[w][1][64 * s + lane] = l[s];
   }
-  __syncthreads();
+  lds_barrier();
   const int at = threadIdx.x, row = 4 * l16 + (at >> 6);   // (column l15)
   double sh = I == J && row == l15 ? -1.0 : 0.0, sl = 0.0;
 #pragma unroll
   for (int q = 0; q < kResWaves; ++q) {
-    const double p = part[q][0][at], s = sh + p, d = s - sh;
-    sl += ((sh - (s - d)) + (p - d)) + part[q][1][at];
+    const double p = L.part[q][0][at], s = sh + p, d = s - sh;
+    sl += ((sh - (s - d)) + (p - d)) + L.part[q][1][at];
     sh = s;
   }
-  res[(step * tri_block(nsb, 0) + tri_block(I, J)) * 256 + (l15 >> 2) * 64 + (l15 & 3) * 16 + row] =
-      -(sh + sl);
+  out[16 * l15 + row] = -(sh + sl);
 }
 
-// T^-1 = Z + R Z from Z (`tri`) and the residual R for the rows in need: superblock 4 x +
-// wave of step blockIdx.y, to `out`.
-__global__ __launch_bounds__(256) void chain_refine_kernel(int nsb, const double* __restrict__ tri,
-                                                           const int* __restrict__ need,
-                                                           const double* __restrict__ res,
-                                                           double* __restrict__ out) {
-  typedef double dv2 __attribute__((ext_vector_type(2)));
-  const int n = tri_block(nsb, 0);
-  const int lane = threadIdx.x & 63;
-  const int x = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
-  if (x >= n) return;
-  int I, J;
-  tri_place(n - 1 - x, I, J);   // (the longest first)
+// Superblock x of step blockIdx.y of the residual of Z (`tri`), for the rows in need.
+template <bool FULL>
+__global__ __launch_bounds__(64 * kResWaves) void chain_resid_kernel(
+    const double* __restrict__ G, int m, int b, int gb, int nsb, const double* __restrict__ tri,
+    const int* __restrict__ need, double* __restrict__ res) {
+  __shared__ ResLds L;
   const int64_t step = blockIdx.y;
+  int I, J;
+  tri_place((int)(gridDim.x - 1 - blockIdx.x), I, J);   // (the longest first)
   if (need[step * nsb + I] == 0) return;
-  const gptr<const double> Z = glb(tri) + step * n * 256;
-  const gptr<const double> R = glb(res) + (step * n + tri_block(I, 0)) * 256 + lane;
+  const int64_t at = step * tri_block(nsb, 0);
+  resid_block<FULL>(glb(G) + step * m * m, m, b, gb, glb(tri) + (at + tri_block(I, 0)) * 256, I, J,
+                    L, glb(res) + (at + tri_block(I, J)) * 256);
+}
+
+// Superblock (I, J) of T^-1 = Z + R Z by a wave, all three of one step.
+__device__ __forceinline__ void refine_block(gptr<const double> Z, gptr<const double> R, int I,
+                                             int J, int lane, gptr<double> out) {
+  typedef double dv2 __attribute__((ext_vector_type(2)));
   constexpr int U = 4;   // products in flight
   double a[U][4], z[U][4], z0[4];
+  const gptr<const double> Rr = R + (int64_t)tri_block(I, 0) * 256 + lane;
   auto load = [&](int t, int q) {
     t = min(t, I);
 #pragma unroll
-    for (int s = 0; s < 4; ++s) a[q][s] = R[(int64_t)t * 256 + 64 * s];
+    for (int s = 0; s < 4; ++s) a[q][s] = Rr[(int64_t)t * 256 + 64 * s];
     tri_load(Z + (int64_t)tri_block(t, J) * 256, lane, z[q]);
   };
   tri_load(Z + (int64_t)tri_block(I, J) * 256, lane, z0);
@@ -437,9 +459,142 @@ __global__ __launch_bounds__(256) void chain_refine_kernel(int nsb, const double
     }
   }
   const d4 c = acc[0] + acc[1];
-  const gptr<double> o = glb(out) + (step * n + tri_block(I, J)) * 256;
+  const gptr<double> o = out + (int64_t)tri_block(I, J) * 256;
   *(gptr<dv2>)(o + 2 * lane) = dv2{z0[0] + c[0], z0[1] + c[1]};
   *(gptr<dv2>)(o + 128 + 2 * lane) = dv2{z0[2] + c[2], z0[3] + c[3]};
+}
+
+// Superblock 4 x + wave of step blockIdx.y of T^-1 from Z (`tri`) and the residual, for the
+// rows in need.
+__global__ __launch_bounds__(256) void chain_refine_kernel(int nsb, const double* __restrict__ tri,
+                                                           const int* __restrict__ need,
+                                                           const double* __restrict__ res,
+                                                           double* __restrict__ out) {
+  const int n = tri_block(nsb, 0);
+  const int x = __builtin_amdgcn_readfirstlane((int)blockIdx.x * 4 + (int)(threadIdx.x >> 6));
+  if (x >= n) return;
+  int I, J;
+  tri_place(n - 1 - x, I, J);   // (the longest first)
+  const int64_t step = blockIdx.y;
+  if (need[step * nsb + I] == 0) return;
+  refine_block(glb(tri) + step * n * 256, glb(res) + step * n * 256, I, J, threadIdx.x & 63,
+               glb(out) + step * n * 256);
+}
+
+// Steps of up to kSmallSuper superblocks: all of the above by one workgroup, wave w
+// superblock row w, with T and Z in registers (Z comes transposed and is the next product's
+// operand as it is).  As launches of their own the parts took 20 us of a call of one step.
+constexpr int kSmallSuper = 4;
+template <bool FULL>
+__global__ __launch_bounds__(64 * kSmallSuper) void chain_small_kernel(
+    const double* __restrict__ G, int m, int b, int gb, int nsb, const int32_t* __restrict__ idx,
+    double* __restrict__ tri, double* __restrict__ raw, double* __restrict__ res,
+    int* __restrict__ link) {
+  static_assert(kSmallSuper == kResWaves, "resid_block takes the workgroup");
+  constexpr int S = kSmallSuper;
+  __shared__ double dt[S][256], zw[tri_block(S, 0)][256], gd[16 * S];
+  __shared__ int ix[16 * S], bad[S], need[S];
+  __shared__ ResLds L;
+  const int64_t step = blockIdx.x;
+  const int n = tri_block(nsb, 0);
+  const int tid = threadIdx.x, lane = tid & 63, l15 = lane & 15, l16 = lane >> 4;
+  const int I = __builtin_amdgcn_readfirstlane(tid >> 6);
+  G += step * m * m;
+  const gptr<const double> Gs = glb(G);
+  const gptr<double> T = glb(tri) + step * n * 256;
+  double a[S][S][4];   // T_tJ of this row's columns
+#pragma unroll
+  for (int J = 0; J < S; ++J)
+#pragma unroll
+    for (int t = J + 1; t < S; ++t)
+      if (t <= I && I < nsb) load_t<FULL>(Gs, m, gb, t, J, lane, a[J][t]);   // uniform
+  if (I == 0) {
+    double e[16];
+    const bool bd = diag_inverse(G, m, b, gb, nsb, l16, l15, e);
+#pragma unroll
+    for (int v = 0; v < 16; ++v) dt[l16][16 * l15 + v] = e[v];
+    if (l15 == 0) bad[l16] = bd ? 1 : 0;
+  } else if (I == 1) {
+    const int p = min(lane, m - 1);
+    const double v = Gs[(int64_t)p * (m + 1)];
+    gd[lane] = lane < m ? v : 0.0;
+    ix[lane] = idx[step * m + p];
+  }
+  __syncthreads();
+  if (tid < m) link[step * m + tid] = link_word(ix, m, tid, bad[tid / gb]);
+  if (I < nsb) {
+    double W[S][4];   // Z_It, transposed
+    gdev::static_for<0, S>([&](auto r) {
+      constexpr int J = S - 1 - r;
+      if (J == I) {   // uniform
+#pragma unroll
+        for (int s = 0; s < 4; ++s) W[J][s] = dt[J][16 * l15 + 4 * s + l16];
+      } else if (J < I) {
+        d4 acc = {0.0, 0.0, 0.0, 0.0};
+#pragma unroll
+        for (int t = J + 1; t < S; ++t)
+          if (t <= I) {
+#pragma unroll
+            for (int s = 0; s < 4; ++s) acc = gdev::mfma(a[J][t][s], W[t][s], acc);
+          }
+        double da[4], v[4];
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          da[s] = dt[J][64 * s + lane];
+          v[s] = acc[s];
+        }
+        const d4 z = times_dinv(da, v);
+#pragma unroll
+        for (int s = 0; s < 4; ++s) W[J][s] = z[s];
+      }
+    });
+    double big = 0.0;
+    const double gr = l15 < gb ? gd[I * gb + l15] : 0.0;
+#pragma unroll
+    for (int t = 0; t < S; ++t)
+      if (t <= I) {
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+          const int k = 4 * s + l16;
+          big = fmax(big, amplified(W[t][s], k < gb ? gd[t * gb + k] : 0.0, gr));
+          zw[tri_block(I, t)][16 * k + l15] = W[t][s];
+        }
+      }
+    for (int o = 32; o > 0; o >>= 1) big = fmax(big, __shfl_xor(big, o, 64));
+    // (with one block a step its inverse is what the solve uses too)
+    if (lane == 0) need[I] = m > b && big > kRefineFrom * kRefineFrom ? 1 : 0;
+  } else if (lane == 0) {
+    need[I] = 0;
+  }
+  __syncthreads();
+  const int any = __builtin_amdgcn_readfirstlane(need[0] | need[1] | need[2] | need[3]);
+  const gptr<double> Z = glb(raw) + step * n * 256, R = glb(res) + step * n * 256;
+  for (int x = I; x < n; x += S) {   // a wave a superblock
+    int i, j;
+    tri_place(x, i, j);
+    const bool final = need[i] == 0;
+#pragma unroll
+    for (int s = 0; s < 4; ++s) {
+      const double z = zw[x][16 * l15 + 4 * s + l16];
+      if (final) T[x * 256 + tri_at(s, lane)] = z;
+      if (any) Z[x * 256 + tri_at(s, lane)] = z;
+    }
+  }
+  if (!any) return;
+  __syncthreads();
+  for (int i = 0; i < nsb; ++i) {
+    if (__builtin_amdgcn_readfirstlane(need[i]) == 0) continue;
+    for (int j = 0; j <= i; ++j) {
+      resid_block<FULL>(Gs, m, b, gb, Z + (int64_t)tri_block(i, 0) * 256, i, j, L,
+                        R + (int64_t)tri_block(i, j) * 256);
+      __syncthreads();
+    }
+  }
+  for (int x = I; x < n; x += S) {
+    int i, j;
+    tri_place(x, i, j);
+    if (need[i] != 0) refine_block(Z, R, i, j, lane, T);
+  }
 }
 
 // ------------------------------------------------------------------ delta = T^-1 c
@@ -1171,8 +1326,7 @@ ChainPlan chain_plan(int m, int b) {
   p.nsb = (m + p.gb - 1) / p.gb;
   p.ok = p.nsb <= kMaxSuper;
   p.tri = (size_t)tri_block(p.nsb, 0) * 256;
-  p.refined = m > b;
-  p.work = (size_t)p.nsb * 257 + (p.refined ? 2 * p.tri : 0);
+  p.work = (size_t)p.nsb * 257 + 2 * p.tri;
   return p;
 }
 
@@ -1180,30 +1334,34 @@ hipError_t launch_chain_prepare(const ChainPlan& p, const double* G, int nsteps,
                                 const int32_t* idx, double* tri, double* work, int* link,
                                 hipStream_t st) {
   if (!p.ok || nsteps < 1 || nsteps > 65535) return hipErrorInvalidValue;
-  // one block a step (refined = false): its inverse is what the solve uses too
-  double* dinv = work;
+  double* raw = work;
+  double* res = raw + (size_t)nsteps * p.tri;
+  double* dinv = res + (size_t)nsteps * p.tri;
   int* bad_block = reinterpret_cast<int*>(dinv + (size_t)nsteps * p.nsb * 256);
   int* need = bad_block + (size_t)nsteps * p.nsb;
-  double* raw = p.refined ? dinv + (size_t)nsteps * p.nsb * 257 : tri;
-  double* res = raw + (size_t)nsteps * p.tri;
+  const bool full = p.gb == 16 && m % 16 == 0;
+  if (p.nsb <= kSmallSuper) {
+    hipLaunchKernelGGL(full ? chain_small_kernel<true> : chain_small_kernel<false>,
+                       dim3((unsigned)nsteps), dim3(64 * kSmallSuper), 0, st, G, m, b, p.gb, p.nsb,
+                       idx, tri, raw, res, link);
+    return hipGetLastError();
+  }
   hipLaunchKernelGGL(chain_diag_kernel, dim3((unsigned)((p.nsb + 3) / 4), (unsigned)nsteps),
                      dim3(64), 0, st, G, m, b, p.gb, p.nsb, raw, dinv, bad_block);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   const size_t lds = std::max((size_t)(2 * kPanelWaves + p.nsb) * 256 * sizeof(double),
                               (size_t)m * sizeof(int));
-  const bool full = p.gb == 16 && m % 16 == 0;
   auto kern = full ? chain_panel_kernel<true> : chain_panel_kernel<false>;
   if (lds > 64 * 1024) {
     e = hipFuncSetAttribute(reinterpret_cast<const void*>(kern),
                             hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
     if (e != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb + (p.refined ? 1 : 0), (unsigned)nsteps),
-                     dim3(64 * kPanelWaves), lds, st, G, m, p.gb, p.nsb, raw, dinv, idx, link,
-                     bad_block, tri, need);
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsb + 1, (unsigned)nsteps), dim3(64 * kPanelWaves),
+                     lds, st, G, m, p.gb, p.nsb, raw, dinv, idx, link, bad_block, tri, need);
   e = hipGetLastError();
-  if (e != hipSuccess || !p.refined) return e;
+  if (e != hipSuccess) return e;
   const unsigned n = (unsigned)tri_block(p.nsb, 0);
   hipLaunchKernelGGL(full ? chain_resid_kernel<true> : chain_resid_kernel<false>,
                      dim3(n, (unsigned)nsteps), dim3(64 * kResWaves), 0, st, G, m, b, p.gb, p.nsb,

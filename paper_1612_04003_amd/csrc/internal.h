@@ -237,7 +237,6 @@ hipError_t launch_invert_diag(double* G, int nsteps, int m, int b, hipStream_t s
 struct ChainPlan {
   bool ok;            // b <= 16 and at most 32 superblocks
   int gb, nsb;        // rows of a superblock (b floor(16 / b)), superblocks
-  bool refined;       // the inverse is refined (more than one block a step)
   size_t tri, work;   // doubles a step: the inverse, and its scratch
 };
 ChainPlan chain_plan(int m, int b);
