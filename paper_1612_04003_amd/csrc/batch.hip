@@ -35,6 +35,7 @@
 #include <cstring>
 #include <numeric>
 #include <type_traits>
+#include <utility>
 #include <vector>
 
 namespace cabcd {
@@ -621,16 +622,15 @@ constexpr double kCuBw = 5.0e12 / 256;
 constexpr double kWgBw = 60e9;
 constexpr double kSolveBlock = 1.5e-6;
 constexpr double kRoundFixed = 10e-6;
-// Bytes of X in one item of an exact monitor (32 problems, 2.5 GB: 0.549 ms at 128
-// KiB, 0.512 at 256, 0.503 at 1 MiB, 0.568 at 4 MiB).
-constexpr int64_t kAuxBytes = 1 << 20;
-// Of the step's rows and r in one item of the other passes: eight items a CU, within
-// these.  An item costs some microseconds beside its bytes.  (Eight rounds with a
-// maintained monitor each, us: 4 problems of 1024 x 2^19, 8 rows, items of 256 KiB 983,
-// 512 KiB 910, 1 MiB 851, as the exact monitors' items 5908; 32 of 512 x 65536, 128
-// rows, 256 KiB 12618, 1 MiB 9611; 3 of 100 x 2^20, 256 rows, 256 KiB 45127, 1 MiB 39723,
-// 2.6 MB 38826.)
-constexpr int64_t kAuxStepMin = 512 << 10, kAuxStepMax = 4 << 20;
+// Bytes read by one item of a monitor pass: eight items a CU, between kAuxMin (X in an
+// exact monitor; in the other passes the step's rows and r: kAuxStepMin) and kAuxMax.  An
+// item costs some microseconds beside its bytes, few items leave CUs idle.  Exact, 32
+// problems, 2.5 GB: 0.549 ms at 128 KiB, 0.512 at 256, 0.503 at 1 MiB, 0.568 at 4 MiB; 4 of
+// 1024 x 2^19, 17 GB: 3.33 at 1 MiB, 3.24 at 4.  Eight rounds with a maintained monitor
+// each (ms): 4 of 1024 x 2^19, 8 rows, 256 KiB 0.98, 512 KiB 0.91, 1 MiB 0.85; 32 of 512 x
+// 2^16, 128 rows, 256 KiB 12.6, 1 MiB 9.6; 3 of 100 x 2^20, 256 rows, 256 KiB 45.1, 1 MiB
+// 39.7, 2.6 MB 38.8.
+constexpr int64_t kAuxMin = 1 << 20, kAuxStepMin = 512 << 10, kAuxMax = 4 << 20;
 constexpr int kAuxItemsPerCu = 8;
 constexpr int kGraphMaxRounds = 64;   // rounds of one captured monitor period, at most
 constexpr int kReplanRounds = 32;     // rounds between checks for re-slicing, about
@@ -945,6 +945,7 @@ void release(cabcd_batch_plan* B) {
 }
 
 cabcd_status capture(cabcd_batch_plan* B);
+std::vector<BItem> monitor_items(const std::vector<int>& which, const std::vector<int>& n);
 
 cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* opts,
                     hipStream_t st, cabcd_batch_plan* B) {
@@ -987,20 +988,27 @@ cabcd_status create(const cabcd_problem* pb, int32_t P, const cabcd_batch_opts* 
   std::vector<int> naux[2];
   const int es = elem_bytes(B->dtype);
   auto step_bytes = [&](int p) { return (int64_t)best[p].b * best[p].s * es + 16; };   // a column
-  int64_t all = 0;
-  for (int p = 0; p < P; ++p) all += pb[p].X.cols * step_bytes(p);
-  const int64_t step_item =
-      std::min(kAuxStepMax, std::max(kAuxStepMin, all / (kAuxItemsPerCu * (int64_t)cus)));
+  double all[2] = {0.0, 0.0};   // bytes of a pass
+  for (int p = 0; p < P; ++p) {
+    all[0] += (double)pb[p].X.cols * pb[p].X.rows * es;
+    all[1] += (double)pb[p].X.cols * step_bytes(p);
+  }
+  auto item_bytes = [&](int l) {
+    const double want = all[l] / (kAuxItemsPerCu * cus);
+    return (int64_t)std::min<double>(kAuxMax, std::max<double>(l == 0 ? kAuxMin : kAuxStepMin, want));
+  };
   for (int l = 0; l < 2; ++l) {
     achunk[l].resize(P);
     naux[l].resize(P);
+    std::vector<int> slabs;
     for (int p : order) {
       const int64_t n = pb[p].X.cols;
-      achunk[l][p] = l == 0 ? aux_chunk(n, pb[p].X.rows * es, B->dtype, kAuxBytes)
-                            : aux_chunk(n, step_bytes(p), B->dtype, step_item);
-      naux[l][p] = (int)((pb[p].X.cols + achunk[l][p] - 1) / achunk[l][p]);
-      for (int q = 0; q < naux[l][p]; ++q) aux[l].push_back(BItem{p, q});
+      achunk[l][p] =
+          aux_chunk(n, l == 0 ? pb[p].X.rows * es : step_bytes(p), B->dtype, item_bytes(l));
+      naux[l][p] = (int)((n + achunk[l][p] - 1) / achunk[l][p]);
+      slabs.push_back(naux[l][p]);
     }
+    aux[l] = monitor_items(order, slabs);
     B->naux[l] = (int)aux[l].size();
   }
 
@@ -1173,6 +1181,21 @@ cabcd_status capture(cabcd_batch_plan* B) {
   return CABCD_OK;
 }
 
+// Items of a monitor pass: n[i] slabs of problem which[i], side by side through the
+// problems, so that problems over one X read it while it is in the caches (an exact monitor
+// of 4 problems over one 1024 x 2^19 matrix: 3.3 ms problem after problem, 2.1 so; 32 over
+// one 512 x 2^16, with a round: 2.06 and 1.41).
+std::vector<BItem> monitor_items(const std::vector<int>& which, const std::vector<int>& n) {
+  std::vector<std::pair<double, BItem>> at;
+  for (size_t i = 0; i < which.size(); ++i)
+    for (int q = 0; q < n[i]; ++q) at.push_back({(q + 0.5) / n[i], BItem{which[i], q}});
+  std::stable_sort(at.begin(), at.end(),
+                   [](const auto& a, const auto& b) { return a.first < b.first; });
+  std::vector<BItem> items;
+  for (const auto& a : at) items.push_back(a.second);
+  return items;
+}
+
 // Re-slicing: once the active problems have halved since the slabs were last
 // cut, their slabs are cut again for the active problems alone (same (b, s),
 // the slab target recomputed from their work), so the GPU stays filled as
@@ -1225,9 +1248,13 @@ cabcd_status replan(cabcd_batch_plan* B, hipStream_t st) {
   // monitor passes keep a retired problem while its last update is pending
   std::vector<BItem> aux[2];
   for (int l = 0; l < 2; ++l) {
+    std::vector<int> which, slabs;
     for (int p = 0; p < B->P; ++p)
-      if (S[p].active || S[p].m_prev > 0)
-        for (int q = 0; q < B->probs[p].naux[l]; ++q) aux[l].push_back(BItem{p, q});
+      if (S[p].active || S[p].m_prev > 0) {
+        which.push_back(p);
+        slabs.push_back(B->probs[p].naux[l]);
+      }
+    aux[l] = monitor_items(which, slabs);
     B->naux[l] = (int)aux[l].size();
     B->grid_aux[l] = std::max(1, std::min(B->naux[l], B->occ_aux * B->cus));
   }
