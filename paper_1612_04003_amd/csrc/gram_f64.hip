@@ -132,7 +132,7 @@ __global__ __launch_bounds__(kRedThreads) void gram_reduce_kernel(
   int sp1 = min(nsplit, sp0 + spg);
   // blocks of padding rows are not read (130 rows of codes as sixteen block rows: 45 of
   // the 136 blocks)
-  if (MODE == 0 && e < (int64_t)nblk * 256) {
+  if (MODE == 0 && m <= 16 * (nb - 1) && e < (int64_t)nblk * 256) {
     int r = 0;
     while (blk_index(r + 1, 0) <= (int)(e >> 8)) ++r;
     if (16 * r >= m) sp1 = sp0;

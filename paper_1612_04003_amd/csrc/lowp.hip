@@ -112,6 +112,14 @@ __global__ __launch_bounds__(kLpThreads) void gram_lp_kernel(
 // against the tile's u segment (DMA'd beside the rows) and keeps one FP64
 // sum per row; the sixteen chunk sums of a row are added in chunk order at
 // the end.
+//
+// FULL: m > 192, every super-block has rows; below, the code that leaves some out costs
+// the whole ones 5 to 8 %.  The buffers are one array and a tile is one pass of the loop,
+// except for FP8 below 192 rows: with arrays of their own (so that reads need not wait
+// for the next tile's DMA) and the loop unrolled over them the eight waves' code is 104
+// KB, more than the instruction cache (FP8, 256 rows, 2^20 columns: one array 59.6 us,
+// two 62.5, and without FULL 63.4 and 66.8; 130 rows, 2^18 columns: 19.0 and 18.5; BF16
+// 23.0 and 24.0).
 __host__ __device__ constexpr int blk_index16(int r, int c) { return r * (r + 1) / 2 + c; }
 
 template <int FMT>
@@ -126,6 +134,7 @@ struct LD16 {
   static constexpr int BUF = TILE + UB;
   static constexpr int DMA_PER_WAVE = TILE / 1024 / 8;   // 8 instructions of 1 KiB
   static constexpr int UDMA = UB / 1024;                 // 1 (BF16) or 2 (FP8)
+  static constexpr bool apart(bool full) { return FMT == CABCD_FP8_E4M3 && !full; }
 };
 
 // Blocks of the 16 x 16 block triangle by wave, in 4 x 4 super-blocks: waves
@@ -180,7 +189,7 @@ __device__ __forceinline__ void lp16_sb_step(Frag frag, Mma mma, f4 (&acc)[20]) 
   }
 }
 
-template <int FMT, int W>
+template <int FMT, int W, bool FULL>
 __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t ld,
                                           int64_t k_begin, int64_t k_end, const int32_t* idx,
                                           int m, const double* __restrict__ u,
@@ -214,7 +223,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   // A tile inside the slab is all DMA (rows that no block of this m reads are left
   // out); the last tile of a slab that ends inside a tile is filled by ordinary loads
   // (zeros past the end).
-  const bool rows_on = 8 * C::DMA_PER_WAVE / 2 * W < (m + 63) / 64 * 64;
+  const bool rows_on = FULL || 8 * C::DMA_PER_WAVE / 2 * W < (m + 63) / 64 * 64;
   auto issue = [&](int t, uint8_t* T) {
     const int64_t k0 = k_begin + (int64_t)t * C::KT;
     if (rows_on) {
@@ -307,7 +316,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
     // 4 windows (BF16, K = 32) or 2 halves (FP8, K = 128) per tile; super-blocks whose
     // rows are all past m are left out
     auto blocks = [&](auto P) {
-      if (64 * lp16_sb_row(W, 10 * P) >= m) return;
+      if (!FULL && 64 * lp16_sb_row(W, 10 * P) >= m) return;
 #pragma unroll
       for (int h = 0; h < (FMT == CABCD_BF16 ? 4 : 2); ++h) {
         if constexpr (FMT == CABCD_BF16) {
@@ -342,7 +351,7 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
       }
 #pragma unroll
       for (int j0 = 0; j0 < YJ; j0 += 4) {
-        if (16 * j0 >= m) break;
+        if (!FULL && 16 * j0 >= m) break;
 #pragma unroll
         for (int j = j0; j < j0 + 4; ++j) {
           const int r = yr0 + 16 * j;
@@ -371,9 +380,14 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
     fill(0, t0);
   __builtin_amdgcn_s_waitcnt(0);   // the LDS-DMA writes count on the vector memory counter
   __syncthreads();
-  for (int t = 0; t < ntiles; t += 2) {
-    step(t, t0, t1);
-    if (t + 1 < ntiles) step(t + 1, t1, t0);
+  if constexpr (LD16<FMT>::apart(FULL)) {
+    for (int t = 0; t < ntiles; t += 2) {
+      step(t, t0, t1);
+      if (t + 1 < ntiles) step(t + 1, t1, t0);
+    }
+  } else {
+    for (int t = 0; t < ntiles; ++t)
+      step(t, t0 + (t & 1) * C::BUF, t0 + ((t + 1) & 1) * C::BUF);
   }
 
   // partial blocks as FP32 (what the accumulators hold; half the bytes of
@@ -403,28 +417,29 @@ __device__ __forceinline__ void lp16_slab(const uint8_t* __restrict__ A, int64_t
   }
 }
 
-template <int FMT>
+template <int FMT, bool FULL>
 __global__ __launch_bounds__(kLpThreads) void gram_lp_dma16_kernel(
     const uint8_t* __restrict__ A, int64_t ld, int64_t cols, const int32_t* __restrict__ idx,
     int m, const double* __restrict__ u, int64_t chunk, double* __restrict__ partials,
     int64_t pstride) {
   using C = LD16<FMT>;
-  // (arrays of their own: the reads of one must not wait for the DMA into the other)
-  __shared__ __attribute__((aligned(16))) uint8_t t0[C::BUF], t1[C::BUF];
+  constexpr bool APART = C::apart(FULL);
+  __shared__ __attribute__((aligned(16))) uint8_t t0[APART ? C::BUF : 2 * C::BUF];
+  __shared__ __attribute__((aligned(16))) uint8_t t1[APART ? C::BUF : 16];
   idx += (int64_t)blockIdx.y * m;            // several outer steps per launch
   partials += (int64_t)blockIdx.y * pstride;
   const int64_t k_begin = (int64_t)blockIdx.x * chunk;
   const int64_t k_end = std::min(cols, k_begin + chunk);
   double* part = partials + (int64_t)blockIdx.x * (C::NBLK * 256 + C::SBP);
   switch (__builtin_amdgcn_readfirstlane(threadIdx.x >> 6)) {
-    case 0: lp16_slab<FMT, 0>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 1: lp16_slab<FMT, 1>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 2: lp16_slab<FMT, 2>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 3: lp16_slab<FMT, 3>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 4: lp16_slab<FMT, 4>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 5: lp16_slab<FMT, 5>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    case 6: lp16_slab<FMT, 6>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
-    default: lp16_slab<FMT, 7>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 0: lp16_slab<FMT, 0, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 1: lp16_slab<FMT, 1, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 2: lp16_slab<FMT, 2, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 3: lp16_slab<FMT, 3, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 4: lp16_slab<FMT, 4, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 5: lp16_slab<FMT, 5, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    case 6: lp16_slab<FMT, 6, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
+    default: lp16_slab<FMT, 7, FULL>(A, ld, k_begin, k_end, idx, m, u, part, t0, t1); break;
   }
 }
 
@@ -432,7 +447,8 @@ template <int FMT>
 hipError_t launch_lp_dma16(const GramPlan& p, const void* A, int64_t ld, int64_t cols,
                            const int32_t* idx, int m, int nsteps, const double* u,
                            double* partials, hipStream_t st) {
-  hipLaunchKernelGGL((gram_lp_dma16_kernel<FMT>), dim3((unsigned)p.nsplit, (unsigned)nsteps),
+  auto kern = m > 192 ? gram_lp_dma16_kernel<FMT, true> : gram_lp_dma16_kernel<FMT, false>;
+  hipLaunchKernelGGL(kern, dim3((unsigned)p.nsplit, (unsigned)nsteps),
                      dim3(kLpThreads), 0, st, static_cast<const uint8_t*>(A), ld, cols, idx, m, u,
                      p.chunk, partials, (int64_t)gram_partial_doubles(p));
   return hipGetLastError();
