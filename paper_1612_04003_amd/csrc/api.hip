@@ -944,8 +944,12 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
   bool pf_ready = false;                          // next batch launched on the side stream
   int64_t pf_h = -1;
   int pf_nst = 0;
-  hipStream_t side = nullptr;                     // (with its events, when first needed)
-  StreamEvents ev;
+  hipStream_t side = K > 1 ? side_stream() : nullptr;
+  StreamEvents ev;                                // (created when first needed)
+  if (K > 1 && side == nullptr) {
+    set_error("creating the second stream failed");
+    return CABCD_EHIP;
+  }
   // steps of the batch starting at iteration hb whose indices are at hand (0: none)
   auto batch_steps = [&](int64_t hb) -> int {
     int64_t avail = (H - hb) / s;
@@ -1067,13 +1071,7 @@ cabcd_status run_bcd(bool dual, const Mat& M, const double* y, double lambda, in
         const int64_t h2 = h + (int64_t)ahead * s;
         const int n2 = batch_steps(h2);
         if (n2 > 0) {
-          if (side == nullptr) {
-            side = side_stream();
-            if (side == nullptr || ev.create() != hipSuccess) {
-              set_error("creating the second stream or its events failed");
-              return CABCD_EHIP;
-            }
-          }
+          if (ev.ready == nullptr) HIP_TRY(ev.create());
           HIP_TRY(hipEventRecord(ev.issued, st));
           HIP_TRY(hipStreamWaitEvent(side, ev.issued, 0));
           HIP_TRY(launch_batch(h2, n2, cur ^ 1, side));
