@@ -321,7 +321,7 @@ def sparse_records(cabcd, torch, synth):
     A = cabcd.CSR(torch.tensor(rowptr, device="cuda"), torch.tensor(colidx, device="cuda"),
                   torch.tensor(vals, device="cuda"), (20000, 1 << 20))
     yd = torch.tensor(ys, device="cuda")
-    steps = 32   # two whole launches of the split Gram (16 steps each) at s b >= 256
+    steps = 32   # split-Gram launches of 8, 16 and 8 steps at s b >= 256
     for s in (1, 8, 32):
         b = 16
         el, ph = timed_primal(cabcd, torch, A, yd, 1e-5, b, s, steps, 2, 2002, dual=True,

@@ -21,8 +21,8 @@
 //     from the registers it was written from (kept in LDS);
 //   * chain_resid_kernel, chain_refine_kernel: T^-1 = Z + (I - Z T) Z for the rows
 //     that need it, the residual summed in twice the working precision.
-// (chain_small_kernel does all of it for up to four superblocks.)  The order and the refinement are for accuracy.  With c = T delta the product Z c
-// is off by (Z T - I) delta, which the substitution has no counterpart to: where
+// (chain_small_kernel does all of it for up to four superblocks.)  The order and the
+// refinement are for accuracy.  With c = T delta the product Z c is off by (Z T - I) delta, which the substitution has no counterpart to: where
 // the rows are nearly collinear, c is far smaller than |T| |delta|.  An inverse by
 // columns keeps T Z - I small and leaves Z T - I large: w of 256 x 4096, b = 8, s =
 // 32, row correlation 0.9999, lambda 1e-5, was off by 5.3e-7 where the substitution
